@@ -24,7 +24,7 @@ __device__ __forceinline__ const T* kv_row(const AttnArgs& a, const void* pool, 
   return base + ((static_cast<size_t>(b) * a.Hkv + g) * a.l_max + p) * a.d;
 }
 
-// Plain-ALU kernel, any storage type: the reference path for fp32 caches.
+// Plain-ALU kernel, any storage type: fp32 caches, and bf16 ones whose page size is no power of two.
 template <typename T, int D>
 __global__ __launch_bounds__(256) void k_attn_split_valu(const AttnArgs a) {
   extern __shared__ float smem[];
@@ -282,13 +282,13 @@ constexpr size_t kCombineLdsMax = 60 * 1024;
 
 size_t combine_lds_bytes(int wgrid) { return (static_cast<size_t>((wgrid + 3) & ~3) + kCombThreads * 4) * sizeof(float); }
 
-bool attn_plan(AttnArgs& a, int num_cus) {
+static bool plan_as(AttnArgs& a, int num_cus, int use_mfma) {
   // The host knows only the upper bound l_max of the lengths; the kernels deal the keys that
   // are really there to the workgroups in equal shares.  Here only the number of workgroups is
   // set: as many as are resident at once (one or two of the matrix-core kernel per compute unit),
   // fewer when even the longest possible caches would leave them less than two granules (128
   // keys) each, more when a share could otherwise exceed what one segment can hold.
-  a.use_mfma = attn_mfma_supported(a) ? 1 : 0;
+  a.use_mfma = use_mfma;
   if (a.B > kAttnMaxSeqs || a.l_max < a.n_blk) return false;
   const int64_t units = static_cast<int64_t>(a.B) * a.Hkv;
   const int64_t gmax = (a.l_max + kAttnGran - 1) / kAttnGran;      // granules of the longest possible unit
@@ -306,6 +306,14 @@ bool attn_plan(AttnArgs& a, int num_cus) {
   if (combine_lds_bytes(static_cast<int>(w)) > kCombineLdsMax) return false;
   a.wgrid = static_cast<int>(w);
   return true;
+}
+
+bool attn_plan(AttnArgs& a, int num_cus) {
+  if (!attn_mfma_supported(a)) return plan_as(a, num_cus, 0);
+  // The matrix-core kernel keeps the page ids of a segment in LDS, which bounds a segment and so asks for
+  // many workgroups where the page tables could hold hundreds of millions of entries.  Where that is
+  // more than the merging kernel takes, 64-wide heads go to the ALU kernel, whose segments are unbounded.
+  return plan_as(a, num_cus, 1) || (a.d == 64 && plan_as(a, num_cus, 0));
 }
 
 int attn_slots(const AttnArgs& a) { return a.wgrid + a.B * a.Hkv; }

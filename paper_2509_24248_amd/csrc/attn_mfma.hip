@@ -1,12 +1,12 @@
-// bf16 verification attention on the matrix cores (head_dim 128), HBM-bound by design.
+// bf16 attention on the matrix cores (head_dim 128 or 64), HBM-bound by design.
 //
 // A workgroup takes an equal share of all keys of the launch (attn_sched.hpp): one or more
 // segments, each a key range of one (sequence, KV head) unit, processed against all
 // R = G * n_q query rows that share that head, so the cache is read once.
 //
 // Inside a workgroup there are two independent tile rings (key groups); ring kg takes the
-// 32-key tiles kg, kg+2, ... of the chunk.  A ring is S slots of 16 KB in LDS (K tile + V
-// tile).  Tiles are brought in by direct global->LDS loads (16 bytes per lane, streaming),
+// 32-key tiles kg, kg+2, ... of the chunk.  A ring is S slots in LDS (K tile + V tile: 16 KB
+// with 128-wide heads, 8 KB with 64-wide ones).  Tiles are brought in by direct global->LDS loads (16 bytes per lane, streaming),
 // issued S-1 tiles ahead by the ring's waves in turn, so most of the LDS holds bytes in
 // flight.  Each of the ring's NR waves owns one 16-row tile of the queries and computes it
 // against every tile of the ring:
@@ -27,19 +27,24 @@ namespace sx {
 namespace {
 
 constexpr int kNK = 2;                 // tile rings (key groups) per workgroup
-constexpr int kSlot = 16384;           // bytes of one ring slot: K tile then V tile
-constexpr int kORow = 132;             // floats per row of the merge buffer (128 + pad)
+constexpr int slot_bytes(int hd) { return 128 * hd; }   // one ring slot: 32 K rows then 32 V rows of hd bf16 values
+constexpr int o_row(int hd) { return hd + 4; }          // floats per row of the merge buffer (padded)
 // From kBigFrom waves per ring (more than 48 query rows per KV head) one workgroup is resident per
 // compute unit (its eight to sixteen waves need more than the 96-128 registers per lane that two
 // workgroups would leave them) and its rings take kBigStages slots; below that, two workgroups of
 // two-slot rings.  Measured at 64 / 72 rows per KV head (8B-like tree block / 32B-like chain block):
 // two resident workgroups with spills 41.6 us against 31.3 us with one; two, three and four slots
 // within 3 % of each other at 72 rows.
-constexpr int kBigFrom = 4, kBigStages = 4;
+// With 64-wide heads the output accumulators and the slots are half as large: two workgroups fit up to
+// four waves per ring, and the rings take twice the slots in the same LDS.  Measured at 64 rows per KV
+// head, contexts 1000-8000 of 8 sequences (74 MB): 26 us, where the ALU kernel that served this width took 356.
+constexpr int big_from(int hd) { return hd == 64 ? 5 : 4; }
+constexpr int stages_of(int hd, int nr) { return (nr >= big_from(hd) ? 4 : 2) * (hd == 64 ? 2 : 1); }
 // K operand reads / V operand read pairs issued ahead of the matrix instructions that use them: as
-// many as the registers allow (one resident workgroup: all eight K reads, four V pairs)
-constexpr int k_ahead(int nr) { return nr >= kBigFrom ? 8 : 4; }
-constexpr int v_ahead(int nr) { return nr >= kBigFrom ? 4 : 3; }
+// many as the registers allow (one resident workgroup: all eight K reads, four V pairs; 64-wide heads
+// have four of each)
+constexpr int k_ahead(int hd, int nr) { return hd == 128 && nr >= big_from(hd) ? 8 : 4; }
+constexpr int v_ahead(int hd, int nr) { return hd == 64 || nr >= big_from(hd) ? 4 : 3; }
 constexpr int kMaxChunkPages = 2048;   // page ids of one chunk kept in LDS (8 KB)
 
 typedef short s16x4_t __attribute__((ext_vector_type(4)));
@@ -49,8 +54,10 @@ typedef const __attribute__((address_space(1))) void* glb_ptr_t;
 // XOR swizzle of the 16-byte chunks of a tile row.  K rows are read one row per lane (16 rows
 // at once): chunk ^ (key % 16) spreads them over all banks.  V rows are read by the transpose
 // load, 4 rows x 2 adjacent chunks at once: chunk ^ (2 (key % 8)) keeps those eight apart.
-__device__ __forceinline__ int swz_k(int key) { return key & 15; }
-__device__ __forceinline__ int swz_v(int key) { return (key & 7) << 1; }
+// A 64-wide row is 8 chunks, two rows to the 256 bytes of all banks: the row's parity already picks
+// one half of them, the other bits of the key spread the chunks of that half.
+template <int HD> __device__ __forceinline__ int swz_k(int key) { return HD == 128 ? key & 15 : (key >> 1) & 7; }
+template <int HD> __device__ __forceinline__ int swz_v(int key) { return HD == 128 ? (key & 7) << 1 : ((key >> 1) & 3) << 1; }
 
 // s_waitcnt immediate that waits for vmcnt <= n only (gfx9 encoding: vmcnt in bits 3:0 and
 // 15:14, expcnt 6:4 and lgkmcnt 11:8 left at their maxima)
@@ -80,25 +87,34 @@ __device__ __forceinline__ void load_to_lds16(const void* src, const void* lds_b
 // LDS words of the schedule's prefix table (B + 1 entries, rounded to 16 bytes)
 __host__ __device__ constexpr int sched_words(int B) { return (B + 1 + 3) & ~3; }
 
-constexpr int front_bytes(int rp, int stages) {
-  return kNK * stages * kSlot > rp * kORow * 4 ? kNK * stages * kSlot : rp * kORow * 4;
+constexpr int front_bytes(int hd, int rp, int stages) {
+  return kNK * stages * slot_bytes(hd) > rp * o_row(hd) * 4 ? kNK * stages * slot_bytes(hd) : rp * o_row(hd) * 4;
 }
 
 // waves per SIMD the register allocation has to leave room for: the resident workgroups' waves on
 // four SIMDs
-constexpr int min_waves_per_simd(int nr) { return ((nr < kBigFrom ? 2 : 1) * kNK * nr + 3) / 4; }
+constexpr int min_waves_per_simd(int hd, int nr) { return ((nr < big_from(hd) ? 2 : 1) * kNK * nr + 3) / 4; }
 
 // NR waves per ring, each owning RTW 16-row tiles of the queries (rows 16 (rr RTW + t) ..).
 // RTW = 2 halves the LDS reads per query row (K and V operands are fetched once per wave and
 // used for both row tiles) at the price of fewer, fatter waves; measured slower than RTW = 1
 // at R = 72, so the launcher below uses one row tile per wave throughout.
-template <int NR, int RTW, int S, bool PAGED>
-__global__ __launch_bounds__(64 * kNK * NR, min_waves_per_simd(NR)) void k_attn_ring(const AttnArgs a) {
+template <int HD, int NR, int RTW, int S, bool PAGED>
+__global__ __launch_bounds__(64 * kNK * NR, min_waves_per_simd(HD, NR)) void k_attn_ring(const AttnArgs a) {
   constexpr int RP = 16 * NR * RTW;             // query rows covered (padded)
-  constexpr int kKAhead = k_ahead(NR), kVAhead = v_ahead(NR);
+  constexpr int kKAhead = k_ahead(HD, NR), kVAhead = v_ahead(HD, NR);
+  constexpr int kSlot = slot_bytes(HD), kORow = o_row(HD);
+  constexpr int kRowB = 2 * HD;                 // bytes of a cache row
+  constexpr int kChunks = HD / 8;               // 16-byte chunks of a cache row
+  constexpr int kKeysPP = 1024 / kRowB;         // keys of a 1 KB piece
+  constexpr int kTileP = 32 / kKeysPP;          // pieces of a K (or V) tile
+  // 64-wide heads keep their probabilities as a bf16 value plus the bf16 rounding of the rest (relative
+  // 2^-17): the ALU kernel that served them multiplied with fp32 probabilities
+  constexpr bool kSplitP = HD == 64;
+  constexpr int kKS = HD / 32, kDT = HD / 16;   // k steps of K Q^T, 16-wide column tiles of the output
   // LDS: [ring 0: S slots][ring 1: S slots] (later overlaid by the merge buffer [RP][kORow]),
   // then the (max, sum) table for the merge, the schedule's prefix table, the page ids of the segment
-  constexpr int kFront = front_bytes(RP, S);
+  constexpr int kFront = front_bytes(HD, RP, S);
   extern __shared__ uint4 smem4[];
   char* smem = reinterpret_cast<char*>(smem4);
   float* ml_lds = reinterpret_cast<float*>(smem + kFront);
@@ -131,7 +147,7 @@ __global__ __launch_bounds__(64 * kNK * NR, min_waves_per_simd(NR)) void k_attn_
   char* ring = smem + kg * (S * kSlot);
 
   // ---- Q^T operand pieces and the mask words of this wave's rows
-  uint4 qf[4][RTW];
+  uint4 qf[kKS][RTW];
   uint64_t rowmask[RTW];
   int rho[RTW];
 #pragma unroll
@@ -140,9 +156,9 @@ __global__ __launch_bounds__(64 * kNK * NR, min_waves_per_simd(NR)) void k_attn_
     const bool valid = rho[t] < R;
     const int i = valid ? rho[t] / G : 0;
     const int hh = valid ? rho[t] - i * G : 0;
-    const bf16_t* qp = static_cast<const bf16_t*>(a.q) + ((static_cast<size_t>(b) * a.n_q + i) * a.Hq + g * G + hh) * 128 + fq * 8;
+    const bf16_t* qp = static_cast<const bf16_t*>(a.q) + ((static_cast<size_t>(b) * a.n_q + i) * a.Hq + g * G + hh) * HD + fq * 8;
 #pragma unroll
-    for (int ks = 0; ks < 4; ++ks)
+    for (int ks = 0; ks < kKS; ++ks)
       qf[ks][t] = valid ? *reinterpret_cast<const uint4*>(qp + ks * 32) : make_uint4(0, 0, 0, 0);
     rowmask[t] = !valid ? 0ull : (a.mask ? a.mask[static_cast<size_t>(b) * a.mask_stride + i] : ((2ull << i) - 1ull));
   }
@@ -161,17 +177,20 @@ __global__ __launch_bounds__(64 * kNK * NR, min_waves_per_simd(NR)) void k_attn_
   __builtin_amdgcn_s_waitcnt(vmcnt_imm(0));    // from here on vmcnt counts tile loads only
   __syncthreads();
 
-  // ---- tile loads: the ring's waves take the 16 one-KB pieces of a tile in turn.  Piece j
-  // holds keys 4 (j % 8) .. + 3; lane l fetches key 4 (j % 8) + l / 16, 16-byte chunk
-  // (l % 16) ^ swizzle(key), and lands at piece base + 16 l, so that LDS entry [key][pos] holds
-  // chunk pos ^ swizzle(key).  The lane's byte offset inside a tile does not depend on the tile.
-  uint32_t lane_off[(16 + NR - 1) / NR];
+  // ---- tile loads: the ring's waves take the one-KB pieces of a tile (K, then V: kTileP each) in
+  // turn.  Piece j holds the kKeysPP keys from kKeysPP (j % kTileP) on; lane l fetches key
+  // l / kChunks of them, 16-byte chunk (l % kChunks) ^ swizzle(key), and lands at piece base + 16 l, so
+  // that LDS entry [key][pos] holds chunk pos ^ swizzle(key).  The lane's byte offset inside a tile
+  // does not depend on the tile.
+  constexpr int kPieces = (2 * kTileP + NR - 1) / NR;   // pieces a wave issues per tile, at most
+  const int lkey = lane / kChunks, lpos = lane % kChunks;
+  uint32_t lane_off[kPieces];
 #pragma unroll
-  for (int u = 0; u < (16 + NR - 1) / NR; ++u) {
-    const int key = 4 * ((rr + u * NR) & 7) + fq;
+  for (int u = 0; u < kPieces; ++u) {
+    const int key = kKeysPP * ((rr + u * NR) & (kTileP - 1)) + lkey;
     const int in_row = PAGED ? (key & (a.page_size - 1)) : key;
-    const int sw = ((rr + u * NR) & 8) ? swz_v(key) : swz_k(key);   // pieces 8..15 are V
-    lane_off[u] = static_cast<uint32_t>(in_row) * 256u + static_cast<uint32_t>((fr ^ sw) << 4);
+    const int sw = ((rr + u * NR) & kTileP) ? swz_v<HD>(key) : swz_k<HD>(key);
+    lane_off[u] = static_cast<uint32_t>(in_row) * kRowB + static_cast<uint32_t>((lpos ^ sw) << 4);
   }
   const size_t seq_row = PAGED ? 0 : (static_cast<size_t>(b) * a.Hkv + g) * a.l_max;
   auto issue = [&](int it) {
@@ -194,11 +213,11 @@ __global__ __launch_bounds__(64 * kNK * NR, min_waves_per_simd(NR)) void k_attn_
       // whole tile inside the range: uniform base per piece + the lane's constant offset
       const size_t in_page = PAGED ? static_cast<size_t>(t0 & (a.page_size - 1)) : static_cast<size_t>(t0);
 #pragma unroll
-      for (int u = 0; u < (16 + NR - 1) / NR; ++u) {
-        const int j = rr + u * NR;             // piece: 0..7 K keys 4j.., 8..15 V keys 4(j-8)..
-        if (j < 16) {
-          const bool second = PAGED && a.page_size == 16 && (j & 4);   // keys 16..31 sit in the next page
-          const char* base = static_cast<const char*>(j < 8 ? a.k : a.v) + ((second ? row_b : row_a) + in_page) * 256;
+      for (int u = 0; u < kPieces; ++u) {
+        const int j = rr + u * NR;
+        if (j < 2 * kTileP) {
+          const bool second = PAGED && a.page_size == 16 && (j & (kTileP / 2));   // keys 16..31 sit in the next page
+          const char* base = static_cast<const char*>(j < kTileP ? a.k : a.v) + ((second ? row_b : row_a) + in_page) * kRowB;
           load_to_lds16(base, lane_off[u], slot + j * 1024);
         }
       }
@@ -206,30 +225,29 @@ __global__ __launch_bounds__(64 * kNK * NR, min_waves_per_simd(NR)) void k_attn_
     }
     const int page0 = t0 >> ps_shift;
 #pragma unroll
-    for (int u = 0; u < (16 + NR - 1) / NR; ++u) {
+    for (int u = 0; u < kPieces; ++u) {
       const int j = rr + u * NR;
-      if (j < 16) {
-        const int i = j & 7;
-        const int key = 4 * i + fq;
+      if (j < 2 * kTileP) {
+        const int key = kKeysPP * (j & (kTileP - 1)) + lkey;
         const int p = min(t0 + key, s1 - 1);   // keys past the range are masked in the softmax
         size_t row;
         if (PAGED) row = ((p >> ps_shift) == page0 ? row_a : row_b) + (p & (a.page_size - 1));
         else row = row_a + p;
-        const char* src = static_cast<const char*>(j < 8 ? a.k : a.v) + row * 256 + ((fr ^ (j < 8 ? swz_k(key) : swz_v(key))) << 4);
+        const char* src = static_cast<const char*>(j < kTileP ? a.k : a.v) + row * kRowB + ((lpos ^ (j < kTileP ? swz_k<HD>(key) : swz_v<HD>(key))) << 4);
         load_to_lds16(src, slot + j * 1024);
       }
     }
   };
-  constexpr int kPiecesMin = 16 / NR;          // pieces every wave of a ring issues per tile, at least
+  constexpr int kPiecesMin = 2 * kTileP / NR;  // pieces every wave of a ring issues per tile, at least
 
-  f32x4_t oacc[8][RTW];
+  f32x4_t oacc[kDT][RTW];
   float m_run[RTW], l_run[RTW];
 #pragma unroll
   for (int t = 0; t < RTW; ++t) {
     m_run[t] = -INFINITY;
     l_run[t] = 0.f;
 #pragma unroll
-    for (int dt = 0; dt < 8; ++dt) oacc[dt][t] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+    for (int dt = 0; dt < kDT; ++dt) oacc[dt][t] = f32x4_t{0.f, 0.f, 0.f, 0.f};
   }
   const float sl2 = a.scale * 1.44269504088896340736f;  // scores are kept in log2 units
 
@@ -251,7 +269,7 @@ __global__ __launch_bounds__(64 * kNK * NR, min_waves_per_simd(NR)) void k_attn_
     if (ti >= ntl) continue;
     const int t0 = s0 + 32 * ti;
     const char* k_lds = ring + (it % S) * kSlot;
-    const char* v_lds = k_lds + 8192;
+    const char* v_lds = k_lds + kSlot / 2;
 
     // ---- S^T = K Q^T for the two 16-key halves.  The K operand reads run kKAhead reads ahead of the
     // matrix instructions that use them, and the first V operand reads are issued here as well (they do
@@ -264,28 +282,29 @@ __global__ __launch_bounds__(64 * kNK * NR, min_waves_per_simd(NR)) void k_attn_
       for (int t = 0; t < RTW; ++t) sacc[j][t] = f32x4_t{0.f, 0.f, 0.f, 0.f};
     auto kread = [&](int i) {       // read i: k step i / 2, key half i % 2
       const int ks = i >> 1, j = i & 1;
-      return reinterpret_cast<const uint4*>(k_lds)[(16 * j + fr) * 16 + ((4 * ks + fq) ^ fr)];
+      return reinterpret_cast<const uint4*>(k_lds)[(16 * j + fr) * kChunks + ((4 * ks + fq) ^ swz_k<HD>(fr))];
     };
     // Transpose load of V: within 16 lanes, lane i = 4 e + c points at key e's four values
     // d0 + 4c .. d0 + 4c + 3 and lane j receives column d0 + j of keys e = 0..3.  Two loads give the
     // 8 keys of the operand in the order P^T uses: 4q..4q+3 of the first half, then of the second half.
     const int ve = fr >> 2, vc = fr & 3;
     const int key0 = 4 * fq + ve, key1 = 16 + key0;
-    s16x4_t vlo[8], vhi[8];
+    s16x4_t vlo[kDT], vhi[kDT];
     auto vread = [&](int dt) {
       const int chunk = 2 * dt + (vc >> 1);
-      const char* p0 = v_lds + key0 * 256 + ((chunk ^ swz_v(key0)) << 4) + ((vc & 1) << 3);
-      const char* p1 = v_lds + key1 * 256 + ((chunk ^ swz_v(key1)) << 4) + ((vc & 1) << 3);
+      const char* p0 = v_lds + key0 * kRowB + ((chunk ^ swz_v<HD>(key0)) << 4) + ((vc & 1) << 3);
+      const char* p1 = v_lds + key1 * kRowB + ((chunk ^ swz_v<HD>(key1)) << 4) + ((vc & 1) << 3);
       vlo[dt] = __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) s16x4_t*)(lds_ptr_t)p0);
       vhi[dt] = __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) s16x4_t*)(lds_ptr_t)p1);
     };
-    uint4 kf[8];
+    constexpr int kReads = 2 * kKS;
+    uint4 kf[kReads];
 #pragma unroll
     for (int i = 0; i < kKAhead; ++i) kf[i] = kread(i);
 #pragma unroll
-    for (int i = 0; i < 8; ++i) {
-      if (i + kKAhead < 8) kf[i + kKAhead] = kread(i + kKAhead);
-      if (i >= 8 - kVAhead) vread(i - (8 - kVAhead));      // the last K steps also start the V reads
+    for (int i = 0; i < kReads; ++i) {
+      if (i + kKAhead < kReads) kf[i + kKAhead] = kread(i + kKAhead);
+      if (i >= kReads - kVAhead) vread(i - (kReads - kVAhead));      // the last K steps also start the V reads
       __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
       for (int t = 0; t < RTW; ++t)
@@ -296,7 +315,7 @@ __global__ __launch_bounds__(64 * kNK * NR, min_waves_per_simd(NR)) void k_attn_
 
     // ---- online softmax; lane (row, q) owns keys t0 + 16 j + 4 q + e of its row
     const bool need_mask = t0 + 32 > min(L, s1);
-    uint4 pf[RTW];
+    uint4 pf[RTW], pl[RTW];
     float alpha[RTW];
     bool rescale = false;
 #pragma unroll
@@ -332,6 +351,12 @@ __global__ __launch_bounds__(64 * kNK * NR, min_waves_per_simd(NR)) void k_attn_
       }
       pf[t] = make_uint4(pack_bf16x2(pr[0], pr[1]), pack_bf16x2(pr[2], pr[3]), pack_bf16x2(pr[4], pr[5]),
                          pack_bf16x2(pr[6], pr[7]));
+      if constexpr (kSplitP) {
+        float hi[8];
+        unpack16(pf[t], hi);
+        pl[t] = make_uint4(pack_bf16x2(pr[0] - hi[0], pr[1] - hi[1]), pack_bf16x2(pr[2] - hi[2], pr[3] - hi[3]),
+                           pack_bf16x2(pr[4] - hi[4], pr[5] - hi[5]), pack_bf16x2(pr[6] - hi[6], pr[7] - hi[7]));
+      }
       l_run[t] = l_run[t] * al + (((pr[0] + pr[1]) + (pr[2] + pr[3])) + ((pr[4] + pr[5]) + (pr[6] + pr[7])));
       m_run[t] = m_new;
       alpha[t] = al;
@@ -341,7 +366,7 @@ __global__ __launch_bounds__(64 * kNK * NR, min_waves_per_simd(NR)) void k_attn_
 #pragma unroll
       for (int t = 0; t < RTW; ++t)
 #pragma unroll
-        for (int dt = 0; dt < 8; ++dt) {
+        for (int dt = 0; dt < kDT; ++dt) {
           oacc[dt][t][0] *= alpha[t]; oacc[dt][t][1] *= alpha[t];
           oacc[dt][t][2] *= alpha[t]; oacc[dt][t][3] *= alpha[t];
         }
@@ -350,14 +375,17 @@ __global__ __launch_bounds__(64 * kNK * NR, min_waves_per_simd(NR)) void k_attn_
     // ---- O^T += V^T P^T, the V operand reads kVAhead matrix instructions ahead
     __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-    for (int dt = 0; dt < 8; ++dt) {
-      if (dt + kVAhead < 8) vread(dt + kVAhead);
+    for (int dt = 0; dt < kDT; ++dt) {
+      if (dt + kVAhead < kDT) vread(dt + kVAhead);
       __builtin_amdgcn_sched_barrier(0);
       const uint2 l2 = __builtin_bit_cast(uint2, vlo[dt]), h2 = __builtin_bit_cast(uint2, vhi[dt]);
       const bf16x8_t va = __builtin_bit_cast(bf16x8_t, make_uint4(l2.x, l2.y, h2.x, h2.y));
 #pragma unroll
-      for (int t = 0; t < RTW; ++t)
+      for (int t = 0; t < RTW; ++t) {
         oacc[dt][t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(va, __builtin_bit_cast(bf16x8_t, pf[t]), oacc[dt][t], 0, 0, 0);
+        if constexpr (kSplitP)
+          oacc[dt][t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(va, __builtin_bit_cast(bf16x8_t, pl[t]), oacc[dt][t], 0, 0, 0);
+      }
       __builtin_amdgcn_sched_barrier(0);
     }
   }
@@ -402,7 +430,7 @@ __global__ __launch_bounds__(64 * kNK * NR, min_waves_per_simd(NR)) void k_attn_
 #pragma unroll
       for (int t = 0; t < RTW; ++t)
 #pragma unroll
-        for (int dt = 0; dt < 8; ++dt) {
+        for (int dt = 0; dt < kDT; ++dt) {
           float4* dst = reinterpret_cast<float4*>(o_lds + rho[t] * kORow + 16 * dt + 4 * fq);
           float4 v = make_float4(oacc[dt][t][0] * fself[t], oacc[dt][t][1] * fself[t], oacc[dt][t][2] * fself[t],
                                  oacc[dt][t][3] * fself[t]);
@@ -415,9 +443,9 @@ __global__ __launch_bounds__(64 * kNK * NR, min_waves_per_simd(NR)) void k_attn_
     }
     __syncthreads();
   }
-  for (int idx = threadIdx.x; idx < R * 32; idx += 64 * kNK * NR) {
-    const int r = idx >> 5, c4 = idx & 31;
-    *reinterpret_cast<float4*>(a.part_o + (unit * R + r) * 128 + c4 * 4) =
+  for (int idx = threadIdx.x; idx < R * (HD / 4); idx += 64 * kNK * NR) {
+    const int r = idx / (HD / 4), c4 = idx % (HD / 4);
+    *reinterpret_cast<float4*>(a.part_o + (unit * R + r) * HD + c4 * 4) =
         *reinterpret_cast<const float4*>(o_lds + r * kORow + c4 * 4);
   }
   // a further segment refills the rings under the merge buffer: its first loads are issued after
@@ -425,23 +453,38 @@ __global__ __launch_bounds__(64 * kNK * NR, min_waves_per_simd(NR)) void k_attn_
   }
 }
 
-template <int NR, int RTW, int S, bool PAGED>
+template <int HD, int NR, int S, bool PAGED>
 hipError_t launch_one(const AttnArgs& a, hipStream_t s) {
-  static_assert(NR * RTW <= 8, "at most 128 query rows");
+  static_assert(NR <= 8, "at most 128 query rows");
   // set once per process; a function-local static is initialised under the language's own lock,
   // so first calls from several host threads are safe
-  static const hipError_t attr = hipFuncSetAttribute(reinterpret_cast<const void*>(&k_attn_ring<NR, RTW, S, PAGED>),
+  static const hipError_t attr = hipFuncSetAttribute(reinterpret_cast<const void*>(&k_attn_ring<HD, NR, 1, S, PAGED>),
                                              hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
   if (attr != hipSuccess) return attr;
-  hipLaunchKernelGGL((k_attn_ring<NR, RTW, S, PAGED>), dim3(a.wgrid), dim3(64 * kNK * NR), attn_mfma_lds_bytes(a), s, a);
+  hipLaunchKernelGGL((k_attn_ring<HD, NR, 1, S, PAGED>), dim3(a.wgrid), dim3(64 * kNK * NR), attn_mfma_lds_bytes(a), s, a);
   return hipGetLastError();
 }
 
-template <int NR, int RTW>
+template <int HD, int NR>
 hipError_t launch_nr(const AttnArgs& a, hipStream_t s) {
-  if constexpr (NR >= kBigFrom)
-    return a.paged ? launch_one<NR, RTW, kBigStages, true>(a, s) : launch_one<NR, RTW, kBigStages, false>(a, s);
-  return a.paged ? launch_one<NR, RTW, 2, true>(a, s) : launch_one<NR, RTW, 2, false>(a, s);
+  constexpr int S = stages_of(HD, NR);
+  return a.paged ? launch_one<HD, NR, S, true>(a, s) : launch_one<HD, NR, S, false>(a, s);
+}
+
+template <int HD>
+hipError_t launch_hd(const AttnArgs& a, hipStream_t s) {
+  const int R = (a.Hq / a.Hkv) * a.n_q;
+  switch ((R + 15) / 16) {
+    case 1: return launch_nr<HD, 1>(a, s);
+    case 2: return launch_nr<HD, 2>(a, s);
+    case 3: return launch_nr<HD, 3>(a, s);
+    case 4: return launch_nr<HD, 4>(a, s);
+    case 5: return launch_nr<HD, 5>(a, s);
+    case 6: return launch_nr<HD, 6>(a, s);
+    case 7: return launch_nr<HD, 7>(a, s);
+    case 8: return launch_nr<HD, 8>(a, s);
+    default: return hipErrorInvalidValue;
+  }
 }
 
 }  // namespace
@@ -449,34 +492,22 @@ hipError_t launch_nr(const AttnArgs& a, hipStream_t s) {
 bool attn_mfma_supported(const AttnArgs& a) {
   const int R = (a.Hq / a.Hkv) * a.n_q;
   const bool pow2 = (a.page_size & (a.page_size - 1)) == 0;
-  return a.dtype == 1 && a.d == 128 && R <= 128 && (!a.paged || (pow2 && a.page_size >= 16));
+  return a.dtype == 1 && (a.d == 128 || a.d == 64) && R <= 128 && (!a.paged || (pow2 && a.page_size >= 16));
 }
 
-// Workgroups per compute unit and ring depth (see kBigFrom).
-int attn_mfma_per_cu(const AttnArgs& a) { return ((a.Hq / a.Hkv) * a.n_q + 15) / 16 >= kBigFrom ? 1 : 2; }
-int attn_mfma_stages(const AttnArgs& a) { return attn_mfma_per_cu(a) == 1 ? kBigStages : 2; }
+// Workgroups per compute unit and ring depth (see big_from).
+static int waves_per_ring(const AttnArgs& a) { return ((a.Hq / a.Hkv) * a.n_q + 15) / 16; }
+int attn_mfma_per_cu(const AttnArgs& a) { return waves_per_ring(a) >= big_from(a.d) ? 1 : 2; }
+int attn_mfma_stages(const AttnArgs& a) { return stages_of(a.d, waves_per_ring(a)); }
 
 size_t attn_mfma_lds_bytes(const AttnArgs& a) {
-  const int rp = 16 * (((a.Hq / a.Hkv) * a.n_q + 15) / 16);
-  return static_cast<size_t>(front_bytes(rp, a.stages)) + static_cast<size_t>(kNK) * rp * 2 * sizeof(float) +
+  const int rp = 16 * waves_per_ring(a);
+  return static_cast<size_t>(front_bytes(a.d, rp, a.stages)) + static_cast<size_t>(kNK) * rp * 2 * sizeof(float) +
          static_cast<size_t>(sched_words(a.B)) * sizeof(int) + (a.paged ? static_cast<size_t>(kMaxChunkPages + 1) * sizeof(int) : 0);
 }
 
 int attn_mfma_max_chunk(const AttnArgs& a) { return a.paged ? kMaxChunkPages * a.page_size : (1 << 30); }
 
-hipError_t launch_attn_mfma(const AttnArgs& a, hipStream_t s) {
-  const int R = (a.Hq / a.Hkv) * a.n_q;
-  switch ((R + 15) / 16) {
-    case 1: return launch_nr<1, 1>(a, s);
-    case 2: return launch_nr<2, 1>(a, s);
-    case 3: return launch_nr<3, 1>(a, s);
-    case 4: return launch_nr<4, 1>(a, s);
-    case 5: return launch_nr<5, 1>(a, s);
-    case 6: return launch_nr<6, 1>(a, s);
-    case 7: return launch_nr<7, 1>(a, s);
-    case 8: return launch_nr<8, 1>(a, s);
-    default: return hipErrorInvalidValue;
-  }
-}
+hipError_t launch_attn_mfma(const AttnArgs& a, hipStream_t s) { return a.d == 64 ? launch_hd<64>(a, s) : launch_hd<128>(a, s); }
 
 }  // namespace sx

@@ -197,7 +197,7 @@ struct AttnArgs {
   int64_t n_pages;           // paged: pages in the pool (page ids are forced into it)
   int* status;               // device error word or nullptr: first out-of-range length / page id seen
   int stages;                // matrix-core kernel: slots per tile ring (attn_plan)
-  int use_mfma;              // matrix-core kernel (bf16, head_dim 128); its maxima are in log2 units
+  int use_mfma;              // matrix-core kernel (bf16); its maxima are in log2 units
 };
 bool attn_mfma_supported(const AttnArgs& a);
 size_t attn_mfma_lds_bytes(const AttnArgs& a);  // dynamic LDS of the matrix-core kernel as planned

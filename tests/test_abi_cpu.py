@@ -83,3 +83,17 @@ def test_generic_workspace_query_agrees_with_the_per_call_queries():
     assert sx.specexit_verify_attn_workspace_bytes(kv, 2000, 7, 32) == 0 and "1024 sequences" in sx.last_error()
     kv.l_max = 4
     assert sx.specexit_verify_attn_workspace_bytes(kv, 1, 7, 32) == 0 and "fewer than the block" in sx.last_error()
+
+
+@pytest.mark.skipif(not os.path.exists(LIB), reason="libspecexit.so not built")
+def test_wide_page_tables_of_narrow_heads_are_still_accepted():
+    # page tables that could hold far more entries than a segment of the matrix-core kernel spans: 64-wide
+    # heads then go to the kernel whose segments are unbounded, instead of being refused
+    from paper_2509_24248_amd import binding as sx
+    kv = sx.KVView()
+    kv.struct_size = ctypes.sizeof(sx.KVView)
+    kv.layout, kv.dtype, kv.n_kv_heads, kv.head_dim, kv.k, kv.v = 1, 1, 8, 64, 256, 256
+    kv.page_table, kv.page_size, kv.n_pages = 256, 16, 1 << 20
+    for max_pages in (64, 8192, 1 << 15):
+        kv.max_pages_per_seq = max_pages
+        assert sx.specexit_verify_attn_workspace_bytes(kv, 1024, 7, 32) > 0, (max_pages, sx.last_error())

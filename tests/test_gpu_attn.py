@@ -67,6 +67,20 @@ def test_many_short_sequences(dtype, B, paged):
     check(shape, L, kv, q, mask, label="many sequences")
 
 
+@pytest.mark.parametrize("n_q,Hq,Hkv,page", [(1, 4, 1, 16), (4, 8, 2, 16), (5, 8, 2, 32), (16, 8, 2, 0), (16, 8, 2, 64), (9, 16, 2, 128),
+                                             (24, 4, 1, 16), (32, 4, 1, 32), (32, 4, 1, 0)])
+def test_narrow_heads_at_tile_edges(n_q, Hq, Hkv, page):
+    # 64-wide heads on the matrix cores: one to eight row tiles with and without a ragged last one, pages
+    # below, at and above the 32-key tile, lengths around the tile and granule edges.  Probabilities keep
+    # 16 bits of mantissa, so the error is the bf16 rounding of the output: at most 2^-9 of the largest value.
+    shape = gen.scaled(gen.config(1), B=6, Hq=Hq, Hkv=Hkv, d=64, n_q=n_q, k=min(5, max(n_q - 1, 1)), ctx=(0, 900), page_size=page or 16)
+    L, kv, q, mask = case(shape, 11, tree=n_q > 1 and page != 0, paged=page > 0)
+    for b, n in enumerate((0, 31, 32, 64 - n_q if n_q < 64 else 1, 63)):
+        L[b] = n
+    err = check(shape, L, kv, q, mask, label=f"d64 page {page}")
+    assert err < 2.0 ** -8
+
+
 def test_paged_equals_contiguous_on_gpu():
     shape = gen.scaled(gen.config(2), B=4, Hq=8, Hkv=2, ctx=(30, 1200))
     L, kv, q, mask = case(shape, 3, paged=False)
