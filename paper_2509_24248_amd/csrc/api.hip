@@ -166,16 +166,17 @@ struct DraftPlan {
   GemvArgs vfc, vqkv, vo, vgu, vdown, vhead;
   AttnArgs attn;
   size_t partial_bytes;
-  int ntiles_head;
+  int head_lists;    // candidate lists per row of the head, at most
 };
 
-void plan_gemm(GemmArgs& g, int N, int K, int M, int planes, bool mfma, int V) {
+void plan_gemm(GemmArgs& g, int N, int K, int M, int planes, bool mfma, int V, int top_b = 0) {
   memset(&g, 0, sizeof(g));
   g.N = N;
   g.K = K;
   g.M = M;
   g.planes = mfma ? planes : 1;
   g.V = V;
+  g.top_b = top_b;
   g.nseg = 1;
   g.seg_end[0] = g.seg_end[1] = g.seg_end[2] = N;
   choose_ksplit(g, mfma, num_cus());
@@ -258,10 +259,10 @@ int32_t make_draft_plan(DraftPlan& p, const specexit_model_desc* d, const specex
     p.vfc.stream = p.vqkv.stream = p.vo.stream = p.vgu.stream = p.vdown.stream = stream;
     p.vhead.stream = 1;
   }
-  plan_gemm(p.head, dm.V + 3, D, B, 2, p.mfma, dm.V);
+  plan_gemm(p.head, dm.V + 3, D, B, 2, p.mfma, dm.V, top_b);
   p.head.n_extra = 3;
-  p.head.top_b = top_b;
-  p.ntiles_head = gemm_ntiles(dm.V + 3);
+  p.head_lists = p.head.wide ? head_wide_groups(p.head) : 1;
+  if (p.gemv && p.vhead.grid > p.head_lists) p.head_lists = p.vhead.grid;
   size_t pb = 0;
   const GemmArgs* all[6] = {&p.fc, &p.qkv, &p.o, &p.gu, &p.down, &p.head};
   for (const GemmArgs* g : all) {
@@ -286,6 +287,7 @@ struct DraftBufs {
   float* ssq;        // [3][rows][groups of D]: pieces of the sums of squares behind the three norms
   int* counters;     // arrival counters of the reducing GEMM epilogues
   int n_counters;
+  char* head_pack;   // the widened head's activations in operand order
   size_t total;
 };
 
@@ -301,14 +303,15 @@ DraftBufs carve_draft(const DraftPlan& p, void* ws) {
   b.q_buf = c.take<char>(es * p.B * p.dm.Hq * p.dm.d);
   b.attn_out = c.take<char>(es * p.B * p.dm.Hq * p.dm.d);
   b.attn_ws = c.take<char>(attn_workspace_bytes(p.attn));
-  b.part_val = c.take<float>(sizeof(float) * p.B * p.ntiles_head * p.top_b);
-  b.part_idx = c.take<int>(sizeof(int) * p.B * p.ntiles_head * p.top_b);
+  b.part_val = c.take<float>(sizeof(float) * p.B * p.head_lists * p.top_b);
+  b.part_idx = c.take<int>(sizeof(int) * p.B * p.head_lists * p.top_b);
   b.head_am = c.take<int32_t>(sizeof(int32_t) * p.B);
   b.extra = c.take<float>(sizeof(float) * p.B * 3);
   const int gd = p.gemv ? 3 * num_cus() : gemm_groups(p.dm.D);   // pieces per row: GEMV workgroups or 128-row groups
   b.ssq = c.take<float>(sizeof(float) * 3 * p.B * gd);
   b.n_counters = 3 * gd + gemm_groups((p.dm.Hq + 2 * p.dm.Hkv) * p.dm.d);
   b.counters = c.take<int>(sizeof(int) * b.n_counters);
+  b.head_pack = c.take<char>(head_wide_pack_bytes(p.head));
   b.total = c.off;
   return b;
 }
@@ -552,14 +555,15 @@ int32_t run_draft(DraftPlan& p, const specexit_draft_weights* w, const specexit_
   }
   {
     ProfScope prof(SPECEXIT_PROF_DRAFT_HEAD_GEMM, s);
+    p.head.a_packed = b.head_pack;
     if ((rc = run_gemm(p.head, mf, bf16, w->w_head, nullptr, nullptr, b, s, "gemm head"))) return rc;
   }
   if (mf) {
+    const int lists = head_wide_groups(p.head);   // candidate lists per row
     if (p.top_b == 1 && !io.cand_logit)
-      return check_hip(launch_argmax_finalize(b.part_val, b.part_idx, p.ntiles_head, B, io.cand_tok, nullptr, s, b.extra,
+      return check_hip(launch_argmax_finalize(b.part_val, b.part_idx, lists, B, io.cand_tok, nullptr, s, b.extra,
                                               dm.rem_activation, io.sig_raw, io.sig), "argmax finalize");
-    // ranked candidates arrive merged per 128-row workgroup, a plain maximum per 16-row tile
-    const int C = (p.top_b > 1 ? gemm_groups(dm.V + 3) : p.ntiles_head) * p.top_b;
+    const int C = lists * p.top_b;
     return check_hip(launch_topb_finalize(b.part_val, b.part_idx, C, C, p.top_b, B, io.cand_tok, io.cand_logit, s,
                                           b.extra, dm.rem_activation, io.sig_raw, io.sig), "top-b finalize");
   }
@@ -718,7 +722,6 @@ namespace {
 struct HeadPlan {
   bool mfma;
   GemmArgs g;
-  int ntiles;
   size_t act_bytes, partial_bytes, pv_bytes, pack_bytes;
 };
 int32_t make_head_plan(HeadPlan& h, int32_t dtype, int32_t M, int32_t D, int32_t V, int32_t n_extra) {
@@ -729,10 +732,9 @@ int32_t make_head_plan(HeadPlan& h, int32_t dtype, int32_t M, int32_t D, int32_t
   h.mfma = dtype == SPECEXIT_BF16 && gemm_mfma_supported(M, 1, D);
   plan_gemm(h.g, V + n_extra, D, M, 1, h.mfma, V);
   h.g.n_extra = n_extra;
-  h.ntiles = gemm_ntiles(V + n_extra);
   h.act_bytes = (!h.mfma && dtype == SPECEXIT_BF16) ? sizeof(float) * M * D : 0;
   h.partial_bytes = h.mfma ? 0 : sizeof(float) * M * (static_cast<size_t>(V) + n_extra);
-  h.pv_bytes = h.mfma ? sizeof(float) * M * (h.g.wide ? head_wide_groups(h.g) : h.ntiles) : 0;
+  h.pv_bytes = h.mfma ? sizeof(float) * M * head_wide_groups(h.g) : 0;
   h.pack_bytes = h.mfma ? head_wide_pack_bytes(h.g) : 0;
   return SPECEXIT_OK;
 }
@@ -779,7 +781,7 @@ int32_t specexit_lmhead_argmax(int32_t dtype, int32_t M, int32_t D, int32_t V, i
       ProfScope prof(SPECEXIT_PROF_LMHEAD_GEMM, s);
       if ((rc = check_hip(launch_gemm_mfma(g, s), "gemm lm head"))) return rc;
     }
-    return check_hip(launch_argmax_finalize(pv, pi, g.wide ? head_wide_groups(g) : h.ntiles, M, argmax, max_logit, s), "argmax finalize");
+    return check_hip(launch_argmax_finalize(pv, pi, head_wide_groups(g), M, argmax, max_logit, s), "argmax finalize");
   }
   if (bf16) {
     if ((rc = check_hip(launch_unpack_rows(hidden, true, M, D, act, s), "unpack hidden"))) return rc;

@@ -1,5 +1,5 @@
-// Skinny weight-streaming GEMMs  out[m][n] = sum_k act[m][k] * w[n][k]  (M <= 144 rows),
-// used for the draft layer's projections, the widened head (Eq. 1) and the target LM head.
+// Skinny weight-streaming GEMMs  out[m][n] = sum_k act[m][k] * w[n][k] of the draft layer's
+// projections (the widened head and the LM head in bf16: gemm_wide.hip).
 // They are HBM-bound: every weight byte is read once, with 16-byte loads coalesced along K.
 //
 //  k_gemv_valu  : plain fp32 ALU path (fp32 weights, or any shape the MFMA path rejects).
@@ -7,8 +7,7 @@
 //                 rows arrive as 256-byte coalesced segments, pass through a wave-private,
 //                 XOR-swizzled LDS tile to reach the MFMA operand layout (row = lane % 16,
 //                 8 consecutive k per lane) and are contracted with pre-packed activation
-//                 fragments by v_mfma_f32_16x16x32_bf16.  The argmax over the vocabulary is
-//                 fused into the epilogue, so logits are never written.
+//                 fragments by v_mfma_f32_16x16x32_bf16.
 #include "common.hpp"
 #include "kernels.hpp"
 
@@ -92,7 +91,6 @@ __global__ __launch_bounds__(256) void k_gemv_valu(const GemmArgs g) {
 
 // ------------------------------------------------------------------------- MFMA path
 constexpr int kGemmWaves = 8;   // waves per workgroup, one 16-row weight tile each
-constexpr int kHeadWaves = 8;    // head-mode kernels (4 and 16 waves per workgroup were measured slower, at 7 and at 56 rows)
 
 typedef uint32_t u32x4_t __attribute__((ext_vector_type(4)));
 
@@ -179,10 +177,10 @@ __device__ __forceinline__ void stage_activations(const GemmArgs& g, uint4* a_ld
   }
 }
 
-template <int MT, int PLANES, bool HEAD>
-__global__ __launch_bounds__(64 * (HEAD ? kHeadWaves : kGemmWaves))
+template <int MT, int PLANES>
+__global__ __launch_bounds__(64 * kGemmWaves)
 void k_gemm_mfma(const GemmArgs g) {
-  constexpr int NW = HEAD ? kHeadWaves : kGemmWaves;
+  constexpr int NW = kGemmWaves;
   // LDS: [activation pieces of one K chunk, or two one-block buffers][per wave: one 16-row x 128-k weight tile, 4 KB]
   // weight tile entry [row][pos] holds the 16-byte piece (pos ^ row) of that row, so both the
   // coalesced writes and the per-row operand reads touch 16 distinct 16-byte slots
@@ -214,7 +212,7 @@ void k_gemm_mfma(const GemmArgs g) {
   const int wv = threadIdx.x >> 6;
   const int ntiles = (g.N + 15) >> 4;
   // tiles of this workgroup: NW in a row, or (plain projections spread over more workgroups) an equal share
-  const bool spread = !HEAD && g.spread > 0 && g.epi == 0;
+  const bool spread = g.spread > 0 && g.epi == 0;
   const int t_lo = spread ? static_cast<int>(static_cast<int64_t>(blockIdx.x) * ntiles / gridDim.x) : static_cast<int>(blockIdx.x) * NW;
   const int t_hi = spread ? static_cast<int>(static_cast<int64_t>(blockIdx.x + 1) * ntiles / gridDim.x) : ntiles;
   const int tile = t_lo + wv;
@@ -252,12 +250,7 @@ void k_gemm_mfma(const GemmArgs g) {
   // register sets after it, and the waits of those copies pull the loads back into the step that
   // issued them.  Waves that have no tile of their own (past the last tile) redo the last tile for the
   // same reason and drop the result.
-  // Split projections run for a few microseconds only: their first blocks are requested before
-  // the activations are staged.  A head with more than 16 activation rows (times planes) has at most
-  // three workgroups per compute unit, each held up by barriers per chunk or block: requests that stay
-  // in flight across those keep the memory system busy (measured at 16 fp32 rows: 272 -> 263 us).
-  // Heads with fewer rows have the waves to do that without and load each block where it is used.
-  constexpr bool AHEAD = !HEAD || MT >= 2;
+  // The first blocks are requested before the activations are staged.
   const int kb_last = kb1 - 1;
   uint4 wA[4], wB[4];
   const char* const spare = static_cast<const char*>(g.w[0]);   // where requests past the end are pointed
@@ -267,18 +260,15 @@ void k_gemm_mfma(const GemmArgs g) {
 #pragma unroll
     for (int i = 0; i < 4; ++i) dst[i] = load_stream16(real ? src[i] + off : spare);
   };
-  if constexpr (AHEAD) {
-    request(wA, kb0);
-    request(wB, kb0 + 1);
-  }
+  request(wA, kb0);
+  request(wB, kb0 + 1);
   // one 128-k block: this wave's weight tile (in wr) through its private LDS tile, transposed
   // into MFMA operands, against the activation pieces at ab0 (k piece 0, row 0 of the block);
   // dead: the half step past an odd block count
   auto one_tile = [&](uint4 (&wr)[4], int kb, const uint4* ab0, bool dead) {
-    if constexpr (!AHEAD) request(wr, kb);
 #pragma unroll
     for (int i = 0; i < 4; ++i) my[(4 * i + (lane >> 4)) * 16 + pos] = wr[i];
-    if constexpr (AHEAD) request(wr, kb + 2);
+    request(wr, kb + 2);
     // the tile is private to this wave, whose LDS operations retire in order: a compiler
     // fence is all that separates the writes from the transposed reads
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
@@ -322,258 +312,160 @@ void k_gemm_mfma(const GemmArgs g) {
     half(wA, kb);
     half(wB, kb + 1);
   }
-  // (a head that reports ranked candidates merges them per workgroup below: its idle waves stay)
-  if (!active && (HEAD ? g.top_b <= 1 : g.epi == 0)) return;
+  if (!active && g.epi == 0) return;
 
   // accumulator layout: lane (c = lane % 16, q = lane / 16) holds rows n0 + 4q + i of
   // activation column 16 t + c
-  if (!HEAD) {
-    if (active) {
+  if (active) {
 #pragma unroll
-      for (int t = 0; t < MT; ++t) {
-        const int v = 16 * t + fr;
-        if (v < Mv) {
-          float* dst = g.partial + (static_cast<size_t>(ks) * Mv + v) * g.N + n0 + 4 * fq;
-          if (g.epi != 0) {
-            // read by another workgroup of this launch (N is a multiple of 4 here)
-            if (n0 + 4 * fq < g.N) store_agent16(dst, acc[t][0], acc[t][1], acc[t][2], acc[t][3]);
-          } else if (n0 + 4 * fq + 3 < g.N && (g.N & 3) == 0) {
-            *reinterpret_cast<float4*>(dst) = make_float4(acc[t][0], acc[t][1], acc[t][2], acc[t][3]);
-          } else {
-#pragma unroll
-            for (int i = 0; i < 4; ++i)
-              if (n0 + 4 * fq + i < g.N) dst[i] = acc[t][i];
-          }
-        }
-      }
-    }
-    if (g.epi == 0) return;
-    // ---- the workgroup that arrives last for this 128-row group reduces it.  The partial
-    // sums are written and read at agent scope; every wave waits for its stores, the
-    // workgroup meets, one thread takes a ticket, and the last workgroup reads all slices in a
-    // fixed order, so the sums do not depend on who is last.
-    __shared__ int s_last;
-    wait_stores();
-    __syncthreads();
-    if (threadIdx.x == 0) {
-      int last = 1;
-      if (gridDim.y > 1) {
-        const int ticket = atomicAdd(&g.counters[blockIdx.x], 1);
-        last = ticket == static_cast<int>(gridDim.y) - 1;
-        if (last) g.counters[blockIdx.x] = 0;     // everyone has arrived: ready for the next launch
-      }
-      s_last = last;
-    }
-    __syncthreads();
-    if (!s_last) return;
-    float4* red = reinterpret_cast<float4*>(dyn_lds);           // the tiles are done with: reuse their LDS
-    float* sq_lds = reinterpret_cast<float*>(red + 64 * kGemmWaves);
-    float* xs = sq_lds + 64 * kGemmWaves;                       // epi = 2: the group's finished rows [M][128]
-    constexpr int NT = 64 * kGemmWaves;
-    const int items = g.M * 32;                                  // float4 outputs of the group
-    int lpi = 1;                                                 // threads sharing one output
-    while (lpi < 16 && items * lpi * 2 <= NT) lpi <<= 1;
-    const int nsl = static_cast<int>(gridDim.y) * PLANES;
-    const int n0g = blockIdx.x * (16 * kGemmWaves);
-    for (int base = 0; base < items; base += NT / lpi) {
-      const int it = base + threadIdx.x / lpi, sub = threadIdx.x % lpi;
-      const int m = it >> 5, f = it & 31;
-      const int n = n0g + 4 * f;
-      const bool ok = it < items && n < g.N;
-      float4 a4 = make_float4(0.f, 0.f, 0.f, 0.f);
-      if (ok) {
-        for (int j = sub; j < nsl; j += 4 * lpi) {
-          const float* src[4];
-#pragma unroll
-          for (int u = 0; u < 4; ++u) {
-            const int jj = min(j + u * lpi, nsl - 1);          // past the end: a valid address, value dropped
-            const size_t row = static_cast<size_t>(jj / PLANES) * Mv + m * PLANES + jj % PLANES;
-            src[u] = g.partial + row * g.N + n;
-          }
-          float4 p4[4];
-          load_agent16x4(src[0], src[1], src[2], src[3], p4);
-#pragma unroll
-          for (int u = 0; u < 4; ++u)
-            if (j + u * lpi < nsl) { a4.x += p4[u].x; a4.y += p4[u].y; a4.z += p4[u].z; a4.w += p4[u].w; }
-        }
-      }
-      red[threadIdx.x] = a4;
-      __syncthreads();
-      float sq = 0.f;
-      if (ok && sub == 0) {
-        float4 sum = g.residual ? *reinterpret_cast<const float4*>(g.residual + static_cast<size_t>(m) * g.N + n)
-                                : make_float4(0.f, 0.f, 0.f, 0.f);
-        for (int u = 0; u < lpi; ++u) {
-          const float4 r4 = red[threadIdx.x + u];
-          sum.x += r4.x; sum.y += r4.y; sum.z += r4.z; sum.w += r4.w;
-        }
-        if (g.epi == 2) *reinterpret_cast<float4*>(xs + m * 128 + 4 * f) = sum;
-        else *reinterpret_cast<float4*>(g.out_x + static_cast<size_t>(m) * g.N + n) = sum;
-        if (g.out_store) {
-          uint2 pk;
-          pk.x = pack_bf16x2(sum.x, sum.y);
-          pk.y = pack_bf16x2(sum.z, sum.w);
-          *reinterpret_cast<uint2*>(static_cast<bf16_t*>(g.out_store) + static_cast<size_t>(m) * g.N + n) = pk;
-        }
-        sq = sum.x * sum.x + sum.y * sum.y + sum.z * sum.z + sum.w * sum.w;
-      }
-      sq_lds[threadIdx.x] = sq;
-      __syncthreads();
-      if (g.out_ssq && it < items && sub == 0 && f == 0) {
-        float tot = 0.f;
-        for (int u = 0; u < 32; ++u) tot += sq_lds[threadIdx.x + u * lpi];
-        g.out_ssq[m * static_cast<int>(gridDim.x) + blockIdx.x] = tot;
-      }
-      __syncthreads();
-    }
-    if (g.epi == 2) {
-      // the group's 128 columns are whole heads of q, k or v: rotate (pairs c, c + d/2) and store
-      const RopeArgs& ra = g.rope;
-      const int half = ra.d >> 1;
-      const int pairs = g.M * 64;                               // (row, pair) items of the group
-      for (int idx = threadIdx.x; idx < pairs; idx += NT) {
-        const int m = idx >> 6, pr = idx & 63;
-        const int hl = pr / half, c = pr - hl * half;           // head inside the group, pair inside the head
-        const int hh = n0g / ra.d + hl;                         // head among q heads, then k heads, then v heads
-        if (hh >= ra.Hq + 2 * ra.Hkv) continue;
-        float x1 = xs[m * 128 + hl * ra.d + c], x2 = xs[m * 128 + hl * ra.d + c + half];
-        const int b = m / ra.W;
-        const int ps = ra.pos[b] + ra.level;
-        const int slot = ra.pos[b] + (ra.node ? ra.node[m % ra.W] : 0);
-        if (hh < ra.Hq + ra.Hkv) {
-          // angle in double (long positions keep their phase), reduced to [-pi, pi] in double,
-          // sine and cosine of the remainder in float
-          const double ang = static_cast<double>(ps) * ra.inv_freq[c];
-          const double turns = rint(ang * 0.15915494309189535);
-          const float red_ang = static_cast<float>(fma(-turns, 6.283185307179586, ang));
-          const float cs = cosf(red_ang), sn = sinf(red_ang);
-          const float r1 = x1 * cs - x2 * sn;
-          const float r2 = x2 * cs + x1 * sn;
-          x1 = r1;
-          x2 = r2;
-        }
-        bf16_t* dst;
-        if (hh < ra.Hq) {
-          dst = static_cast<bf16_t*>(ra.q_out) + (static_cast<size_t>(m) * ra.Hq + hh) * ra.d;
+    for (int t = 0; t < MT; ++t) {
+      const int v = 16 * t + fr;
+      if (v < Mv) {
+        float* dst = g.partial + (static_cast<size_t>(ks) * Mv + v) * g.N + n0 + 4 * fq;
+        if (g.epi != 0) {
+          // read by another workgroup of this launch (N is a multiple of 4 here)
+          if (n0 + 4 * fq < g.N) store_agent16(dst, acc[t][0], acc[t][1], acc[t][2], acc[t][3]);
+        } else if (n0 + 4 * fq + 3 < g.N && (g.N & 3) == 0) {
+          *reinterpret_cast<float4*>(dst) = make_float4(acc[t][0], acc[t][1], acc[t][2], acc[t][3]);
         } else {
-          if (slot < 0 || slot >= ra.l_max) continue;           // an entry outside the cache is not written
-          const bool is_k = hh < ra.Hq + ra.Hkv;
-          const int h = is_k ? hh - ra.Hq : hh - ra.Hq - ra.Hkv;
-          size_t off;
-          if (ra.paged) {
-            const int page = ra.page_table[static_cast<size_t>(b) * ra.max_pages + slot / ra.page_size];
-            if (!page_in_pool(page, ra.n_pages, ra.status)) continue;
-            off = ((static_cast<size_t>(page) * ra.Hkv + h) * ra.page_size + slot % ra.page_size) * ra.d;
-          } else {
-            off = ((static_cast<size_t>(b) * ra.Hkv + h) * ra.l_max + slot) * ra.d;
-          }
-          dst = static_cast<bf16_t*>(is_k ? ra.kc : ra.vc) + off;
+#pragma unroll
+          for (int i = 0; i < 4; ++i)
+            if (n0 + 4 * fq + i < g.N) dst[i] = acc[t][i];
         }
-        dst[c] = f32_to_bf16(x1);
-        dst[c + half] = f32_to_bf16(x2);
-      }
-    }
-    return;
-  }
-  // head mode: fused argmax (or the top_b best, best first) over rows < V of this tile,
-  // signal rows routed to extra_out.  With ranked candidates (top_b > 1) the waves of the
-  // workgroup first merge their tiles' lists through LDS, so the merging launch sees one list per
-  // 128 weight rows instead of one per 16.
-  const int TB = g.top_b > 1 ? g.top_b : 1;
-  const bool merge = TB > 1;
-  float* cv = reinterpret_cast<float*>(dyn_lds);              // [wave][M][TB] values, then indices
-  int* ci = reinterpret_cast<int*>(cv + NW * g.M * TB);
-  if (merge) __syncthreads();                                 // every wave is done with the activation pieces
-#pragma unroll
-  for (int t = 0; t < MT; ++t) {
-    const int v = 16 * t + fr;
-    float val[4];
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      val[i] = acc[t][i];
-      if (PLANES == 2) val[i] += __shfl_xor(acc[t][i], 1, 64);
-    }
-    const bool owner = (v < Mv) && (PLANES == 1 || (fr & 1) == 0);
-    const int m = v / PLANES;
-    float cur[4];
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      const int n = n0 + 4 * fq + i;
-      cur[i] = -INFINITY;
-      if (owner && active && n < g.N) {
-        if (n < g.V) {
-          if (g.logits_dbg) g.logits_dbg[static_cast<size_t>(m) * g.V + n] = val[i];
-          cur[i] = val[i];
-        } else if (g.extra_out) {
-          g.extra_out[m * g.n_extra + (n - g.V)] = val[i];
-        }
-      }
-    }
-    for (int r = 0; r < TB; ++r) {
-      float bv = -INFINITY;
-      int bi = INT_MAX;
-#pragma unroll
-      for (int i = 0; i < 4; ++i)
-        if (cur[i] > bv) { bv = cur[i]; bi = n0 + 4 * fq + i; }
-#pragma unroll
-      for (int o = 16; o < 64; o <<= 1) {
-        const float ov = __shfl_xor(bv, o, 64);
-        const int oi = __shfl_xor(bi, o, 64);
-        if (better(ov, oi, bv, bi)) { bv = ov; bi = oi; }
-      }
-      if (owner && fq == 0) {
-        if (merge) {
-          cv[(wv * g.M + m) * TB + r] = bv;
-          ci[(wv * g.M + m) * TB + r] = bi;
-        } else {
-          g.part_val[(static_cast<size_t>(m) * ntiles + tile) * TB + r] = bv;
-          g.part_idx[(static_cast<size_t>(m) * ntiles + tile) * TB + r] = bi;
-        }
-      }
-      if (r + 1 < TB) {
-#pragma unroll
-        for (int i = 0; i < 4; ++i)
-          if (n0 + 4 * fq + i == bi) cur[i] = -INFINITY;   // taken: out of the next pass
       }
     }
   }
-  if (merge) {
-    __syncthreads();
-    // half a wave per activation row, one lane per candidate of the NW lists (at most 8 x 4):
-    // pass r keeps what comes after pass r-1's pick (value descending, lower index first among
-    // equals; INT_MAX marks an empty slot) and takes the best of it by a butterfly
-    for (int m = 2 * wv + (lane >> 5); m < g.M; m += 2 * NW) {
-      const int slot = lane & 31;
-      const bool have = slot < NW * TB;
-      const int w = have ? slot / TB : 0, q = have ? slot - w * TB : 0;
-      const float cval = have ? cv[(w * g.M + m) * TB + q] : -INFINITY;
-      const int cidx = have ? ci[(w * g.M + m) * TB + q] : INT_MAX;
-      float prev_v = INFINITY;
-      int prev_i = -1;
-      for (int r = 0; r < TB; ++r) {
-        const bool after = cval < prev_v || (cval == prev_v && cidx > prev_i);
-        float bv = (cidx != INT_MAX && after) ? cval : -INFINITY;
-        int bi = (cidx != INT_MAX && after) ? cidx : INT_MAX;
+  if (g.epi == 0) return;
+  // ---- the workgroup that arrives last for this 128-row group reduces it.  The partial
+  // sums are written and read at agent scope; every wave waits for its stores, the
+  // workgroup meets, one thread takes a ticket, and the last workgroup reads all slices in a
+  // fixed order, so the sums do not depend on who is last.
+  __shared__ int s_last;
+  wait_stores();
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    int last = 1;
+    if (gridDim.y > 1) {
+      const int ticket = atomicAdd(&g.counters[blockIdx.x], 1);
+      last = ticket == static_cast<int>(gridDim.y) - 1;
+      if (last) g.counters[blockIdx.x] = 0;     // everyone has arrived: ready for the next launch
+    }
+    s_last = last;
+  }
+  __syncthreads();
+  if (!s_last) return;
+  float4* red = reinterpret_cast<float4*>(dyn_lds);           // the tiles are done with: reuse their LDS
+  float* sq_lds = reinterpret_cast<float*>(red + 64 * kGemmWaves);
+  float* xs = sq_lds + 64 * kGemmWaves;                       // epi = 2: the group's finished rows [M][128]
+  constexpr int NT = 64 * kGemmWaves;
+  const int items = g.M * 32;                                  // float4 outputs of the group
+  int lpi = 1;                                                 // threads sharing one output
+  while (lpi < 16 && items * lpi * 2 <= NT) lpi <<= 1;
+  const int nsl = static_cast<int>(gridDim.y) * PLANES;
+  const int n0g = blockIdx.x * (16 * kGemmWaves);
+  for (int base = 0; base < items; base += NT / lpi) {
+    const int it = base + threadIdx.x / lpi, sub = threadIdx.x % lpi;
+    const int m = it >> 5, f = it & 31;
+    const int n = n0g + 4 * f;
+    const bool ok = it < items && n < g.N;
+    float4 a4 = make_float4(0.f, 0.f, 0.f, 0.f);
+    if (ok) {
+      for (int j = sub; j < nsl; j += 4 * lpi) {
+        const float* src[4];
 #pragma unroll
-        for (int o = 16; o > 0; o >>= 1) {
-          const float ov = __shfl_xor(bv, o, 64);
-          const int oi = __shfl_xor(bi, o, 64);
-          if (better(ov, oi, bv, bi)) { bv = ov; bi = oi; }
+        for (int u = 0; u < 4; ++u) {
+          const int jj = min(j + u * lpi, nsl - 1);          // past the end: a valid address, value dropped
+          const size_t row = static_cast<size_t>(jj / PLANES) * Mv + m * PLANES + jj % PLANES;
+          src[u] = g.partial + row * g.N + n;
         }
-        if (slot == 0) {
-          g.part_val[(static_cast<size_t>(m) * gridDim.x + blockIdx.x) * TB + r] = bv;
-          g.part_idx[(static_cast<size_t>(m) * gridDim.x + blockIdx.x) * TB + r] = bi;
-        }
-        prev_v = bv;
-        prev_i = bi;
+        float4 p4[4];
+        load_agent16x4(src[0], src[1], src[2], src[3], p4);
+#pragma unroll
+        for (int u = 0; u < 4; ++u)
+          if (j + u * lpi < nsl) { a4.x += p4[u].x; a4.y += p4[u].y; a4.z += p4[u].z; a4.w += p4[u].w; }
       }
+    }
+    red[threadIdx.x] = a4;
+    __syncthreads();
+    float sq = 0.f;
+    if (ok && sub == 0) {
+      float4 sum = g.residual ? *reinterpret_cast<const float4*>(g.residual + static_cast<size_t>(m) * g.N + n)
+                              : make_float4(0.f, 0.f, 0.f, 0.f);
+      for (int u = 0; u < lpi; ++u) {
+        const float4 r4 = red[threadIdx.x + u];
+        sum.x += r4.x; sum.y += r4.y; sum.z += r4.z; sum.w += r4.w;
+      }
+      if (g.epi == 2) *reinterpret_cast<float4*>(xs + m * 128 + 4 * f) = sum;
+      else *reinterpret_cast<float4*>(g.out_x + static_cast<size_t>(m) * g.N + n) = sum;
+      if (g.out_store) {
+        uint2 pk;
+        pk.x = pack_bf16x2(sum.x, sum.y);
+        pk.y = pack_bf16x2(sum.z, sum.w);
+        *reinterpret_cast<uint2*>(static_cast<bf16_t*>(g.out_store) + static_cast<size_t>(m) * g.N + n) = pk;
+      }
+      sq = sum.x * sum.x + sum.y * sum.y + sum.z * sum.z + sum.w * sum.w;
+    }
+    sq_lds[threadIdx.x] = sq;
+    __syncthreads();
+    if (g.out_ssq && it < items && sub == 0 && f == 0) {
+      float tot = 0.f;
+      for (int u = 0; u < 32; ++u) tot += sq_lds[threadIdx.x + u * lpi];
+      g.out_ssq[m * static_cast<int>(gridDim.x) + blockIdx.x] = tot;
+    }
+    __syncthreads();
+  }
+  if (g.epi == 2) {
+    // the group's 128 columns are whole heads of q, k or v: rotate (pairs c, c + d/2) and store
+    const RopeArgs& ra = g.rope;
+    const int half = ra.d >> 1;
+    const int pairs = g.M * 64;                               // (row, pair) items of the group
+    for (int idx = threadIdx.x; idx < pairs; idx += NT) {
+      const int m = idx >> 6, pr = idx & 63;
+      const int hl = pr / half, c = pr - hl * half;           // head inside the group, pair inside the head
+      const int hh = n0g / ra.d + hl;                         // head among q heads, then k heads, then v heads
+      if (hh >= ra.Hq + 2 * ra.Hkv) continue;
+      float x1 = xs[m * 128 + hl * ra.d + c], x2 = xs[m * 128 + hl * ra.d + c + half];
+      const int b = m / ra.W;
+      const int ps = ra.pos[b] + ra.level;
+      const int slot = ra.pos[b] + (ra.node ? ra.node[m % ra.W] : 0);
+      if (hh < ra.Hq + ra.Hkv) {
+        // angle in double (long positions keep their phase), reduced to [-pi, pi] in double,
+        // sine and cosine of the remainder in float
+        const double ang = static_cast<double>(ps) * ra.inv_freq[c];
+        const double turns = rint(ang * 0.15915494309189535);
+        const float red_ang = static_cast<float>(fma(-turns, 6.283185307179586, ang));
+        const float cs = cosf(red_ang), sn = sinf(red_ang);
+        const float r1 = x1 * cs - x2 * sn;
+        const float r2 = x2 * cs + x1 * sn;
+        x1 = r1;
+        x2 = r2;
+      }
+      bf16_t* dst;
+      if (hh < ra.Hq) {
+        dst = static_cast<bf16_t*>(ra.q_out) + (static_cast<size_t>(m) * ra.Hq + hh) * ra.d;
+      } else {
+        if (slot < 0 || slot >= ra.l_max) continue;           // an entry outside the cache is not written
+        const bool is_k = hh < ra.Hq + ra.Hkv;
+        const int h = is_k ? hh - ra.Hq : hh - ra.Hq - ra.Hkv;
+        size_t off;
+        if (ra.paged) {
+          const int page = ra.page_table[static_cast<size_t>(b) * ra.max_pages + slot / ra.page_size];
+          if (!page_in_pool(page, ra.n_pages, ra.status)) continue;
+          off = ((static_cast<size_t>(page) * ra.Hkv + h) * ra.page_size + slot % ra.page_size) * ra.d;
+        } else {
+          off = ((static_cast<size_t>(b) * ra.Hkv + h) * ra.l_max + slot) * ra.d;
+        }
+        dst = static_cast<bf16_t*>(is_k ? ra.kc : ra.vc) + off;
+      }
+      dst[c] = f32_to_bf16(x1);
+      dst[c + half] = f32_to_bf16(x2);
     }
   }
 }
 
 constexpr int kFinalThreads = 1024;
 
-// One block per activation row: reduce the per-tile (max, index) pairs; for the draft head
+// One block per activation row: reduce the (max, index) candidates; for the draft head
 // the same block also turns the three signal logits into signals (Eqs. 3-5).
 __global__ __launch_bounds__(kFinalThreads) void k_argmax_finalize(const float* __restrict__ part_val,
                                                                    const int* __restrict__ part_idx, int ntiles,
@@ -587,7 +479,7 @@ __global__ __launch_bounds__(kFinalThreads) void k_argmax_finalize(const float* 
   const int m = blockIdx.x;
   float bv = -INFINITY;
   int bi = INT_MAX;
-  constexpr int U = 10;   // candidates per thread requested at once (9497 tiles of a 151939-row head: 10)
+  constexpr int U = 2;   // candidates per thread requested at once (256 workgroups x up to 4 slots, or 512 of the row stream: 1)
   for (int t0 = threadIdx.x; t0 < ntiles; t0 += U * kFinalThreads) {
     float v[U];
     int i[U];
@@ -636,7 +528,7 @@ __global__ __launch_bounds__(kFinalThreads) void k_argmax_finalize(const float* 
 }
 
 // The top_b best of each row, best first (value descending, lower index first among equals),
-// from per-tile candidates (part_idx != nullptr: C = ntiles * top_b pairs, INT_MAX marks an
+// from candidate lists (part_idx != nullptr: C pairs per row, INT_MAX marks an
 // empty slot) or from a full logits row (part_idx == nullptr: candidate c is (row[c], c)).
 // Pass r takes the best candidate that comes after pass r-1's pick in that order.
 __global__ __launch_bounds__(kFinalThreads) void k_topb_finalize(const float* __restrict__ vals,
@@ -654,10 +546,10 @@ __global__ __launch_bounds__(kFinalThreads) void k_topb_finalize(const float* __
   const int* ri = idxs ? idxs + static_cast<size_t>(m) * stride : nullptr;
   float prev_v = INFINITY;
   int prev_i = -1;
-  // candidate lists (9497 tiles x 1, or 1188 workgroups x 4 for a 151939-row head) are read once,
-  // all requests at once, and the passes run from registers; a full logits row is streamed in
-  // every pass.  Kept short on purpose: this kernel runs once on a cold instruction cache.
-  constexpr int U = 10;
+  // candidate lists (up to 256 workgroups x 4 slots x 4) are read once, all requests at once, and the passes
+  // run from registers; a full logits row is streamed in every pass.  Kept short on purpose: this kernel runs
+  // once on a cold instruction cache.
+  constexpr int U = 4;
   const bool held = ri != nullptr && C <= U * kFinalThreads;
   float hv[U];
   int hi[U];
@@ -800,13 +692,12 @@ void choose_ksplit(GemmArgs& g, bool mfma, int num_cus) {
   const int Mv = g.M * g.planes;
   const int Mvs = gemm_lds_row_stride(Mv);
   const int block_bytes = Mvs * 128 * 2;       // LDS bytes of one 128-k block of activation pieces
-  int budget;
+  int budget = 0;
   if (g.V >= 0) {
     g.ksplit = 1;
     g.kb_per_split = KB;
-    // head-mode kernels run for 100+ us: a smaller activation chunk lets three workgroups share a
-    // compute unit, which is worth more than the extra chunk barriers (measured at M = 8, 56, 64)
-    budget = (Mv > 32 ? 32 : 20) * 1024;
+    head_wide_plan(g, num_cus);      // a kernel of its own
+    return;
   } else {
     // The projections run for some tens of microseconds, so what counts is that all their
     // workgroups are resident at once and keep enough loads in flight: kGemmPerCu workgroups
@@ -834,8 +725,6 @@ void choose_ksplit(GemmArgs& g, bool mfma, int num_cus) {
   if (kcb < 1) kcb = 1;
   if (kcb > g.kb_per_split) kcb = g.kb_per_split;
   g.kc = kcb * 128;
-  // the LM head over more than 32 rows has a kernel of its own
-  head_wide_plan(g, num_cus);
 }
 
 __global__ void k_zero_i32(int* p, int n) {
@@ -860,46 +749,44 @@ hipError_t launch_gemm_valu(const GemmArgs& g, bool bf16, hipStream_t s) {
 size_t gemm_mfma_lds_bytes(const GemmArgs& g) {
   // activation pieces, one weight tile per wave, the rows' 1 / rms; the reducing epilogue
   // overlays 512 float4 + 512 float on the front
-  const size_t main = (static_cast<size_t>(g.kc >> 3) * gemm_lds_row_stride(g.M * g.planes) + static_cast<size_t>(g.V >= 0 ? kHeadWaves : kGemmWaves) * 256) * 16 +
+  const size_t main = (static_cast<size_t>(g.kc >> 3) * gemm_lds_row_stride(g.M * g.planes) + static_cast<size_t>(kGemmWaves) * 256) * 16 +
                       ((static_cast<size_t>(g.M) * sizeof(float) + 15) & ~static_cast<size_t>(15));
   const size_t overlay = g.epi == 0 ? 0 : static_cast<size_t>(64 * kGemmWaves) * 20 + (g.epi == 2 ? static_cast<size_t>(g.M) * 512 : 0);
   return main > overlay ? main : overlay;
 }
 
-template <int MT, int PLANES, bool HEAD>
+template <int MT, int PLANES>
 static hipError_t launch_one(const GemmArgs& g, hipStream_t s) {
   // set once per process; a function-local static is initialised under the language's own lock,
   // so first calls from several host threads are safe
-  static const hipError_t attr = hipFuncSetAttribute(reinterpret_cast<const void*>(&k_gemm_mfma<MT, PLANES, HEAD>),
+  static const hipError_t attr = hipFuncSetAttribute(reinterpret_cast<const void*>(&k_gemm_mfma<MT, PLANES>),
                                              hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024 - 256);
   if (attr != hipSuccess) return attr;
-  constexpr int NW = HEAD ? kHeadWaves : kGemmWaves;
-  const bool spread = !HEAD && g.spread > 0 && g.epi == 0 && g.ksplit == 1;
+  constexpr int NW = kGemmWaves;
+  const bool spread = g.spread > 0 && g.epi == 0 && g.ksplit == 1;
   const dim3 grid(spread ? g.spread : (gemm_ntiles(g.N) + NW - 1) / NW, g.ksplit);
-  hipLaunchKernelGGL((k_gemm_mfma<MT, PLANES, HEAD>), grid, dim3(64 * NW), gemm_mfma_lds_bytes(g), s, g);
+  hipLaunchKernelGGL((k_gemm_mfma<MT, PLANES>), grid, dim3(64 * NW), gemm_mfma_lds_bytes(g), s, g);
   return hipGetLastError();
 }
 
-template <int PLANES, bool HEAD>
+template <int PLANES>
 static hipError_t launch_mfma_planes(const GemmArgs& g, hipStream_t s) {
   switch (gemm_mt(g.M, PLANES)) {
-    case 1: return launch_one<1, PLANES, HEAD>(g, s);
-    case 2: return launch_one<2, PLANES, HEAD>(g, s);
-    case 3: return launch_one<3, PLANES, HEAD>(g, s);
-    case 4: return launch_one<4, PLANES, HEAD>(g, s);
-    case 5: return launch_one<5, PLANES, HEAD>(g, s);
-    case 6: return launch_one<6, PLANES, HEAD>(g, s);
-    case 7: return launch_one<7, PLANES, HEAD>(g, s);
-    case 8: return launch_one<8, PLANES, HEAD>(g, s);
-    case 9: return launch_one<9, PLANES, HEAD>(g, s);
+    case 1: return launch_one<1, PLANES>(g, s);
+    case 2: return launch_one<2, PLANES>(g, s);
+    case 3: return launch_one<3, PLANES>(g, s);
+    case 4: return launch_one<4, PLANES>(g, s);
+    case 5: return launch_one<5, PLANES>(g, s);
+    case 6: return launch_one<6, PLANES>(g, s);
+    case 7: return launch_one<7, PLANES>(g, s);
+    case 8: return launch_one<8, PLANES>(g, s);
     default: return hipErrorInvalidValue;
   }
 }
 
 hipError_t launch_gemm_mfma(const GemmArgs& g, hipStream_t s) {
-  if (g.wide) return launch_head_wide(g, s);
-  if (g.V >= 0) return g.planes == 2 ? launch_mfma_planes<2, true>(g, s) : launch_mfma_planes<1, true>(g, s);
-  return g.planes == 2 ? launch_mfma_planes<2, false>(g, s) : launch_mfma_planes<1, false>(g, s);
+  if (g.V >= 0) return launch_head_wide(g, s);
+  return g.planes == 2 ? launch_mfma_planes<2>(g, s) : launch_mfma_planes<1>(g, s);
 }
 
 hipError_t launch_argmax_finalize(const float* part_val, const int* part_idx, int ntiles, int M,

@@ -1,36 +1,33 @@
-// LM-head GEMM + argmax over many activation rows (more than 32: the verification block of a
-// batch), bf16 x bf16 -> fp32, logits never stored (Alg. 1, target tokens of the block).
+// The two heads in bf16: widened head of the draft (Eq. 1; fp32 rows under an RMSNorm as two bf16 planes) and LM
+// head over the verification block (Alg. 1), GEMM + argmax or ranked candidates, logits never stored.
 //
-// With that many rows the activations no longer fit beside the weights: staging them block by
-// block in LDS, as the kernel for fewer rows does, fills the LDS with activations, leaves two
-// 4 KB weight blocks per wave in flight and makes every wave read all activations from LDS for
-// each 16-row weight tile.  Here the roles are swapped:
+// A pure weight stream with up to 160 activation rows beside it:
 //   - one workgroup per compute unit walks an equal share of the weight tiles (16 rows each),
 //     whatever the vocabulary size: no rounds of workgroups, no refill of the pipeline between them;
 //   - the WEIGHTS pass through an LDS ring of S stages, one 128-k block of TG tiles per stage.  Two
 //     producer waves do nothing but bring stages in with direct global->LDS loads (16 bytes per
 //     lane, streaming), S-1 stages ahead; their load counters hold nothing else, so three stages
 //     stay in flight across the barriers;
-//   - the ACTIVATIONS stay in registers: consumer wave c owns RTW 16-row tiles of the rows and
+//   - the ACTIVATIONS stay in registers: a consumer wave owns RT 16-row tiles of the rows and
 //     loads their operand pieces of the next k block (L2 hits) while it works on this one, from a
-//     copy of the activations in operand order (k_pack_act) so that a load covers whole cache lines;
+//     copy of the activations in operand order (k_pack_act, k_pack_norm) so that a load covers whole cache
+//     lines; up to 32 plain bf16 rows are read in place;
 //   - a pass takes 2 TG tiles through all k blocks, the two halves of a k block one after the other,
-//     so the activation pieces of a k block are fetched once for 256 weight rows; every consumer
-//     multiplies every weight tile of a stage with its own rows: one LDS read (the transposed
-//     weight operand) feeds RTW matrix instructions.
+//     so the activation pieces of a k block are fetched once for 256 weight rows; one LDS read (the
+//     transposed weight operand) feeds RT matrix instructions.
 // One workgroup barrier per stage hands a landed stage to the consumers and the stage read
-// before it back to the producers.  The epilogue of a pass reduces each activation row's logits
-// over a half's 16 TG weight rows to one (value, index) candidate.
-// What bounds it (measured by leaving parts out, 144 rows, V = 151936, D = 5120, event times of a
-// stand-alone loop): the producers alone stream at 7 TB/s (230 us), the consumers alone (no weight
-// stream) take 225 us, together 340 us whether the ring has three, four or five stages; of that the
-// LDS reads and barriers cost 45 us, the matrix instructions 45 us, the activation loads 25 us
-// (80 us before they covered whole cache lines: a wave's load straight from the row-major matrix is
-// 16 rows x 64 bytes, and such half-line requests, not their bytes, were the cost).  One row of
-// workgroups per 128 weight rows, refilled five times per compute unit, took 437 us in the same loop.
-// At 56 and 64 rows (V = 151936, D = 4096) it takes 241 us where the LDS-staged kernel took 272 us; up to
-// 32 rows (one consumer wave) the LDS-staged kernel is as fast or faster (8 / 16 / 32 rows, D = 5120: 236 /
-// 242 / 271 us against 247 / 249 / 272 us), so this kernel starts at 33 rows.
+// before it back to the producers.  Every lane keeps the best of the logits it has seen; they become one
+// candidate per workgroup and row (and column split) at the end.
+// What bounds it: the weight stream.  V = 151936, D = 4096, whole call: 8 / 24 / 56 / 144 rows 190 / 191 / 213 /
+// 234 us = 6.5 / 6.5 / 5.8 / 5.3 TB/s, where a kernel that staged the activations in LDS for every eight
+// weight tiles took 230 / 233 us for the first two and the same form with one wave per 32 rows 225 us
+// for the third.  Draft head with 8 / 64 fp32 rows, same size: 230 -> 190 and 503 -> 236 us (that kernel read all
+// 128 virtual rows from LDS for every tile: the LDS was the bound).  Many rows are slower: by leaving parts out
+// at 144 rows (D = 5120), the producers alone stream at 7 TB/s (230 us), the consumers alone take 225 us, of
+// that the LDS reads and barriers 45 us, the matrix instructions 45 us, the activation loads 25 us (80 us
+// before they covered whole cache lines: straight from the row-major matrix a load is 16 rows x 64 bytes,
+// and those half-line requests, not their bytes, were the cost).
+#include "../../include/specexit.h"
 #include "common.hpp"
 #include "kernels.hpp"
 
@@ -56,51 +53,137 @@ __device__ __forceinline__ void load_to_lds16(const void* src, const void* lds_b
   asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off nt" ::"s"(l), "v"(src) : "memory");
 }
 
+// The order in which a workgroup takes the k blocks of a pass.  The workgroups run in step, and where the
+// weight rows are a multiple of 4 KB apart the reads of one k block by all of them fall on one of the
+// sixteen 256-byte-interleaved channels of each L2 (8 rows, D = 2048: V = 128259 in 112 us, 83 us with four
+// starting points, 81 with eight; D = 4096: V = 32000 in 58, 44, 44 us, V = 151936 in 193, 190, 199).  So K is cut into 2^LV chunks, and workgroup w takes them in the
+// order i ^ s, s from w.  Identical weight rows must give identical bits in whichever workgroup they are (ties
+// go to the lowest index): every chunk is summed on its own, and the chunks are added as a balanced binary
+// tree, in which the order i ^ s only exchanges the two operands of an addition.
+template <int LV>
+struct KOrder {
+  static constexpr int P = 1 << LV;
+  int KB, s, lv, ci, kb, hi;    // ci: position in the order; chunk ci ^ s = k blocks .. hi - 1, now at kb
+  __device__ __forceinline__ explicit KOrder(int KB_) : KB(KB_) {
+    lv = KB >= P ? LV : 0;      // (fewer k blocks than chunks: one chunk)
+    s = lv ? (static_cast<int>(blockIdx.x) >> 3) & (P - 1) : 0;    // neighbours on one XCD are eight apart
+    ci = 0;
+    enter();
+  }
+  __device__ __forceinline__ void enter() {
+    kb = ((ci ^ s) * KB) >> lv;
+    hi = (((ci ^ s) + 1) * KB) >> lv;
+  }
+  __device__ __forceinline__ bool last_of_chunk() const { return kb + 1 == hi; }
+  // after the last k block of a pass comes the first of the next one
+  __device__ __forceinline__ void next() {
+    if (++kb < hi) return;
+    ci = ci + 1 == (1 << lv) ? 0 : ci + 1;
+    enter();
+  }
+};
+
 // The stages of a workgroup in the order they pass through the ring.  The workgroup's tiles
 // [t_lo, t_hi) are cut into "halves" of TG tiles; a pass takes two halves (the last pass one, if the
 // count is odd) through all k blocks, the halves of a k block one after the other, so that the
 // consumers fetch their activation pieces of a k block once for 2 TG tiles.
+template <int LV>
 struct StageCursor {
-  int half0, nh, kb, h;   // first half and number of halves of the current pass; k block; half within the pass
+  int half0, nh, h, n;   // first half and number of halves of the current pass; half within the pass; k blocks done
+  KOrder<LV> k;
   static constexpr int kNH = 2;
-  __device__ __forceinline__ void start(int nhalf) { half0 = 0; nh = min(kNH, nhalf); kb = 0; h = 0; }
+  __device__ __forceinline__ StageCursor(int nhalf, int KB) : half0(0), nh(min(kNH, nhalf)), h(0), n(0), k(KB) {}
   __device__ __forceinline__ void advance(int nhalf, int KB) {
     if (++h < nh) return;
     h = 0;
-    if (++kb < KB) return;
-    kb = 0;
+    k.next();
+    if (++n < KB) return;
+    n = 0;
     half0 += nh;
     nh = min(kNH, nhalf - half0);
   }
 };
 
-// The consumer side of k_head_wide for a wave that owns RT row tiles (from row tile rt0 on) and, of
-// every half, the JN weight tiles from jc0 on (all TG, or half of them when a last odd row tile is
-// shared by two waves): one barrier per stage, an argmax epilogue per pass.  A row has two candidate
-// slots per half, one per column half; a wave that covers the whole half fills the second with nothing.
-template <int RT, int JN, int TG, int S>
+// The TB best (value, index) pairs a lane has seen, best first.  Values arrive with growing indices, so
+// a strict comparison keeps the lowest index among equals in front; a value that is not above
+// the initial -inf is never taken (index INT_MAX: empty).
+template <int TB>
+struct Best {
+  float v[TB];
+  int i[TB];
+  __device__ __forceinline__ void clear() {
+#pragma unroll
+    for (int r = 0; r < TB; ++r) { v[r] = -INFINITY; i[r] = INT_MAX; }
+  }
+  __device__ __forceinline__ void add(float x, int n) {
+#pragma unroll
+    for (int r = TB - 1; r >= 0; --r) {
+      const bool here = x > v[r];
+      if (r > 0) {
+        const bool above = x > v[r - 1];
+        v[r] = here ? (above ? v[r - 1] : x) : v[r];
+        i[r] = here ? (above ? i[r - 1] : n) : i[r];
+      } else {
+        v[0] = here ? x : v[0];
+        i[0] = here ? n : i[0];
+      }
+    }
+  }
+  // first entry out
+  __device__ __forceinline__ void pop() {
+#pragma unroll
+    for (int r = 0; r + 1 < TB; ++r) { v[r] = v[r + 1]; i[r] = i[r + 1]; }
+    v[TB - 1] = -INFINITY;
+    i[TB - 1] = INT_MAX;
+  }
+};
+
+// The consumer side of k_head_wide for a wave that owns RT row tiles of the operand (from tile rt0 on) and, of
+// every half, the JN weight tiles from jc0 on: one barrier per stage, a candidate update per pass.
+// PL = 2: tiles 2 o and 2 o + 1 are the bf16 value and the bf16 rounding of the rest of the same 16
+// activation rows, whose two products are added at the end.  Every lane keeps the TB best of what it has seen;
+// they are merged over the four lanes of a row when the workgroup's share is done.
+// A row has `slots` candidate slots per workgroup, one per column split; a wave that covers the whole half
+// (JN = TG) where others split it fills the remaining one with nothing.
+template <int RT, int JN, int TG, int S, int PL, int TB, int LV>
 struct Consumer {
   static constexpr int kStage = TG * 4096;
+  static constexpr int RO = RT / PL;        // 16-row tiles of results
   const GemmArgs& g;
   char* lds;
-  int rt0, jc0, fr, fq, t_lo, t_hi, KB, slots;
-  const uint4* apack[RT];   // this lane's piece of row tile t in the packed activations, k block 0, k step 0
+  int rt0, jc0, fr, fq, t_lo, t_hi, KB;
+  KOrder<LV> k;             // at the k block whose pieces `b` holds
+  const uint4* apack[RT];   // this lane's piece of row tile t, k block 0, k step 0
   size_t kb_stride;         // uint4 entries from one k block to the next
+  int s_stride;             // and from one k step to the next
   uint4 bn[RT][2];  // pieces 0 and 1 of the next k block, on their way
-  uint4 b[RT][4];   // activation operand pieces of the current k block: row 16 (wv RTW + t) + fr, k = 32 s + 8 fq .. + 7
+  uint4 b[RT][4];   // activation operand pieces of the current k block: row 16 tile + fr, k = 32 s + 8 fq .. + 7
   int stage_no;     // stages consumed so far: stage i lives in ring slot i % S
+  Best<TB> best[RO];
 
-  __device__ __forceinline__ Consumer(const GemmArgs& g_, char* lds_, int rt0_, int jc0_, int NT, int lane, int t_lo_, int t_hi_, int KB_, int slots_)
-      : g(g_), lds(lds_), rt0(rt0_), jc0(jc0_), fr(lane & 15), fq(lane >> 4), t_lo(t_lo_), t_hi(t_hi_), KB(KB_), slots(slots_), stage_no(0) {
-    // packed activations: [k block][row tile][k step][lane] 16-byte pieces (NT row tiles), so that one
-    // load instruction of a wave reads 1 KB of consecutive bytes
-    kb_stride = static_cast<size_t>(NT) * 256;
+  __device__ __forceinline__ Consumer(const GemmArgs& g_, char* lds_, int rt0_, int jc0_, int NT, int lane, int t_lo_, int t_hi_, int KB_)
+      : g(g_), lds(lds_), rt0(rt0_), jc0(jc0_), fr(lane & 15), fq(lane >> 4), t_lo(t_lo_), t_hi(t_hi_), KB(KB_), k(KB_), stage_no(0) {
+    if (g.a_packed) {
+      // packed activations: [k block][row tile][k step][lane] 16-byte pieces (NT row tiles), so that one
+      // load instruction of a wave reads 1 KB of consecutive bytes
+      kb_stride = static_cast<size_t>(NT) * 256;
+      s_stride = 64;
 #pragma unroll
-    for (int t = 0; t < RT; ++t) apack[t] = static_cast<const uint4*>(g.a_packed) + static_cast<size_t>(rt0 + t) * 256 + lane;
+      for (int t = 0; t < RT; ++t) apack[t] = static_cast<const uint4*>(g.a_packed) + static_cast<size_t>(rt0 + t) * 256 + lane;
+    } else {
+      // straight from the row-major bf16 matrix (few rows); rows from M on repeat the last one, dropped later
+      kb_stride = 16;
+      s_stride = 4;
+#pragma unroll
+      for (int t = 0; t < RT; ++t)
+        apack[t] = static_cast<const uint4*>(g.a_src) + static_cast<size_t>(min(16 * (rt0 + t) + fr, g.M - 1)) * (g.K >> 3) + fq;
+    }
 #pragma unroll
     for (int t = 0; t < RT; ++t)
 #pragma unroll
-      for (int s = 0; s < 4; ++s) b[t][s] = apack[t][s * 64];
+      for (int s = 0; s < 4; ++s) b[t][s] = apack[t][k.kb * kb_stride + s * s_stride];
+#pragma unroll
+    for (int o = 0; o < RO; ++o) best[o].clear();
   }
 
   // one pass: NH halves starting at half `half0`
@@ -112,13 +195,15 @@ struct Consumer {
 #pragma unroll
       for (int j = 0; j < NH * JN; ++j) acc[t][j] = f32x4_t{0.f, 0.f, 0.f, 0.f};
 
+    f32x4_t left[LV > 0 ? LV : 1][RT][NH * JN];     // finished left siblings of the chunk tree, per level
+
     // The waves go through a stage's four k steps in read groups of CH tiles, the operand reads one
     // group ahead of the matrix instructions (k steps outermost: between two matrix instructions on the
     // same accumulator lie those of all other tiles; the scheduler is kept from sinking the reads back
     // to their uses).  The barrier that hands over the next stage sits before the last group's matrix
     // instructions, whose operands are in registers by then: the first reads of the next stage are in
     // flight while those instructions run, so neither the LDS nor the matrix cores idle around a barrier.
-    constexpr int CH = 4;                 // tiles per read group
+    constexpr int CH = JN < 4 ? JN : 4;   // tiles per read group
     constexpr int GPS = JN / CH;          // read groups per k step
     constexpr int NCH = 4 * GPS;          // read groups per stage: group c = k step c / GPS, this wave's tiles CH (c % GPS) ..
     uint4 wf[2][CH];
@@ -140,8 +225,11 @@ struct Consumer {
     read_group(wf[0], stage, 0);
 #pragma unroll 1
     for (int kb = 0; kb < KB; ++kb) {
-      // the pieces of the next k block (of the first one again after the last: the next pass starts there)
-      const size_t noff = static_cast<size_t>(kb + 1 == KB ? 0 : kb + 1) * kb_stride;
+      // the pieces of the next k block (after the last one that is where the next pass starts)
+      const int ci = k.ci;
+      const bool chunk_end = LV > 0 && k.lv > 0 && k.last_of_chunk();
+      k.next();
+      const size_t noff = static_cast<size_t>(k.kb) * kb_stride;
 #pragma unroll
       for (int h = 0; h < NH; ++h) {
 #pragma unroll
@@ -169,81 +257,75 @@ struct Consumer {
 #pragma unroll
             for (int t = 0; t < RT; ++t) {
               bn[t][0] = apack[t][noff];
-              bn[t][1] = apack[t][noff + 64];
+              bn[t][1] = apack[t][noff + s_stride];
             }
           }
           if (h == NH - 1 && (c + 1) % GPS == 0) {
 #pragma unroll
             for (int t = 0; t < RT; ++t) {
               if (s < 2) b[t][s] = bn[t][s];
-              else b[t][s] = apack[t][noff + s * 64];
+              else b[t][s] = apack[t][noff + s * s_stride];
             }
           }
           __builtin_amdgcn_sched_barrier(0);
         }
       }
+      // a chunk is summed: up the tree as far as its right siblings go
+      if constexpr (LV > 0) {
+        if (chunk_end) {
+          bool up = true;
+#pragma unroll
+          for (int l = 0; l < LV; ++l) {
+            if (!up) continue;
+            if (ci >> l & 1) {
+#pragma unroll
+              for (int t = 0; t < RT; ++t)
+#pragma unroll
+                for (int j = 0; j < NH * JN; ++j) acc[t][j] += left[l][t][j];
+            } else {
+              up = false;
+#pragma unroll
+              for (int t = 0; t < RT; ++t)
+#pragma unroll
+                for (int j = 0; j < NH * JN; ++j) { left[l][t][j] = acc[t][j]; acc[t][j] = f32x4_t{0.f, 0.f, 0.f, 0.f}; }
+            }
+          }
+        }
+      }
     }
 
     // ---- epilogue: lane (c = lane % 16, q = lane / 16) holds weight rows 16 (tile0 + j) + 4 q + i of
-    // activation row 16 (rt0 + t) + c; rows below V enter the argmax (lowest index on ties), the
-    // rows V.. are the widened head's extra rows.  One candidate per row, half and column half.
-    const size_t nslot = static_cast<size_t>(gridDim.x) * slots * 2;
+    // activation row 16 (rt0 / PL + o) + c; rows below V enter the lane's best, the rows V.. are the
+    // widened head's extra rows.
 #pragma unroll
     for (int h = 0; h < NH; ++h) {
       const int tile0 = t_lo + (half0 + h) * TG + jc0;      // this wave's first tile of the half
 #pragma unroll
-      for (int t = 0; t < RT; ++t) {
-        const int m = 16 * (rt0 + t) + fr;
+      for (int o = 0; o < RO; ++o) {
+        const int m = 16 * (rt0 / PL + o) + fr;
         const bool owner = m < g.M;
-        float bv = -INFINITY;
-        int bi = INT_MAX;
         // tiles that lie wholly inside the share and below the signal rows (all but the last of a
         // launch) need no checks per element: the consumers stand still during the epilogue while
         // the ring fills up, so its length counts
         const bool plain = !g.logits_dbg && tile0 + JN <= t_hi && (tile0 + JN) * 16 <= g.V;    // uniform
-        if (plain) {
-          const int nb = tile0 * 16 + 4 * fq;
+        const int nb = tile0 * 16 + 4 * fq;
 #pragma unroll
-          for (int j = 0; j < JN; ++j) {
+        for (int j = 0; j < JN; ++j) {
 #pragma unroll
-            for (int i = 0; i < 4; ++i) {
-              const float val = acc[t][h * JN + j][i];
-              const bool up = val > bv;                      // n grows with j and i: '>' keeps the lowest index
-              bv = up ? val : bv;
-              bi = up ? nb + 16 * j + i : bi;
-            }
-          }
-        } else {
-#pragma unroll
-          for (int j = 0; j < JN; ++j) {
-#pragma unroll
-            for (int i = 0; i < 4; ++i) {
-              const int n = (tile0 + j) * 16 + 4 * fq + i;
-              const float val = acc[t][h * JN + j][i];
-              if (owner && tile0 + j < t_hi && n < g.N) {    // (tiles past the workgroup's range hold a copy of its last tile)
-                if (n < g.V) {
-                  if (g.logits_dbg) g.logits_dbg[static_cast<size_t>(m) * g.V + n] = val;
-                  if (val > bv) { bv = val; bi = n; }
-                } else if (g.extra_out) {
-                  g.extra_out[m * g.n_extra + (n - g.V)] = val;
-                }
+          for (int i = 0; i < 4; ++i) {
+            const int n = nb + 16 * j + i;
+            float val = acc[PL * o][h * JN + j][i];
+            if constexpr (PL == 2) val += acc[2 * o + 1][h * JN + j][i];
+            if (plain) {
+              best[o].add(val, n);                           // n grows with h, j and i
+            } else if (owner && tile0 + j < t_hi && n < g.N) {    // (tiles past the workgroup's range hold a copy of its last tile)
+              if (n < g.V) {
+                if (g.logits_dbg) g.logits_dbg[static_cast<size_t>(m) * g.V + n] = val;
+                best[o].add(val, n);
+              } else if (g.extra_out) {
+                g.extra_out[m * g.n_extra + (n - g.V)] = val;
               }
             }
-          }
-        }
-#pragma unroll
-        for (int o = 16; o < 64; o <<= 1) {
-          const float ov = __shfl_xor(bv, o, 64);
-          const int oi = __shfl_xor(bi, o, 64);
-          if (better(ov, oi, bv, bi)) { bv = ov; bi = oi; }
-        }
-        if (owner && fq == 0) {
-          const size_t at = static_cast<size_t>(m) * nslot + (static_cast<size_t>(blockIdx.x) * slots + (half0 + h)) * 2;
-          g.part_val[at + (jc0 ? 1 : 0)] = bv;
-          g.part_idx[at + (jc0 ? 1 : 0)] = bi;
-          if (JN == TG) {
-            g.part_val[at + 1] = -INFINITY;
-            g.part_idx[at + 1] = INT_MAX;
           }
         }
       }
@@ -257,19 +339,35 @@ struct Consumer {
       if (half0 + 1 < nhalf) pass<2>(half0);
       else pass<1>(half0);
     }
-    // candidate slots this workgroup does not use (its share of the tiles is one half shorter than the longest)
-    if (fq == 0 && jc0 == 0) {
-      const size_t nslot = static_cast<size_t>(gridDim.x) * slots * 2;
-      for (int q = nhalf; q < slots; ++q)
+    // the row's best over its four lanes, one candidate (list) per workgroup and column split
+    const int slots = g.wide_slots;
+    const int top_b = TB > 1 ? g.top_b : 1;
 #pragma unroll
-        for (int t = 0; t < RT; ++t) {
-          const int m = 16 * (rt0 + t) + fr;
-          if (m < g.M) {
-            const size_t at = static_cast<size_t>(m) * nslot + (static_cast<size_t>(blockIdx.x) * slots + q) * 2;
-            g.part_val[at] = g.part_val[at + 1] = -INFINITY;
-            g.part_idx[at] = g.part_idx[at + 1] = INT_MAX;
+    for (int o = 0; o < RO; ++o) {
+      const int m = 16 * (rt0 / PL + o) + fr;
+      const size_t at = (static_cast<size_t>(m) * gridDim.x + blockIdx.x) * slots * top_b;
+      const int mine = jc0 / JN;
+#pragma unroll
+      for (int r = 0; r < TB; ++r) {
+        if (r >= top_b) break;
+        float bv = best[o].v[0];
+        int bi = best[o].i[0];
+#pragma unroll
+        for (int x = 16; x < 64; x <<= 1) {
+          const float ov = __shfl_xor(bv, x, 64);
+          const int oi = __shfl_xor(bi, x, 64);
+          if (better(ov, oi, bv, bi)) { bv = ov; bi = oi; }
+        }
+        if (best[o].i[0] == bi) best[o].pop();               // (an index belongs to one lane; popping an empty list changes nothing)
+        if (m < g.M && fq == 0) {
+          g.part_val[at + mine * top_b + r] = bv;
+          g.part_idx[at + mine * top_b + r] = bi;
+          if (JN == TG && slots == 2) {
+            g.part_val[at + top_b + r] = -INFINITY;
+            g.part_idx[at + top_b + r] = INT_MAX;
           }
         }
+      }
     }
   }
 };
@@ -295,11 +393,55 @@ __global__ __launch_bounds__(256) void k_pack_act(const bf16_t* __restrict__ src
   for (int s = 0; s < 4; ++s) dst[(static_cast<size_t>(unit) * 4 + s) * 64 + lane] = m < M ? v[s] : uint4{0u, 0u, 0u, 0u};
 }
 
-// NC consumer waves of RTW row tiles, then the producers; SPLIT: the last consumer's second row tile does not
-// exist (an odd number of row tiles), and its one tile is shared with a further wave after the producers,
-// each taking half of the columns: no SIMD then carries three row tiles' worth of matrix instructions.
-template <int NC, int RTW, int TG, int S, bool SPLIT>
-__global__ __launch_bounds__(64 * (NC + kProducers + (SPLIT ? 1 : 0))) void k_head_wide(const GemmArgs g) {
+// The same for fp32 rows under an RMSNorm, x rsqrt(mean x^2 + eps) gain, split into two bf16 planes: row tile
+// 2 o holds the bf16 rounding of rows 16 o .. + 15, row tile 2 o + 1 the bf16 rounding of what that lost.
+__global__ __launch_bounds__(256) void k_pack_norm(const float* __restrict__ src, const float* __restrict__ ssq, int nssq,
+                                                   const bf16_t* __restrict__ gain, float eps, uint4* __restrict__ dst, int M, int K, int NO) {
+  const int lane = threadIdx.x & 63;
+  const int unit = blockIdx.x * 4 + (threadIdx.x >> 6);     // (kb, rows 16 o ..)
+  const int KB = K >> 7;
+  if (unit >= KB * NO) return;
+  const int kb = unit / NO, o = unit - kb * NO;
+  const int m = 16 * o + (lane & 15), q = lane >> 4;
+  const int row = m < M ? m : 0;
+  const float* p = src + static_cast<size_t>(row) * K + 128 * kb + 8 * q;
+  const bf16_t* gp = gain + 128 * kb + 8 * q;
+  float4 x[4][2];
+  uint4 gn[4];
+#pragma unroll
+  for (int s = 0; s < 4; ++s) {
+    x[s][0] = *reinterpret_cast<const float4*>(p + 32 * s);
+    x[s][1] = *reinterpret_cast<const float4*>(p + 32 * s + 4);
+    gn[s] = *reinterpret_cast<const uint4*>(gp + 32 * s);
+  }
+  float t = 0.f;
+  for (int j = q; j < nssq; j += 4) t += ssq[row * nssq + j];
+  t += __shfl_xor(t, 16, 64);
+  t += __shfl_xor(t, 32, 64);
+  const float rs = 1.0f / sqrtf(t / static_cast<float>(K) + eps);
+#pragma unroll
+  for (int s = 0; s < 4; ++s) {
+    float f[8] = {x[s][0].x, x[s][0].y, x[s][0].z, x[s][0].w, x[s][1].x, x[s][1].y, x[s][1].z, x[s][1].w}, gf[8], hf[8];
+    unpack16(gn[s], gf);
+#pragma unroll
+    for (int e = 0; e < 8; ++e) f[e] = m < M ? f[e] * rs * gf[e] : 0.f;
+    const uint4 hi = make_uint4(pack_bf16x2(f[0], f[1]), pack_bf16x2(f[2], f[3]), pack_bf16x2(f[4], f[5]), pack_bf16x2(f[6], f[7]));
+    unpack16(hi, hf);
+    const uint4 lo = make_uint4(pack_bf16x2(f[0] - hf[0], f[1] - hf[1]), pack_bf16x2(f[2] - hf[2], f[3] - hf[3]),
+                                pack_bf16x2(f[4] - hf[4], f[5] - hf[5]), pack_bf16x2(f[6] - hf[6], f[7] - hf[7]));
+    uint4* d = dst + static_cast<size_t>(kb * 2 * NO + 2 * o) * 256 + s * 64 + lane;
+    d[0] = hi;
+    d[256] = lo;
+  }
+}
+
+// RG groups of RT row tiles, each group's columns split over CS waves; then the producers.  SPLIT (CS = 1): the
+// last group's second row tile does not exist (an odd number of row tiles), and its one tile is shared with
+// a further wave after the producers, each taking half of the columns: no SIMD then carries three row
+// tiles' worth of matrix instructions.
+template <int RG, int RT, int CS, int PL, int TB, int TG, int S, bool SPLIT, int LV>
+__global__ __launch_bounds__(64 * (RG * CS + kProducers + (SPLIT ? 1 : 0))) void k_head_wide(const GemmArgs g) {
+  constexpr int NC = RG * CS;
   static_assert((4 * TG) % kProducers == 0, "the pieces of a stage are dealt evenly to the producers");
   constexpr int PP = 4 * TG / kProducers;       // 1 KB pieces (4 weight rows x 256 bytes) per producer and stage
   static_assert((S - 2) * PP < 64, "the load counter has six bits");
@@ -325,8 +467,7 @@ __global__ __launch_bounds__(64 * (NC + kProducers + (SPLIT ? 1 : 0))) void k_he
     // Every stage is TG tiles: past the workgroup's last tile that tile is fetched again (an L2 hit),
     // so that every stage counts the same number of loads; the consumers mask those copies.
     const int pw = wv - NC;
-    StageCursor cur;
-    cur.start(nhalf);
+    StageCursor<LV> cur(nhalf, KB);
     auto issue = [&](int slot) {
       char* stage = lds + slot * kStage;
       const int tile0 = t_lo + (cur.half0 + cur.h) * TG;
@@ -337,7 +478,7 @@ __global__ __launch_bounds__(64 * (NC + kProducers + (SPLIT ? 1 : 0))) void k_he
         const int tile = min(tile0 + (j >> 2), t_hi - 1);
         const int row = min(tile * 16 + r, g.N - 1);               // rows past the end repeat the last one, masked later
         const char* src = static_cast<const char*>(g.w[0]) + static_cast<size_t>(row) * row_bytes + (((lane & 15) ^ r) << 4) +
-                          (static_cast<size_t>(cur.kb) << 8);
+                          (static_cast<size_t>(cur.k.kb) << 8);
         load_to_lds16(src, stage + j * 1024);
       }
       cur.advance(nhalf, KB);
@@ -361,14 +502,15 @@ __global__ __launch_bounds__(64 * (NC + kProducers + (SPLIT ? 1 : 0))) void k_he
   }
 
   // -------------------------------------------------------------------- consumer
-  constexpr int NT = NC * RTW;     // row tiles of the packed activations
+  constexpr int NT = RG * RT;      // row tiles of the packed activations
   if constexpr (SPLIT) {
-    static_assert(RTW == 2, "a split last tile is the first of a pair");
-    if (wv == NC - 1) Consumer<1, TG / 2, TG, S>(g, lds, (NC - 1) * RTW, 0, NT, lane, t_lo, t_hi, KB, g.wide_slots).run();
-    else if (wv > NC) Consumer<1, TG / 2, TG, S>(g, lds, (NC - 1) * RTW, TG / 2, NT, lane, t_lo, t_hi, KB, g.wide_slots).run();
-    else Consumer<RTW, TG, TG, S>(g, lds, wv * RTW, 0, NT, lane, t_lo, t_hi, KB, g.wide_slots).run();
+    static_assert(RT == 2 && CS == 1 && PL == 1, "a split last tile is the first of a pair");
+    if (wv == NC - 1) Consumer<1, TG / 2, TG, S, PL, TB, LV>(g, lds, (NC - 1) * RT, 0, NT, lane, t_lo, t_hi, KB).run();
+    else if (wv > NC) Consumer<1, TG / 2, TG, S, PL, TB, LV>(g, lds, (NC - 1) * RT, TG / 2, NT, lane, t_lo, t_hi, KB).run();
+    else Consumer<RT, TG, TG, S, PL, TB, LV>(g, lds, wv * RT, 0, NT, lane, t_lo, t_hi, KB).run();
   } else {
-    Consumer<RTW, TG, TG, S>(g, lds, wv * RTW, 0, NT, lane, t_lo, t_hi, KB, g.wide_slots).run();
+    constexpr int JN = TG / CS;
+    Consumer<RT, JN, TG, S, PL, TB, LV>(g, lds, (wv / CS) * RT, (wv % CS) * JN, NT, lane, t_lo, t_hi, KB).run();
   }
 }
 
@@ -378,55 +520,104 @@ __global__ __launch_bounds__(64 * (NC + kProducers + (SPLIT ? 1 : 0))) void k_he
 // row tile shared by two waves instead of one wave next to a full consumer on its SIMD: 1.5 % faster.
 constexpr int kWideTiles = 8, kWideStages = 4;
 
-template <int NC, int RTW, bool SPLIT>
+// How the rows are dealt to consumer waves.  One plane: pairs of row tiles per wave from 33 rows on (one LDS read
+// then feeds two matrix instructions); fewer rows leave one or two row tiles, whose columns are split
+// over four waves, one per SIMD.  Two planes: the pair is value and rest of the same 16 rows.
+struct WideShape { int rg, rt, cs, split; };
+WideShape wide_shape(int M, int planes) {
+  const int tiles = (M + 15) / 16;
+  if (planes == 2) return {tiles, 2, tiles == 1 ? 4 : tiles == 2 ? 2 : 1, 0};
+  if (tiles <= 2) return {tiles, 1, tiles == 1 ? 4 : 2, 0};
+  return {(tiles + 1) / 2, 2, 1, tiles & 1};
+}
+
+template <int RG, int RT, int CS, int PL, int TB, bool SPLIT>
 hipError_t launch_wide_as(const GemmArgs& g, hipStream_t s) {
   constexpr int TG = kWideTiles, S = kWideStages;
+  // levels of the chunk tree: as many as the registers hold beside the accumulators of a pass (4, 8, 16 or 32
+  // 16 x 16 tiles per wave)
+  constexpr int kAcc = RT * (TG / CS) * 2;
+  constexpr int LV = kAcc <= 8 ? 2 : kAcc <= 16 && TB == 1 ? 1 : 0;
   // set once per process; a function-local static is initialised under the language's own lock
-  static const hipError_t attr = hipFuncSetAttribute(reinterpret_cast<const void*>(&k_head_wide<NC, RTW, TG, S, SPLIT>),
+  static const hipError_t attr = hipFuncSetAttribute(reinterpret_cast<const void*>(&k_head_wide<RG, RT, CS, PL, TB, TG, S, SPLIT, LV>),
                                                      hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
   if (attr != hipSuccess) return attr;
-  const int units = (g.K >> 7) * NC * RTW;
-  hipLaunchKernelGGL(k_pack_act, dim3((units + 3) / 4), dim3(256), 0, s, static_cast<const bf16_t*>(g.a_src),
-                     static_cast<uint4*>(g.a_packed), g.M, g.K, NC * RTW);
-  hipLaunchKernelGGL((k_head_wide<NC, RTW, TG, S, SPLIT>), dim3(g.wide_w), dim3(64 * (NC + kProducers + (SPLIT ? 1 : 0))),
+  hipLaunchKernelGGL((k_head_wide<RG, RT, CS, PL, TB, TG, S, SPLIT, LV>), dim3(g.wide_w), dim3(64 * (RG * CS + kProducers + (SPLIT ? 1 : 0))),
                      static_cast<size_t>(S) * TG * 4096, s, g);
   return hipGetLastError();
 }
 
-// an odd number of 16-row tiles: the last one is shared by two waves
-template <int NC, int RTW>
-hipError_t launch_wide(const GemmArgs& g, hipStream_t s) {
-  return ((g.M + 15) / 16) % 2 ? launch_wide_as<NC, RTW, true>(g, s) : launch_wide_as<NC, RTW, false>(g, s);
+// two planes (the draft's widened head): argmax or ranked candidates
+template <int RG, int CS>
+hipError_t launch_wide2(const GemmArgs& g, hipStream_t s) {
+  return g.top_b > 1 ? launch_wide_as<RG, 2, CS, 2, SPECEXIT_MAX_TOP_B, false>(g, s) : launch_wide_as<RG, 2, CS, 2, 1, false>(g, s);
+}
+
+// one plane: an odd number of row tiles above two has its last one shared by two waves
+template <int RG>
+hipError_t launch_wide1(const GemmArgs& g, bool split, hipStream_t s) {
+  return split ? launch_wide_as<RG, 2, 1, 1, 1, true>(g, s) : launch_wide_as<RG, 2, 1, 1, 1, false>(g, s);
 }
 
 }  // namespace
 
 bool head_wide_supported(const GemmArgs& g) {
-  return g.V >= 0 && g.planes == 1 && g.top_b <= 1 && g.M > 32 && g.M <= 160 && g.K % 128 == 0 && g.nseg == 1;
+  if (g.V < 0 || g.K % 128 != 0 || g.nseg != 1 || g.M < 1) return false;
+  return g.planes == 2 ? g.M <= 64 && g.top_b <= SPECEXIT_MAX_TOP_B : g.top_b <= 1 && g.M <= 160;
 }
 
 // One workgroup per compute unit, each walking an equal share of the weight tiles (at least one
-// stage's worth); candidate slots per workgroup = the halves of the longest share.
+// stage's worth); one candidate slot per workgroup and column split.
 void head_wide_plan(GemmArgs& g, int num_cus) {
   g.wide = head_wide_supported(g) ? 1 : 0;
   if (!g.wide) return;
   const int ntiles = gemm_ntiles(g.N);
+  const WideShape sh = wide_shape(g.M, g.planes);
   g.wide_w = std::max(1, std::min(num_cus, ntiles / kWideTiles));
-  g.wide_slots = ((ntiles + g.wide_w - 1) / g.wide_w + kWideTiles - 1) / kWideTiles;
+  g.wide_slots = sh.split ? 2 : sh.cs;
 }
 
-int head_wide_groups(const GemmArgs& g) { return g.wide_w * g.wide_slots * 2; }
+int head_wide_groups(const GemmArgs& g) { return g.wide_w * g.wide_slots; }
 
-// bytes of the packed activations: the row tiles the consumer waves cover (32 rows each) x K
-size_t head_wide_pack_bytes(const GemmArgs& g) { return g.wide ? static_cast<size_t>((g.M + 31) / 32) * 32 * g.K * 2 : 0; }
+// bytes of the packed activations: the row tiles the consumer waves cover x K (none: read in place)
+size_t head_wide_pack_bytes(const GemmArgs& g) {
+  if (!g.wide) return 0;
+  const WideShape sh = wide_shape(g.M, g.planes);
+  if (g.planes == 1 && sh.rt == 1) return 0;
+  return static_cast<size_t>(sh.rg) * sh.rt * 16 * g.K * 2;
+}
 
-hipError_t launch_head_wide(const GemmArgs& g, hipStream_t s) {
-  if (!head_wide_supported(g) || g.a_mode != 1 || g.wide_w < 1 || !g.a_packed) return hipErrorInvalidValue;
-  switch ((g.M + 31) / 32) {
-    case 2: return launch_wide<2, 2>(g, s);      // 33 ..  64 rows
-    case 3: return launch_wide<3, 2>(g, s);      // 65 ..  96
-    case 4: return launch_wide<4, 2>(g, s);      // 97 .. 128
-    case 5: return launch_wide<5, 2>(g, s);      // 129 .. 160
+hipError_t launch_head_wide(const GemmArgs& ga, hipStream_t s) {
+  if (!head_wide_supported(ga) || ga.wide_w < 1) return hipErrorInvalidValue;
+  const WideShape sh = wide_shape(ga.M, ga.planes);
+  GemmArgs g = ga;
+  const int KB = g.K >> 7;
+  if (g.planes == 2) {
+    if (g.a_mode != 3 || !g.a_packed) return hipErrorInvalidValue;
+    hipLaunchKernelGGL(k_pack_norm, dim3((KB * sh.rg + 3) / 4), dim3(256), 0, s, static_cast<const float*>(g.a_src), g.a_ssq, g.a_nssq,
+                       static_cast<const bf16_t*>(g.a_gain), g.a_eps, static_cast<uint4*>(g.a_packed), g.M, g.K, sh.rg);
+    switch (sh.rg) {
+      case 1: return launch_wide2<1, 4>(g, s);     //  1 .. 16 rows
+      case 2: return launch_wide2<2, 2>(g, s);     // 17 .. 32
+      case 3: return launch_wide2<3, 1>(g, s);     // 33 .. 48
+      case 4: return launch_wide2<4, 1>(g, s);     // 49 .. 64
+      default: return hipErrorInvalidValue;
+    }
+  }
+  if (g.a_mode != 1) return hipErrorInvalidValue;
+  if (sh.rt == 1) {
+    g.a_packed = nullptr;
+    return sh.rg == 1 ? launch_wide_as<1, 1, 4, 1, 1, false>(g, s) : launch_wide_as<2, 1, 2, 1, 1, false>(g, s);
+  }
+  if (!g.a_packed) return hipErrorInvalidValue;
+  const int units = KB * sh.rg * sh.rt;
+  hipLaunchKernelGGL(k_pack_act, dim3((units + 3) / 4), dim3(256), 0, s, static_cast<const bf16_t*>(g.a_src),
+                     static_cast<uint4*>(g.a_packed), g.M, g.K, sh.rg * sh.rt);
+  switch (sh.rg) {
+    case 2: return launch_wide1<2>(g, sh.split, s);      // 33 ..  64 rows
+    case 3: return launch_wide1<3>(g, sh.split, s);      // 65 ..  96
+    case 4: return launch_wide1<4>(g, sh.split, s);      // 97 .. 128
+    case 5: return launch_wide1<5>(g, sh.split, s);      // 129 .. 160
     default: return hipErrorInvalidValue;
   }
 }

@@ -75,10 +75,10 @@ struct GemmArgs {
   int a_vocab;
   int* status;         // device error word or nullptr (first out-of-range token id seen)
   int kc;              // K elements of activations staged in LDS at a time (multiple of 128)
-  int wide;            // head mode over more than 32 bf16 rows: the kernel of gemm_wide.hip (weights through an LDS
-                       // ring, activations in registers); head_wide_groups() candidates per row
+  int wide;            // head mode: the kernel of gemm_wide.hip (weights through an LDS ring, activations in
+                       // registers); head_wide_groups() candidates per row
   int wide_w;          //   its workgroups (each walks an equal share of the weight tiles)
-  int wide_slots;      //   candidate slots per workgroup and row
+  int wide_slots;      //   candidate slots per workgroup and row, each of max(top_b, 1) candidates
   void* a_packed;      //   scratch of head_wide_pack_bytes() for the activations in operand order
   float* partial;      // [ksplit][M*planes][N] fp32, or nullptr in head mode
   // epi = 1: the workgroup that finishes a 128-row group last adds up the group's partial
@@ -92,9 +92,9 @@ struct GemmArgs {
   RopeArgs rope;       // epi = 2: the finished rows are q / k / v heads (bf16 outputs)
   int V;               // head mode when >= 0
   int n_extra;
-  int top_b;           // head mode: candidates kept per tile (0 or 1 = the argmax only)
-  float* part_val;     // head mode: [M][ntiles][top_b] best values per 16-row tile, best first
-  int* part_idx;       //            [M][ntiles][top_b] their row indices (INT_MAX = none)
+  int top_b;           // head mode: candidates kept per slot (0 or 1 = the argmax only)
+  float* part_val;     // head mode: [M][head_wide_groups][top_b] best values, best first
+  int* part_idx;       //            their row indices (INT_MAX = none)
   float* extra_out;    // [M][n_extra] or nullptr
   float* logits_dbg;   // [M][V] or nullptr
 };

@@ -74,6 +74,14 @@ def test_small_bf16_mfma(B, paged):
     one_step(shape, w, kv, tok, g, pos, label="small mfma")
 
 
+@pytest.mark.parametrize("B", [17, 32, 33, 49, 64])
+def test_row_tile_edges(B):
+    shape = gen.scaled(gen.config(2), D=512, Hq=4, Hkv=2, d=128, I=768, V=3001, B=B, ctx=(0, 60), k=2)
+    w, kv, tok, g, pos = setup(shape, B, std=0.05)
+    w = force_draft_gap(shape, w, kv, tok, g, pos)
+    one_step(shape, w, kv, tok, g, pos, label="row tile edges")
+
+
 def test_small_bf16_alu_fallback():
     shape = gen.scaled(gen.config(1), D=192, Hq=4, Hkv=2, d=64, I=320, V=1000, B=2, ctx=(5, 90), k=2)
     w, kv, tok, g, pos = setup(shape, 1, std=0.05)

@@ -70,6 +70,15 @@ def test_small_bf16_trees(B, paged, seed):
     check_tree(shape, w, kv, tok0, g0, L, parent, rank, 3, "small bf16")
 
 
+@pytest.mark.parametrize("B,top_b", [(2, 4), (14, 3), (20, 3)])
+def test_levels_of_many_rows(B, top_b):
+    # levels of 2 to 60 rows: ranked candidates at one, two, three and four row tiles, the last one ragged or full
+    shape = gen.scaled(gen.config(3), D=768, Hq=4, Hkv=2, d=64, I=512, V=3000, B=B, ctx=(0, 100), n_q=8, k=3)
+    parent, rank = np.array([-1, 0, 0, 0, 1, 2, 3, 3], np.int32), np.array([0, 0, 1, 2, 0, 0, 0, 1], np.int32)
+    w, kv, tok0, g0, L = setup(shape, B)
+    check_tree(shape, w, kv, tok0, g0, L, parent, rank, top_b, "many rows")
+
+
 def test_a_path_shaped_tree_matches_the_chain_entry_point():
     """W = 1, top_b = 1: the level call must reproduce specexit_draft_step step by step."""
     shape = gen.scaled(gen.config(1), D=256, Hq=4, Hkv=2, d=128, I=512, V=2000, B=2, ctx=(40, 200), n_q=5, k=4)

@@ -82,6 +82,26 @@ def test_tie_takes_lowest_index_across_tiles(M, V, rows):
     assert am[2] == rows[0] and logits[2, rows[0]] == logits[2, rows[1]] == logits[2, rows[2]]
 
 
+@pytest.mark.parametrize("M,D,V", [(1, 2048, 4500), (16, 512, 4500), (17, 2048, 300), (32, 640, 20000), (33, 2048, 4500), (48, 256, 4500), (49, 512, 70)])
+def test_bf16_row_tile_edges_and_k_chunks(M, D, V):
+    # the wave splits change at 16, 32, 48 rows; K in four chunks (4, 5 and 16 blocks) and in one (2); one workgroup, a few, many
+    err = run_case(gen.scaled(gen.config(1), V=V, D=D), M, 2, M + D, "row tile edges")
+    assert err < 1e-3
+
+
+@pytest.mark.parametrize("M", [2, 30])
+def test_tie_takes_lowest_index_across_workgroups_that_take_k_in_another_order(M):
+    shape = gen.scaled(gen.config(1), V=40000, D=2048)
+    hidden = gen.hidden_rows(shape, M, 5)
+    w = gen.lm_head(shape, 5)
+    win = gen.store(shape, (hidden[1] / np.abs(hidden[1]).max()).astype(np.float32))
+    rows = tuple(range(1259, 40000, 1259))                  # one in every eighth workgroup's share, all chunk orders
+    for row in rows:
+        w[row] = win
+    am, mx, _, logits = gpu_lmhead(shape, hidden, w)
+    assert am[1] == rows[0] and len({float(logits[1, r]) for r in rows}) == 1
+
+
 @pytest.mark.parametrize("M", [16, 72, 144])
 def test_repeated_calls_give_identical_bits(M):
     # fixed summation and merge orders: no atomics, no dependence on which workgroup finishes first
