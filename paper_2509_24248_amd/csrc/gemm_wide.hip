@@ -83,10 +83,19 @@ struct KOrder {
   }
 };
 
-// The stages of a workgroup in the order they pass through the ring.  The workgroup's tiles
-// [t_lo, t_hi) are cut into "halves" of TG tiles; a pass takes two halves (the last pass one, if the
-// count is odd) through all k blocks, the halves of a k block one after the other, so that the
-// consumers fetch their activation pieces of a k block once for 2 TG tiles.
+// The workgroup's tiles [t_lo, t_hi) in equal "halves" of at most TG tiles (equal: 17 tiles as 8 + 8 + 1 would
+// take the last one through all k blocks at one tile per stage, too little in flight to fill the latency).
+struct Halves {
+  int t_lo, n, count, most;     // tiles, halves, tiles of the largest half
+  __device__ __forceinline__ Halves(int lo, int hi, int TG) : t_lo(lo), n(hi - lo), count((hi - lo + TG - 1) / TG) {
+    most = (n + count - 1) / count;
+  }
+  __device__ __forceinline__ int first(int h) const { return t_lo + n * h / count; }
+};
+
+// The stages of a workgroup in the order they pass through the ring.  A pass takes two halves (the last
+// pass one, if the count is odd) through all k blocks, the halves of a k block one after the other, so that
+// the consumers fetch their activation pieces of a k block once for both.
 template <int LV>
 struct StageCursor {
   int half0, nh, h, n;   // first half and number of halves of the current pass; half within the pass; k blocks done
@@ -151,7 +160,8 @@ struct Consumer {
   static constexpr int RO = RT / PL;        // 16-row tiles of results
   const GemmArgs& g;
   char* lds;
-  int rt0, jc0, fr, fq, t_lo, t_hi, KB;
+  int rt0, jc0, fr, fq, KB;
+  Halves halves;
   KOrder<LV> k;             // at the k block whose pieces `b` holds
   const uint4* apack[RT];   // this lane's piece of row tile t, k block 0, k step 0
   size_t kb_stride;         // uint4 entries from one k block to the next
@@ -161,8 +171,8 @@ struct Consumer {
   int stage_no;     // stages consumed so far: stage i lives in ring slot i % S
   Best<TB> best[RO];
 
-  __device__ __forceinline__ Consumer(const GemmArgs& g_, char* lds_, int rt0_, int jc0_, int NT, int lane, int t_lo_, int t_hi_, int KB_)
-      : g(g_), lds(lds_), rt0(rt0_), jc0(jc0_), fr(lane & 15), fq(lane >> 4), t_lo(t_lo_), t_hi(t_hi_), KB(KB_), k(KB_), stage_no(0) {
+  __device__ __forceinline__ Consumer(const GemmArgs& g_, char* lds_, int rt0_, int jc0_, int NT, int lane, const Halves& halves_, int KB_)
+      : g(g_), lds(lds_), rt0(rt0_), jc0(jc0_), fr(lane & 15), fq(lane >> 4), KB(KB_), halves(halves_), k(KB_), stage_no(0) {
     if (g.a_packed) {
       // packed activations: [k block][row tile][k step][lane] 16-byte pieces (NT row tiles), so that one
       // load instruction of a wave reads 1 KB of consecutive bytes
@@ -299,18 +309,19 @@ struct Consumer {
     // widened head's extra rows.
 #pragma unroll
     for (int h = 0; h < NH; ++h) {
-      const int tile0 = t_lo + (half0 + h) * TG + jc0;      // this wave's first tile of the half
+      const int tile0 = halves.first(half0 + h) + jc0;      // this wave's first tile of the half
+      const int tile1 = halves.first(half0 + h + 1);        // (the stage repeats the half's last tile from here on)
 #pragma unroll
       for (int o = 0; o < RO; ++o) {
         const int m = 16 * (rt0 / PL + o) + fr;
         const bool owner = m < g.M;
-        // tiles that lie wholly inside the share and below the signal rows (all but the last of a
-        // launch) need no checks per element: the consumers stand still during the epilogue while
-        // the ring fills up, so its length counts
-        const bool plain = !g.logits_dbg && tile0 + JN <= t_hi && (tile0 + JN) * 16 <= g.V;    // uniform
+        // tiles that lie wholly below the signal rows (all but the last of a launch) need no checks per
+        // element: the consumers stand still during the epilogue while the ring fills up, so its length counts
+        const bool plain = !g.logits_dbg && (tile0 + JN) * 16 <= g.V;    // uniform
         const int nb = tile0 * 16 + 4 * fq;
 #pragma unroll
         for (int j = 0; j < JN; ++j) {
+          if (tile0 + j >= tile1) break;                     // uniform
 #pragma unroll
           for (int i = 0; i < 4; ++i) {
             const int n = nb + 16 * j + i;
@@ -318,7 +329,7 @@ struct Consumer {
             if constexpr (PL == 2) val += acc[2 * o + 1][h * JN + j][i];
             if (plain) {
               best[o].add(val, n);                           // n grows with h, j and i
-            } else if (owner && tile0 + j < t_hi && n < g.N) {    // (tiles past the workgroup's range hold a copy of its last tile)
+            } else if (owner && n < g.N) {
               if (n < g.V) {
                 if (g.logits_dbg) g.logits_dbg[static_cast<size_t>(m) * g.V + n] = val;
                 best[o].add(val, n);
@@ -333,10 +344,9 @@ struct Consumer {
   }
 
   __device__ __forceinline__ void run() {
-    const int nhalf = (t_hi - t_lo + TG - 1) / TG;
 #pragma unroll 1
-    for (int half0 = 0; half0 < nhalf; half0 += 2) {
-      if (half0 + 1 < nhalf) pass<2>(half0);
+    for (int half0 = 0; half0 < halves.count; half0 += 2) {
+      if (half0 + 1 < halves.count) pass<2>(half0);
       else pass<1>(half0);
     }
     // the row's best over its four lanes, one candidate (list) per workgroup and column split
@@ -435,6 +445,15 @@ __global__ __launch_bounds__(256) void k_pack_norm(const float* __restrict__ src
   }
 }
 
+// s_waitcnt vmcnt(PER * n) for n = 1 .. N (the count is part of the instruction)
+template <int N, int PER>
+__device__ __forceinline__ void wait_tiles(int n) {
+  if constexpr (N > 1) {
+    if (n < N) { wait_tiles<N - 1, PER>(n); return; }
+  }
+  __builtin_amdgcn_s_waitcnt(vmcnt_imm(PER * N));
+}
+
 // RG groups of RT row tiles, each group's columns split over CS waves; then the producers.  SPLIT (CS = 1): the
 // last group's second row tile does not exist (an odd number of row tiles), and its one tile is shared with
 // a further wave after the producers, each taking half of the columns: no SIMD then carries three row
@@ -454,7 +473,8 @@ __global__ __launch_bounds__(64 * (RG * CS + kProducers + (SPLIT ? 1 : 0))) void
   // this workgroup's share of the weight tiles: equal shares whatever the vocabulary size
   const int t_lo = static_cast<int>(static_cast<int64_t>(blockIdx.x) * ntiles / gridDim.x);
   const int t_hi = static_cast<int>(static_cast<int64_t>(blockIdx.x + 1) * ntiles / gridDim.x);
-  const int nhalf = (t_hi - t_lo + TG - 1) / TG;
+  const Halves halves(t_lo, t_hi, TG);
+  const int nhalf = halves.count;
   const int KB = g.K >> 7;
   const int total = nhalf * KB;                 // stages of this workgroup
   const size_t row_bytes = static_cast<size_t>(g.K) * 2;
@@ -464,18 +484,21 @@ __global__ __launch_bounds__(64 * (RG * CS + kProducers + (SPLIT ? 1 : 0))) void
     // piece j of a stage = rows 4 (j % 4) .. + 3 of tile j / 4; lane l fetches row 4 (j % 4) + l / 16,
     // 16-byte piece (l % 16) ^ row and lands at piece base + 16 l, so that tile entry [row][pos]
     // holds piece pos ^ row: the consumers' per-row operand reads then touch 16 distinct slots.
-    // Every stage is TG tiles: past the workgroup's last tile that tile is fetched again (an L2 hit),
-    // so that every stage counts the same number of loads; the consumers mask those copies.
+    // Every stage is as many tiles as the largest half has: a half of one tile less fetches its last one
+    // again (an L2 hit), so that every stage counts the same number of loads.
     const int pw = wv - NC;
+    static_assert(PP == 2 * TG, "each producer brings in half of every tile");
+    const int per_stage = 2 * halves.most;
     StageCursor<LV> cur(nhalf, KB);
     auto issue = [&](int slot) {
       char* stage = lds + slot * kStage;
-      const int tile0 = t_lo + (cur.half0 + cur.h) * TG;
+      const int tile0 = halves.first(cur.half0 + cur.h), tile1 = halves.first(cur.half0 + cur.h + 1);
 #pragma unroll
       for (int u = 0; u < PP; ++u) {
+        if (u >= per_stage) break;               // uniform
         const int j = pw + u * kProducers;
         const int r = 4 * (j & 3) + (lane >> 4);
-        const int tile = min(tile0 + (j >> 2), t_hi - 1);
+        const int tile = min(tile0 + (j >> 2), tile1 - 1);
         const int row = min(tile * 16 + r, g.N - 1);               // rows past the end repeat the last one, masked later
         const char* src = static_cast<const char*>(g.w[0]) + static_cast<size_t>(row) * row_bytes + (((lane & 15) ^ r) << 4) +
                           (static_cast<size_t>(cur.k.kb) << 8);
@@ -488,7 +511,7 @@ __global__ __launch_bounds__(64 * (RG * CS + kProducers + (SPLIT ? 1 : 0))) void
     for (int i = 0; i < total; ++i) {
       // this wave's pieces of stage i have landed once at most the pieces of the S-2 stages issued
       // after it are outstanding (loads return in order); near the end simply wait for all
-      if (i + S - 1 < total) __builtin_amdgcn_s_waitcnt(vmcnt_imm((S - 2) * PP));
+      if (i + S - 1 < total) wait_tiles<TG, (S - 2) * 2>(halves.most);
       else __builtin_amdgcn_s_waitcnt(vmcnt_imm(0));
       __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
       __builtin_amdgcn_s_barrier();              // stage i is complete; the slot of stage i-1 is free
@@ -505,12 +528,12 @@ __global__ __launch_bounds__(64 * (RG * CS + kProducers + (SPLIT ? 1 : 0))) void
   constexpr int NT = RG * RT;      // row tiles of the packed activations
   if constexpr (SPLIT) {
     static_assert(RT == 2 && CS == 1 && PL == 1, "a split last tile is the first of a pair");
-    if (wv == NC - 1) Consumer<1, TG / 2, TG, S, PL, TB, LV>(g, lds, (NC - 1) * RT, 0, NT, lane, t_lo, t_hi, KB).run();
-    else if (wv > NC) Consumer<1, TG / 2, TG, S, PL, TB, LV>(g, lds, (NC - 1) * RT, TG / 2, NT, lane, t_lo, t_hi, KB).run();
-    else Consumer<RT, TG, TG, S, PL, TB, LV>(g, lds, wv * RT, 0, NT, lane, t_lo, t_hi, KB).run();
+    if (wv == NC - 1) Consumer<1, TG / 2, TG, S, PL, TB, LV>(g, lds, (NC - 1) * RT, 0, NT, lane, halves, KB).run();
+    else if (wv > NC) Consumer<1, TG / 2, TG, S, PL, TB, LV>(g, lds, (NC - 1) * RT, TG / 2, NT, lane, halves, KB).run();
+    else Consumer<RT, TG, TG, S, PL, TB, LV>(g, lds, wv * RT, 0, NT, lane, halves, KB).run();
   } else {
     constexpr int JN = TG / CS;
-    Consumer<RT, JN, TG, S, PL, TB, LV>(g, lds, (wv / CS) * RT, (wv % CS) * JN, NT, lane, t_lo, t_hi, KB).run();
+    Consumer<RT, JN, TG, S, PL, TB, LV>(g, lds, (wv / CS) * RT, (wv % CS) * JN, NT, lane, halves, KB).run();
   }
 }
 
@@ -523,11 +546,16 @@ constexpr int kWideTiles = 8, kWideStages = 4;
 // How the rows are dealt to consumer waves.  One plane: pairs of row tiles per wave from 33 rows on (one LDS read
 // then feeds two matrix instructions); fewer rows leave one or two row tiles, whose columns are split
 // over four waves, one per SIMD.  Two planes: the pair is value and rest of the same 16 rows.
+// With four row tiles two waves per pair (which leaves the registers for a chunk tree of one level) are as fast
+// or faster (64 rows, V = 151936: D = 2560 / 4096 / 5120 139 / 221 / 262 us against 146 / 219 / 268); with three, five
+// or six they lose 4 % (D = 4096, V = 100000, 80 rows: 164 against 158), except where rows are a power of two of
+// at most 4 KB apart and the common k block costs more (D = 2048, V = 128259, 48 / 80 rows: 95 / 102 against 125 / 127).
 struct WideShape { int rg, rt, cs, split; };
-WideShape wide_shape(int M, int planes) {
+WideShape wide_shape(int M, int planes, int K) {
   const int tiles = (M + 15) / 16;
-  if (planes == 2) return {tiles, 2, tiles == 1 ? 4 : tiles == 2 ? 2 : 1, 0};
+  if (planes == 2) return {tiles, 2, tiles == 1 ? 4 : tiles <= 3 ? 2 : 1, 0};
   if (tiles <= 2) return {tiles, 1, tiles == 1 ? 4 : 2, 0};
+  if (tiles == 4 || (tiles <= 6 && K <= 2048 && (K & (K - 1)) == 0)) return {(tiles + 1) / 2, 2, 2, 0};
   return {(tiles + 1) / 2, 2, 1, tiles & 1};
 }
 
@@ -555,8 +583,10 @@ hipError_t launch_wide2(const GemmArgs& g, hipStream_t s) {
 
 // one plane: an odd number of row tiles above two has its last one shared by two waves
 template <int RG>
-hipError_t launch_wide1(const GemmArgs& g, bool split, hipStream_t s) {
-  return split ? launch_wide_as<RG, 2, 1, 1, 1, true>(g, s) : launch_wide_as<RG, 2, 1, 1, 1, false>(g, s);
+hipError_t launch_wide1(const GemmArgs& g, const WideShape& sh, hipStream_t s) {
+  if constexpr (RG <= 3)
+    if (sh.cs == 2) return launch_wide_as<RG, 2, 2, 1, 1, false>(g, s);
+  return sh.split ? launch_wide_as<RG, 2, 1, 1, 1, true>(g, s) : launch_wide_as<RG, 2, 1, 1, 1, false>(g, s);
 }
 
 }  // namespace
@@ -572,7 +602,7 @@ void head_wide_plan(GemmArgs& g, int num_cus) {
   g.wide = head_wide_supported(g) ? 1 : 0;
   if (!g.wide) return;
   const int ntiles = gemm_ntiles(g.N);
-  const WideShape sh = wide_shape(g.M, g.planes);
+  const WideShape sh = wide_shape(g.M, g.planes, g.K);
   g.wide_w = std::max(1, std::min(num_cus, ntiles / kWideTiles));
   g.wide_slots = sh.split ? 2 : sh.cs;
 }
@@ -582,14 +612,14 @@ int head_wide_groups(const GemmArgs& g) { return g.wide_w * g.wide_slots; }
 // bytes of the packed activations: the row tiles the consumer waves cover x K (none: read in place)
 size_t head_wide_pack_bytes(const GemmArgs& g) {
   if (!g.wide) return 0;
-  const WideShape sh = wide_shape(g.M, g.planes);
+  const WideShape sh = wide_shape(g.M, g.planes, g.K);
   if (g.planes == 1 && sh.rt == 1) return 0;
   return static_cast<size_t>(sh.rg) * sh.rt * 16 * g.K * 2;
 }
 
 hipError_t launch_head_wide(const GemmArgs& ga, hipStream_t s) {
   if (!head_wide_supported(ga) || ga.wide_w < 1) return hipErrorInvalidValue;
-  const WideShape sh = wide_shape(ga.M, ga.planes);
+  const WideShape sh = wide_shape(ga.M, ga.planes, ga.K);
   GemmArgs g = ga;
   const int KB = g.K >> 7;
   if (g.planes == 2) {
@@ -599,7 +629,7 @@ hipError_t launch_head_wide(const GemmArgs& ga, hipStream_t s) {
     switch (sh.rg) {
       case 1: return launch_wide2<1, 4>(g, s);     //  1 .. 16 rows
       case 2: return launch_wide2<2, 2>(g, s);     // 17 .. 32
-      case 3: return launch_wide2<3, 1>(g, s);     // 33 .. 48
+      case 3: return launch_wide2<3, 2>(g, s);     // 33 .. 48
       case 4: return launch_wide2<4, 1>(g, s);     // 49 .. 64
       default: return hipErrorInvalidValue;
     }
@@ -614,10 +644,10 @@ hipError_t launch_head_wide(const GemmArgs& ga, hipStream_t s) {
   hipLaunchKernelGGL(k_pack_act, dim3((units + 3) / 4), dim3(256), 0, s, static_cast<const bf16_t*>(g.a_src),
                      static_cast<uint4*>(g.a_packed), g.M, g.K, sh.rg * sh.rt);
   switch (sh.rg) {
-    case 2: return launch_wide1<2>(g, sh.split, s);      // 33 ..  64 rows
-    case 3: return launch_wide1<3>(g, sh.split, s);      // 65 ..  96
-    case 4: return launch_wide1<4>(g, sh.split, s);      // 97 .. 128
-    case 5: return launch_wide1<5>(g, sh.split, s);      // 129 .. 160
+    case 2: return launch_wide1<2>(g, sh, s);      // 33 ..  64 rows
+    case 3: return launch_wide1<3>(g, sh, s);      // 65 ..  96
+    case 4: return launch_wide1<4>(g, sh, s);      // 97 .. 128
+    case 5: return launch_wide1<5>(g, sh, s);      // 129 .. 160
     default: return hipErrorInvalidValue;
   }
 }
