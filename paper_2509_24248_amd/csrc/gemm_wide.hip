@@ -319,22 +319,52 @@ struct Consumer {
         // element: the consumers stand still during the epilogue while the ring fills up, so its length counts
         const bool plain = !g.logits_dbg && (tile0 + JN) * 16 <= g.V;    // uniform
         const int nb = tile0 * 16 + 4 * fq;
+        if constexpr (TB > 1) {
+          // ranked candidates: the values pass through a corner of the LDS (this lane's own 16 bytes per tile), so
+          // that the insertion exists once, in a loop.  Unrolled over the accumulators it is several KB of code
+          // that arrives line by line behind the weight stream (16 rows, V = 151936, D = 4096: 213 us; 187 without
+          // ranked candidates).
+          float4* mine = reinterpret_cast<float4*>(lds + S * kStage) + (threadIdx.x >> 6) * (JN * 64) + (threadIdx.x & 63);
 #pragma unroll
-        for (int j = 0; j < JN; ++j) {
-          if (tile0 + j >= tile1) break;                     // uniform
+          for (int j = 0; j < JN; ++j) {
+            f32x4_t v = acc[PL * o][h * JN + j];
+            if constexpr (PL == 2) v += acc[2 * o + 1][h * JN + j];
+            mine[j * 64] = make_float4(v[0], v[1], v[2], v[3]);
+          }
+          const int left_j = min(JN, tile1 - tile0);
+#pragma unroll 1
+          for (int x = 0; x < 4 * left_j; ++x) {
+            const float val = reinterpret_cast<const float*>(mine + (x >> 2) * 64)[x & 3];
+            const int n = nb + 16 * (x >> 2) + (x & 3);
+            if (n < g.V) best[o].add(val, n);
+            else if (owner && n < g.N && g.extra_out) g.extra_out[m * g.n_extra + (n - g.V)] = val;
+          }
+        } else if (plain) {
 #pragma unroll
-          for (int i = 0; i < 4; ++i) {
-            const int n = nb + 16 * j + i;
-            float val = acc[PL * o][h * JN + j][i];
-            if constexpr (PL == 2) val += acc[2 * o + 1][h * JN + j][i];
-            if (plain) {
-              best[o].add(val, n);                           // n grows with h, j and i
-            } else if (owner && n < g.N) {
-              if (n < g.V) {
-                if (g.logits_dbg) g.logits_dbg[static_cast<size_t>(m) * g.V + n] = val;
-                best[o].add(val, n);
-              } else if (g.extra_out) {
-                g.extra_out[m * g.n_extra + (n - g.V)] = val;
+          for (int j = 0; j < JN; ++j) {
+            const bool inside = tile0 + j < tile1;           // uniform
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+              float val = acc[PL * o][h * JN + j][i];
+              if constexpr (PL == 2) val += acc[2 * o + 1][h * JN + j][i];
+              best[o].add(inside ? val : -INFINITY, nb + 16 * j + i);    // n grows with h, j and i
+            }
+          }
+        } else {
+#pragma unroll
+          for (int j = 0; j < JN; ++j) {
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+              const int n = nb + 16 * j + i;
+              float val = acc[PL * o][h * JN + j][i];
+              if constexpr (PL == 2) val += acc[2 * o + 1][h * JN + j][i];
+              if (owner && tile0 + j < tile1 && n < g.N) {
+                if (n < g.V) {
+                  if (g.logits_dbg) g.logits_dbg[static_cast<size_t>(m) * g.V + n] = val;
+                  best[o].add(val, n);
+                } else if (g.extra_out) {
+                  g.extra_out[m * g.n_extra + (n - g.V)] = val;
+                }
               }
             }
           }
@@ -357,9 +387,8 @@ struct Consumer {
       const int m = 16 * (rt0 / PL + o) + fr;
       const size_t at = (static_cast<size_t>(m) * gridDim.x + blockIdx.x) * slots * top_b;
       const int mine = jc0 / JN;
-#pragma unroll
-      for (int r = 0; r < TB; ++r) {
-        if (r >= top_b) break;
+#pragma unroll 1
+      for (int r = 0; r < top_b; ++r) {
         float bv = best[o].v[0];
         int bi = best[o].i[0];
 #pragma unroll
@@ -571,7 +600,7 @@ hipError_t launch_wide_as(const GemmArgs& g, hipStream_t s) {
                                                      hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
   if (attr != hipSuccess) return attr;
   hipLaunchKernelGGL((k_head_wide<RG, RT, CS, PL, TB, TG, S, SPLIT, LV>), dim3(g.wide_w), dim3(64 * (RG * CS + kProducers + (SPLIT ? 1 : 0))),
-                     static_cast<size_t>(S) * TG * 4096, s, g);
+                     static_cast<size_t>(S) * TG * 4096 + (TB > 1 ? RG * TG * 1024 : 0), s, g);
   return hipGetLastError();
 }
 
