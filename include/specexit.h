@@ -53,7 +53,7 @@ typedef enum { SPECEXIT_KV_CONTIG = 0, SPECEXIT_KV_PAGED = 1 } specexit_kv_layou
 /* flags bit: the workspace passed to specexit_draft_step / specexit_draft_tree_level was
  * zero-filled once (specexit_workspace_prepare) and has since been written only by calls of
  * that same entry point with the same descriptor, cache view and row counts.  The call then
- * skips the launch that clears its arrival counters (every kernel leaves them at zero). */
+ * may skip clearing what has to start at zero (no kernel of this version needs it). */
 #define SPECEXIT_FLAG_WORKSPACE_PREPARED 1u
 /* flags bit: report out-of-range device data.  The kernels of the call write the first problem
  * they see into the status word of the calling host thread (specexit_set_dev_status), if that

@@ -9,6 +9,7 @@
 #include <stdio.h>
 #include <string.h>
 
+#include <algorithm>
 #include <atomic>
 #include <mutex>
 #include <vector>
@@ -161,7 +162,8 @@ struct DraftPlan {
   int nseq, W;  // sequences, rows (tree nodes of one level) per sequence
   int top_b;    // continuations reported per row
   int Kmax;
-  GemmArgs fc, qkv, o, gu, down, head;
+  GemmArgs fc, qkv, o, gu, down, head;    // plain-ALU path; head: both paths
+  ProjArgs pfc, pqkv, po, pgu, pdown;     // matrix-core path
   bool gemv;         // few rows: the layer's projections run as row-streaming GEMVs
   GemvArgs vfc, vqkv, vo, vgu, vdown, vhead;
   AttnArgs attn;
@@ -169,22 +171,43 @@ struct DraftPlan {
   int head_lists;    // candidate lists per row of the head, at most
 };
 
-void plan_gemm(GemmArgs& g, int N, int K, int M, int planes, bool mfma, int V, int top_b = 0) {
+void plan_gemm(GemmArgs& g, int N, int K, int M) {
   memset(&g, 0, sizeof(g));
   g.N = N;
   g.K = K;
   g.M = M;
-  g.planes = mfma ? planes : 1;
-  g.V = V;
-  g.top_b = top_b;
+  g.planes = 1;
+  g.V = -1;
   g.nseg = 1;
   g.seg_end[0] = g.seg_end[1] = g.seg_end[2] = N;
-  choose_ksplit(g, mfma, num_cus());
 }
 
-size_t partial_bytes_of(const GemmArgs& g, bool mfma) {
-  if (g.V >= 0 && mfma) return 0;
-  return static_cast<size_t>(g.ksplit) * g.M * g.planes * g.N * sizeof(float);
+void plan_head(GemmArgs& g, int N, int K, int M, int planes, int V, int n_extra, int top_b) {
+  plan_gemm(g, N, K, M);
+  g.planes = planes;
+  g.V = V;
+  g.n_extra = n_extra;
+  g.top_b = top_b;
+  head_wide_plan(g, num_cus());
+}
+
+void plan_proj(ProjArgs& g, int N, int K, int M, int planes) {
+  memset(&g, 0, sizeof(g));
+  g.N = N;
+  g.K = K;
+  g.M = M;
+  g.planes = planes;
+  g.nseg = 1;
+  g.seg_end[0] = g.seg_end[1] = g.seg_end[2] = N;
+  proj_plan(g, num_cus());
+}
+
+template <typename G>
+void three_blocks(G& g, int e0, int e1, int e2, int n) {
+  g.nseg = n;
+  g.seg_end[0] = e0;
+  g.seg_end[1] = e1;
+  g.seg_end[2] = e2;
 }
 
 int32_t make_draft_plan(DraftPlan& p, const specexit_model_desc* d, const specexit_kv_view* kv, int32_t nseq,
@@ -214,20 +237,26 @@ int32_t make_draft_plan(DraftPlan& p, const specexit_model_desc* d, const specex
   const int D = dm.D, Hd = dm.Hq * dm.d, I = dm.I;
   p.Kmax = 2 * D > Hd ? 2 * D : Hd;
   if (I > p.Kmax) p.Kmax = I;
-  p.mfma = dm.dtype == SPECEXIT_BF16 && gemm_mfma_supported(B, 2, 2 * D) && gemm_mfma_supported(B, 2, D) &&
-           gemm_mfma_supported(B, 2, Hd) && gemm_mfma_supported(B, 2, I);
-  plan_gemm(p.fc, D, 2 * D, B, 1, p.mfma, -1);
-  plan_gemm(p.qkv, (dm.Hq + 2 * dm.Hkv) * dm.d, D, B, 2, p.mfma, -1);
-  p.qkv.nseg = 3;
-  p.qkv.seg_end[0] = Hd;
-  p.qkv.seg_end[1] = Hd + dm.Hkv * dm.d;
-  p.qkv.seg_end[2] = Hd + 2 * dm.Hkv * dm.d;
-  plan_gemm(p.o, D, Hd, B, 1, p.mfma, -1);
-  plan_gemm(p.gu, 2 * I, D, B, 2, p.mfma, -1);
-  p.gu.nseg = 2;
-  p.gu.seg_end[0] = I;
-  p.gu.seg_end[1] = p.gu.seg_end[2] = 2 * I;
-  plan_gemm(p.down, D, I, B, 2, p.mfma, -1);
+  const int Hkd = dm.Hkv * dm.d, Nq = Hd + 2 * Hkd;
+  p.mfma = dm.dtype == SPECEXIT_BF16 && proj_supported(B, D, 2 * D) && D % 128 == 0 && proj_supported(B, Nq, D) && proj_supported(B, D, Hd) &&
+           proj_supported(B, 2 * I, D) && proj_supported(B, D, I);
+  if (p.mfma) {
+    plan_proj(p.pfc, D, 2 * D, B, 1);
+    plan_proj(p.pqkv, Nq, D, B, 2);
+    three_blocks(p.pqkv, Hd, Hd + Hkd, Nq, 3);
+    plan_proj(p.po, D, Hd, B, 1);
+    plan_proj(p.pgu, 2 * I, D, B, 2);
+    three_blocks(p.pgu, I, 2 * I, 2 * I, 2);
+    plan_proj(p.pdown, D, I, B, 2);
+  } else {
+    plan_gemm(p.fc, D, 2 * D, B);
+    plan_gemm(p.qkv, Nq, D, B);
+    three_blocks(p.qkv, Hd, Hd + Hkd, Nq, 3);
+    plan_gemm(p.o, D, Hd, B);
+    plan_gemm(p.gu, 2 * I, D, B);
+    three_blocks(p.gu, I, 2 * I, 2 * I, 2);
+    plan_gemm(p.down, D, I, B);
+  }
   p.gemv = p.mfma && gemv_supported(B, D, 2 * D) && gemv_supported(B, (dm.Hq + 2 * dm.Hkv) * dm.d, D) &&
            gemv_supported(B, D, Hd) && gemv_supported(B, 2 * I, D) && gemv_supported(B, D, I) && (dm.d % 2) == 0;
   if (p.gemv) {
@@ -259,24 +288,27 @@ int32_t make_draft_plan(DraftPlan& p, const specexit_model_desc* d, const specex
     p.vfc.stream = p.vqkv.stream = p.vo.stream = p.vgu.stream = p.vdown.stream = stream;
     p.vhead.stream = 1;
   }
-  plan_gemm(p.head, dm.V + 3, D, B, 2, p.mfma, dm.V, top_b);
-  p.head.n_extra = 3;
-  p.head_lists = p.head.wide ? head_wide_groups(p.head) : 1;
-  if (p.gemv && p.vhead.grid > p.head_lists) p.head_lists = p.vhead.grid;
-  size_t pb = 0;
-  const GemmArgs* all[6] = {&p.fc, &p.qkv, &p.o, &p.gu, &p.down, &p.head};
-  for (const GemmArgs* g : all) {
-    const size_t b = partial_bytes_of(*g, p.mfma);
-    if (b > pb) pb = b;
+  p.head_lists = 1;
+  if (p.mfma) {
+    plan_head(p.head, dm.V + 3, D, B, 2, dm.V, 3, top_b);
+    p.head_lists = head_wide_groups(p.head);
+    if (p.gemv && p.vhead.grid > p.head_lists) p.head_lists = p.vhead.grid;
+  } else {
+    plan_gemm(p.head, dm.V + 3, D, B);
   }
-  p.partial_bytes = pb;
+  p.partial_bytes = 0;
+  if (p.mfma && !p.gemv) {
+    for (const ProjArgs* g : {&p.pfc, &p.pqkv, &p.po, &p.pgu, &p.pdown}) p.partial_bytes = std::max(p.partial_bytes, proj_partial_bytes(*g));
+  } else if (!p.mfma) {
+    for (const GemmArgs* g : {&p.fc, &p.qkv, &p.o, &p.gu, &p.down, &p.head})
+      p.partial_bytes = std::max(p.partial_bytes, static_cast<size_t>(g->M) * g->N * sizeof(float));
+  }
   return SPECEXIT_OK;
 }
 
 struct DraftBufs {
-  float* act;
+  float* act;        // fp32 rows (row-streaming and plain-ALU paths), or the next projection's operand (matrix cores)
   float* partial;
-  float* partial2;   // the down projection's partial sums (its input lives in `partial`)
   float *x_buf, *a_buf;
   void *q_buf, *attn_out;
   void* attn_ws;
@@ -284,9 +316,7 @@ struct DraftBufs {
   int* part_idx;
   int32_t* head_am;
   float* extra;
-  float* ssq;        // [3][rows][groups of D]: pieces of the sums of squares behind the three norms
-  int* counters;     // arrival counters of the reducing GEMM epilogues
-  int n_counters;
+  float* ssq;        // [3][rows][workgroups]: pieces of the sums of squares behind the three norms
   char* head_pack;   // the widened head's activations in operand order
   size_t total;
 };
@@ -295,9 +325,10 @@ DraftBufs carve_draft(const DraftPlan& p, void* ws) {
   Carver c(ws);
   DraftBufs b;
   const size_t es = esize(p.dm.dtype);
-  b.act = c.take<float>(sizeof(float) * p.B * p.Kmax);
+  size_t act = sizeof(float) * p.B * p.Kmax;
+  if (p.mfma && !p.gemv) act = std::max(act, static_cast<size_t>(packed_tiles(p.B, 2)) * 32 * p.Kmax);
+  b.act = c.take<float>(act);
   b.partial = c.take<float>(p.partial_bytes);
-  b.partial2 = c.take<float>(p.mfma ? partial_bytes_of(p.down, true) : 0);
   b.x_buf = c.take<float>(sizeof(float) * p.B * p.dm.D);
   b.a_buf = c.take<float>(sizeof(float) * p.B * p.dm.D);
   b.q_buf = c.take<char>(es * p.B * p.dm.Hq * p.dm.d);
@@ -307,25 +338,25 @@ DraftBufs carve_draft(const DraftPlan& p, void* ws) {
   b.part_idx = c.take<int>(sizeof(int) * p.B * p.head_lists * p.top_b);
   b.head_am = c.take<int32_t>(sizeof(int32_t) * p.B);
   b.extra = c.take<float>(sizeof(float) * p.B * 3);
-  const int gd = p.gemv ? 3 * num_cus() : gemm_groups(p.dm.D);   // pieces per row: GEMV workgroups or 128-row groups
-  b.ssq = c.take<float>(sizeof(float) * 3 * p.B * gd);
-  b.n_counters = 3 * gd + gemm_groups((p.dm.Hq + 2 * p.dm.Hkv) * p.dm.d);
-  b.counters = c.take<int>(sizeof(int) * b.n_counters);
+  b.ssq = c.take<float>(p.gemv ? sizeof(float) * 3 * p.B * 3 * num_cus() : 0);   // a piece per row and GEMV workgroup
   b.head_pack = c.take<char>(head_wide_pack_bytes(p.head));
   b.total = c.off;
   return b;
 }
 
-int32_t run_gemm(GemmArgs g, bool mfma, bool bf16, const void* w0, const void* w1, const void* w2,
-                 const DraftBufs& b, hipStream_t s, const char* what) {
+// plain-ALU path
+int32_t run_gemm(GemmArgs g, bool bf16, const void* w0, const void* w1, const void* w2, const DraftBufs& b, hipStream_t s, const char* what) {
   g.w[0] = w0; g.w[1] = w1; g.w[2] = w2;
   g.act = b.act;
-  if (g.a_mode == 0) g.a_src = b.act;
   g.partial = b.partial;
-  g.part_val = b.part_val;
-  g.part_idx = b.part_idx;
-  g.extra_out = b.extra;
-  return check_hip(mfma ? launch_gemm_mfma(g, s) : launch_gemm_valu(g, bf16, s), what);
+  return check_hip(launch_gemm_valu(g, bf16, s), what);
+}
+
+// matrix-core path: the projection's partial sums; `p` keeps its weights and buffers for the kernel behind it
+int32_t run_proj(ProjArgs& p, const void* w0, const void* w1, const void* w2, const DraftBufs& b, hipStream_t s, const char* what) {
+  p.w[0] = w0; p.w[1] = w1; p.w[2] = w2;
+  p.partial = b.partial;
+  return check_hip(launch_proj(p, s), what);
 }
 
 // Inputs and outputs of one draft forward over p.B = nseq * W rows (row r = sequence r / W).
@@ -343,6 +374,16 @@ struct DraftIO {
   float *sig_raw, *sig;      // [rows, 3]
   uint32_t flags;
 };
+
+void fill_rope(RopeArgs& ra, const DraftPlan& p, const DraftIO& io, const specexit_kv_view* draft_kv, void* q_out, int* status) {
+  const DraftDims& dm = p.dm;
+  ra.pos = io.pos; ra.level = io.level; ra.node = io.node; ra.W = p.W; ra.theta = dm.rope_theta;
+  for (int c = 0; c < dm.d / 2; ++c) ra.inv_freq[c] = pow(static_cast<double>(dm.rope_theta), -2.0 * c / dm.d);
+  ra.Hq = dm.Hq; ra.Hkv = dm.Hkv; ra.d = dm.d; ra.q_out = q_out; ra.paged = p.attn.paged;
+  ra.kc = draft_kv->k; ra.vc = draft_kv->v; ra.page_table = draft_kv->page_table;
+  ra.page_size = p.attn.page_size; ra.max_pages = p.attn.max_pages; ra.l_max = p.attn.l_max;
+  ra.n_pages = p.attn.n_pages; ra.status = status;
+}
 
 int32_t run_draft(DraftPlan& p, const specexit_draft_weights* w, const specexit_kv_view* draft_kv, const DraftIO& io,
                   void* workspace, size_t workspace_bytes, hipStream_t s) {
@@ -363,7 +404,6 @@ int32_t run_draft(DraftPlan& p, const specexit_draft_weights* w, const specexit_
   const bool mf = p.mfma;
   int* const status = status_for(io.flags);
 
-  const int gd = gemm_groups(dm.D);
   g_prof_hook(SPECEXIT_PROF_DRAFT_PROJ_IN, 0, s);
   if (p.gemv) {
     // Few rows: every projection is a row-streaming GEMV whose epilogue finishes the job
@@ -383,69 +423,30 @@ int32_t run_draft(DraftPlan& p, const specexit_draft_weights* w, const specexit_
     g.w[0] = w->w_q; g.w[1] = w->w_k; g.w[2] = w->w_v;
     normed(g, 0, p.vfc, b.x_buf, w->ln_attn);
     g.epi = 1;
-    {
-      RopeArgs& ra = g.rope;
-      ra.pos = io.pos; ra.level = io.level; ra.node = io.node; ra.W = p.W; ra.theta = dm.rope_theta;
-      for (int c = 0; c < dm.d / 2; ++c) ra.inv_freq[c] = pow(static_cast<double>(dm.rope_theta), -2.0 * c / dm.d);
-      ra.Hq = dm.Hq; ra.Hkv = dm.Hkv; ra.d = dm.d; ra.q_out = b.q_buf; ra.paged = p.attn.paged;
-      ra.kc = draft_kv->k; ra.vc = draft_kv->v; ra.page_table = draft_kv->page_table;
-      ra.page_size = p.attn.page_size; ra.max_pages = p.attn.max_pages; ra.l_max = p.attn.l_max;
-      ra.n_pages = p.attn.n_pages; ra.status = status;
-    }
+    fill_rope(g.rope, p, io, draft_kv, b.q_buf, status);
     if ((rc = check_hip(launch_gemv(g, s), "gemv qkv"))) return rc;
   } else if (mf) {
-    // Fused form: each projection back into the hidden size finishes its own split-K sums
-    // (+ residual) in the workgroup that arrives last, leaving the rows and the pieces of
-    // their sums of squares; the next GEMM applies the RMSNorm while it stages its activations,
-    // and the down projection applies the SiLU gate the same way.
-    // the counters must start at zero and every kernel leaves them at zero: a caller that keeps
-    // a zero-filled workspace to this call (same shapes) may say so and save the clearing launch
-    if (!(io.flags & SPECEXIT_FLAG_WORKSPACE_PREPARED))
-      if ((rc = check_hip(launch_zero_i32(b.counters, b.n_counters, s), "zero counters"))) return rc;
-    auto reducing = [&](GemmArgs& g, int which, const float* residual, float* out_x, void* out_store) {
-      g.epi = 1;
-      g.counters = b.counters + which * gd;
-      g.residual = residual;
-      g.out_x = out_x;
-      g.out_store = out_store;
-      g.out_ssq = b.ssq + static_cast<size_t>(which) * B * gd;
-    };
-    auto normed = [&](GemmArgs& g, int which, const float* x, const void* gain) {
-      g.a_mode = 3;
-      g.a_src = x;
-      g.a_ssq = b.ssq + static_cast<size_t>(which) * B * gd;
-      g.a_nssq = gd;
-      g.a_gain = gain;
-      g.a_eps = dm.rms_eps;
-    };
-    // x = W_fc [embed[tok] ; hidden_in]
-    p.fc.a_mode = 2;   // the GEMM gathers [embed[tok] ; hidden_in] itself
-    p.fc.a_src = io.hidden_in;
-    p.fc.a_embed = w->embed;
-    p.fc.a_tok = io.tok;
-    p.fc.a_vocab = dm.V;
-    p.fc.status = status;
-    reducing(p.fc, 0, nullptr, b.x_buf, nullptr);
-    if ((rc = run_gemm(p.fc, mf, bf16, w->w_fc, nullptr, nullptr, b, s, "gemm fc"))) return rc;
-    // q, k, v; rotary; cache write; attention over the draft's own cache
-    normed(p.qkv, 0, b.x_buf, w->ln_attn);
-    p.qkv.epi = 2;     // finished heads are rotated and stored as q / cache entries by the GEMM itself
-    p.qkv.counters = b.counters + 3 * gd;
-    RopeArgs& ra = p.qkv.rope;
-    ra.pos = io.pos; ra.level = io.level; ra.node = io.node; ra.W = p.W; ra.theta = dm.rope_theta;
-    for (int c = 0; c < dm.d / 2; ++c) ra.inv_freq[c] = pow(static_cast<double>(dm.rope_theta), -2.0 * c / dm.d);
-    ra.Hq = dm.Hq; ra.Hkv = dm.Hkv; ra.d = dm.d; ra.q_out = b.q_buf; ra.paged = p.attn.paged;
-    ra.kc = draft_kv->k; ra.vc = draft_kv->v; ra.page_table = draft_kv->page_table;
-    ra.page_size = p.attn.page_size; ra.max_pages = p.attn.max_pages; ra.l_max = p.attn.l_max;
-    ra.n_pages = p.attn.n_pages; ra.status = status;
-    if ((rc = run_gemm(p.qkv, mf, bf16, w->w_q, w->w_k, w->w_v, b, s, "gemm qkv"))) return rc;
+    // Every projection leaves partial sums; the small kernel behind it adds them, does the layer's row-wise
+    // arithmetic and writes the next projection's activations in operand order.
+    p.pfc.a_src = io.hidden_in;               // x = W_fc [embed[tok] ; hidden_in], gathered by the projection itself
+    p.pfc.a_embed = w->embed;
+    p.pfc.a_tok = io.tok;
+    p.pfc.a_vocab = dm.V;
+    p.pfc.status = status;
+    if ((rc = run_proj(p.pfc, w->w_fc, nullptr, nullptr, b, s, "proj fc"))) return rc;
+    if ((rc = check_hip(launch_proj_norm(p.pfc, nullptr, w->ln_attn, dm.rms_eps, b.x_buf, nullptr, b.act, s), "proj fc sums"))) return rc;
+    p.pqkv.a_packed = b.act;                  // q, k, v; rotary; cache write; attention over the draft's own cache
+    if ((rc = run_proj(p.pqkv, w->w_q, w->w_k, w->w_v, b, s, "proj qkv"))) return rc;
+    RopeArgs ra;
+    fill_rope(ra, p, io, draft_kv, b.q_buf, status);
+    if ((rc = check_hip(launch_proj_rope(p.pqkv, ra, s), "proj qkv sums"))) return rc;
   } else {
     if ((rc = check_hip(launch_embed_concat(dm, B, w->embed, io.tok, io.hidden_in, b.act, s, status), "embed_concat"))) return rc;
-    if ((rc = run_gemm(p.fc, mf, bf16, w->w_fc, nullptr, nullptr, b, s, "gemm fc"))) return rc;
-    if ((rc = check_hip(launch_reduce_norm(dm, B, dm.D, b.partial, p.fc.ksplit, p.fc.planes, nullptr, w->ln_attn,
+    if ((rc = run_gemm(p.fc, bf16, w->w_fc, nullptr, nullptr, b, s, "gemm fc"))) return rc;
+    if ((rc = check_hip(launch_reduce_norm(dm, B, dm.D, b.partial, 1, 1, nullptr, w->ln_attn,
                                            b.x_buf, nullptr, b.act, s), "norm attn"))) return rc;
-    if ((rc = run_gemm(p.qkv, mf, bf16, w->w_q, w->w_k, w->w_v, b, s, "gemm qkv"))) return rc;
-    if ((rc = check_hip(launch_rope_kvwrite(dm, B, p.W, b.partial, p.qkv.ksplit, p.qkv.planes, io.pos, io.level, io.node,
+    if ((rc = run_gemm(p.qkv, bf16, w->w_q, w->w_k, w->w_v, b, s, "gemm qkv"))) return rc;
+    if ((rc = check_hip(launch_rope_kvwrite(dm, B, p.W, b.partial, 1, 1, io.pos, io.level, io.node,
                                             b.q_buf, p.attn.paged, draft_kv->k, draft_kv->v, draft_kv->page_table,
                                             p.attn.page_size, p.attn.max_pages, p.attn.l_max, s, p.attn.n_pages, status), "rope"))) return rc;
   }
@@ -485,56 +486,25 @@ int32_t run_draft(DraftPlan& p, const specexit_draft_weights* w, const specexit_
     p.head.a_gain = w->ln_final;
     p.head.a_eps = dm.rms_eps;
   } else if (mf) {
-    // a = x + W_o attn
-    p.o.a_mode = 1;    // attention output is read in its storage type
-    p.o.a_src = b.attn_out;
-    p.o.epi = 1;
-    p.o.counters = b.counters + gd;
-    p.o.residual = b.x_buf;
-    p.o.out_x = b.a_buf;
-    p.o.out_ssq = b.ssq + static_cast<size_t>(1) * B * gd;
-    if ((rc = run_gemm(p.o, mf, bf16, w->w_o, nullptr, nullptr, b, s, "gemm o"))) return rc;
-    // y = a + W_down (silu(W_gate m) * W_up m), m = RMSNorm(a)
-    p.gu.a_mode = 3;
-    p.gu.a_src = b.a_buf;
-    p.gu.a_ssq = p.o.out_ssq;
-    p.gu.a_nssq = gd;
-    p.gu.a_gain = w->ln_mlp;
-    p.gu.a_eps = dm.rms_eps;
-    if ((rc = run_gemm(p.gu, mf, bf16, w->w_gate, w->w_up, nullptr, b, s, "gemm gate/up"))) return rc;
-    // silu(gate) * up once, as fp32 rows: each of the down projection's workgroups stages a K range
-    // of all rows, and forming the product there (from the gate/up partial sums) made every one of
-    // them re-read and re-add four times the bytes (measured at 16 rows, I = 25600: 104 -> 60 us)
-    if ((rc = check_hip(launch_silu_mul(dm, B, b.partial, p.gu.ksplit, p.gu.planes, b.act, s), "silu"))) return rc;
-    p.down.a_mode = 0;
-    p.down.a_src = b.act;
-    p.down.epi = 1;
-    p.down.counters = b.counters + 2 * gd;
-    p.down.residual = b.a_buf;
-    p.down.out_x = b.x_buf;            // y (x is no longer needed)
-    p.down.out_store = io.hidden_out;
-    p.down.out_ssq = b.ssq + static_cast<size_t>(2) * B * gd;
-    {
-      GemmArgs g = p.down;
-      g.w[0] = w->w_down;
-      g.partial = b.partial2;
-      if ((rc = check_hip(launch_gemm_mfma(g, s), "gemm down"))) return rc;
-    }
-    p.head.a_mode = 3;
-    p.head.a_src = b.x_buf;
-    p.head.a_ssq = p.down.out_ssq;
-    p.head.a_nssq = gd;
-    p.head.a_gain = w->ln_final;
-    p.head.a_eps = dm.rms_eps;
+    p.po.a_src = b.attn_out;                  // a = x + W_o attn
+    if ((rc = run_proj(p.po, w->w_o, nullptr, nullptr, b, s, "proj o"))) return rc;
+    if ((rc = check_hip(launch_proj_norm(p.po, b.x_buf, w->ln_mlp, dm.rms_eps, b.a_buf, nullptr, b.act, s), "proj o sums"))) return rc;
+    p.pgu.a_packed = b.act;                   // y = a + W_down (silu(W_gate m) * W_up m), m = RMSNorm(a)
+    if ((rc = run_proj(p.pgu, w->w_gate, w->w_up, nullptr, b, s, "proj gate/up"))) return rc;
+    if ((rc = check_hip(launch_proj_silu(p.pgu, b.act, s), "proj gate/up sums"))) return rc;
+    p.pdown.a_packed = b.act;
+    if ((rc = run_proj(p.pdown, w->w_down, nullptr, nullptr, b, s, "proj down"))) return rc;
+    if ((rc = check_hip(launch_proj_norm(p.pdown, b.a_buf, w->ln_final, dm.rms_eps, nullptr, io.hidden_out, b.head_pack, s), "proj down sums"))) return rc;
+    p.head.a_mode = 4;
   } else {
     if ((rc = check_hip(launch_unpack_rows(b.attn_out, bf16, B, dm.Hq * dm.d, b.act, s), "unpack attn"))) return rc;
-    if ((rc = run_gemm(p.o, mf, bf16, w->w_o, nullptr, nullptr, b, s, "gemm o"))) return rc;
-    if ((rc = check_hip(launch_reduce_norm(dm, B, dm.D, b.partial, p.o.ksplit, p.o.planes, b.x_buf, w->ln_mlp,
+    if ((rc = run_gemm(p.o, bf16, w->w_o, nullptr, nullptr, b, s, "gemm o"))) return rc;
+    if ((rc = check_hip(launch_reduce_norm(dm, B, dm.D, b.partial, 1, 1, b.x_buf, w->ln_mlp,
                                            b.a_buf, nullptr, b.act, s), "norm mlp"))) return rc;
-    if ((rc = run_gemm(p.gu, mf, bf16, w->w_gate, w->w_up, nullptr, b, s, "gemm gate/up"))) return rc;
-    if ((rc = check_hip(launch_silu_mul(dm, B, b.partial, p.gu.ksplit, p.gu.planes, b.act, s), "silu"))) return rc;
-    if ((rc = run_gemm(p.down, mf, bf16, w->w_down, nullptr, nullptr, b, s, "gemm down"))) return rc;
-    if ((rc = check_hip(launch_reduce_norm(dm, B, dm.D, b.partial, p.down.ksplit, p.down.planes, b.a_buf, w->ln_final,
+    if ((rc = run_gemm(p.gu, bf16, w->w_gate, w->w_up, nullptr, b, s, "gemm gate/up"))) return rc;
+    if ((rc = check_hip(launch_silu_mul(dm, B, b.partial, 1, 1, b.act, s), "silu"))) return rc;
+    if ((rc = run_gemm(p.down, bf16, w->w_down, nullptr, nullptr, b, s, "gemm down"))) return rc;
+    if ((rc = check_hip(launch_reduce_norm(dm, B, dm.D, b.partial, 1, 1, b.a_buf, w->ln_final,
                                            nullptr, io.hidden_out, b.act, s), "norm final"))) return rc;
   }
   g_prof_hook(SPECEXIT_PROF_DRAFT_PROJ_OUT, 1, s);
@@ -555,8 +525,17 @@ int32_t run_draft(DraftPlan& p, const specexit_draft_weights* w, const specexit_
   }
   {
     ProfScope prof(SPECEXIT_PROF_DRAFT_HEAD_GEMM, s);
-    p.head.a_packed = b.head_pack;
-    if ((rc = run_gemm(p.head, mf, bf16, w->w_head, nullptr, nullptr, b, s, "gemm head"))) return rc;
+    if (mf) {
+      GemmArgs g = p.head;
+      g.w[0] = w->w_head;
+      g.a_packed = b.head_pack;
+      g.part_val = b.part_val;
+      g.part_idx = b.part_idx;
+      g.extra_out = b.extra;
+      if ((rc = check_hip(launch_head_wide(g, s), "gemm head"))) return rc;
+    } else if ((rc = run_gemm(p.head, bf16, w->w_head, nullptr, nullptr, b, s, "gemm head"))) {
+      return rc;
+    }
   }
   if (mf) {
     const int lists = head_wide_groups(p.head);   // candidate lists per row
@@ -729,9 +708,8 @@ int32_t make_head_plan(HeadPlan& h, int32_t dtype, int32_t M, int32_t D, int32_t
   if (M < 1 || M > 144) return fail(SPECEXIT_EINVAL, "lmhead_argmax: M %d outside 1..144", M);
   if (D < 8 || D % 8) return fail(SPECEXIT_EUNSUPPORTED, "lmhead_argmax: D %d must be a multiple of 8", D);
   if (V < 1 || n_extra < 0 || n_extra > 16) return fail(SPECEXIT_EINVAL, "lmhead_argmax: bad V or n_extra");
-  h.mfma = dtype == SPECEXIT_BF16 && gemm_mfma_supported(M, 1, D);
-  plan_gemm(h.g, V + n_extra, D, M, 1, h.mfma, V);
-  h.g.n_extra = n_extra;
+  plan_head(h.g, V + n_extra, D, M, 1, V, n_extra, 0);
+  h.mfma = dtype == SPECEXIT_BF16 && head_wide_supported(h.g);
   h.act_bytes = (!h.mfma && dtype == SPECEXIT_BF16) ? sizeof(float) * M * D : 0;
   h.partial_bytes = h.mfma ? 0 : sizeof(float) * M * (static_cast<size_t>(V) + n_extra);
   h.pv_bytes = h.mfma ? sizeof(float) * M * head_wide_groups(h.g) : 0;
@@ -779,7 +757,7 @@ int32_t specexit_lmhead_argmax(int32_t dtype, int32_t M, int32_t D, int32_t V, i
     g.part_idx = pi;
     {
       ProfScope prof(SPECEXIT_PROF_LMHEAD_GEMM, s);
-      if ((rc = check_hip(launch_gemm_mfma(g, s), "gemm lm head"))) return rc;
+      if ((rc = check_hip(launch_head_wide(g, s), "gemm lm head"))) return rc;
     }
     return check_hip(launch_argmax_finalize(pv, pi, head_wide_groups(g), M, argmax, max_logit, s), "argmax finalize");
   }

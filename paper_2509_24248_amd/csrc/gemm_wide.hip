@@ -28,8 +28,8 @@
 // before they covered whole cache lines: straight from the row-major matrix a load is 16 rows x 64 bytes,
 // and those half-line requests, not their bytes, were the cost).
 #include "../../include/specexit.h"
-#include "common.hpp"
 #include "kernels.hpp"
+#include "stream.hpp"
 
 #include <limits.h>
 
@@ -38,20 +38,6 @@
 namespace sx {
 
 namespace {
-
-constexpr int kProducers = 2;
-
-typedef __attribute__((address_space(3))) void* lds_ptr_t;
-
-constexpr int vmcnt_imm(int n) { return 0x0F70 | (n & 15) | (((n >> 4) & 3) << 14); }
-
-// Direct global -> LDS load, 16 bytes per lane: lane l's bytes land at lds_base + 16 l (lds_base
-// wave-uniform).  Written as an instruction so that the kernel paces these loads itself with
-// s_waitcnt vmcnt and a barrier.  "nt": the weights are read once.
-__device__ __forceinline__ void load_to_lds16(const void* src, const void* lds_base) {
-  const uint32_t l = static_cast<uint32_t>(reinterpret_cast<uintptr_t>((lds_ptr_t)lds_base));
-  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off nt" ::"s"(l), "v"(src) : "memory");
-}
 
 // The order in which a workgroup takes the k blocks of a pass.  The workgroups run in step, and where the
 // weight rows are a multiple of 4 KB apart the reads of one k block by all of them fall on one of the
@@ -519,19 +505,34 @@ __global__ __launch_bounds__(64 * (RG * CS + kProducers + (SPLIT ? 1 : 0))) void
     static_assert(PP == 2 * TG, "each producer brings in half of every tile");
     const int per_stage = 2 * halves.most;
     StageCursor<LV> cur(nhalf, KB);
+    // the lane's offset in a tile: rows 4 (j % 4) .. of this producer's pieces, which alternate between two values
+    const int r0 = 4 * pw + (lane >> 4), r1 = r0 + 8;
+    const uint32_t lane_off0 = r0 * static_cast<uint32_t>(row_bytes) + (((lane & 15) ^ r0) << 4);
+    const uint32_t lane_off1 = r1 * static_cast<uint32_t>(row_bytes) + (((lane & 15) ^ r1) << 4);
+    static_assert(kProducers == 2, "two producers: each has rows 0-3 and 8-11 or 4-7 and 12-15 of a tile");
     auto issue = [&](int slot) {
       char* stage = lds + slot * kStage;
       const int tile0 = halves.first(cur.half0 + cur.h), tile1 = halves.first(cur.half0 + cur.h + 1);
+      const uint64_t stride = 16 * row_bytes;
+      uint64_t base = reinterpret_cast<uint64_t>(g.w[0]) + static_cast<uint64_t>(tile0) * stride + (static_cast<uint64_t>(cur.k.kb) << 8);
+      if (tile1 * 16 <= g.N) {
+        // (one addition per tile: what a request costs this wave in instructions has to stay below what it costs the memory)
 #pragma unroll
-      for (int u = 0; u < PP; ++u) {
-        if (u >= per_stage) break;               // uniform
-        const int j = pw + u * kProducers;
-        const int r = 4 * (j & 3) + (lane >> 4);
-        const int tile = min(tile0 + (j >> 2), tile1 - 1);
-        const int row = min(tile * 16 + r, g.N - 1);               // rows past the end repeat the last one, masked later
-        const char* src = static_cast<const char*>(g.w[0]) + static_cast<size_t>(row) * row_bytes + (((lane & 15) ^ r) << 4) +
-                          (static_cast<size_t>(cur.k.kb) << 8);
-        load_to_lds16(src, stage + j * 1024);
+        for (int u = 0; u < PP; ++u) {
+          if (u >= per_stage) break;             // uniform
+          if ((u & 1) == 0 && u > 0 && tile0 + u / 2 < tile1) base += stride;
+          load_to_lds16(reinterpret_cast<const char*>(base), u & 1 ? lane_off1 : lane_off0, stage + (pw + u * kProducers) * 1024);
+        }
+      } else {
+        // the half with the launch's last, ragged tile: rows past the end repeat the last one, masked later
+#pragma unroll 1
+        for (int u = 0; u < per_stage; ++u) {
+          if ((u & 1) == 0 && u > 0 && tile0 + u / 2 < tile1) base += stride;
+          const int j = pw + u * kProducers, r = 4 * (j & 3) + (lane >> 4);
+          const int tile = min(tile0 + (j >> 2), tile1 - 1);
+          const uint32_t off = min(r, g.N - 1 - tile * 16) * static_cast<uint32_t>(row_bytes) + (((lane & 15) ^ r) << 4);
+          load_to_lds16(reinterpret_cast<const char*>(base), off, stage + j * 1024);
+        }
       }
       cur.advance(nhalf, KB);
     };
@@ -628,8 +629,7 @@ bool head_wide_supported(const GemmArgs& g) {
 // One workgroup per compute unit, each walking an equal share of the weight tiles (at least one
 // stage's worth); one candidate slot per workgroup and column split.
 void head_wide_plan(GemmArgs& g, int num_cus) {
-  g.wide = head_wide_supported(g) ? 1 : 0;
-  if (!g.wide) return;
+  if (!head_wide_supported(g)) return;
   const int ntiles = gemm_ntiles(g.N);
   const WideShape sh = wide_shape(g.M, g.planes, g.K);
   g.wide_w = std::max(1, std::min(num_cus, ntiles / kWideTiles));
@@ -640,7 +640,7 @@ int head_wide_groups(const GemmArgs& g) { return g.wide_w * g.wide_slots; }
 
 // bytes of the packed activations: the row tiles the consumer waves cover x K (none: read in place)
 size_t head_wide_pack_bytes(const GemmArgs& g) {
-  if (!g.wide) return 0;
+  if (g.wide_w < 1) return 0;
   const WideShape sh = wide_shape(g.M, g.planes, g.K);
   if (g.planes == 1 && sh.rt == 1) return 0;
   return static_cast<size_t>(sh.rg) * sh.rt * 16 * g.K * 2;
@@ -652,9 +652,10 @@ hipError_t launch_head_wide(const GemmArgs& ga, hipStream_t s) {
   GemmArgs g = ga;
   const int KB = g.K >> 7;
   if (g.planes == 2) {
-    if (g.a_mode != 3 || !g.a_packed) return hipErrorInvalidValue;
-    hipLaunchKernelGGL(k_pack_norm, dim3((KB * sh.rg + 3) / 4), dim3(256), 0, s, static_cast<const float*>(g.a_src), g.a_ssq, g.a_nssq,
-                       static_cast<const bf16_t*>(g.a_gain), g.a_eps, static_cast<uint4*>(g.a_packed), g.M, g.K, sh.rg);
+    if ((g.a_mode != 3 && g.a_mode != 4) || !g.a_packed) return hipErrorInvalidValue;
+    if (g.a_mode == 3)
+      hipLaunchKernelGGL(k_pack_norm, dim3((KB * sh.rg + 3) / 4), dim3(256), 0, s, static_cast<const float*>(g.a_src), g.a_ssq, g.a_nssq,
+                         static_cast<const bf16_t*>(g.a_gain), g.a_eps, static_cast<uint4*>(g.a_packed), g.M, g.K, sh.rg);
     switch (sh.rg) {
       case 1: return launch_wide2<1, 4>(g, s);     //  1 .. 16 rows
       case 2: return launch_wide2<2, 2>(g, s);     // 17 .. 32

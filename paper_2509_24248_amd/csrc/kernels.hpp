@@ -6,13 +6,7 @@
 
 namespace sx {
 
-// out[m][n] = sum_k act[m][k] * w[n][k] for a weight matrix given as up to three
-// row blocks (q/k/v or gate/up share one launch).  Results are written as split-K
-// partial sums  partial[ks][v][n]  with v = m * planes + plane: consumers add the
-// ksplit * planes slices.  In head mode (V >= 0) rows n < V enter a fused argmax and
-// rows V.. are the signal rows of the widened head.
-// Rotary embedding + cache write done by the q/k/v projection's reducing epilogue (epi = 2):
-// row r of the step is sequence r / W, rotary position pos[r / W] + level, cache entry
+// Rotary embedding + cache write behind the q/k/v projection: row r of the step is sequence r / W, rotary position pos[r / W] + level, cache entry
 // pos[r / W] + node[r % W] (node null: the entry at pos).
 struct RopeArgs {
   const int32_t* pos;
@@ -32,69 +26,75 @@ struct RopeArgs {
   int* status;               // device error word or nullptr
 };
 
-// MFMA GEMM, activation pieces in LDS: one row of 16-byte entries per 8-wide k piece, one entry per
-// virtual activation row v.  With 16 or more virtual rows the distance between the rows is a
-// multiple of 16 entries and row v of k piece q sits at entry v ^ gemm_lds_swizzle(planes, q).
-// That keeps both access patterns free of bank conflicts (measured with single-wave timing loops:
-// 29.9 clocks per ds_write_b128 against 40.4 unswizzled, operand reads at the floor of 19.3):
-// the staging writes, where eight neighbouring lanes hold two activation rows x four k pieces,
-// and the operand reads, where 16 lanes hold 16 neighbouring rows of one k piece and the hardware
-// pairs halves of neighbouring 16-lane groups.
-__host__ __device__ inline int gemm_lds_row_stride(int Mv) { return Mv < 16 ? Mv : (Mv + 15) & ~15; }
-__host__ __device__ inline int gemm_lds_swizzle(int Mv, int planes, int q) {
-  if (Mv < 16) return 0;
-  return planes == 1 ? 2 * q : ((q & 1) | ((q & 2) << 1));
+// Activations in the operand order of the weight-stream kernels: [k block of 128][16-row tile][k step of 32][lane]
+// 16-byte pieces; lane (c = lane % 16, q = lane / 16) of a piece holds row c of the tile, k = 32 step + 8 q .. + 7.
+// With two planes tile 2 o holds the bf16 rounding of rows 16 o .. + 15, tile 2 o + 1 the bf16 rounding of the rest.
+__host__ __device__ inline int packed_tiles(int M, int planes) { return (M + 15) / 16 * planes; }
+__host__ __device__ inline size_t packed_byte(int NT, int tile, int m, int k) {
+  return ((static_cast<size_t>(k >> 7) * NT + tile) * 4 + ((k >> 5) & 3)) * 1024 + ((k >> 3) & 3) * 256 + (m & 15) * 16 + (k & 7) * 2;
 }
 
+// Projection of the draft layer over 5 and more rows (gemm_proj.hip): partial sums, added by the kernel behind it.
+struct ProjArgs {
+  const void* w[3];    // up to three row blocks (q/k/v or gate/up share one launch)
+  int seg_end[3];      // exclusive end row of each block in the concatenated row space, multiples of 16
+  int nseg;
+  int N, K, M;
+  int planes;          // 1: bf16 activations, 2: bf16 value + rest
+  const void* a_packed;  // activations in operand order, or nullptr (one plane):
+  const void* a_src;     // bf16 rows [M][K]; with a_embed [embed[tok[m]] ; a_src[m]], each K/2 wide
+  const void* a_embed;   // embedding table [V][K/2] or nullptr
+  const int32_t* a_tok;  // token ids [M], forced into 0 .. a_vocab-1
+  int a_vocab;
+  int* status;         // device error word or nullptr (first out-of-range token id seen)
+  int W;               // workgroups
+  float* partial;      // proj_partial_bytes()
+};
+// where the partial sums of a projection lie (see gemm_proj.hip)
+struct ProjSum {
+  const float* partial;   // [slot][M][128]
+  int64_t T;              // blocks of the projection
+  double inv_T;           // 1 / T
+  int KB, W, M;           // k blocks of a group, workgroups, rows
+};
+__host__ __device__ inline int proj_groups(int N) { return (N + 127) / 128; }
+bool proj_supported(int M, int N, int K);
+void proj_plan(ProjArgs& g, int num_cus);
+size_t proj_partial_bytes(const ProjArgs& g);
+hipError_t launch_proj(const ProjArgs& g, hipStream_t s);
+// rows = sums (+ residual) -> out_x fp32 / out_store bf16 (either may be null); RMSNorm of the rows -> packed (two planes)
+hipError_t launch_proj_norm(const ProjArgs& g, const float* residual, const void* gain, float eps, float* out_x, void* out_store, void* packed,
+                            hipStream_t s);
+// silu(gate) * up of the gate|up projection -> packed (two planes)
+hipError_t launch_proj_silu(const ProjArgs& g, void* packed, hipStream_t s);
+hipError_t launch_proj_rope(const ProjArgs& g, const RopeArgs& ra, hipStream_t s);
+
+// Head GEMMs (gemm_wide.hip) and the plain-ALU GEMM (gemm.hip): out[m][n] = sum_k act[m][k] * w[n][k].
+// Head: rows n < V enter a fused argmax, rows V.. are the signal rows of the widened head.
 struct GemmArgs {
-  const void* w[3];
+  const void* w[3];    // up to three row blocks
   int seg_end[3];      // exclusive end row of each block in the concatenated row space
   int nseg;
   int N, K, M;
-  int planes;          // MFMA path: 1 = activations exact in bf16, 2 = bf16 hi + lo parts
-  int ksplit;          // number of K ranges
-  int kb_per_split;    // MFMA path: 128-element K blocks per range
-  int spread;          // MFMA path, one K range, plain partial output (epi 0): workgroups to spread the 16-row tiles over in
-                       // equal shares (each gets fewer than 8, its spare waves idle), or 0: 8 tiles per workgroup
-  const float* act;    // VALU path: fp32 [M][K]
-  // MFMA path: where the activations come from
-  int a_mode;          // 0: fp32 rows [M][K]; 1: bf16 rows [M][K];
-                       // 2: bf16 [embed[tok[m]] ; hidden[m]], each K/2 wide (the draft's fuse input)
-                       // 3: RMSNorm of fp32 rows: a_src[m][k] * rsqrt(sum_j a_ssq[m][j] / K + a_eps) * a_gain[k]
-                       // 4: silu(gate) * up, gate = columns k, up = columns K + k of the a_nslices
-                       //    partial slices a_src left by a GEMM with N = 2K
-  const void* a_src;   // rows (modes 0, 1, 3), hidden rows (mode 2) or partial sums (mode 4)
+  int planes;          // head: 1 = activations exact in bf16, 2 = bf16 hi + lo parts
+  const float* act;    // ALU path: fp32 [M][K]
+  float* partial;      // ALU path: out [M][N]
+  // head: where the activations come from
+  int a_mode;          // 1: bf16 rows [M][K]; 3: RMSNorm of fp32 rows: a_src[m][k] * rsqrt(sum_j a_ssq[m][j] / K + a_eps) * a_gain[k];
+                       // 4: a_packed already holds them in operand order
+  const void* a_src;
   const float* a_ssq;  // mode 3: [M][a_nssq] pieces of the rows' sums of squares
   int a_nssq;
   const void* a_gain;  // mode 3: [K] bf16 norm gain
   float a_eps;
-  int a_nslices;       // mode 4: ksplit * planes of the producing GEMM
-  int a_src_planes;    //         and its planes
-  const void* a_embed; // mode 2: embedding table [V][K/2]
-  const int32_t* a_tok;  // mode 2: token ids [M], forced into 0 .. a_vocab-1
-  int a_vocab;
-  int* status;         // device error word or nullptr (first out-of-range token id seen)
-  int kc;              // K elements of activations staged in LDS at a time (multiple of 128)
-  int wide;            // head mode: the kernel of gemm_wide.hip (weights through an LDS ring, activations in
-                       // registers); head_wide_groups() candidates per row
-  int wide_w;          //   its workgroups (each walks an equal share of the weight tiles)
-  int wide_slots;      //   candidate slots per workgroup and row, each of max(top_b, 1) candidates
-  void* a_packed;      //   scratch of head_wide_pack_bytes() for the activations in operand order
-  float* partial;      // [ksplit][M*planes][N] fp32, or nullptr in head mode
-  // epi = 1: the workgroup that finishes a 128-row group last adds up the group's partial
-  // sums in a fixed order (+ residual) and writes the finished rows
-  int epi;
-  int* counters;       // [groups], zero before the launch and again after it
-  const float* residual;  // [M][N] or nullptr
-  float* out_x;        // [M][N] fp32
-  void* out_store;     // [M][N] bf16 or nullptr
-  float* out_ssq;      // [M][groups] sum of squares of the group's columns, or nullptr
-  RopeArgs rope;       // epi = 2: the finished rows are q / k / v heads (bf16 outputs)
-  int V;               // head mode when >= 0
+  void* a_packed;      // head_wide_pack_bytes() for the activations in operand order
+  int wide_w;          // workgroups (each walks an equal share of the weight tiles)
+  int wide_slots;      // candidate slots per workgroup and row, each of max(top_b, 1) candidates
+  int V;               // head when >= 0
   int n_extra;
-  int top_b;           // head mode: candidates kept per slot (0 or 1 = the argmax only)
-  float* part_val;     // head mode: [M][head_wide_groups][top_b] best values, best first
-  int* part_idx;       //            their row indices (INT_MAX = none)
+  int top_b;           // candidates kept per slot (0 or 1 = the argmax only)
+  float* part_val;     // [M][head_wide_groups][top_b] best values, best first
+  int* part_idx;       // their row indices (INT_MAX = none)
   float* extra_out;    // [M][n_extra] or nullptr
   float* logits_dbg;   // [M][V] or nullptr
 };
@@ -106,7 +106,7 @@ struct GemvArgs {
   int seg_end[3];
   int nseg;
   int N, K, M;
-  int a_mode;            // as GemmArgs: 0 fp32 rows, 1 bf16 rows, 2 [embed[tok] ; hidden], 3 RMSNorm of fp32 rows
+  int a_mode;            // 0 fp32 rows, 1 bf16 rows, 2 [embed[tok] ; hidden], 3 RMSNorm of fp32 rows
   const void* a_src;
   const void* a_embed;
   const int32_t* a_tok;  // mode 2: token ids [M], forced into 0 .. a_vocab-1
@@ -139,16 +139,10 @@ void gemv_plan(GemvArgs& g, int num_cus, int per_cu = 3);   // at most per_cu wo
 hipError_t launch_gemv(const GemvArgs& g, hipStream_t s);
 
 inline int gemm_ntiles(int N) { return (N + 15) / 16; }
-inline int gemm_groups(int N) { return (gemm_ntiles(N) + 7) / 8; }   // 128-row groups = workgroups along N
 hipError_t launch_zero_i32(int* p, int n, hipStream_t s);
-inline int gemm_mt(int M, int planes) { return (M * planes + 15) / 16; }
-
-bool gemm_mfma_supported(int M, int planes, int K);
-void choose_ksplit(GemmArgs& g, bool mfma, int num_cus);
 hipError_t launch_gemm_valu(const GemmArgs& g, bool bf16, hipStream_t s);
-hipError_t launch_gemm_mfma(const GemmArgs& g, hipStream_t s);
 bool head_wide_supported(const GemmArgs& g);
-void head_wide_plan(GemmArgs& g, int num_cus);   // sets wide, wide_w, wide_slots
+void head_wide_plan(GemmArgs& g, int num_cus);   // sets wide_w, wide_slots
 int head_wide_groups(const GemmArgs& g);      // candidates per activation row
 size_t head_wide_pack_bytes(const GemmArgs& g);
 hipError_t launch_head_wide(const GemmArgs& g, hipStream_t s);
