@@ -39,7 +39,7 @@ __global__ __launch_bounds__(256) void k_attn_split_valu(const AttnArgs a) {
   float* Ms = Ss + R * kTK;         // [R] running max
   float* Ls = Ms + R;               // [R] running sum
   float* As = Ls + R;               // [R] rescale of this tile
-  int* sched_lds = reinterpret_cast<int*>(As + R);   // [B + 1]
+  int* sched_lds = reinterpret_cast<int*>(As + R);   // [2 B + 1]
   attn_sched_build(a, sched_lds);
   const int Tg = a.Hkv * sched_lds[a.B];     // granules on the line
   const int W = attn_sched_workgroups(Tg, a.wgrid);
@@ -259,9 +259,87 @@ __global__ __launch_bounds__(kCombThreads) void k_attn_combine(const AttnArgs a)
   }
 }
 
+size_t combine_lds_bytes(int wgrid) { return (static_cast<size_t>((wgrid + 3) & ~3) + kCombThreads * 4) * sizeof(float); }
+
+// The same with one wave per output row, for launches whose units have few segments: there are then
+// many rows, and a workgroup for each spends its time starting.  Whole call, 64 sequences of 200-600 entries x 5
+// queries x 32 heads 48.5 -> 37 us; 32 sequences x 7 x 32 (64-wide heads) 26 -> 18; 16 long ones x 9 x 64 322 -> 312.
+template <typename T, int D>
+__global__ __launch_bounds__(256) void k_attn_combine_rows(const AttnArgs a) {
+  constexpr int EPL = D / 64;               // columns per lane
+  const int lane = threadIdx.x & 63;
+  const int row = blockIdx.x * 4 + (threadIdx.x >> 6);
+  if (row >= a.B * a.n_q * a.Hq) return;
+  const int b = row / (a.n_q * a.Hq), ih = row - b * (a.n_q * a.Hq), i = ih / a.Hq, h = ih - i * a.Hq;
+  const int G = a.Hq / a.Hkv;
+  const int R = G * a.n_q;
+  const int g = h / G, r = i * G + h % G;
+  const int n_b = a.sched[b + 1] - a.sched[b];
+  const int Tg = a.Hkv * a.sched[a.B], W = a.sched[a.B + 1];
+  const int p_u = a.Hkv * a.sched[b] + g * n_b;
+  const int w_first = attn_sched_owner(p_u, Tg, W);
+  const int nact = attn_sched_owner(p_u + n_b - 1, Tg, W) - w_first + 1;
+  const size_t unit0 = static_cast<size_t>(w_first) + static_cast<size_t>(b) * a.Hkv + g;
+  const float* ml = a.part_ml + (unit0 * R + r) * 2;
+  const float* po = a.part_o + (unit0 * R + r) * D + lane * EPL;
+  float mmax = -INFINITY;
+  for (int s = lane; s < nact; s += 64) mmax = fmaxf(mmax, ml[static_cast<size_t>(s) * R * 2]);
+  mmax = wave_max(mmax);
+  float den = 0.f, acc[EPL];
+#pragma unroll
+  for (int e = 0; e < EPL; ++e) acc[e] = 0.f;
+  for (int s0 = 0; s0 < nact; s0 += 64) {
+    const int s = s0 + lane;
+    float w = 0.f, l = 0.f;
+    if (s < nact) {
+      const float ms = ml[static_cast<size_t>(s) * R * 2];
+      if (ms != -INFINITY) {
+        w = a.use_mfma ? exp2f(ms - mmax) : expf(ms - mmax);
+        l = ml[static_cast<size_t>(s) * R * 2 + 1];
+      }
+    }
+    den += wave_sum(w != 0.f ? w * l : 0.f);
+    const int n = min(64, nact - s0);
+    for (int j = 0; j < n; j += 4) {
+      float o[4][EPL], ws[4];
+#pragma unroll
+      for (int u = 0; u < 4; ++u) {
+        const int jj = min(j + u, n - 1);
+        ws[u] = j + u < n ? __shfl(w, jj, 64) : 0.f;
+        const float* src = po + static_cast<size_t>(s0 + jj) * R * D;
+#pragma unroll
+        for (int e = 0; e < EPL; ++e) o[u][e] = src[e];
+      }
+#pragma unroll
+      for (int u = 0; u < 4; ++u)
+        if (ws[u] != 0.f) {
+#pragma unroll
+          for (int e = 0; e < EPL; ++e) acc[e] = fmaf(ws[u], o[u][e], acc[e]);
+        }
+    }
+  }
+  T* dst = static_cast<T*>(a.out) + static_cast<size_t>(row) * D + lane * EPL;
+#pragma unroll
+  for (int e = 0; e < EPL; ++e) Elem<T>::store(dst + e, acc[e] / den);
+}
+
+template <typename T, int D>
+hipError_t launch_combine(const AttnArgs& a, hipStream_t s) {
+  // segments per unit, on average: the row kernel takes them one after the other, the other one side by side.
+  // (The lengths are not known here; a unit with many segments in a launch of short ones is slower, not wrong.)
+  const int64_t units = static_cast<int64_t>(a.B) * a.Hkv;
+  if (a.wgrid <= 4 * units) {
+    const int64_t rows = static_cast<int64_t>(a.B) * a.n_q * a.Hq;
+    hipLaunchKernelGGL((k_attn_combine_rows<T, D>), dim3(static_cast<unsigned>((rows + 3) / 4)), dim3(256), 0, s, a);
+  } else {
+    hipLaunchKernelGGL((k_attn_combine<T, D>), dim3(a.Hq, a.n_q, a.B), dim3(kCombThreads), combine_lds_bytes(a.wgrid), s, a);
+  }
+  return hipGetLastError();
+}
+
 size_t valu_smem_bytes(const AttnArgs& a) {
   const int R = (a.Hq / a.Hkv) * a.n_q;
-  return sizeof(float) * (static_cast<size_t>(R) * a.d + 2 * kTK * (a.d + 4) + static_cast<size_t>(R) * kTK + 3 * R + a.B + 1);
+  return sizeof(float) * (static_cast<size_t>(R) * a.d + 2 * kTK * (a.d + 4) + static_cast<size_t>(R) * kTK + 3 * R + attn_sched_words(a.B));
 }
 
 template <typename T, int D>
@@ -280,14 +358,12 @@ hipError_t launch_valu(const AttnArgs& a, hipStream_t s) {
 
 constexpr size_t kCombineLdsMax = 60 * 1024;
 
-size_t combine_lds_bytes(int wgrid) { return (static_cast<size_t>((wgrid + 3) & ~3) + kCombThreads * 4) * sizeof(float); }
-
 static bool plan_as(AttnArgs& a, int num_cus, int use_mfma) {
   // The host knows only the upper bound l_max of the lengths; the kernels deal the keys that
   // are really there to the workgroups in equal shares.  Here only the number of workgroups is
   // set: as many as are resident at once (one or two of the matrix-core kernel per compute unit),
-  // fewer when even the longest possible caches would leave them less than two granules (128
-  // keys) each, more when a share could otherwise exceed what one segment can hold.
+  // fewer when even the longest possible caches would leave them too few granules
+  // (attn_sched_workgroups), more when a share could otherwise exceed what one segment can hold.
   a.use_mfma = use_mfma;
   if (a.B > kAttnMaxSeqs || a.l_max < a.n_blk) return false;
   const int64_t units = static_cast<int64_t>(a.B) * a.Hkv;
@@ -296,8 +372,7 @@ static bool plan_as(AttnArgs& a, int num_cus, int use_mfma) {
   if (tmax >= (1ll << 30)) return false;
   a.stages = a.use_mfma ? attn_mfma_stages(a) : 0;
   const int64_t resident = static_cast<int64_t>(num_cus) * (a.use_mfma ? attn_mfma_per_cu(a) : 1);
-  int64_t w = tmax / 2 < resident ? tmax / 2 : resident;
-  if (w < 1) w = 1;
+  int64_t w = attn_sched_workgroups(static_cast<int>(tmax), static_cast<int>(resident));
   if (a.use_mfma) {
     const int64_t seg_gran = attn_mfma_max_chunk(a) / kAttnGran;   // granules one segment may span
     const int64_t need = (tmax + seg_gran - 1) / seg_gran;
@@ -353,16 +428,8 @@ hipError_t launch_attn(const AttnArgs& a, hipStream_t s, KernelHook hook, int ho
   }
   if (hook) hook(hook_id, 1, s);
   if (e != hipSuccess) return e;
-  const dim3 grid(a.Hq, a.n_q, a.B);
-  const size_t lds = combine_lds_bytes(a.wgrid);   // attn_plan made sure it fits
-  if (a.dtype == 1) {
-    if (a.d == 128) hipLaunchKernelGGL((k_attn_combine<bf16_t, 128>), grid, dim3(kCombThreads), lds, s, a);
-    else hipLaunchKernelGGL((k_attn_combine<bf16_t, 64>), grid, dim3(kCombThreads), lds, s, a);
-  } else {
-    if (a.d == 128) hipLaunchKernelGGL((k_attn_combine<float, 128>), grid, dim3(kCombThreads), lds, s, a);
-    else hipLaunchKernelGGL((k_attn_combine<float, 64>), grid, dim3(kCombThreads), lds, s, a);
-  }
-  return hipGetLastError();
+  if (a.dtype == 1) return a.d == 128 ? launch_combine<bf16_t, 128>(a, s) : launch_combine<bf16_t, 64>(a, s);
+  return a.d == 128 ? launch_combine<float, 128>(a, s) : launch_combine<float, 64>(a, s);
 }
 
 }  // namespace sx

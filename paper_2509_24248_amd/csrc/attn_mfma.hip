@@ -84,9 +84,6 @@ __device__ __forceinline__ void load_to_lds16(const void* src, const void* lds_b
   asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off nt" ::"s"(l), "v"(src) : "memory");
 }
 
-// LDS words of the schedule's prefix table (B + 1 entries, rounded to 16 bytes)
-__host__ __device__ constexpr int sched_words(int B) { return (B + 1 + 3) & ~3; }
-
 constexpr int front_bytes(int hd, int rp, int stages) {
   return kNK * stages * slot_bytes(hd) > rp * o_row(hd) * 4 ? kNK * stages * slot_bytes(hd) : rp * o_row(hd) * 4;
 }
@@ -119,7 +116,7 @@ __global__ __launch_bounds__(64 * kNK * NR, min_waves_per_simd(HD, NR)) void k_a
   char* smem = reinterpret_cast<char*>(smem4);
   float* ml_lds = reinterpret_cast<float*>(smem + kFront);
   int* sched_lds = reinterpret_cast<int*>(smem + kFront + kNK * RP * 2 * sizeof(float));
-  int* pg_lds = sched_lds + sched_words(a.B);
+  int* pg_lds = sched_lds + attn_sched_words(a.B);
   const int lane = threadIdx.x & 63;
   const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int kg = wv / NR, rr = wv % NR;
@@ -251,20 +248,22 @@ __global__ __launch_bounds__(64 * kNK * NR, min_waves_per_simd(HD, NR)) void k_a
   }
   const float sl2 = a.scale * 1.44269504088896340736f;  // scores are kept in log2 units
 
+  // every slot is free here: a short segment has all its tiles in flight at once
 #pragma unroll
-  for (int it = 0; it < S - 1; ++it) issue(it);
+  for (int it = 0; it < S; ++it) issue(it);
 
   for (int it = 0; it < nit; ++it) {
-    // this wave's pieces of tile `it` have landed once at most the pieces of the S-2 tiles
-    // issued after it are outstanding (loads return in order); near the end simply wait for all
-    if (S > 2 && it + S - 1 < nit) __builtin_amdgcn_s_waitcnt(vmcnt_imm((S - 2) * kPiecesMin));
+    // this wave's pieces of tile `it` have landed once at most the pieces of the S-2 tiles (S-1 before
+    // the first) issued after it are outstanding (loads return in order); near the end simply wait for all
+    if (it == 0 && (S - 1) * kNK + kg < ntl) __builtin_amdgcn_s_waitcnt(vmcnt_imm((S - 1) * kPiecesMin));
+    else if (S > 2 && it > 0 && it + S - 1 < nit) __builtin_amdgcn_s_waitcnt(vmcnt_imm((S - 2) * kPiecesMin));
     else __builtin_amdgcn_s_waitcnt(vmcnt_imm(0));
     // plain barrier (no memory fence: a fence would wait for the loads still in flight); the
     // wave-scope fences only keep the compiler from moving LDS accesses across it
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
     __builtin_amdgcn_s_barrier();              // tile `it` complete; slot of tile it-1 free
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-    issue(it + S - 1);
+    if (it > 0) issue(it + S - 1);
     const int ti = it * kNK + kg;
     if (ti >= ntl) continue;
     const int t0 = s0 + 32 * ti;
@@ -503,7 +502,7 @@ int attn_mfma_stages(const AttnArgs& a) { return stages_of(a.d, waves_per_ring(a
 size_t attn_mfma_lds_bytes(const AttnArgs& a) {
   const int rp = 16 * waves_per_ring(a);
   return static_cast<size_t>(front_bytes(a.d, rp, a.stages)) + static_cast<size_t>(kNK) * rp * 2 * sizeof(float) +
-         static_cast<size_t>(sched_words(a.B)) * sizeof(int) + (a.paged ? static_cast<size_t>(kMaxChunkPages + 1) * sizeof(int) : 0);
+         static_cast<size_t>(attn_sched_words(a.B)) * sizeof(int) + (a.paged ? static_cast<size_t>(kMaxChunkPages + 1) * sizeof(int) : 0);
 }
 
 int attn_mfma_max_chunk(const AttnArgs& a) { return a.paged ? kMaxChunkPages * a.page_size : (1 << 30); }

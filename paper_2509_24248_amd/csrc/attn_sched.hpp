@@ -29,8 +29,11 @@ __device__ __forceinline__ int attn_ctx_len(const AttnArgs& a, int b) {
   return L;
 }
 
-// Prefix sums S[0 .. B] of the sequences' granule counts, built by the first wave; every thread
-// of the workgroup calls this, and the table is ready when it returns.
+// LDS words of the table below.
+__host__ __device__ constexpr int attn_sched_words(int B) { return (2 * B + 1 + 3) & ~3; }
+
+// Prefix sums S[0 .. B] of the sequences' granule counts and, behind them, the sequences' context lengths, built by the
+// first wave; every thread of the workgroup calls this, and the table is ready when it returns.
 __device__ __forceinline__ void attn_sched_build(const AttnArgs& a, int* S) {
   if (threadIdx.x < 64) {
     const int lane = threadIdx.x;
@@ -38,7 +41,11 @@ __device__ __forceinline__ void attn_sched_build(const AttnArgs& a, int* S) {
     for (int c = 0; c < a.B; c += 64) {
       const int b = c + lane;
       int x = 0;
-      if (b < a.B) x = (attn_ctx_len(a, b) + a.n_blk + kAttnGran - 1) / kAttnGran;
+      if (b < a.B) {
+        const int L = attn_ctx_len(a, b);
+        S[a.B + 1 + b] = L;
+        x = (L + a.n_blk + kAttnGran - 1) / kAttnGran;
+      }
 #pragma unroll
       for (int o = 1; o < 64; o <<= 1) {
         const int y = __shfl_up(x, o, 64);
@@ -52,16 +59,26 @@ __device__ __forceinline__ void attn_sched_build(const AttnArgs& a, int* S) {
   __syncthreads();
 }
 
-// Workgroups that take part: at least two granules each while there are that many.
-__device__ __forceinline__ int attn_sched_workgroups(int T, int wgrid) { return max(1, min(wgrid, T >> 1)); }
-
-__device__ __forceinline__ int attn_sched_lo(int w, int T, int W) {
-  return static_cast<int>(static_cast<int64_t>(w) * T / W);
+// Workgroups that take part: at least two granules each, one where the launch has a compute unit for every granule.
+constexpr int kAttnSpread = 256;
+__host__ __device__ __forceinline__ int attn_sched_workgroups(int T, int wgrid) {
+  const int want = T <= kAttnSpread ? T : (T >> 1) < kAttnSpread ? kAttnSpread : T >> 1;
+  return want < 1 ? 1 : want < wgrid ? want : wgrid;
 }
+
+// a b / c for a >= 0, b, c >= 1 whose quotient fits 32 bits.  A 64-bit division is some 150 dependent instructions,
+// and these kernels start with two of them: 32 bits where the product allows it (uniform).
+__device__ __forceinline__ int mul_div(int a, int b, int add, int c) {
+  const int64_t x = static_cast<int64_t>(a) * b + add;
+  if (x <= 0x7fffffff) return static_cast<int>(static_cast<uint32_t>(x) / static_cast<uint32_t>(c));
+  return static_cast<int>(x / c);
+}
+
+__device__ __forceinline__ int attn_sched_lo(int w, int T, int W) { return mul_div(w, T, 0, W); }
 
 // first and last workgroup whose range holds a granule of [p, p + n)
 __device__ __forceinline__ int attn_sched_owner(int p, int T, int W) {
-  return static_cast<int>((static_cast<int64_t>(p + 1) * W - 1) / T);
+  return mul_div(p + 1, W, -1, T);
 }
 
 struct AttnSeg {
@@ -89,7 +106,7 @@ __device__ __forceinline__ AttnSeg attn_sched_segment(const AttnArgs& a, const i
   s.g = min(rel / n, a.Hkv - 1);
   const int g0 = min(rel - s.g * n, n - 1);     // first granule inside the unit
   const int g1 = min(n, g0 + (hi - x));
-  s.L = attn_ctx_len(a, b);
+  s.L = S[a.B + 1 + b];
   s.s0 = g0 * kAttnGran;
   s.s1 = min(s.L + a.n_blk, g1 * kAttnGran);
   s.next = x + max(g1 - g0, 1);                 // (the minima above cannot bind while S is the table of these lengths)
