@@ -81,6 +81,16 @@ def test_narrow_heads_at_tile_edges(n_q, Hq, Hkv, page):
     assert err < 2.0 ** -8
 
 
+@pytest.mark.parametrize("dtype,d", [("bf16", 64), ("bf16", 128), ("f32", 64)])
+def test_one_long_sequence_among_short_ones(dtype, d):
+    # few segments per unit on average, so a wave merges each output row, and one unit with more of them than a wave has lanes
+    shape = gen.scaled(gen.config(1), dtype=dtype, B=70, Hq=4, Hkv=2, d=d, n_q=3, ctx=(0, 40))
+    L = gen.context_lengths(shape, 3)
+    L[33] = 9000
+    kv = gen.kv_cache(shape, L, shape.n_q, 3, paged=True)
+    check(shape, L, kv, gen.queries(shape, 3), None, label="one long sequence")
+
+
 def test_paged_equals_contiguous_on_gpu():
     shape = gen.scaled(gen.config(2), B=4, Hq=8, Hkv=2, ctx=(30, 1200))
     L, kv, q, mask = case(shape, 3, paged=False)
