@@ -497,8 +497,13 @@ int32_t run_draft(DraftPlan& p, const specexit_draft_weights* w, const specexit_
     if ((rc = check_hip(launch_proj_norm(p.pdown, b.a_buf, w->ln_final, dm.rms_eps, nullptr, io.hidden_out, b.head_pack, s), "proj down sums"))) return rc;
     p.head.a_mode = 4;
   } else {
-    if ((rc = check_hip(launch_unpack_rows(b.attn_out, bf16, B, dm.Hq * dm.d, b.act, s), "unpack attn"))) return rc;
-    if ((rc = run_gemm(p.o, bf16, w->w_o, nullptr, nullptr, b, s, "gemm o"))) return rc;
+    DraftBufs bo = b;
+    if (bf16) {
+      if ((rc = check_hip(launch_unpack_rows(b.attn_out, true, B, dm.Hq * dm.d, b.act, s), "unpack attn"))) return rc;
+    } else {
+      bo.act = static_cast<float*>(b.attn_out);     // fp32 rows as they are
+    }
+    if ((rc = run_gemm(p.o, bf16, w->w_o, nullptr, nullptr, bo, s, "gemm o"))) return rc;
     if ((rc = check_hip(launch_reduce_norm(dm, B, dm.D, b.partial, 1, 1, b.x_buf, w->ln_mlp,
                                            b.a_buf, nullptr, b.act, s), "norm mlp"))) return rc;
     if ((rc = run_gemm(p.gu, bf16, w->w_gate, w->w_up, nullptr, b, s, "gemm gate/up"))) return rc;
@@ -546,9 +551,10 @@ int32_t run_draft(DraftPlan& p, const specexit_draft_weights* w, const specexit_
     return check_hip(launch_topb_finalize(b.part_val, b.part_idx, C, C, p.top_b, B, io.cand_tok, io.cand_logit, s,
                                           b.extra, dm.rem_activation, io.sig_raw, io.sig), "top-b finalize");
   }
-  if ((rc = check_hip(launch_argmax_rows(b.partial, B, dm.V + 3, dm.V, 3, b.head_am, nullptr, b.extra, nullptr, s), "argmax rows"))) return rc;
   if (p.top_b == 1 && !io.cand_logit)
-    return check_hip(launch_head_finalize(dm, B, b.head_am, b.extra, io.cand_tok, io.sig_raw, io.sig, s), "head finalize");
+    return check_hip(launch_argmax_rows(b.partial, B, dm.V + 3, dm.V, 3, io.cand_tok, nullptr, nullptr, nullptr, s, dm.rem_activation,
+                                        io.sig_raw, io.sig), "argmax rows");
+  if ((rc = check_hip(launch_argmax_rows(b.partial, B, dm.V + 3, dm.V, 3, b.head_am, nullptr, b.extra, nullptr, s), "argmax rows"))) return rc;
   return check_hip(launch_topb_finalize(b.partial, nullptr, dm.V, dm.V + 3, p.top_b, B, io.cand_tok, io.cand_logit, s,
                                         b.extra, dm.rem_activation, io.sig_raw, io.sig), "top-b rows");
 }

@@ -186,30 +186,6 @@ __global__ __launch_bounds__(256) void k_silu_mul(int B, int I, const float* __r
   }
 }
 
-__global__ void k_head_finalize(int B, int rem_activation, const int32_t* __restrict__ argmax_in,
-                                const float* __restrict__ extra, int32_t* __restrict__ next_tok,
-                                float* __restrict__ sig_raw, float* __restrict__ sig) {
-  const int b = blockIdx.x * blockDim.x + threadIdx.x;
-  if (b >= B) return;
-  next_tok[b] = argmax_in[b];
-  const float zc = extra[b * 3 + 0], zp = extra[b * 3 + 1], zr = extra[b * 3 + 2];
-  sig_raw[b * 3 + 0] = zc;
-  sig_raw[b * 3 + 1] = zp;
-  sig_raw[b * 3 + 2] = zr;
-  // confidence and progress pass through a sigmoid (Eqs. 3-4); the remaining-length head
-  // regresses log(1 + r) (Eq. 5), so r = expm1(z), floored at zero
-  sig[b * 3 + 0] = sigmoidf_(zc);
-  sig[b * 3 + 1] = sigmoidf_(zp);
-  float r;
-  if (rem_activation == 0)
-    r = fmaxf(0.f, expm1f(zr));
-  else if (rem_activation == 1)
-    r = sigmoidf_(zr);
-  else
-    r = zr;
-  sig[b * 3 + 2] = r;
-}
-
 }  // namespace
 
 hipError_t launch_embed_concat(const DraftDims& dm, int B, const void* embed, const int32_t* tok,
@@ -255,13 +231,6 @@ hipError_t launch_silu_mul(const DraftDims& dm, int B, const float* partial, int
                            float* act, hipStream_t s) {
   const int gy = (dm.I / 8 + 255) / 256;
   hipLaunchKernelGGL(k_silu_mul, dim3(B, gy), dim3(256), 0, s, B, dm.I, partial, nslices, planes, act);
-  return hipGetLastError();
-}
-
-hipError_t launch_head_finalize(const DraftDims& dm, int B, const int32_t* argmax_in, const float* extra,
-                                int32_t* next_tok, float* sig_raw, float* sig, hipStream_t s) {
-  hipLaunchKernelGGL(k_head_finalize, dim3(1), dim3(64), 0, s, B, dm.rem_activation, argmax_in, extra, next_tok,
-                     sig_raw, sig);
   return hipGetLastError();
 }
 

@@ -84,6 +84,16 @@ __global__ __launch_bounds__(256) void k_gemv_valu(const GemmArgs g) {
 
 constexpr int kFinalThreads = 1024;
 
+// Signal logits -> signals: confidence and progress pass through a sigmoid (Eqs. 3-4); the remaining-length head
+// regresses log(1 + r) (Eq. 5), so r = expm1(z), floored at zero (or the activation the descriptor names)
+__device__ __forceinline__ void write_signals(const float* z, int rem_activation, float* sig_raw, float* sig) {
+  const float zc = z[0], zp = z[1], zr = z[2];
+  sig_raw[0] = zc; sig_raw[1] = zp; sig_raw[2] = zr;
+  sig[0] = sigmoidf_(zc);
+  sig[1] = sigmoidf_(zp);
+  sig[2] = rem_activation == 0 ? fmaxf(0.f, expm1f(zr)) : (rem_activation == 1 ? sigmoidf_(zr) : zr);
+}
+
 // One block per activation row: reduce the (max, index) candidates; for the draft head
 // the same block also turns the three signal logits into signals (Eqs. 3-5).
 __global__ __launch_bounds__(kFinalThreads) void k_argmax_finalize(const float* __restrict__ part_val,
@@ -137,13 +147,7 @@ __global__ __launch_bounds__(kFinalThreads) void k_argmax_finalize(const float* 
       if (max_logit) max_logit[m] = bv;
     }
   }
-  if (sig && threadIdx.x == 64) {
-    const float zc = extra[m * 3 + 0], zp = extra[m * 3 + 1], zr = extra[m * 3 + 2];
-    sig_raw[m * 3 + 0] = zc; sig_raw[m * 3 + 1] = zp; sig_raw[m * 3 + 2] = zr;
-    sig[m * 3 + 0] = sigmoidf_(zc);
-    sig[m * 3 + 1] = sigmoidf_(zp);
-    sig[m * 3 + 2] = rem_activation == 0 ? fmaxf(0.f, expm1f(zr)) : (rem_activation == 1 ? sigmoidf_(zr) : zr);
-  }
+  if (sig && threadIdx.x == 64) write_signals(extra + m * 3, rem_activation, sig_raw + m * 3, sig + m * 3);
 }
 
 // The top_b best of each row, best first (value descending, lower index first among equals),
@@ -239,32 +243,40 @@ __global__ __launch_bounds__(kFinalThreads) void k_topb_finalize(const float* __
     prev_v = pick_v;
     prev_i = pick_i;
   }
-  if (sig && threadIdx.x == 64) {
-    const float zc = extra[m * 3 + 0], zp = extra[m * 3 + 1], zr = extra[m * 3 + 2];
-    sig_raw[m * 3 + 0] = zc; sig_raw[m * 3 + 1] = zp; sig_raw[m * 3 + 2] = zr;
-    sig[m * 3 + 0] = sigmoidf_(zc);
-    sig[m * 3 + 1] = sigmoidf_(zp);
-    sig[m * 3 + 2] = rem_activation == 0 ? fmaxf(0.f, expm1f(zr)) : (rem_activation == 1 ? sigmoidf_(zr) : zr);
-  }
+  if (sig && threadIdx.x == 64) write_signals(extra + m * 3, rem_activation, sig_raw + m * 3, sig + m * 3);
 }
 
-__global__ __launch_bounds__(256) void k_argmax_rows(const float* __restrict__ logits, int N, int V,
+// One block per row of fp32 logits: argmax over the rows n < V, copy of the signal rows and (debug) of the logits;
+// for the draft head also the signals (Eqs. 3-5).  Latency-bound: 1024 threads with four values each under way
+// (4096 logits: 7.4 us with 256 threads and one value at a time, plus 2 us for the signals in a launch of their own).
+__global__ __launch_bounds__(kFinalThreads) void k_argmax_rows(const float* __restrict__ logits, int N, int V,
                                                      int n_extra, int32_t* __restrict__ argmax,
                                                      float* __restrict__ max_logit,
                                                      float* __restrict__ extra_out,
-                                                     float* __restrict__ logits_dbg) {
-  __shared__ float sv[4];
-  __shared__ int si[4];
+                                                     float* __restrict__ logits_dbg, int rem_activation,
+                                                     float* __restrict__ sig_raw, float* __restrict__ sig) {
+  __shared__ float sv[kFinalThreads / 64];
+  __shared__ int si[kFinalThreads / 64];
   const int m = blockIdx.x;
   const float* row = logits + static_cast<size_t>(m) * N;
   float bv = -INFINITY;
   int bi = INT_MAX;
-  for (int n = threadIdx.x; n < V; n += 256) {
-    const float v = row[n];
-    if (logits_dbg) logits_dbg[static_cast<size_t>(m) * V + n] = v;
-    if (better(v, n, bv, bi)) { bv = v; bi = n; }
+  constexpr int U = 4;
+  for (int n0 = threadIdx.x; n0 < V; n0 += U * kFinalThreads) {
+    float v[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) v[u] = row[min(n0 + u * kFinalThreads, V - 1)];
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const int n = n0 + u * kFinalThreads;
+      if (n < V) {
+        if (logits_dbg) logits_dbg[static_cast<size_t>(m) * V + n] = v[u];
+        if (better(v[u], n, bv, bi)) { bv = v[u]; bi = n; }
+      }
+    }
   }
   if (extra_out && static_cast<int>(threadIdx.x) < n_extra) extra_out[m * n_extra + threadIdx.x] = row[V + threadIdx.x];
+  if (sig && threadIdx.x == 64) write_signals(row + V, rem_activation, sig_raw + m * 3, sig + m * 3);
 #pragma unroll
   for (int o = 32; o > 0; o >>= 1) {
     const float ov = __shfl_xor(bv, o, 64);
@@ -274,7 +286,7 @@ __global__ __launch_bounds__(256) void k_argmax_rows(const float* __restrict__ l
   if ((threadIdx.x & 63) == 0) { sv[threadIdx.x >> 6] = bv; si[threadIdx.x >> 6] = bi; }
   __syncthreads();
   if (threadIdx.x == 0) {
-    for (int w = 1; w < 4; ++w)
+    for (int w = 1; w < kFinalThreads / 64; ++w)
       if (better(sv[w], si[w], bv, bi)) { bv = sv[w]; bi = si[w]; }
     argmax[m] = bi;
     if (max_logit) max_logit[m] = bv;
@@ -325,10 +337,10 @@ hipError_t launch_topb_finalize(const float* vals, const int* idxs, int C, int s
   return hipGetLastError();
 }
 
-hipError_t launch_argmax_rows(const float* logits, int M, int N, int V, int n_extra, int32_t* argmax,
-                              float* max_logit, float* extra_out, float* logits_dbg, hipStream_t s) {
-  hipLaunchKernelGGL(k_argmax_rows, dim3(M), dim3(256), 0, s, logits, N, V, n_extra, argmax, max_logit,
-                     extra_out, logits_dbg);
+hipError_t launch_argmax_rows(const float* logits, int M, int N, int V, int n_extra, int32_t* argmax, float* max_logit, float* extra_out,
+                              float* logits_dbg, hipStream_t s, int rem_activation, float* sig_raw, float* sig) {
+  hipLaunchKernelGGL(k_argmax_rows, dim3(M), dim3(kFinalThreads), 0, s, logits, N, V, n_extra, argmax, max_logit, extra_out, logits_dbg,
+                     rem_activation, sig_raw, sig);
   return hipGetLastError();
 }
 

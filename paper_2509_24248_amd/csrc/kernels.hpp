@@ -161,7 +161,8 @@ hipError_t launch_topb_finalize(const float* vals, const int* idxs, int C, int s
 // VALU head path: logits [M][N] -> argmax over n < V, copy of signal rows and of logits
 hipError_t launch_argmax_rows(const float* logits, int M, int N, int V, int n_extra,
                               int32_t* argmax, float* max_logit, float* extra_out,
-                              float* logits_dbg, hipStream_t s);
+                              float* logits_dbg, hipStream_t s, int rem_activation = 0, float* sig_raw = nullptr,
+                              float* sig = nullptr);   // (with `sig` set: the three signal rows' activations too)
 // storage-type rows -> fp32 rows (ALU GEMM path only)
 hipError_t launch_unpack_rows(const void* src, bool bf16, int M, int K, float* act, hipStream_t s);
 
@@ -228,9 +229,6 @@ hipError_t launch_rope_kvwrite(const DraftDims& dm, int M, int W, const float* p
                                int* status = nullptr);
 hipError_t launch_silu_mul(const DraftDims& dm, int B, const float* partial, int nslices, int planes,
                            float* act, hipStream_t s);
-hipError_t launch_head_finalize(const DraftDims& dm, int B, const int32_t* argmax_in,
-                                const float* extra, int32_t* next_tok, float* sig_raw, float* sig,
-                                hipStream_t s);
 
 // ---- measurement aid: copy of known size through the streaming load path -------------------
 hipError_t launch_copy_probe(const void* src, void* dst, size_t bytes, bool nontemporal, hipStream_t s);
