@@ -34,49 +34,65 @@ __device__ __forceinline__ SegRef find_segment(const GemmArgs& g, int n) {
 }
 
 // ------------------------------------------------------------------------- VALU path
-template <typename WT>
+// A wave takes NR weight rows and up to eight activation rows (blockIdx.y: which eight).  With several activation
+// rows their reads are the bound (every weight row reads all of them from L1 / L2), so four weight rows share them;
+// with one or two, one weight row per wave gives the most waves.
+template <typename WT, int NR>
 __global__ __launch_bounds__(256) void k_gemv_valu(const GemmArgs g) {
   constexpr int EPV = Elem<WT>::kPer16B;
   const int lane = threadIdx.x & 63;
-  const int n = blockIdx.x * 4 + (threadIdx.x >> 6);
+  const int n = (blockIdx.x * 4 + (threadIdx.x >> 6)) * NR;
   if (n >= g.N) return;
-  const SegRef sg = find_segment(g, n);
-  const uint4* wrow = reinterpret_cast<const uint4*>(sg.base + static_cast<size_t>(n - sg.row0) * g.K * sizeof(WT));
+  const SegRef sg = find_segment(g, n);        // (segment ends are multiples of 4: the rows lie in one)
+  const uint4* wrow[NR];
+#pragma unroll
+  for (int r = 0; r < NR; ++r)
+    wrow[r] = reinterpret_cast<const uint4*>(sg.base + static_cast<size_t>(min(n - sg.row0 + r, sg.rows - 1)) * g.K * sizeof(WT));
   const int nvec = g.K / EPV;
-  for (int m0 = 0; m0 < g.M; m0 += 8) {
-    const int mc = min(8, g.M - m0);
-    float acc[8];
+  const int m0 = blockIdx.y * 8;
+  const int mc = min(8, g.M - m0);
+  float acc[8][NR];
 #pragma unroll
-    for (int i = 0; i < 8; ++i) acc[i] = 0.f;
-    for (int c = lane; c < nvec; c += 64) {
-      const uint4 wv = wrow[c];
-      float wf[8];
+  for (int i = 0; i < 8; ++i)
+#pragma unroll
+    for (int r = 0; r < NR; ++r) acc[i][r] = 0.f;
+  for (int c = lane; c < nvec; c += 64) {
+    float wf[NR][8];
+#pragma unroll
+    for (int r = 0; r < NR; ++r) {
+      const uint4 wv = wrow[r][c];
       if (EPV == 8) {
-        unpack16(wv, wf);
+        unpack16(wv, wf[r]);
       } else {
-        wf[0] = __uint_as_float(wv.x); wf[1] = __uint_as_float(wv.y);
-        wf[2] = __uint_as_float(wv.z); wf[3] = __uint_as_float(wv.w);
-      }
-#pragma unroll
-      for (int mm = 0; mm < 8; ++mm) {
-        if (mm < mc) {
-          const float* a = g.act + static_cast<size_t>(m0 + mm) * g.K + static_cast<size_t>(c) * EPV;
-#pragma unroll
-          for (int e = 0; e < EPV; e += 4) {
-            const float4 av = *reinterpret_cast<const float4*>(a + e);
-            acc[mm] = fmaf(av.x, wf[e + 0], acc[mm]);
-            acc[mm] = fmaf(av.y, wf[e + 1], acc[mm]);
-            acc[mm] = fmaf(av.z, wf[e + 2], acc[mm]);
-            acc[mm] = fmaf(av.w, wf[e + 3], acc[mm]);
-          }
-        }
+        wf[r][0] = __uint_as_float(wv.x); wf[r][1] = __uint_as_float(wv.y);
+        wf[r][2] = __uint_as_float(wv.z); wf[r][3] = __uint_as_float(wv.w);
       }
     }
 #pragma unroll
     for (int mm = 0; mm < 8; ++mm) {
       if (mm < mc) {
-        const float v = wave_sum(acc[mm]);
-        if (lane == 0) g.partial[static_cast<size_t>(m0 + mm) * g.N + n] = v;
+        const float* a = g.act + static_cast<size_t>(m0 + mm) * g.K + static_cast<size_t>(c) * EPV;
+#pragma unroll
+        for (int e = 0; e < EPV; e += 4) {
+          const float4 av = *reinterpret_cast<const float4*>(a + e);
+#pragma unroll
+          for (int r = 0; r < NR; ++r) {
+            acc[mm][r] = fmaf(av.x, wf[r][e + 0], acc[mm][r]);
+            acc[mm][r] = fmaf(av.y, wf[r][e + 1], acc[mm][r]);
+            acc[mm][r] = fmaf(av.z, wf[r][e + 2], acc[mm][r]);
+            acc[mm][r] = fmaf(av.w, wf[r][e + 3], acc[mm][r]);
+          }
+        }
+      }
+    }
+  }
+#pragma unroll
+  for (int mm = 0; mm < 8; ++mm) {
+    if (mm < mc) {
+#pragma unroll
+      for (int r = 0; r < NR; ++r) {
+        const float v = wave_sum(acc[mm][r]);
+        if (lane == 0 && n + r < g.N) g.partial[static_cast<size_t>(m0 + mm) * g.N + n + r] = v;
       }
     }
   }
@@ -313,11 +329,18 @@ hipError_t launch_zero_i32(int* p, int n, hipStream_t s) {
 }
 
 hipError_t launch_gemm_valu(const GemmArgs& g, bool bf16, hipStream_t s) {
-  const dim3 grid((g.N + 3) / 4);
-  if (bf16)
-    hipLaunchKernelGGL(k_gemv_valu<bf16_t>, grid, dim3(256), 0, s, g);
-  else
-    hipLaunchKernelGGL(k_gemv_valu<float>, grid, dim3(256), 0, s, g);
+  // (fp32, K = 1024: N = 20000 with 4 / 24 rows 31 -> 27.5 / 111 -> 79 us, N = 4096 with 24 rows 26 -> 22.6; with 12 rows,
+  // 2048 waves, four weight rows would take 21.7 us against 16.5)
+  const int64_t waves4 = static_cast<int64_t>((g.N + 3) / 4) * ((g.M + 7) / 8);
+  const int nr = g.M >= 4 && waves4 >= 3000 ? 4 : 1;
+  const dim3 grid((g.N + 4 * nr - 1) / (4 * nr), (g.M + 7) / 8);
+  if (bf16) {
+    if (nr == 4) hipLaunchKernelGGL((k_gemv_valu<bf16_t, 4>), grid, dim3(256), 0, s, g);
+    else hipLaunchKernelGGL((k_gemv_valu<bf16_t, 1>), grid, dim3(256), 0, s, g);
+  } else {
+    if (nr == 4) hipLaunchKernelGGL((k_gemv_valu<float, 4>), grid, dim3(256), 0, s, g);
+    else hipLaunchKernelGGL((k_gemv_valu<float, 1>), grid, dim3(256), 0, s, g);
+  }
   return hipGetLastError();
 }
 
