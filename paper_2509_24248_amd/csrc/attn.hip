@@ -178,6 +178,69 @@ __global__ __launch_bounds__(256) void k_attn_split_valu(const AttnArgs a) {
   }
 }
 
+// One output row of a 64-wide bf16 launch again, by one wave, with fp32 probabilities.  The matrix-core kernel
+// multiplies V with a probability in two parts, of which the second is 0 or negative as often as not: an infinite V
+// entry then becomes inf - inf or 0 inf, although its probability is positive.  So the merging kernels hand every row
+// that is not finite to this function: infinities come out as the one product p v gives them, and NaN where the
+// inputs ask for it (a NaN among them, infinities of both signs, an infinite entry that the mask hides: 0 inf).
+// Eight lanes take a key, eight of its columns each; the running maximum moves every eight keys.  A launch without
+// such rows pays for the test only (verify_attn, 8 sequences of 1000-8000 entries, 16 queries: 35.0 -> 35.7 us; 64 of
+// 500, 8 queries: 27 us either way); one in which every row is infinite takes 1.2 ms at the first of these sizes.
+__device__ __forceinline__ void attn_row_again(const AttnArgs& a, int b, int i, int h) {
+  const int lane = threadIdx.x & 63;
+  const int kq = lane >> 3, c = lane & 7;
+  const int G = a.Hq / a.Hkv, g = h / G;
+  const int L = attn_ctx_len(a, b), n = L + a.n_blk;
+  const size_t row = ((static_cast<size_t>(b) * a.n_q + i) * a.Hq + h) * 64;
+  const uint64_t seen = a.mask ? a.mask[static_cast<size_t>(b) * a.mask_stride + i] : ((2ull << i) - 1ull);
+  float q[8], acc[8], m = -INFINITY, sum = 0.f;
+  unpack16(*reinterpret_cast<const uint4*>(static_cast<const bf16_t*>(a.q) + row + 8 * c), q);
+#pragma unroll
+  for (int e = 0; e < 8; ++e) acc[e] = 0.f;
+#pragma unroll 1
+  for (int p0 = 0; p0 < n; p0 += 8) {
+    const int p = p0 + kq;
+    const bool in = p < n;
+    const uint4 kr = *reinterpret_cast<const uint4*>(kv_row<bf16_t>(a, a.k, b, g, min(p, n - 1)) + 8 * c);
+    const uint4 vr = *reinterpret_cast<const uint4*>(kv_row<bf16_t>(a, a.v, b, g, min(p, n - 1)) + 8 * c);
+    float kf[8], vf[8], x = 0.f;
+    unpack16(kr, kf);
+    unpack16(vr, vf);
+#pragma unroll
+    for (int e = 0; e < 8; ++e) x = fmaf(q[e], kf[e], x);
+#pragma unroll
+    for (int o = 1; o < 8; o <<= 1) x += __shfl_xor(x, o, 64);
+    const bool vis = in && (p < L || (seen >> (p - L) & 1ull));
+    x = vis ? x * a.scale : -INFINITY;
+    float mt = x;
+#pragma unroll
+    for (int o = 8; o < 64; o <<= 1) mt = fmaxf(mt, __shfl_xor(mt, o, 64));
+    const float m_new = fmaxf(m, mt);
+    float al = 1.f, pr = 0.f;
+    if (m_new != -INFINITY) {
+      al = m == -INFINITY ? 0.f : expf(m - m_new);
+      pr = expf(x - m_new);
+    }
+    m = m_new;
+    sum = fmaf(sum, al, pr);
+#pragma unroll
+    for (int e = 0; e < 8; ++e) acc[e] = fmaf(pr, in ? vf[e] : 0.f, acc[e] * al);
+  }
+#pragma unroll
+  for (int o = 8; o < 64; o <<= 1) {
+    sum += __shfl_xor(sum, o, 64);
+#pragma unroll
+    for (int e = 0; e < 8; ++e) acc[e] += __shfl_xor(acc[e], o, 64);
+  }
+  if (kq == 0) {
+    bf16_t* dst = static_cast<bf16_t*>(a.out) + row + 8 * c;
+#pragma unroll
+    for (int e = 0; e < 8; ++e) Elem<bf16_t>::store(dst + e, acc[e] / sum);
+  }
+}
+// (uniform over the wave: one of its lanes holds a value that is no number or infinite)
+__device__ __forceinline__ bool any_not_finite(float v) { return __builtin_amdgcn_ballot_w64(!(fabsf(v) < INFINITY)) != 0ull; }
+
 // Merge the segments of one (sequence, query, head): exact log-sum-exp combination.  One
 // workgroup per output row: the chunks' weights exp(m_s - max) are formed once in LDS, then
 // the threads split into groups that each take every NG-th chunk of one float4 column, so
@@ -247,15 +310,25 @@ __global__ __launch_bounds__(kCombThreads) void k_attn_combine(const AttnArgs a)
   float4* gs = reinterpret_cast<float4*>(w_lds + ((a.wgrid + 3) & ~3));
   gs[sg * C4 + c4] = acc;
   __syncthreads();
+  float4 sum = make_float4(0.f, 0.f, 0.f, 0.f);
   if (sg == 0) {
-    float4 sum = gs[c4];
+    sum = gs[c4];
     for (int u = 1; u < NG; ++u) {
       const float4 v = gs[u * C4 + c4];
       sum.x += v.x; sum.y += v.y; sum.z += v.z; sum.w += v.w;
     }
+    sum.x /= den; sum.y /= den; sum.z /= den; sum.w /= den;
+  }
+  if constexpr (D == 64 && sizeof(T) == 2) {
+    if (a.use_mfma && threadIdx.x < 64 && any_not_finite((sum.x + sum.y) + (sum.z + sum.w))) {
+      attn_row_again(a, b, i, h);
+      return;
+    }
+  }
+  if (sg == 0) {
     T* dst = static_cast<T*>(a.out) + ((static_cast<size_t>(b) * a.n_q + i) * a.Hq + h) * D + c4 * 4;
-    Elem<T>::store(dst + 0, sum.x / den); Elem<T>::store(dst + 1, sum.y / den);
-    Elem<T>::store(dst + 2, sum.z / den); Elem<T>::store(dst + 3, sum.w / den);
+    Elem<T>::store(dst + 0, sum.x); Elem<T>::store(dst + 1, sum.y);
+    Elem<T>::store(dst + 2, sum.z); Elem<T>::store(dst + 3, sum.w);
   }
 }
 
@@ -316,6 +389,12 @@ __global__ __launch_bounds__(256) void k_attn_combine_rows(const AttnArgs a) {
 #pragma unroll
           for (int e = 0; e < EPL; ++e) acc[e] = fmaf(ws[u], o[u][e], acc[e]);
         }
+    }
+  }
+  if constexpr (D == 64 && sizeof(T) == 2) {
+    if (a.use_mfma && any_not_finite(acc[0] / den)) {
+      attn_row_again(a, b, i, h);
+      return;
     }
   }
   T* dst = static_cast<T*>(a.out) + static_cast<size_t>(row) * D + lane * EPL;

@@ -81,6 +81,33 @@ def test_narrow_heads_at_tile_edges(n_q, Hq, Hkv, page):
     assert err < 2.0 ** -8
 
 
+@pytest.mark.parametrize("B,n_q,page", [(2, 5, 16), (2, 16, 0), (40, 3, 64)])
+def test_infinite_values_of_narrow_heads(B, n_q, page):
+    # 64-wide heads: an infinite V entry that a row sees makes its column of that row infinite, with its sign (the
+    # probability is positive), and changes no other column.  Few and many segments per unit: both merging kernels.
+    shape = gen.scaled(gen.config(1), B=B, Hq=8, Hkv=2, d=64, n_q=n_q, ctx=(20, 500), page_size=page or 16)
+    L, kv, q, _ = case(shape, 5, paged=page > 0)
+    # (sequence, KV head, entry, column, value); the last one is the block's last entry, which only the last query sees
+    put = [(0, 0, 3, 5, np.inf), (0, 1, int(L[0]) - 1, 63, -np.inf), (1, 0, 17, 0, -np.inf), (1, 0, 19, 0, -np.inf), (1, 1, int(L[1]) + n_q - 1, 8, np.inf)]
+    for b, g, p, c, x in put:
+        if kv.paged:
+            kv.v[kv.page_table[b, p // kv.page_size], g, p % kv.page_size, c] = x
+        else:
+            kv.v[b, g, p, c] = x
+    print(f"infinite V: B={B} n_q={n_q} page={page}", flush=True)
+    got = gpu_verify_attn(shape, kv, q, L, None)
+    with np.errstate(invalid="ignore"):
+        ref = oracle_verify_attn(kv, q, L, None)
+    plain = np.ones(got.shape, bool)
+    G = shape.Hq // shape.Hkv
+    for b, g, p, c, x in put:
+        rows = slice(n_q - 1, None) if p >= L[b] else slice(None)
+        assert (got[b, rows, g * G:(g + 1) * G, c] == x).all(), (b, g, p, c, got[b, rows, g * G:(g + 1) * G, c])
+        plain[b, :, g * G:(g + 1) * G, c] = False
+    assert np.isfinite(got[plain]).all()
+    assert rel_err(got[plain], ref[plain]) < TOL["bf16"]
+
+
 @pytest.mark.parametrize("dtype,d", [("bf16", 64), ("bf16", 128), ("f32", 64)])
 def test_one_long_sequence_among_short_ones(dtype, d):
     # few segments per unit on average, so a wave merges each output row, and one unit with more of them than a wave has lanes
