@@ -45,6 +45,16 @@ constexpr int stages_of(int hd, int nr) { return (nr >= big_from(hd) ? 4 : 2) * 
 // have four of each)
 constexpr int k_ahead(int hd, int nr) { return hd == 128 && nr >= big_from(hd) ? 8 : 4; }
 constexpr int v_ahead(int hd, int nr) { return hd == 64 || nr >= big_from(hd) ? 4 : 3; }
+// From kPairFrom row tiles on (97 and more query rows per KV head, 128-wide heads) a wave takes two row tiles: four
+// waves per ring with 256 registers a lane, which read every K and V operand once for 32 rows.  One tile per
+// wave leaves the seven or eight waves of a ring 128 registers, of which 8 to 150 bytes a lane go to scratch memory.
+// Whole calls, contiguous / paged: 16 sequences of 4000-16000 entries, 64 query heads, 104 rows 182 / 192 -> 152 / 161 us,
+// 128 rows 164 / 175 -> 166 / 174; 32 query heads, 8 sequences of 2000-8000, 128 rows 64 / 69 -> 58 / 60; 1 of 20000, 100
+// rows 43.5 / 44 -> 35.5 / 36; a 16-node tree over 4 sequences of 300-900, 128 rows 35.5 -> 31.8.  With fewer rows nothing
+// spills and one tile per wave is faster (measured at 72 rows).  Paged caches at 33..48 rows keep 16 bytes a lane in scratch
+// memory: without the last slot's early request they would not, at the same time (40 rows 53.8 / 53.5 us).
+constexpr int kPairFrom = 7;
+constexpr int tiles_per_wave(int hd, int tiles) { return hd == 128 && tiles >= kPairFrom ? 2 : 1; }
 constexpr int kMaxChunkPages = 2048;   // page ids of one chunk kept in LDS (8 KB)
 
 typedef short s16x4_t __attribute__((ext_vector_type(4)));
@@ -94,8 +104,7 @@ constexpr int min_waves_per_simd(int hd, int nr) { return ((nr < big_from(hd) ? 
 
 // NR waves per ring, each owning RTW 16-row tiles of the queries (rows 16 (rr RTW + t) ..).
 // RTW = 2 halves the LDS reads per query row (K and V operands are fetched once per wave and
-// used for both row tiles) at the price of fewer, fatter waves; measured slower than RTW = 1
-// at R = 72, so the launcher below uses one row tile per wave throughout.
+// used for both row tiles) at the price of fewer, fatter waves (see kPairFrom).
 template <int HD, int NR, int RTW, int S, bool PAGED>
 __global__ __launch_bounds__(64 * kNK * NR, min_waves_per_simd(HD, NR)) void k_attn_ring(const AttnArgs a) {
   constexpr int RP = 16 * NR * RTW;             // query rows covered (padded)
@@ -452,36 +461,36 @@ __global__ __launch_bounds__(64 * kNK * NR, min_waves_per_simd(HD, NR)) void k_a
   }
 }
 
-template <int HD, int NR, int S, bool PAGED>
+template <int HD, int NR, int RTW, int S, bool PAGED>
 hipError_t launch_one(const AttnArgs& a, hipStream_t s) {
-  static_assert(NR <= 8, "at most 128 query rows");
+  static_assert(NR * RTW <= 8, "at most 128 query rows");
   // set once per process; a function-local static is initialised under the language's own lock,
   // so first calls from several host threads are safe
-  static const hipError_t attr = hipFuncSetAttribute(reinterpret_cast<const void*>(&k_attn_ring<HD, NR, 1, S, PAGED>),
+  static const hipError_t attr = hipFuncSetAttribute(reinterpret_cast<const void*>(&k_attn_ring<HD, NR, RTW, S, PAGED>),
                                              hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
   if (attr != hipSuccess) return attr;
-  hipLaunchKernelGGL((k_attn_ring<HD, NR, 1, S, PAGED>), dim3(a.wgrid), dim3(64 * kNK * NR), attn_mfma_lds_bytes(a), s, a);
+  hipLaunchKernelGGL((k_attn_ring<HD, NR, RTW, S, PAGED>), dim3(a.wgrid), dim3(64 * kNK * NR), attn_mfma_lds_bytes(a), s, a);
   return hipGetLastError();
 }
 
-template <int HD, int NR>
-hipError_t launch_nr(const AttnArgs& a, hipStream_t s) {
-  constexpr int S = stages_of(HD, NR);
-  return a.paged ? launch_one<HD, NR, S, true>(a, s) : launch_one<HD, NR, S, false>(a, s);
+template <int HD, int TILES>
+hipError_t launch_tiles(const AttnArgs& a, hipStream_t s) {
+  constexpr int RTW = tiles_per_wave(HD, TILES), NR = (TILES + RTW - 1) / RTW, S = stages_of(HD, NR);
+  return a.paged ? launch_one<HD, NR, RTW, S, true>(a, s) : launch_one<HD, NR, RTW, S, false>(a, s);
 }
 
 template <int HD>
 hipError_t launch_hd(const AttnArgs& a, hipStream_t s) {
   const int R = (a.Hq / a.Hkv) * a.n_q;
   switch ((R + 15) / 16) {
-    case 1: return launch_nr<HD, 1>(a, s);
-    case 2: return launch_nr<HD, 2>(a, s);
-    case 3: return launch_nr<HD, 3>(a, s);
-    case 4: return launch_nr<HD, 4>(a, s);
-    case 5: return launch_nr<HD, 5>(a, s);
-    case 6: return launch_nr<HD, 6>(a, s);
-    case 7: return launch_nr<HD, 7>(a, s);
-    case 8: return launch_nr<HD, 8>(a, s);
+    case 1: return launch_tiles<HD, 1>(a, s);
+    case 2: return launch_tiles<HD, 2>(a, s);
+    case 3: return launch_tiles<HD, 3>(a, s);
+    case 4: return launch_tiles<HD, 4>(a, s);
+    case 5: return launch_tiles<HD, 5>(a, s);
+    case 6: return launch_tiles<HD, 6>(a, s);
+    case 7: return launch_tiles<HD, 7>(a, s);
+    case 8: return launch_tiles<HD, 8>(a, s);
     default: return hipErrorInvalidValue;
   }
 }
@@ -495,12 +504,16 @@ bool attn_mfma_supported(const AttnArgs& a) {
 }
 
 // Workgroups per compute unit and ring depth (see big_from).
-static int waves_per_ring(const AttnArgs& a) { return ((a.Hq / a.Hkv) * a.n_q + 15) / 16; }
+static int row_tiles(const AttnArgs& a) { return ((a.Hq / a.Hkv) * a.n_q + 15) / 16; }
+static int waves_per_ring(const AttnArgs& a) {
+  const int per = tiles_per_wave(a.d, row_tiles(a));
+  return (row_tiles(a) + per - 1) / per;
+}
 int attn_mfma_per_cu(const AttnArgs& a) { return waves_per_ring(a) >= big_from(a.d) ? 1 : 2; }
 int attn_mfma_stages(const AttnArgs& a) { return stages_of(a.d, waves_per_ring(a)); }
 
 size_t attn_mfma_lds_bytes(const AttnArgs& a) {
-  const int rp = 16 * waves_per_ring(a);
+  const int rp = 16 * waves_per_ring(a) * tiles_per_wave(a.d, row_tiles(a));
   return static_cast<size_t>(front_bytes(a.d, rp, a.stages)) + static_cast<size_t>(kNK) * rp * 2 * sizeof(float) +
          static_cast<size_t>(attn_sched_words(a.B)) * sizeof(int) + (a.paged ? static_cast<size_t>(kMaxChunkPages + 1) * sizeof(int) : 0);
 }

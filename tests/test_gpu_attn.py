@@ -135,6 +135,16 @@ def test_block_size_extremes(n_q, Hq, Hkv):
     check(shape, L, kv, q, mask, label="extremes")
 
 
+@pytest.mark.parametrize("n_q,Hq,Hkv", [(24, 8, 2), (25, 8, 2), (14, 16, 2), (29, 4, 1), (8, 16, 1)])
+@pytest.mark.parametrize("page", [0, 16, 64])
+def test_many_query_rows(n_q, Hq, Hkv, page):
+    # 96 to 128 rows per KV head: from 97 on a wave takes two row tiles, the last of them ragged or empty
+    shape = gen.scaled(gen.config(1), B=9, Hq=Hq, Hkv=Hkv, n_q=n_q, k=5, ctx=(0, 1500), page_size=page or 16)
+    L, kv, q, mask = case(shape, 6, tree=page != 16, paged=page > 0)
+    L[0], L[1] = 0, 1
+    check(shape, L, kv, q, mask, label="many rows")
+
+
 def test_self_only_mask_with_empty_context_returns_own_value():
     shape = gen.scaled(gen.config(1), B=2, Hq=4, Hkv=2, n_q=5, ctx=(0, 0))
     L, kv, q, _ = case(shape, 5)
