@@ -461,8 +461,15 @@ __global__ __launch_bounds__(64 * kNK * NR, min_waves_per_simd(HD, NR)) void k_a
   }
 }
 
+constexpr size_t lds_bytes(int hd, int rp, int stages, int B, bool paged) {
+  return static_cast<size_t>(front_bytes(hd, rp, stages)) + static_cast<size_t>(kNK) * rp * 2 * sizeof(float) +
+         static_cast<size_t>(attn_sched_words(B)) * sizeof(int) + (paged ? static_cast<size_t>(kMaxChunkPages + 1) * sizeof(int) : 0);
+}
+
 template <int HD, int NR, int RTW, int S, bool PAGED>
 hipError_t launch_one(const AttnArgs& a, hipStream_t s) {
+  // as many workgroups as attn_mfma_per_cu counts on fit the 160 KB of a compute unit, at any number of sequences
+  static_assert(lds_bytes(HD, 16 * NR * RTW, S, kAttnMaxSeqs, PAGED) * (NR >= big_from(HD) ? 1 : 2) <= 160 * 1024, "the LDS of a compute unit");
   static_assert(NR * RTW <= 8, "at most 128 query rows");
   // set once per process; a function-local static is initialised under the language's own lock,
   // so first calls from several host threads are safe
@@ -514,8 +521,7 @@ int attn_mfma_stages(const AttnArgs& a) { return stages_of(a.d, waves_per_ring(a
 
 size_t attn_mfma_lds_bytes(const AttnArgs& a) {
   const int rp = 16 * waves_per_ring(a) * tiles_per_wave(a.d, row_tiles(a));
-  return static_cast<size_t>(front_bytes(a.d, rp, a.stages)) + static_cast<size_t>(kNK) * rp * 2 * sizeof(float) +
-         static_cast<size_t>(attn_sched_words(a.B)) * sizeof(int) + (a.paged ? static_cast<size_t>(kMaxChunkPages + 1) * sizeof(int) : 0);
+  return lds_bytes(a.d, rp, a.stages, a.B, a.paged);
 }
 
 int attn_mfma_max_chunk(const AttnArgs& a) { return a.paged ? kMaxChunkPages * a.page_size : (1 << 30); }

@@ -30,10 +30,15 @@ __device__ __forceinline__ int attn_ctx_len(const AttnArgs& a, int b) {
 }
 
 // LDS words of the table below.
-__host__ __device__ constexpr int attn_sched_words(int B) { return (2 * B + 1 + 3) & ~3; }
+__host__ __device__ constexpr int attn_sched_words(int B) { return (B + 1 + (B + 3) / 4 + 3) & ~3; }
 
-// Prefix sums S[0 .. B] of the sequences' granule counts and, behind them, the sequences' context lengths, built by the
-// first wave; every thread of the workgroup calls this, and the table is ready when it returns.
+// Prefix sums S[0 .. B] of the sequences' granule counts and, behind them, a byte per sequence: how far its entries fall
+// short of full granules, which with the count gives its length back.  (Whole lengths take four times that, and with
+// more than 930 sequences a second workgroup of a paged launch then finds no room in the compute unit's LDS: B = 1000,
+// 4 queries of 8 heads, contexts 200-500: 141 us; 111 this way, and 114 -> 80 with 64-wide heads.)
+__device__ __forceinline__ unsigned char* attn_sched_short(const AttnArgs& a, int* S) { return reinterpret_cast<unsigned char*>(S + a.B + 1); }
+
+// Built by the first wave; every thread of the workgroup calls this, and the table is ready when it returns.
 __device__ __forceinline__ void attn_sched_build(const AttnArgs& a, int* S) {
   if (threadIdx.x < 64) {
     const int lane = threadIdx.x;
@@ -42,9 +47,9 @@ __device__ __forceinline__ void attn_sched_build(const AttnArgs& a, int* S) {
       const int b = c + lane;
       int x = 0;
       if (b < a.B) {
-        const int L = attn_ctx_len(a, b);
-        S[a.B + 1 + b] = L;
-        x = (L + a.n_blk + kAttnGran - 1) / kAttnGran;
+        const int n = attn_ctx_len(a, b) + a.n_blk;
+        x = (n + kAttnGran - 1) / kAttnGran;
+        attn_sched_short(a, S)[b] = static_cast<unsigned char>(x * kAttnGran - n);
       }
 #pragma unroll
       for (int o = 1; o < 64; o <<= 1) {
@@ -90,7 +95,7 @@ struct AttnSeg {
 
 // The segment that starts at granule x of the line and ends at the unit's end or at `hi`.
 // Uniform over the workgroup; S in LDS.
-__device__ __forceinline__ AttnSeg attn_sched_segment(const AttnArgs& a, const int* S, int x, int hi) {
+__device__ __forceinline__ AttnSeg attn_sched_segment(const AttnArgs& a, int* S, int x, int hi) {
   const int lane = threadIdx.x & 63;
   int b = 0;
   for (int c = 0; c < a.B; c += 64) {
@@ -106,7 +111,7 @@ __device__ __forceinline__ AttnSeg attn_sched_segment(const AttnArgs& a, const i
   s.g = min(rel / n, a.Hkv - 1);
   const int g0 = min(rel - s.g * n, n - 1);     // first granule inside the unit
   const int g1 = min(n, g0 + (hi - x));
-  s.L = S[a.B + 1 + b];
+  s.L = n * kAttnGran - attn_sched_short(a, S)[b] - a.n_blk;
   s.s0 = g0 * kAttnGran;
   s.s1 = min(s.L + a.n_blk, g1 * kAttnGran);
   s.next = x + max(g1 - g0, 1);                 // (the minima above cannot bind while S is the table of these lengths)
