@@ -334,9 +334,30 @@ __global__ __launch_bounds__(kCombThreads) void k_attn_combine(const AttnArgs a)
 
 size_t combine_lds_bytes(int wgrid) { return (static_cast<size_t>((wgrid + 3) & ~3) + kCombThreads * 4) * sizeof(float); }
 
-// The same with one wave per output row, for launches whose units have few segments: there are then
-// many rows, and a workgroup for each spends its time starting.  Whole call, 64 sequences of 200-600 entries x 5
-// queries x 32 heads 48.5 -> 37 us; 32 sequences x 7 x 32 (64-wide heads) 26 -> 18; 16 long ones x 9 x 64 322 -> 312.
+// acc += weight x partial output of the segments j .. j + U - 1 of at most 64 (n of them; lane i holds segment i's weight),
+// requested together and added one after the other
+template <int U, int EPL>
+__device__ __forceinline__ void combine_add(float (&acc)[EPL], const float* po, size_t stride, float w, int j, int n) {
+  float o[U][EPL], ws[U];
+#pragma unroll
+  for (int u = 0; u < U; ++u) {
+    const int jj = min(j + u, n - 1);
+    ws[u] = j + u < n ? __shfl(w, jj, 64) : 0.f;
+    const float* src = po + static_cast<size_t>(jj) * stride;
+#pragma unroll
+    for (int e = 0; e < EPL; ++e) o[u][e] = src[e];
+  }
+#pragma unroll
+  for (int u = 0; u < U; ++u)
+    if (ws[u] != 0.f) {
+#pragma unroll
+      for (int e = 0; e < EPL; ++e) acc[e] = fmaf(ws[u], o[u][e], acc[e]);
+    }
+}
+
+// The same with one wave per output row: for many rows, where a workgroup each spends its time starting.  Sixteen
+// segments are requested together, so that a unit of many segments in a batch of short ones costs a few memory round trips
+// (four at a time: one context of 32768 among 15 of 300, 2 queries, 41.7 us; 38.6 this way).
 template <typename T, int D>
 __global__ __launch_bounds__(256) void k_attn_combine_rows(const AttnArgs a) {
   constexpr int EPL = D / 64;               // columns per lane
@@ -373,23 +394,9 @@ __global__ __launch_bounds__(256) void k_attn_combine_rows(const AttnArgs a) {
     }
     den += wave_sum(w != 0.f ? w * l : 0.f);
     const int n = min(64, nact - s0);
-    for (int j = 0; j < n; j += 4) {
-      float o[4][EPL], ws[4];
-#pragma unroll
-      for (int u = 0; u < 4; ++u) {
-        const int jj = min(j + u, n - 1);
-        ws[u] = j + u < n ? __shfl(w, jj, 64) : 0.f;
-        const float* src = po + static_cast<size_t>(s0 + jj) * R * D;
-#pragma unroll
-        for (int e = 0; e < EPL; ++e) o[u][e] = src[e];
-      }
-#pragma unroll
-      for (int u = 0; u < 4; ++u)
-        if (ws[u] != 0.f) {
-#pragma unroll
-          for (int e = 0; e < EPL; ++e) acc[e] = fmaf(ws[u], o[u][e], acc[e]);
-        }
-    }
+    int j = 0;
+    for (; j + 8 < n; j += 16) combine_add<16, EPL>(acc, po + static_cast<size_t>(s0) * R * D, static_cast<size_t>(R) * D, w, j, n);
+    for (; j < n; j += 4) combine_add<4, EPL>(acc, po + static_cast<size_t>(s0) * R * D, static_cast<size_t>(R) * D, w, j, n);
   }
   if constexpr (D == 64 && sizeof(T) == 2) {
     if (a.use_mfma && any_not_finite(acc[0] / den)) {
@@ -404,11 +411,18 @@ __global__ __launch_bounds__(256) void k_attn_combine_rows(const AttnArgs a) {
 
 template <typename T, int D>
 hipError_t launch_combine(const AttnArgs& a, hipStream_t s) {
-  // segments per unit, on average: the row kernel takes them one after the other, the other one side by side.
-  // (The lengths are not known here; a unit with many segments in a launch of short ones is slower, not wrong.)
+  // A workgroup per row costs about 1 us per 1000 rows, a wave per row about 0.05 us per segment of the unit.  Whole
+  // calls, workgroup / wave, 32768 entries in all, 32 query heads over 8 KV heads:
+  //   segments per unit    64          32          16          8           4           2           1
+  //   1 query              29.9 / 32.6 29.4 / 30.7 29.2 / 29.8 29.4 / 29.8 30.2 / 29.8 30.7 / 30.0 31.4 / 30.6
+  //   5 queries            30.3 / 32.8 30.1 / 30.9 30.2 / 30.3 31.2 / 30.3 34.2 / 31.4 37.6 / 32.5 44.1 / 34.0
+  //   12 queries           44.3 / 47.4 44.3 / 44.4 44.1 / 43.7 47.0 / 43.8 51.0 / 45.2 59.3 / 48.9 75.7 / 55.0
+  // The lengths are not known here, and one long sequence among short ones has more segments than the average: 32768
+  // among n - 1 of 300, n = 16 / 32 / 64, 2 queries 36.4 / 38.6, 39.6 / 40.4, 61.5 / 59.0, 8 queries 45.2 / 43.2, 54.2 / 48.2,
+  // 86 / 72.  So the wave's side starts at 256 rows per segment of an average unit, where it leads with room to spare.
   const int64_t units = static_cast<int64_t>(a.B) * a.Hkv;
-  if (a.wgrid <= 4 * units) {
-    const int64_t rows = static_cast<int64_t>(a.B) * a.n_q * a.Hq;
+  const int64_t rows = static_cast<int64_t>(a.B) * a.n_q * a.Hq;
+  if (rows * units > 256 * static_cast<int64_t>(a.wgrid)) {
     hipLaunchKernelGGL((k_attn_combine_rows<T, D>), dim3(static_cast<unsigned>((rows + 3) / 4)), dim3(256), 0, s, a);
   } else {
     hipLaunchKernelGGL((k_attn_combine<T, D>), dim3(a.Hq, a.n_q, a.B), dim3(kCombThreads), combine_lds_bytes(a.wgrid), s, a);
