@@ -90,6 +90,15 @@ def test_bf16_row_tile_edges_and_k_chunks(M, D, V):
     assert err < 1e-3
 
 
+@pytest.mark.parametrize("M", [3, 24, 40, 64])
+@pytest.mark.parametrize("V", [2, 17, 129, 255, 2049, 36887])
+def test_bf16_ragged_last_tile(M, V):
+    # the launch's last weight tile with 1, 2, 7 or 15 of its rows, in the only half, at the end of a shorter or a longer one
+    # (36887: 2306 tiles in 256 shares of 9 and 10, halves of 4 and 5)
+    err = run_case(gen.scaled(gen.config(1), V=V, D=384), M, 0, M + V, "ragged last tile")
+    assert err < 1e-3          # bf16 inputs are exact; only fp32 summation order differs
+
+
 @pytest.mark.parametrize("M", [2, 30])
 def test_tie_takes_lowest_index_across_workgroups_that_take_k_in_another_order(M):
     shape = gen.scaled(gen.config(1), V=40000, D=2048)
