@@ -626,13 +626,15 @@ bool head_wide_supported(const GemmArgs& g) {
   return g.planes == 2 ? g.M <= 64 && g.top_b <= SPECEXIT_MAX_TOP_B : g.top_b <= 1 && g.M <= 160;
 }
 
-// One workgroup per compute unit, each walking an equal share of the weight tiles (at least one
-// stage's worth); one candidate slot per workgroup and column split.
+// One workgroup per compute unit, each walking an equal share of the weight tiles, one candidate slot per workgroup and
+// column split.  Vocabularies of less than a stage per compute unit: workgroups of at most one stage's tiles.  (Of at
+// least one stage's, the share of 2001 tiles among 250 workgroups is nine, two halves where one would do, and twice the
+// stages: V = 32003, D = 5120, 1 / 8 rows 59.5 / 58.5 -> 54 us; V = 4001, D = 4096, 1 / 56 rows 36 / 48 -> 26 / 37.)
 void head_wide_plan(GemmArgs& g, int num_cus) {
   if (!head_wide_supported(g)) return;
   const int ntiles = gemm_ntiles(g.N);
   const WideShape sh = wide_shape(g.M, g.planes, g.K);
-  g.wide_w = std::max(1, std::min(num_cus, ntiles / kWideTiles));
+  g.wide_w = std::min(num_cus, (ntiles + kWideTiles - 1) / kWideTiles);
   g.wide_slots = sh.split ? 2 : sh.cs;
 }
 

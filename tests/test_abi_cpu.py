@@ -97,3 +97,13 @@ def test_wide_page_tables_of_narrow_heads_are_still_accepted():
     for max_pages in (64, 8192, 1 << 15):
         kv.max_pages_per_seq = max_pages
         assert sx.specexit_verify_attn_workspace_bytes(kv, 1024, 7, 32) > 0, (max_pages, sx.last_error())
+
+
+@pytest.mark.skipif(not os.path.exists(LIB), reason="libspecexit.so not built")
+@pytest.mark.parametrize("V,workgroups", [(1, 1), (128, 1), (129, 2), (4001, 32), (32003, 251), (32768, 256), (32769, 256), (151936, 256)])
+def test_head_workgroups_take_one_stage_of_small_vocabularies(V, workgroups):
+    # 16 rows of bf16 activations, four candidates per row and workgroup (its column splits): 256 bytes of values and as
+    # many of indices per workgroup, and nothing else in the workspace.  A share of more than eight 16-row tiles where
+    # eight would do takes twice the stages.
+    from paper_2509_24248_amd import binding as sx
+    assert sx.specexit_lmhead_argmax_workspace_bytes(sx.BF16, 16, 4096, V, 0) == 512 * workgroups
