@@ -576,26 +576,32 @@ constexpr int kWideTiles = 8, kWideStages = 4;
 // How the rows are dealt to consumer waves.  One plane: pairs of row tiles per wave from 33 rows on (one LDS read
 // then feeds two matrix instructions); fewer rows leave one or two row tiles, whose columns are split
 // over four waves, one per SIMD.  Two planes: the pair is value and rest of the same 16 rows.
-// With four row tiles two waves per pair (which leaves the registers for a chunk tree of one level) are as fast
-// or faster (64 rows, V = 151936: D = 2560 / 4096 / 5120 139 / 221 / 262 us against 146 / 219 / 268); with three, five
-// or six they lose 4 % (D = 4096, V = 100000, 80 rows: 164 against 158), except where rows are a power of two of
-// at most 4 KB apart and the common k block costs more (D = 2048, V = 128259, 48 / 80 rows: 95 / 102 against 125 / 127).
-struct WideShape { int rg, rt, cs, split; };
-WideShape wide_shape(int M, int planes, int K) {
-  const int tiles = (M + 15) / 16;
-  if (planes == 2) return {tiles, 2, tiles == 1 ? 4 : tiles <= 3 ? 2 : 1, 0};
-  if (tiles <= 2) return {tiles, 1, tiles == 1 ? 4 : 2, 0};
-  if (tiles == 4 || (tiles <= 6 && K <= 2048 && (K & (K - 1)) == 0)) return {(tiles + 1) / 2, 2, 2, 0};
-  return {(tiles + 1) / 2, 2, 1, tiles & 1};
+// Four row tiles: two waves per pair, half of the columns each, so that all four SIMDs work (64 rows, D = 2560 / 5120:
+// V = 57000 52 / 98 us, 57 / 106 with one wave per pair; V = 151936 133 / 257 and 139 / 264).  With three, five or six
+// an odd last tile is shared by two waves instead, or all SIMDs are busy anyway.
+//
+// lv: levels of the chunk tree.  Two where the accumulators of a pass take at most 32 registers (one row tile per
+// wave, or the draft head's first).  Otherwise the finished siblings do not fit beside them: one level leaves 24 to 52
+// bytes a lane in scratch memory and costs 5 to 12 % (V = 40000, 64 rows, D = 2560 / 5120 46.8 / 84 us, 41 / 73 without it;
+// the draft step of D = 4096, 40 rows 383, 375).  It pays all the same where rows are 4 KB apart, and every workgroup on
+// the same k block keeps one memory channel busy: D = 2048, V = 151936, 40 / 64 / 80 rows 114 / 115 / 124 us, 133 / 141 / 138
+// without it; the draft step of 40 rows 188, 185 to 205.  (Half of an 8 KB row is where the same channel comes round
+// again: at D = 4096 one level changes nothing.  Rows of 2 KB and less spread over the channels by themselves: D = 1024, 40 /
+// 56 / 80 rows, V = 65536 40 / 40 / 43, 30 / 29 / 31 without it, V = 151936 63 / 63 / 69, 57 / 55 / 59.)
+struct WideShape { int rg, rt, cs, split, lv; };
+WideShape wide_shape(const GemmArgs& g) {
+  const int tiles = (g.M + 15) / 16;
+  const bool aligned = g.K == 2048;
+  if (g.planes == 2) return {tiles, 2, tiles == 1 ? 4 : tiles <= 3 ? 2 : 1, 0, tiles == 1 ? 2 : aligned && tiles <= 3 && g.top_b <= 1 ? 1 : 0};
+  if (tiles <= 2) return {tiles, 1, tiles == 1 ? 4 : 2, 0, 2};
+  if (aligned && tiles <= 6) return {(tiles + 1) / 2, 2, 2, 0, 1};
+  if (tiles == 4) return {2, 2, 2, 0, 0};
+  return {(tiles + 1) / 2, 2, 1, tiles & 1, 0};
 }
 
-template <int RG, int RT, int CS, int PL, int TB, bool SPLIT>
+template <int RG, int RT, int CS, int PL, int TB, bool SPLIT, int LV>
 hipError_t launch_wide_as(const GemmArgs& g, hipStream_t s) {
   constexpr int TG = kWideTiles, S = kWideStages;
-  // levels of the chunk tree: as many as the registers hold beside the accumulators of a pass (4, 8, 16 or 32
-  // 16 x 16 tiles per wave)
-  constexpr int kAcc = RT * (TG / CS) * 2;
-  constexpr int LV = kAcc <= 8 ? 2 : kAcc <= 16 && TB == 1 ? 1 : 0;
   // set once per process; a function-local static is initialised under the language's own lock
   static const hipError_t attr = hipFuncSetAttribute(reinterpret_cast<const void*>(&k_head_wide<RG, RT, CS, PL, TB, TG, S, SPLIT, LV>),
                                                      hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
@@ -605,18 +611,20 @@ hipError_t launch_wide_as(const GemmArgs& g, hipStream_t s) {
   return hipGetLastError();
 }
 
-// two planes (the draft's widened head): argmax or ranked candidates
-template <int RG, int CS>
+// two planes (the draft's widened head): argmax or ranked candidates (those without the one-level tree)
+template <int RG, int CS, int LV>
 hipError_t launch_wide2(const GemmArgs& g, hipStream_t s) {
-  return g.top_b > 1 ? launch_wide_as<RG, 2, CS, 2, SPECEXIT_MAX_TOP_B, false>(g, s) : launch_wide_as<RG, 2, CS, 2, 1, false>(g, s);
+  if (g.top_b > 1) return launch_wide_as<RG, 2, CS, 2, SPECEXIT_MAX_TOP_B, false, LV == 2 ? 2 : 0>(g, s);
+  return launch_wide_as<RG, 2, CS, 2, 1, false, LV>(g, s);
 }
 
-// one plane: an odd number of row tiles above two has its last one shared by two waves
+// one plane, pairs of row tiles
 template <int RG>
 hipError_t launch_wide1(const GemmArgs& g, const WideShape& sh, hipStream_t s) {
   if constexpr (RG <= 3)
-    if (sh.cs == 2) return launch_wide_as<RG, 2, 2, 1, 1, false>(g, s);
-  return sh.split ? launch_wide_as<RG, 2, 1, 1, 1, true>(g, s) : launch_wide_as<RG, 2, 1, 1, 1, false>(g, s);
+    if (sh.lv == 1) return launch_wide_as<RG, 2, 2, 1, 1, false, 1>(g, s);
+  if (sh.split) return launch_wide_as<RG, 2, 1, 1, 1, true, 0>(g, s);
+  return launch_wide_as<RG, 2, RG == 2 ? 2 : 1, 1, 1, false, 0>(g, s);
 }
 
 }  // namespace
@@ -633,7 +641,7 @@ bool head_wide_supported(const GemmArgs& g) {
 void head_wide_plan(GemmArgs& g, int num_cus) {
   if (!head_wide_supported(g)) return;
   const int ntiles = gemm_ntiles(g.N);
-  const WideShape sh = wide_shape(g.M, g.planes, g.K);
+  const WideShape sh = wide_shape(g);
   g.wide_w = std::min(num_cus, (ntiles + kWideTiles - 1) / kWideTiles);
   g.wide_slots = sh.split ? 2 : sh.cs;
 }
@@ -643,14 +651,14 @@ int head_wide_groups(const GemmArgs& g) { return g.wide_w * g.wide_slots; }
 // bytes of the packed activations: the row tiles the consumer waves cover x K (none: read in place)
 size_t head_wide_pack_bytes(const GemmArgs& g) {
   if (g.wide_w < 1) return 0;
-  const WideShape sh = wide_shape(g.M, g.planes, g.K);
+  const WideShape sh = wide_shape(g);
   if (g.planes == 1 && sh.rt == 1) return 0;
   return static_cast<size_t>(sh.rg) * sh.rt * 16 * g.K * 2;
 }
 
 hipError_t launch_head_wide(const GemmArgs& ga, hipStream_t s) {
   if (!head_wide_supported(ga) || ga.wide_w < 1) return hipErrorInvalidValue;
-  const WideShape sh = wide_shape(ga.M, ga.planes, ga.K);
+  const WideShape sh = wide_shape(ga);
   GemmArgs g = ga;
   const int KB = g.K >> 7;
   if (g.planes == 2) {
@@ -659,17 +667,17 @@ hipError_t launch_head_wide(const GemmArgs& ga, hipStream_t s) {
       hipLaunchKernelGGL(k_pack_norm, dim3((KB * sh.rg + 3) / 4), dim3(256), 0, s, static_cast<const float*>(g.a_src), g.a_ssq, g.a_nssq,
                          static_cast<const bf16_t*>(g.a_gain), g.a_eps, static_cast<uint4*>(g.a_packed), g.M, g.K, sh.rg);
     switch (sh.rg) {
-      case 1: return launch_wide2<1, 4>(g, s);     //  1 .. 16 rows
-      case 2: return launch_wide2<2, 2>(g, s);     // 17 .. 32
-      case 3: return launch_wide2<3, 2>(g, s);     // 33 .. 48
-      case 4: return launch_wide2<4, 1>(g, s);     // 49 .. 64
+      case 1: return launch_wide2<1, 4, 2>(g, s);                                              //  1 .. 16 rows
+      case 2: return sh.lv ? launch_wide2<2, 2, 1>(g, s) : launch_wide2<2, 2, 0>(g, s);        // 17 .. 32
+      case 3: return sh.lv ? launch_wide2<3, 2, 1>(g, s) : launch_wide2<3, 2, 0>(g, s);        // 33 .. 48
+      case 4: return launch_wide2<4, 1, 0>(g, s);                                              // 49 .. 64
       default: return hipErrorInvalidValue;
     }
   }
   if (g.a_mode != 1) return hipErrorInvalidValue;
   if (sh.rt == 1) {
     g.a_packed = nullptr;
-    return sh.rg == 1 ? launch_wide_as<1, 1, 4, 1, 1, false>(g, s) : launch_wide_as<2, 1, 2, 1, 1, false>(g, s);
+    return sh.rg == 1 ? launch_wide_as<1, 1, 4, 1, 1, false, 2>(g, s) : launch_wide_as<2, 1, 2, 1, 1, false, 2>(g, s);
   }
   if (!g.a_packed) return hipErrorInvalidValue;
   const int units = KB * sh.rg * sh.rt;

@@ -74,9 +74,10 @@ def test_small_bf16_mfma(B, paged):
     one_step(shape, w, kv, tok, g, pos, label="small mfma")
 
 
-@pytest.mark.parametrize("B", [17, 32, 33, 49, 64])
-def test_row_tile_edges(B):
-    shape = gen.scaled(gen.config(2), D=512, Hq=4, Hkv=2, d=128, I=768, V=3001, B=B, ctx=(0, 60), k=2)
+@pytest.mark.parametrize("B,D", [(17, 512), (32, 512), (33, 512), (49, 512), (64, 512), (20, 2048), (40, 2048)])
+def test_row_tile_edges(B, D):
+    # (weight rows 4 KB apart, D = 2048: the head sums K in two chunks)
+    shape = gen.scaled(gen.config(2), D=D, Hq=4, Hkv=2, d=128, I=768, V=3001, B=B, ctx=(0, 60), k=2)
     w, kv, tok, g, pos = setup(shape, B, std=0.05)
     w = force_draft_gap(shape, w, kv, tok, g, pos)
     one_step(shape, w, kv, tok, g, pos, label="row tile edges")

@@ -83,7 +83,7 @@ def test_tie_takes_lowest_index_across_tiles(M, V, rows):
 
 
 @pytest.mark.parametrize("M,D,V", [(1, 2048, 4500), (16, 512, 4500), (17, 2048, 300), (32, 640, 20000), (33, 2048, 4500), (48, 256, 4500), (49, 512, 70),
-                                   (48, 384, 2100), (80, 1024, 4500), (96, 2048, 300), (81, 640, 4000)])
+                                   (48, 384, 2100), (80, 1024, 4500), (96, 2048, 300), (81, 640, 4000), (64, 2048, 2100), (64, 640, 2100)])
 def test_bf16_row_tile_edges_and_k_chunks(M, D, V):
     # the wave splits change at 16, 32, 48 rows; K in four chunks (4, 5 and 16 blocks) and in one (2); one workgroup, a few, many
     err = run_case(gen.scaled(gen.config(1), V=V, D=D), M, 2, M + D, "row tile edges")

@@ -16,6 +16,7 @@ LIB = os.path.join(ROOT, "paper_2509_24248_amd", "libspecexit.so")
 # beside the kernel.
 SPILLS = {
     "k_attn_ring<128, 3, 1, 2, true>": 16,     # paged caches, 33..48 query rows per KV head
+    # the one-level chunk tree of the heads, for weight rows 4 KB apart
     "k_head_wide<2, 2, 2, 2, 1, 8, 4, false, 1>": 28,
     "k_head_wide<3, 2, 2, 2, 1, 8, 4, false, 1>": 24,
     "k_head_wide<2, 2, 2, 1, 1, 8, 4, false, 1>": 52,
@@ -71,6 +72,15 @@ def readable(mangled):
     names = [{"t": "unsigned short", "f": "float"}.get(a) or (a[2:-1] if a[1] == "i" else ("true" if a[2] == "1" else "false"))
              for a in re.findall(r"L[ib]\d+E|[tf]", args.group(1))]
     return f"{mangled[m.end():end]}<{', '.join(names)}>"
+
+
+@pytest.mark.skipif(not os.path.exists(LIB), reason="libspecexit.so not built")
+def test_heads_of_other_depths_have_a_form_that_does_not_spill():
+    # the same wave splits without the tree (last argument 0) exist beside the ones listed above
+    names = {readable(k[".name"]) for elf in code_objects(LIB) for k in kernels(elf)}
+    for n in SPILLS:
+        if n.startswith("k_head_wide<") and not n.startswith("k_head_wide<3, 2, 2, 1,"):      # (there the other form shares a tile)
+            assert n.replace("false, 1>", "false, 0>") in names
 
 
 @pytest.mark.skipif(not os.path.exists(LIB), reason="libspecexit.so not built")
