@@ -238,7 +238,7 @@ int32_t make_draft_plan(DraftPlan& p, const specexit_model_desc* d, const specex
   p.Kmax = 2 * D > Hd ? 2 * D : Hd;
   if (I > p.Kmax) p.Kmax = I;
   const int Hkd = dm.Hkv * dm.d, Nq = Hd + 2 * Hkd;
-  p.mfma = dm.dtype == SPECEXIT_BF16 && proj_supported(B, D, 2 * D) && D % 128 == 0 && proj_supported(B, Nq, D) && proj_supported(B, D, Hd) &&
+  p.mfma = dm.dtype == SPECEXIT_BF16 && proj_supported(B, D, 2 * D) && proj_supported(B, Nq, D) && proj_supported(B, D, Hd) &&
            proj_supported(B, 2 * I, D) && proj_supported(B, D, I);
   if (p.mfma) {
     plan_proj(p.pfc, D, 2 * D, B, 1);
@@ -443,10 +443,9 @@ int32_t run_draft(DraftPlan& p, const specexit_draft_weights* w, const specexit_
   } else {
     if ((rc = check_hip(launch_embed_concat(dm, B, w->embed, io.tok, io.hidden_in, b.act, s, status), "embed_concat"))) return rc;
     if ((rc = run_gemm(p.fc, bf16, w->w_fc, nullptr, nullptr, b, s, "gemm fc"))) return rc;
-    if ((rc = check_hip(launch_reduce_norm(dm, B, dm.D, b.partial, 1, 1, nullptr, w->ln_attn,
-                                           b.x_buf, nullptr, b.act, s), "norm attn"))) return rc;
+    if ((rc = check_hip(launch_row_norm(dm, B, dm.D, b.partial, nullptr, w->ln_attn, b.x_buf, nullptr, b.act, s), "norm attn"))) return rc;
     if ((rc = run_gemm(p.qkv, bf16, w->w_q, w->w_k, w->w_v, b, s, "gemm qkv"))) return rc;
-    if ((rc = check_hip(launch_rope_kvwrite(dm, B, p.W, b.partial, 1, 1, io.pos, io.level, io.node,
+    if ((rc = check_hip(launch_rope_kvwrite(dm, B, p.W, b.partial, io.pos, io.level, io.node,
                                             b.q_buf, p.attn.paged, draft_kv->k, draft_kv->v, draft_kv->page_table,
                                             p.attn.page_size, p.attn.max_pages, p.attn.l_max, s, p.attn.n_pages, status), "rope"))) return rc;
   }
@@ -504,13 +503,11 @@ int32_t run_draft(DraftPlan& p, const specexit_draft_weights* w, const specexit_
       bo.act = static_cast<float*>(b.attn_out);     // fp32 rows as they are
     }
     if ((rc = run_gemm(p.o, bf16, w->w_o, nullptr, nullptr, bo, s, "gemm o"))) return rc;
-    if ((rc = check_hip(launch_reduce_norm(dm, B, dm.D, b.partial, 1, 1, b.x_buf, w->ln_mlp,
-                                           b.a_buf, nullptr, b.act, s), "norm mlp"))) return rc;
+    if ((rc = check_hip(launch_row_norm(dm, B, dm.D, b.partial, b.x_buf, w->ln_mlp, b.a_buf, nullptr, b.act, s), "norm mlp"))) return rc;
     if ((rc = run_gemm(p.gu, bf16, w->w_gate, w->w_up, nullptr, b, s, "gemm gate/up"))) return rc;
-    if ((rc = check_hip(launch_silu_mul(dm, B, b.partial, 1, 1, b.act, s), "silu"))) return rc;
+    if ((rc = check_hip(launch_silu_mul(dm, B, b.partial, b.act, s), "silu"))) return rc;
     if ((rc = run_gemm(p.down, bf16, w->w_down, nullptr, nullptr, b, s, "gemm down"))) return rc;
-    if ((rc = check_hip(launch_reduce_norm(dm, B, dm.D, b.partial, 1, 1, b.a_buf, w->ln_final,
-                                           nullptr, io.hidden_out, b.act, s), "norm final"))) return rc;
+    if ((rc = check_hip(launch_row_norm(dm, B, dm.D, b.partial, b.a_buf, w->ln_final, nullptr, io.hidden_out, b.act, s), "norm final"))) return rc;
   }
   g_prof_hook(SPECEXIT_PROF_DRAFT_PROJ_OUT, 1, s);
   // widened head (Eq. 1): argmax (or the top_b best) over the vocabulary rows, three signal rows on the side

@@ -21,6 +21,7 @@
 #include "attn_sched.hpp"
 #include "common.hpp"
 #include "kernels.hpp"
+#include "stream.hpp"
 
 namespace sx {
 
@@ -58,8 +59,6 @@ constexpr int tiles_per_wave(int hd, int tiles) { return hd == 128 && tiles >= k
 constexpr int kMaxChunkPages = 2048;   // page ids of one chunk kept in LDS (8 KB)
 
 typedef short s16x4_t __attribute__((ext_vector_type(4)));
-typedef __attribute__((address_space(3))) void* lds_ptr_t;
-typedef const __attribute__((address_space(1))) void* glb_ptr_t;
 
 // XOR swizzle of the 16-byte chunks of a tile row.  K rows are read one row per lane (16 rows
 // at once): chunk ^ (key % 16) spreads them over all banks.  V rows are read by the transpose
@@ -68,31 +67,6 @@ typedef const __attribute__((address_space(1))) void* glb_ptr_t;
 // one half of them, the other bits of the key spread the chunks of that half.
 template <int HD> __device__ __forceinline__ int swz_k(int key) { return HD == 128 ? key & 15 : (key >> 1) & 7; }
 template <int HD> __device__ __forceinline__ int swz_v(int key) { return HD == 128 ? (key & 7) << 1 : ((key >> 1) & 3) << 1; }
-
-// s_waitcnt immediate that waits for vmcnt <= n only (gfx9 encoding: vmcnt in bits 3:0 and
-// 15:14, expcnt 6:4 and lgkmcnt 11:8 left at their maxima)
-constexpr int vmcnt_imm(int n) { return 0x0F70 | (n & 15) | (((n >> 4) & 3) << 14); }
-
-// Direct global -> LDS load, 16 bytes per lane: lane l's bytes land at lds_base + 16 l
-// (lds_base wave-uniform).  Written as an instruction rather than through the builtin so that
-// the compiler does not put a full vector-memory wait in front of every later LDS read; the
-// kernel paces these loads itself with s_waitcnt vmcnt and a barrier.  "nt" marks the stream
-// as read-once.  m0 is written here and used by nothing else in these kernels.
-// Same with a wave-uniform 64-bit base and a 32-bit per-lane byte offset.
-__device__ __forceinline__ void load_to_lds16(const void* base, uint32_t off, const void* lds_base) {
-  const uint32_t l = static_cast<uint32_t>(reinterpret_cast<uintptr_t>((lds_ptr_t)lds_base));
-  const uint64_t b64 = reinterpret_cast<uint64_t>(base);   // uniform by construction: pin it to scalar registers
-  // (readfirstlane returns a signed int: go through uint32_t so the low half is not sign-extended)
-  const uint32_t lo = static_cast<uint32_t>(__builtin_amdgcn_readfirstlane(static_cast<int>(static_cast<uint32_t>(b64))));
-  const uint32_t hi = static_cast<uint32_t>(__builtin_amdgcn_readfirstlane(static_cast<int>(static_cast<uint32_t>(b64 >> 32))));
-  const uint64_t sb = static_cast<uint64_t>(lo) | (static_cast<uint64_t>(hi) << 32);
-  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2 nt" ::"s"(l), "v"(off), "s"(sb) : "memory");
-}
-
-__device__ __forceinline__ void load_to_lds16(const void* src, const void* lds_base) {
-  const uint32_t l = static_cast<uint32_t>(reinterpret_cast<uintptr_t>((lds_ptr_t)lds_base));
-  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off nt" ::"s"(l), "v"(src) : "memory");
-}
 
 constexpr int front_bytes(int hd, int rp, int stages) {
   return kNK * stages * slot_bytes(hd) > rp * o_row(hd) * 4 ? kNK * stages * slot_bytes(hd) : rp * o_row(hd) * 4;

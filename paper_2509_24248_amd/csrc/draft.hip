@@ -1,30 +1,11 @@
-// Row-wise glue of the draft step (Sec. 3.1; Alg. 1 first loop line): everything between
-// the weight-streaming GEMMs.  Each kernel reduces the split-K partial sums of the GEMM
-// before it, applies the layer's elementwise math in fp32 and emits the next GEMM's
-// activations as fp32 rows (the MFMA GEMM splits them into bf16 hi + lo parts itself).
+// Row-wise glue of the draft step (Sec. 3.1; Alg. 1 first loop line) around the plain-ALU GEMMs: each kernel takes
+// the fp32 rows of the GEMM before it, applies the layer's elementwise math and leaves the next GEMM's fp32 rows.
 #include "common.hpp"
 #include "kernels.hpp"
 
 namespace sx {
 
 namespace {
-
-// sum over split-K ranges and planes of 8 consecutive outputs of row b
-__device__ __forceinline__ void gather_partial(const float* partial, int nslices, int planes, int B,
-                                               int N, int b, int n, float (&f)[8]) {
-  const int Mv = B * planes;
-#pragma unroll
-  for (int e = 0; e < 8; ++e) f[e] = 0.f;
-  for (int ks = 0; ks < nslices; ++ks) {
-    for (int p = 0; p < planes; ++p) {
-      const float4* src = reinterpret_cast<const float4*>(
-          partial + (static_cast<size_t>(ks) * Mv + b * planes + p) * N + n);
-      const float4 a = src[0], c = src[1];
-      f[0] += a.x; f[1] += a.y; f[2] += a.z; f[3] += a.w;
-      f[4] += c.x; f[5] += c.y; f[6] += c.z; f[7] += c.w;
-    }
-  }
-}
 
 template <typename T>
 __global__ __launch_bounds__(256) void k_embed_concat(int D, int V, int* status, const T* __restrict__ embed,
@@ -49,16 +30,13 @@ constexpr int kNormThreads = 1024;
 constexpr int kNormIters = 2;   // float4 per thread per iteration: rows up to 2 * 1024 * 4 = 8192 wide
 
 template <typename T>
-__global__ __launch_bounds__(kNormThreads) void k_reduce_norm(int B, int N, const float* __restrict__ partial,
-                                                              int nslices, int planes,
+__global__ __launch_bounds__(kNormThreads) void k_row_norm(int N, const float* __restrict__ rows,
                                                               const float* __restrict__ residual,
                                                               const T* __restrict__ gain, float eps,
                                                               float* __restrict__ sum_out, T* __restrict__ hidden_out,
                                                               float* __restrict__ act) {
   __shared__ float sh[kNormThreads / 64];
   const int b = blockIdx.x;
-  const int Mv = B * planes;
-  const int total = nslices * planes;   // partial rows to add: slice j -> row (j / planes) * Mv + b * planes + j % planes
   float4 vals[kNormIters];
   float ssq = 0.f;
 #pragma unroll
@@ -66,23 +44,10 @@ __global__ __launch_bounds__(kNormThreads) void k_reduce_norm(int B, int N, cons
     const int n = (threadIdx.x + it * kNormThreads) * 4;
     float4 acc = make_float4(0.f, 0.f, 0.f, 0.f);
     if (n < N) {
-      if (residual) acc = *reinterpret_cast<const float4*>(residual + static_cast<size_t>(b) * N + n);
-      int j = 0;
-      for (; j + 4 <= total; j += 4) {
-        float4 v[4];
-#pragma unroll
-        for (int u = 0; u < 4; ++u) {
-          const int jj = j + u;
-          const size_t row = static_cast<size_t>(jj / planes) * Mv + b * planes + jj % planes;
-          v[u] = *reinterpret_cast<const float4*>(partial + row * N + n);
-        }
-#pragma unroll
-        for (int u = 0; u < 4; ++u) { acc.x += v[u].x; acc.y += v[u].y; acc.z += v[u].z; acc.w += v[u].w; }
-      }
-      for (; j < total; ++j) {
-        const size_t row = static_cast<size_t>(j / planes) * Mv + b * planes + j % planes;
-        const float4 v = *reinterpret_cast<const float4*>(partial + row * N + n);
-        acc.x += v.x; acc.y += v.y; acc.z += v.z; acc.w += v.w;
+      acc = *reinterpret_cast<const float4*>(rows + static_cast<size_t>(b) * N + n);
+      if (residual) {
+        const float4 r = *reinterpret_cast<const float4*>(residual + static_cast<size_t>(b) * N + n);
+        acc.x += r.x; acc.y += r.y; acc.z += r.z; acc.w += r.w;
       }
       ssq += acc.x * acc.x + acc.y * acc.y + acc.z * acc.z + acc.w * acc.w;
       if (sum_out) *reinterpret_cast<float4*>(sum_out + static_cast<size_t>(b) * N + n) = acc;
@@ -119,24 +84,17 @@ __global__ __launch_bounds__(kNormThreads) void k_reduce_norm(int B, int N, cons
 // its K/V go to cache entry pos[r / W] + node[r % W] (chain step: W = 1, level 0, node null
 // = entry pos itself; tree level: position = context + depth, entry = context + node id).
 template <typename T>
-__global__ void k_rope_kvwrite(int M, int W, int Hq, int Hkv, int d, const float* __restrict__ partial,
-                               int nslices, int planes, const int32_t* __restrict__ pos, int level,
-                               const int32_t* __restrict__ node, float theta,
+__global__ void k_rope_kvwrite(int W, int Hq, int Hkv, int d, const float* __restrict__ rows,
+                               const int32_t* __restrict__ pos, int level, const int32_t* __restrict__ node, float theta,
                                T* __restrict__ q_out, int paged, T* __restrict__ kc, T* __restrict__ vc,
                                const int32_t* __restrict__ page_table, int page_size, int max_pages,
                                int64_t l_max, int64_t n_pages, int* status) {
   const int r = blockIdx.x, hh = blockIdx.y, c = threadIdx.x;  // c in [0, d/2)
   const int b = r / W;
   const int N = (Hq + 2 * Hkv) * d;
-  const int Mv = M * planes;
   const int half = d >> 1;
-  float x1 = 0.f, x2 = 0.f;
-  for (int ks = 0; ks < nslices; ++ks)
-    for (int p = 0; p < planes; ++p) {
-      const float* src = partial + (static_cast<size_t>(ks) * Mv + r * planes + p) * N + hh * d;
-      x1 += src[c];
-      x2 += src[c + half];
-    }
+  const float* src = rows + static_cast<size_t>(r) * N + hh * d;
+  float x1 = src[c], x2 = src[c + half];
   const int ps = pos[b] + level;
   const int slot = pos[b] + (node ? node[r % W] : 0);
   if (hh < Hq + Hkv) {
@@ -172,17 +130,13 @@ __global__ void k_rope_kvwrite(int M, int W, int Hq, int Hkv, int d, const float
   Elem<T>::store(dst + c + half, x2);
 }
 
-__global__ __launch_bounds__(256) void k_silu_mul(int B, int I, const float* __restrict__ partial,
-                                                  int nslices, int planes, float* __restrict__ act) {
+__global__ __launch_bounds__(256) void k_silu_mul(int I, const float* __restrict__ rows, float* __restrict__ act) {
   const int b = blockIdx.x;
-  for (int g8 = blockIdx.y * 256 + threadIdx.x; g8 < I / 8; g8 += 256 * gridDim.y) {
-    float gt[8], up[8], f[8];
-    gather_partial(partial, nslices, planes, B, 2 * I, b, g8 * 8, gt);
-    gather_partial(partial, nslices, planes, B, 2 * I, b, I + g8 * 8, up);
-#pragma unroll
-    for (int e = 0; e < 8; ++e) f[e] = gt[e] * sigmoidf_(gt[e]) * up[e];
-#pragma unroll
-    for (int e = 0; e < 8; ++e) act[static_cast<size_t>(b) * I + g8 * 8 + e] = f[e];
+  for (int k = (blockIdx.y * 256 + threadIdx.x) * 4; k < I; k += 1024 * gridDim.y) {
+    const float4 gt = *reinterpret_cast<const float4*>(rows + static_cast<size_t>(b) * 2 * I + k);
+    const float4 up = *reinterpret_cast<const float4*>(rows + static_cast<size_t>(b) * 2 * I + I + k);
+    *reinterpret_cast<float4*>(act + static_cast<size_t>(b) * I + k) =
+        make_float4(gt.x * sigmoidf_(gt.x) * up.x, gt.y * sigmoidf_(gt.y) * up.y, gt.z * sigmoidf_(gt.z) * up.z, gt.w * sigmoidf_(gt.w) * up.w);
   }
 }
 
@@ -199,38 +153,35 @@ hipError_t launch_embed_concat(const DraftDims& dm, int B, const void* embed, co
   return hipGetLastError();
 }
 
-hipError_t launch_reduce_norm(const DraftDims& dm, int B, int N, const float* partial, int nslices,
-                              int planes, const float* residual, const void* gain, float* sum_out,
-                              void* hidden_out, float* act, hipStream_t s) {
+hipError_t launch_row_norm(const DraftDims& dm, int B, int N, const float* rows, const float* residual, const void* gain, float* sum_out,
+                           void* hidden_out, float* act, hipStream_t s) {
   if (dm.dtype == 1)
-    hipLaunchKernelGGL(k_reduce_norm<bf16_t>, dim3(B), dim3(kNormThreads), 0, s, B, N, partial, nslices, planes, residual,
+    hipLaunchKernelGGL(k_row_norm<bf16_t>, dim3(B), dim3(kNormThreads), 0, s, N, rows, residual,
                        static_cast<const bf16_t*>(gain), dm.rms_eps, sum_out, static_cast<bf16_t*>(hidden_out), act);
   else
-    hipLaunchKernelGGL(k_reduce_norm<float>, dim3(B), dim3(kNormThreads), 0, s, B, N, partial, nslices, planes, residual,
+    hipLaunchKernelGGL(k_row_norm<float>, dim3(B), dim3(kNormThreads), 0, s, N, rows, residual,
                        static_cast<const float*>(gain), dm.rms_eps, sum_out, static_cast<float*>(hidden_out), act);
   return hipGetLastError();
 }
 
-hipError_t launch_rope_kvwrite(const DraftDims& dm, int M, int W, const float* partial, int nslices,
-                               int planes, const int32_t* pos, int level, const int32_t* node, void* q_out,
-                               int kv_paged, void* kc, void* vc, const int32_t* page_table, int page_size,
-                               int max_pages, int64_t l_max, hipStream_t s, int64_t n_pages, int* status) {
+hipError_t launch_rope_kvwrite(const DraftDims& dm, int M, int W, const float* rows, const int32_t* pos, int level,
+                               const int32_t* node, void* q_out, int kv_paged, void* kc, void* vc, const int32_t* page_table,
+                               int page_size, int max_pages, int64_t l_max, hipStream_t s, int64_t n_pages, int* status) {
   const dim3 grid(M, dm.Hq + 2 * dm.Hkv), block(dm.d / 2);
   if (dm.dtype == 1)
-    hipLaunchKernelGGL(k_rope_kvwrite<bf16_t>, grid, block, 0, s, M, W, dm.Hq, dm.Hkv, dm.d, partial, nslices, planes,
+    hipLaunchKernelGGL(k_rope_kvwrite<bf16_t>, grid, block, 0, s, W, dm.Hq, dm.Hkv, dm.d, rows,
                        pos, level, node, dm.rope_theta, static_cast<bf16_t*>(q_out), kv_paged,
                        static_cast<bf16_t*>(kc), static_cast<bf16_t*>(vc), page_table, page_size, max_pages, l_max, n_pages, status);
   else
-    hipLaunchKernelGGL(k_rope_kvwrite<float>, grid, block, 0, s, M, W, dm.Hq, dm.Hkv, dm.d, partial, nslices, planes,
+    hipLaunchKernelGGL(k_rope_kvwrite<float>, grid, block, 0, s, W, dm.Hq, dm.Hkv, dm.d, rows,
                        pos, level, node, dm.rope_theta, static_cast<float*>(q_out), kv_paged,
                        static_cast<float*>(kc), static_cast<float*>(vc), page_table, page_size, max_pages, l_max, n_pages, status);
   return hipGetLastError();
 }
 
-hipError_t launch_silu_mul(const DraftDims& dm, int B, const float* partial, int nslices, int planes,
-                           float* act, hipStream_t s) {
-  const int gy = (dm.I / 8 + 255) / 256;
-  hipLaunchKernelGGL(k_silu_mul, dim3(B, gy), dim3(256), 0, s, B, dm.I, partial, nslices, planes, act);
+hipError_t launch_silu_mul(const DraftDims& dm, int B, const float* rows, float* act, hipStream_t s) {
+  const int gy = (dm.I / 4 + 255) / 256;
+  hipLaunchKernelGGL(k_silu_mul, dim3(B, gy), dim3(256), 0, s, dm.I, rows, act);
   return hipGetLastError();
 }
 

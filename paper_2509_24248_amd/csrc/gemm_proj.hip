@@ -100,7 +100,7 @@ __global__ __launch_bounds__(64 * (RG * KS + kProducers)) void k_proj(const Proj
         have = cur.g;
 #pragma unroll
         for (int t = 0; t < kTG; ++t) {
-          const int n0 = min((cur.g * kTG + t) * 16, g.N - 16);           // (N is a multiple of 16: tiles past the end repeat the last one)
+          const int n0 = (cur.g * kTG + t) * 16;
           // weight block of the tile (block ends are multiples of 16); sums of conditional distances, because a choice
           // between pointers makes the compiler keep them in scratch memory
           const int64_t dist = (n0 >= end0 ? d1 : 0) + (n0 >= end1 ? d2 : 0);
@@ -149,24 +149,23 @@ __global__ __launch_bounds__(64 * (RG * KS + kProducers)) void k_proj(const Proj
   // -------------------------------------------------------------------- consumer
   const int rt0 = (wv / KS) * RT, ks = wv % KS;
   const int fr = lane & 15, fq = lane >> 4;
-  // operand pieces of row tile t at k block kb, k step s: packed [k block][row tile][k step][lane], or in place
-  // from bf16 rows [K] (with a_embed: k blocks of the first half of K from the row's embedding; rows from M on
+  // operand pieces of row tile t at k block kb, k step s: two planes packed [k block][row tile][k step][lane], one in
+  // place from bf16 rows [K] (with a_embed: k blocks of the first half of K from the row's embedding; rows from M on
   // repeat the last one, dropped later)
   const char* p0[RT];
   int64_t to_second[RT];          // from there to the row of the second half of K, less the first half's blocks
-  const int s_stride = g.a_packed ? 1024 : 64;
-  const size_t kb_stride = g.a_packed ? static_cast<size_t>(RG * RT) * 4096 : 256;
-  const int kb_half = g.a_embed ? KB >> 1 : KB;
+  constexpr int s_stride = PL == 2 ? 1024 : 64;
+  constexpr size_t kb_stride = PL == 2 ? static_cast<size_t>(RG * RT) * 4096 : 256;
+  const int kb_half = PL == 1 && g.a_embed ? KB >> 1 : KB;
 #pragma unroll
   for (int t = 0; t < RT; ++t) {
-    if (g.a_packed) {
+    to_second[t] = 0;
+    if constexpr (PL == 2) {
       p0[t] = static_cast<const char*>(g.a_packed) + (static_cast<size_t>(rt0 + t) * 256 + lane) * 16;
-      to_second[t] = 0;
     } else {
       const int m = min(16 * (rt0 + t) + fr, g.M - 1);
       const size_t width = g.a_embed ? g.K : 2 * g.K;             // bytes of a row of a_src
       p0[t] = static_cast<const char*>(g.a_src) + m * width + fq * 16;
-      to_second[t] = 0;
       if (g.a_embed) {
         const char* e = static_cast<const char*>(g.a_embed) + checked_token(g.a_tok[m], g.a_vocab, g.status) * width + fq * 16;
         to_second[t] = reinterpret_cast<int64_t>(p0[t]) - reinterpret_cast<int64_t>(e) - static_cast<int64_t>(width);
@@ -176,7 +175,7 @@ __global__ __launch_bounds__(64 * (RG * KS + kProducers)) void k_proj(const Proj
   }
   uint4 b[RT][SPW], bn[RT][SPW];
   auto fetch = [&](uint4 (&dst)[RT][SPW], int kb) {
-    const bool second = kb >= kb_half;                            // uniform
+    const bool second = PL == 1 && kb >= kb_half;                 // uniform
     const size_t off = static_cast<size_t>(kb) * kb_stride;
 #pragma unroll
     for (int t = 0; t < RT; ++t) {
@@ -508,7 +507,7 @@ ProjSum sum_of(const ProjArgs& g) {
 
 }  // namespace
 
-bool proj_supported(int M, int N, int K) { return M >= 1 && M <= 64 && N % 16 == 0 && N >= 16 && K % 128 == 0 && K >= 128; }
+bool proj_supported(int M, int N, int K) { return M >= 1 && M <= 64 && N % 128 == 0 && N >= 128 && K % 128 == 0 && K >= 128; }
 
 // One workgroup per compute unit, each with at least two blocks while there are that many.
 void proj_plan(ProjArgs& g, int num_cus) {
@@ -521,8 +520,8 @@ size_t proj_partial_bytes(const ProjArgs& g) { return static_cast<size_t>(g.W + 
 hipError_t launch_proj(const ProjArgs& g, hipStream_t s) {
   if (!proj_supported(g.M, g.N, g.K) || g.W < 1) return hipErrorInvalidValue;
   const int tiles = (g.M + 15) / 16;
+  if (g.planes == 2 ? !g.a_packed : !g.a_src) return hipErrorInvalidValue;
   if (g.planes == 2) {
-    if (!g.a_packed) return hipErrorInvalidValue;
     switch (tiles) {
       case 1: return launch_as<1, 2, 4, 2>(g, s);
       case 2: return launch_as<2, 2, 2, 2>(g, s);
@@ -539,7 +538,7 @@ hipError_t launch_proj(const ProjArgs& g, hipStream_t s) {
 
 hipError_t launch_proj_norm(const ProjArgs& g, const float* residual, const void* gain, float eps, float* out_x, void* out_store, void* packed,
                             hipStream_t s) {
-  if (g.N > kRowThreads * kRowIters * 4 || g.N % 128) return hipErrorInvalidValue;
+  if (g.N > kRowThreads * kRowIters * 4) return hipErrorInvalidValue;
   hipLaunchKernelGGL(k_proj_norm, dim3(g.M), dim3(kRowThreads), 0, s, sum_of(g), g.N, residual, static_cast<const bf16_t*>(gain), eps, out_x,
                      static_cast<bf16_t*>(out_store), static_cast<char*>(packed), packed_tiles(g.M, 2));
   return hipGetLastError();

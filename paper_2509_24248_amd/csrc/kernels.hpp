@@ -41,8 +41,8 @@ struct ProjArgs {
   int nseg;
   int N, K, M;
   int planes;          // 1: bf16 activations, 2: bf16 value + rest
-  const void* a_packed;  // activations in operand order, or nullptr (one plane):
-  const void* a_src;     // bf16 rows [M][K]; with a_embed [embed[tok[m]] ; a_src[m]], each K/2 wide
+  const void* a_packed;  // two planes: activations in operand order
+  const void* a_src;     // one plane: bf16 rows [M][K]; with a_embed [embed[tok[m]] ; a_src[m]], each K/2 wide
   const void* a_embed;   // embedding table [V][K/2] or nullptr
   const int32_t* a_tok;  // token ids [M], forced into 0 .. a_vocab-1
   int a_vocab;
@@ -57,7 +57,7 @@ struct ProjSum {
   double inv_T;           // 1 / T
   int KB, W, M;           // k blocks of a group, workgroups, rows
 };
-__host__ __device__ inline int proj_groups(int N) { return (N + 127) / 128; }
+__host__ __device__ inline int proj_groups(int N) { return N / 128; }
 bool proj_supported(int M, int N, int K);
 void proj_plan(ProjArgs& g, int num_cus);
 size_t proj_partial_bytes(const ProjArgs& g);
@@ -216,19 +216,16 @@ struct DraftDims {
 };
 hipError_t launch_embed_concat(const DraftDims& dm, int B, const void* embed, const int32_t* tok,
                                const void* hidden_in, float* act, hipStream_t s, int* status = nullptr);
-// v[b][:] = residual[b][:] + sum of partial slices; optional copy to `sum_out` (fp32) and
+// v[b][:] = rows[b][:] (+ residual[b][:]); optional copy to `sum_out` (fp32) and
 // `hidden_out` (storage type); then RMSNorm with gain -> act (fp32)
-hipError_t launch_reduce_norm(const DraftDims& dm, int B, int N, const float* partial, int nslices,
-                              int planes, const float* residual, const void* gain, float* sum_out,
-                              void* hidden_out, float* act, hipStream_t s);
+hipError_t launch_row_norm(const DraftDims& dm, int B, int N, const float* rows, const float* residual, const void* gain, float* sum_out,
+                           void* hidden_out, float* act, hipStream_t s);
 // rows r = b * W + w: rotary position pos[b] + level, cache entry pos[b] + node[w] (node null: pos[b])
-hipError_t launch_rope_kvwrite(const DraftDims& dm, int M, int W, const float* partial, int nslices,
-                               int planes, const int32_t* pos, int level, const int32_t* node, void* q_out,
-                               int kv_paged, void* kc, void* vc, const int32_t* page_table, int page_size,
-                               int max_pages, int64_t l_max, hipStream_t s, int64_t n_pages = 0x7fffffff,
+hipError_t launch_rope_kvwrite(const DraftDims& dm, int M, int W, const float* rows, const int32_t* pos, int level,
+                               const int32_t* node, void* q_out, int kv_paged, void* kc, void* vc, const int32_t* page_table,
+                               int page_size, int max_pages, int64_t l_max, hipStream_t s, int64_t n_pages = 0x7fffffff,
                                int* status = nullptr);
-hipError_t launch_silu_mul(const DraftDims& dm, int B, const float* partial, int nslices, int planes,
-                           float* act, hipStream_t s);
+hipError_t launch_silu_mul(const DraftDims& dm, int B, const float* rows, float* act, hipStream_t s);
 
 // ---- measurement aid: copy of known size through the streaming load path -------------------
 hipError_t launch_copy_probe(const void* src, void* dst, size_t bytes, bool nontemporal, hipStream_t s);

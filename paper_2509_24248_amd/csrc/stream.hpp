@@ -1,4 +1,5 @@
-// Pieces shared by the kernels that stream weights through an LDS ring (gemm_wide.hip, gemm_proj.hip).
+// Pieces shared by the kernels that stream weights or cache entries through an LDS ring (gemm_wide.hip, gemm_proj.hip,
+// attn_mfma.hip).
 #pragma once
 #include "common.hpp"
 
@@ -8,12 +9,14 @@ constexpr int kProducers = 2;       // waves of a workgroup that only bring weig
 
 typedef __attribute__((address_space(3))) void* lds_ptr_t;
 
-// s_waitcnt immediate that waits for vmcnt <= n only
+// s_waitcnt immediate that waits for vmcnt <= n only (gfx9 encoding: vmcnt in bits 3:0 and 15:14, expcnt 6:4 and
+// lgkmcnt 11:8 left at their maxima)
 constexpr int vmcnt_imm(int n) { return 0x0F70 | (n & 15) | (((n >> 4) & 3) << 14); }
 
 // Direct global -> LDS load, 16 bytes per lane: lane l's bytes land at lds_base + 16 l (lds_base
-// wave-uniform).  Written as an instruction so that the kernel paces these loads itself with
-// s_waitcnt vmcnt and a barrier.  "nt": the weights are read once.
+// wave-uniform).  Written as an instruction rather than through the builtin so that the compiler does not put a full
+// vector-memory wait in front of every later LDS read; the kernels pace these loads themselves with s_waitcnt vmcnt and a
+// barrier.  "nt": the stream is read once.  m0 is written here and used by nothing else in these kernels.
 __device__ __forceinline__ void load_to_lds16(const void* src, const void* lds_base) {
   const uint32_t l = static_cast<uint32_t>(reinterpret_cast<uintptr_t>((lds_ptr_t)lds_base));
   asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off nt" ::"s"(l), "v"(src) : "memory");
