@@ -83,6 +83,15 @@ def test_row_tile_edges(B, D):
     one_step(shape, w, kv, tok, g, pos, label="row tile edges")
 
 
+@pytest.mark.parametrize("B", [5, 9, 40])
+def test_odd_number_of_narrow_kv_heads(B):
+    # the k block and the v block of the q|k|v projection then begin inside a group of 128 rows
+    shape = gen.scaled(gen.config(2), D=256, Hq=6, Hkv=3, d=64, I=384, V=1000, B=B, ctx=(0, 60), k=2)
+    w, kv, tok, g, pos = setup(shape, B, std=0.05)
+    w = force_draft_gap(shape, w, kv, tok, g, pos)
+    one_step(shape, w, kv, tok, g, pos, label="odd kv heads")
+
+
 def test_small_bf16_alu_fallback():
     shape = gen.scaled(gen.config(1), D=192, Hq=4, Hkv=2, d=64, I=320, V=1000, B=2, ctx=(5, 90), k=2)
     w, kv, tok, g, pos = setup(shape, 1, std=0.05)
@@ -164,8 +173,8 @@ def test_full_size_config_4_sixteen_rows():
 
 
 def test_prepared_workspace_flag_gives_the_same_results_call_after_call():
-    """With the workspace zero-filled once and the flag set, the call skips clearing its
-    arrival counters; every kernel must leave them at zero for the next call."""
+    """The flag promises a workspace that was zero-filled once and then kept to this call.  No kernel needs that
+    today: with and without it, call after call, the results are the same."""
     shape = gen.scaled(gen.config(2), D=512, Hq=8, Hkv=2, d=128, I=1024, V=5000, B=3, ctx=(10, 400), k=2)
     w, kv, tok, g, pos = setup(shape, 7, std=0.05)
     w = force_draft_gap(shape, w, kv, tok, g, pos)
@@ -181,8 +190,8 @@ def test_prepared_workspace_flag_gives_the_same_results_call_after_call():
 
 
 def test_reducing_epilogues_give_identical_bits_every_time():
-    """The split-K sums are finished by whichever workgroup arrives last, always in the same
-    order: forty repetitions of one step (six rows: the matrix-core path) must agree bit for bit,
+    """Partial sums over K ranges are added in their order, whichever workgroup finished first:
+    forty repetitions of one step (six rows: the matrix-core path) must agree bit for bit,
     outputs and cache entry alike."""
     shape = gen.scaled(gen.config(2), D=1024, Hq=8, Hkv=2, d=128, I=2560, V=9000, B=6, ctx=(100, 900), k=2)
     w, kv, tok, g, pos = setup(shape, 11, paged=True, std=0.05)
