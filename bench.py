@@ -307,18 +307,21 @@ def threads_used():
     return int(os.environ.get("OMP_NUM_THREADS", os.cpu_count() or 1))
 
 
-def stored_traffic(kernel_key, shape_name):
+def stored_traffic(kernel_key, shape_name, folder=os.path.join(ROOT, "profiles"), lib=None):
     """HBM bytes per launch of a kernel from the committed counter summary (FETCH_SIZE + WRITE_SIZE
-    runs of this same command, scaled by the copy probe), if present."""
-    path = os.path.join(ROOT, "profiles", f"hbm_traffic_{kernel_key}_{shape_name}.txt")
+    runs of this same command, scaled by the copy probe).  None if there is no summary, or if it was taken on
+    kernels that the built library does not hold (any more): it names their symbols."""
     try:
-        with open(path) as fh:
-            for line in fh:
-                if line.startswith("bytes_per_launch"):
-                    return int(line.split()[1])
-    except Exception:
-        pass
-    return None
+        with open(os.path.join(folder, f"hbm_traffic_{kernel_key}_{shape_name}.txt")) as fh:
+            fields = [line.split() for line in fh if line.startswith(("symbol ", "bytes_per_launch "))]
+        with open(lib or os.path.join(ROOT, "paper_2509_24248_amd", "libspecexit.so"), "rb") as fh:
+            built = fh.read()
+    except OSError:
+        return None
+    symbols = [f[1].encode() for f in fields if f[0] == "symbol"]
+    if not symbols or any(s + b"\0" not in built for s in symbols):
+        return None
+    return next((int(f[1]) for f in fields if f[0] == "bytes_per_launch"), None)
 
 
 def round_bytes(shape, rnd, n_steps, rows, draft_keys, keys_ctx):
@@ -480,15 +483,15 @@ def main():
     pages = lambda extra: int(sum(-(-(int(l) + extra) // shape.page_size) for l in rnd.L)) if shape.paged else 0
     draft_keys = keys_ctx + shape.B * ((n_steps + 1) / 2.0 if rnd.levels is None else shape.n_q / 2.0)   # mean over the steps
     spec = {
-        # weights once + fp32 rows in, bf16 rows out + one (value, index) candidate per 16-row tile
-        "draft_head_gemm": dict(bytes=e * (shape.V + 3) * shape.D + e * 2 * rows * shape.D + 8 * rows * ((shape.V + 18) // 16),
+        # weights once + fp32 rows in + one (value, index) result per row
+        "draft_head_gemm": dict(bytes=e * (shape.V + 3) * shape.D + e * 2 * rows * shape.D + 8 * rows,
                                 flops=2.0 * rows * (shape.V + 3) * shape.D, launches=n_steps,
                                 what="widened-head GEMM + argmax of the draft step"),
         # K and V of every cache entry once + q in, out out + page ids
         "draft_attn_split": dict(bytes=2 * e * shape.Hkv * shape.d * draft_keys + 2 * e * rows * shape.Hq * shape.d + 4 * pages(n_steps),
                                  flops=4.0 * (rows / shape.B) * shape.Hq * shape.d * draft_keys, launches=n_steps,
                                  what="split-KV attention of the draft layer over its own cache"),
-        "lmhead_gemm": dict(bytes=e * shape.V * shape.D + e * shape.B * shape.n_q * shape.D + 8 * shape.B * shape.n_q * ((shape.V + 15) // 16),
+        "lmhead_gemm": dict(bytes=e * shape.V * shape.D + e * shape.B * shape.n_q * shape.D + 8 * shape.B * shape.n_q,
                             flops=2.0 * shape.B * shape.n_q * shape.D * shape.V, launches=1,
                             what="target LM-head GEMM + argmax over the block rows"),
         "verify_attn_split": dict(bytes=2 * e * shape.Hkv * shape.d * (keys_ctx + shape.B * shape.n_q) + 2 * e * shape.B * shape.n_q * shape.Hq * shape.d + 4 * pages(shape.n_q),
