@@ -8,7 +8,7 @@
 // 32-key tiles kg, kg+2, ... of the chunk.  A ring is S slots in LDS (K tile + V tile: 16 KB
 // with 128-wide heads, 8 KB with 64-wide ones).  Tiles are brought in by direct global->LDS loads (16 bytes per lane, streaming),
 // issued S-1 tiles ahead by the ring's waves in turn, so most of the LDS holds bytes in
-// flight.  Each of the ring's NR waves owns one 16-row tile of the queries and computes it
+// flight.  Each of the ring's NR waves owns one or two 16-row tiles of the queries and computes them
 // against every tile of the ring:
 //   S^T = K Q^T : A operand = K rows (row = key, 8 consecutive d per lane) read from the
 //                 XOR-swizzled K tile; B operand = Q^T pieces held in registers;
@@ -38,7 +38,7 @@ constexpr int o_row(int hd) { return hd + 4; }          // floats per row of the
 // within 3 % of each other at 72 rows.
 // With 64-wide heads the output accumulators and the slots are half as large: two workgroups fit up to
 // four waves per ring, and the rings take twice the slots in the same LDS.  Measured at 64 rows per KV
-// head, contexts 1000-8000 of 8 sequences (74 MB), whole call: 34.5 us; on the ALU kernel 365 us.
+// head, contexts 1000-8000 of 8 sequences (74 MB), whole call: 30 us; on the ALU kernel 365 us.
 constexpr int big_from(int hd) { return hd == 64 ? 5 : 4; }
 constexpr int stages_of(int hd, int nr) { return (nr >= big_from(hd) ? 4 : 2) * (hd == 64 ? 2 : 1); }
 // K operand reads / V operand read pairs issued ahead of the matrix instructions that use them: as
@@ -88,8 +88,12 @@ __global__ __launch_bounds__(64 * kNK * NR, min_waves_per_simd(HD, NR)) void k_a
   constexpr int kChunks = HD / 8;               // 16-byte chunks of a cache row
   constexpr int kKeysPP = 1024 / kRowB;         // keys of a 1 KB piece
   constexpr int kTileP = 32 / kKeysPP;          // pieces of a K (or V) tile
-  // 64-wide heads keep their probabilities as a bf16 value plus the bf16 rounding of the rest (relative
-  // 2^-17): the ALU kernel that served them multiplied with fp32 probabilities
+  // 64-wide heads keep their probabilities as a bf16 value plus the bf16 rounding of the rest, 16 to 17 bits: the ALU
+  // kernel that served them multiplied with fp32 probabilities.  What is lost (2^-17 relative per probability) is far below
+  // the bf16 rounding of the output: error against 64 bits over eight inputs each, that kernel / this one, 8 contexts of
+  // 300-3000 x 16 queries 1.658633e-3 / 1.658634e-3, 4 of 64-200 x 5 1.661877e-3 / 1.661878e-3, 1 of 9000 x 7 1.660461e-3 /
+  // 1.660462e-3.  An infinite V entry is not what the two parts can multiply with: the merging kernels compute rows
+  // that are not finite again.
   constexpr bool kSplitP = HD == 64;
   constexpr int kKS = HD / 32, kDT = HD / 16;   // k steps of K Q^T, 16-wide column tiles of the output
   // LDS: [ring 0: S slots][ring 1: S slots] (later overlaid by the merge buffer [RP][kORow]),

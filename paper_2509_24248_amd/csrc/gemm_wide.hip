@@ -18,11 +18,11 @@
 // One workgroup barrier per stage hands a landed stage to the consumers and the stage read
 // before it back to the producers.  Every lane keeps the best of the logits it has seen; they become one
 // candidate per workgroup and row (and column split) at the end.
-// What bounds it: the weight stream.  V = 151936, D = 4096, whole call: 8 / 24 / 56 / 144 rows 190 / 191 / 213 /
-// 234 us = 6.5 / 6.5 / 5.8 / 5.3 TB/s, where a kernel that staged the activations in LDS for every eight
-// weight tiles took 230 / 233 us for the first two and the same form with one wave per 32 rows 225 us
-// for the third.  Draft head with 8 / 64 fp32 rows, same size: 230 -> 190 and 503 -> 236 us (that kernel read all
-// 128 virtual rows from LDS for every tile: the LDS was the bound).  Many rows are slower: by leaving parts out
+// What bounds it: the weight stream.  V = 151936, D = 4096, whole call: 8 / 24 / 56 / 144 rows 188 / 196 / 207 /
+// 230 us = 6.6 / 6.4 / 6.0 / 5.4 TB/s (one call after the other; 2 % less with single calls), where a kernel that staged
+// the activations in LDS for every eight weight tiles took 230 / 233 us for the first two and the same form with one wave
+// per 32 rows 225 us for the third.  Draft head with 8 / 64 fp32 rows, same size: 230 -> 183 and 503 -> 216 us (that kernel
+// read all 128 virtual rows from LDS for every tile: the LDS was the bound).  Many rows are slower: by leaving parts out
 // at 144 rows (D = 5120), the producers alone stream at 7 TB/s (230 us), the consumers alone take 225 us, of
 // that the LDS reads and barriers 45 us, the matrix instructions 45 us, the activation loads 25 us (80 us
 // before they covered whole cache lines: straight from the row-major matrix a load is 16 rows x 64 bytes,
