@@ -81,10 +81,11 @@ def test_narrow_heads_at_tile_edges(n_q, Hq, Hkv, page):
     assert err < 2.0 ** -8
 
 
-@pytest.mark.parametrize("B,n_q,page", [(2, 5, 16), (2, 16, 0), (40, 3, 64)])
+@pytest.mark.parametrize("B,n_q,page", [(2, 5, 16), (2, 16, 0), (40, 3, 64), (40, 7, 64)])
 def test_infinite_values_of_narrow_heads(B, n_q, page):
     # 64-wide heads: an infinite V entry that a row sees makes its column of that row infinite, with its sign (the
-    # probability is positive), and changes no other column.  Few and many segments per unit: both merging kernels.
+    # probability is positive), and changes no other column.  The last case has the rows (2240 x 80 units on 320 workgroups)
+    # that a wave each merges, the others a workgroup each.
     shape = gen.scaled(gen.config(1), B=B, Hq=8, Hkv=2, d=64, n_q=n_q, ctx=(20, 500), page_size=page or 16)
     L, kv, q, _ = case(shape, 5, paged=page > 0)
     # (sequence, KV head, entry, column, value); the last one is the block's last entry, which only the last query sees
@@ -108,10 +109,11 @@ def test_infinite_values_of_narrow_heads(B, n_q, page):
     assert rel_err(got[plain], ref[plain]) < TOL["bf16"]
 
 
-@pytest.mark.parametrize("dtype,d", [("bf16", 64), ("bf16", 128), ("f32", 64)])
-def test_one_long_sequence_among_short_ones(dtype, d):
-    # few segments per unit on average, so a wave merges each output row, and one unit with more of them than a wave has lanes
-    shape = gen.scaled(gen.config(1), dtype=dtype, B=70, Hq=4, Hkv=2, d=d, n_q=3, ctx=(0, 40))
+@pytest.mark.parametrize("dtype,d,n_q", [("bf16", 64, 3), ("bf16", 128, 3), ("f32", 64, 3), ("bf16", 64, 5), ("bf16", 128, 5)])
+def test_one_long_sequence_among_short_ones(dtype, d, n_q):
+    # one unit with more segments than a wave has lanes among many of one or two: merged by a wave per output row (fp32, whose
+    # launch has 256 workgroups, and five queries on 512) and by a workgroup per row (three queries on 512)
+    shape = gen.scaled(gen.config(1), dtype=dtype, B=70, Hq=4, Hkv=2, d=d, n_q=n_q, ctx=(0, 40))
     L = gen.context_lengths(shape, 3)
     L[33] = 9000
     kv = gen.kv_cache(shape, L, shape.n_q, 3, paged=True)
