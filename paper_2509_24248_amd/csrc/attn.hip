@@ -8,6 +8,8 @@
 #include "common.hpp"
 #include "kernels.hpp"
 
+#include <algorithm>
+
 namespace sx {
 
 namespace {
@@ -41,17 +43,16 @@ __global__ __launch_bounds__(256) void k_attn_split_valu(const AttnArgs a) {
   float* As = Ls + R;               // [R] rescale of this tile
   int* sched_lds = reinterpret_cast<int*>(As + R);   // [2 B + 1]
   attn_sched_build(a, sched_lds);
-  const int Tg = a.Hkv * sched_lds[a.B];     // granules on the line
-  const int W = attn_sched_workgroups(Tg, a.wgrid);
+  const AttnLine line = attn_sched_line(sched_lds[a.B], a.B, a.Hkv, a.pad, a.wide_from, a.wgrid);
   if (blockIdx.x == 0) {
     for (int i = tid; i <= a.B; i += 256) a.sched[i] = sched_lds[i];
-    if (tid == 0) a.sched[a.B + 1] = W;
   }
-  if (static_cast<int>(blockIdx.x) >= W) return;
-  const int x_hi = attn_sched_lo(blockIdx.x + 1, Tg, W);
-  for (int x_cur = attn_sched_lo(blockIdx.x, Tg, W); x_cur < x_hi;) {
-  const AttnSeg seg = attn_sched_segment(a, sched_lds, x_cur, x_hi);
+  if (static_cast<int>(blockIdx.x) >= line.W) return;
+  const int x_hi = attn_sched_lo(line, blockIdx.x + 1);
+  for (int x_cur = attn_sched_lo(line, blockIdx.x); x_cur < x_hi;) {
+  const AttnSeg seg = attn_sched_segment(a, sched_lds, line.pad, x_cur, x_hi);
   x_cur = seg.next;
+  if (seg.s1 <= seg.s0) continue;
   const int g = seg.g, b = seg.b, L = seg.L, s0 = seg.s0, s1 = seg.s1;
 
   for (int idx = tid; idx < R * D; idx += 256) {
@@ -241,83 +242,97 @@ __device__ __forceinline__ void attn_row_again(const AttnArgs& a, int b, int i, 
 // (uniform over the wave: one of its lanes holds a value that is no number or infinite)
 __device__ __forceinline__ bool any_not_finite(float v) { return __builtin_amdgcn_ballot_w64(!(fabsf(v) < INFINITY)) != 0ull; }
 
-// Merge the segments of one (sequence, query, head): exact log-sum-exp combination.  One
-// workgroup per output row: the chunks' weights exp(m_s - max) are formed once in LDS, then
-// the threads split into groups that each take every NG-th chunk of one float4 column, so
-// all partial outputs are requested at once; the groups are added in a fixed order.
+// The segments of an output row: consecutive slots, one per workgroup whose share holds keys of its unit.
+struct RowSegs {
+  const float *ml, *po;   // segment s: (max, sum) at ml[s * ml_step], partial output at po[s * po_step]
+  size_t ml_step, po_step;
+  int n;
+};
+template <int D>
+__device__ __forceinline__ RowSegs row_segments(const AttnArgs& a, int b, int i, int h) {
+  const int G = a.G, R = G * a.n_q, g = h / G, r = i * G + h - g * G;
+  const int s0 = a.sched[b], s1 = a.sched[b + 1], sB = a.sched[a.B];
+  const AttnLine line = attn_sched_line(sB, a.B, a.Hkv, a.pad, a.wide_from, a.wgrid);
+  const int p_u = a.Hkv * (s0 + line.pad * b) + g * (s1 - s0 + line.pad) + line.pad;     // the unit's first keys on the line
+  const int w_first = attn_sched_owner(line, p_u);
+  const size_t slot = static_cast<size_t>(w_first) + static_cast<size_t>(b) * a.Hkv + g;
+  RowSegs q;
+  q.n = attn_sched_owner(line, p_u + s1 - s0 - 1) - w_first + 1;
+  q.ml = a.part_ml + (slot * R + r) * 2;
+  q.po = a.part_o + (slot * R + r) * D;
+  q.ml_step = 2 * static_cast<size_t>(R);
+  q.po_step = static_cast<size_t>(R) * D;
+  return q;
+}
+__device__ __forceinline__ float seg_exp(const AttnArgs& a, float x) { return a.use_mfma ? exp2f(x) : expf(x); }
+
+// Merge the segments of one (sequence, query, head): exact log-sum-exp combination.  One workgroup per output row; groups
+// of lanes take every NG-th segment of one float4 column and are added in a fixed order.
+// Latency is all there is (a row reads 17 KB at 33 segments): the length table, the workgroups' range, one round to memory, a
+// meeting of the groups.  The first kEarly partial outputs of every group are requested together with the (max, sum) pairs,
+// every wave works out all weights for itself (lane s holds those of segments s, s + 64, ..), and the maximum and the sum over
+// the lanes are taken without LDS: no barrier before the one at which the groups meet.  Segments beyond 64 in rounds.
 constexpr int kCombThreads = 256;
+constexpr int kEarly = 6;
 
 template <typename T, int D>
 __global__ __launch_bounds__(kCombThreads) void k_attn_combine(const AttnArgs a) {
   constexpr int C4 = D / 4;                 // float4 columns of a row
-  constexpr int NG = kCombThreads / C4;     // chunk groups
-  extern __shared__ float w_lds[];          // [wgrid] weights (a unit has at most that many segments), then NG x C4 float4 for the group sums
-  __shared__ float red[kCombThreads / 64];
+  constexpr int NG = kCombThreads / C4;     // groups
+  __shared__ float4 gs[NG][C4];
   const int h = blockIdx.x, i = blockIdx.y, b = blockIdx.z;
-  const int G = a.Hq / a.Hkv;
-  const int R = G * a.n_q;
-  const int g = h / G, r = i * G + h % G;
-  // the segments of this row's unit: consecutive slots, one per workgroup whose range touched it
-  const int n_b = a.sched[b + 1] - a.sched[b];
-  const int Tg = a.Hkv * a.sched[a.B], W = a.sched[a.B + 1];
-  const int p_u = a.Hkv * a.sched[b] + g * n_b;
-  const int w_first = attn_sched_owner(p_u, Tg, W);
-  const int nact = attn_sched_owner(p_u + n_b - 1, Tg, W) - w_first + 1;
-  const size_t unit0 = static_cast<size_t>(w_first) + static_cast<size_t>(b) * a.Hkv + g;
-  const float* ml = a.part_ml + (unit0 * R + r) * 2;          // segment s at ml[s * R * 2]
-  const float* po = a.part_o + (unit0 * R + r) * D;            // segment s at po[s * R * D]
-  float mloc = -INFINITY;
-  for (int s = threadIdx.x; s < nact; s += kCombThreads) mloc = fmaxf(mloc, ml[static_cast<size_t>(s) * R * 2]);
-  mloc = wave_max(mloc);
-  if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = mloc;
-  __syncthreads();
-  float mmax = red[0];
-#pragma unroll
-  for (int w = 1; w < kCombThreads / 64; ++w) mmax = fmaxf(mmax, red[w]);
-  __syncthreads();
-  float dloc = 0.f;
-  for (int s = threadIdx.x; s < nact; s += kCombThreads) {
-    const float ms = ml[static_cast<size_t>(s) * R * 2];
-    float w = 0.f;
-    if (ms != -INFINITY) w = a.use_mfma ? exp2f(ms - mmax) : expf(ms - mmax);
-    w_lds[s] = w;
-    dloc = fmaf(w, w != 0.f ? ml[static_cast<size_t>(s) * R * 2 + 1] : 0.f, dloc);
-  }
-  dloc = wave_sum(dloc);
-  if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = dloc;
-  __syncthreads();
-  float den = 0.f;
-#pragma unroll
-  for (int w = 0; w < kCombThreads / 64; ++w) den += red[w];
+  const int lane = threadIdx.x & 63;
+  const RowSegs q = row_segments<D>(a, b, i, h);
   const int sg = threadIdx.x / C4, c4 = threadIdx.x % C4;
+  const float* po = q.po + c4 * 4;
+  float2 ml = *reinterpret_cast<const float2*>(q.ml + min(lane, q.n - 1) * q.ml_step);
+  float4 o[kEarly];
+#pragma unroll
+  for (int u = 0; u < kEarly; ++u) o[u] = *reinterpret_cast<const float4*>(po + min(sg + u * NG, q.n - 1) * q.po_step);
+  float mmax = ml.x;
+  for (int s = 64 + lane; s < q.n; s += 64) mmax = fmaxf(mmax, q.ml[s * q.ml_step]);
+  mmax = wave_max_dpp(mmax);
+  float den = 0.f;
   float4 acc = make_float4(0.f, 0.f, 0.f, 0.f);
-  for (int s = sg; s < nact; s += 4 * NG) {
-    float4 o[4];
-    float w[4];
+  for (int s0 = 0; s0 < q.n; s0 += 64) {
+    if (s0 > 0) ml = *reinterpret_cast<const float2*>(q.ml + min(s0 + lane, q.n - 1) * q.ml_step);
+    const float w = s0 + lane < q.n && ml.x != -INFINITY ? seg_exp(a, ml.x - mmax) : 0.f;
+    den += w != 0.f ? w * ml.y : 0.f;       // (lane by lane, summed behind the loop)
+    const int n = min(64, q.n - s0);
+    for (int sb = 0; sb < n; sb += kEarly * NG) {     // (uniform: a shuffle reads lanes that take part only)
+      const int s = sb + sg;
+      if (s0 + sb > 0) {
 #pragma unroll
-    for (int u = 0; u < 4; ++u) {
-      const int ss = min(s + u * NG, nact - 1);
-      w[u] = s + u * NG < nact ? w_lds[ss] : 0.f;
-      o[u] = *reinterpret_cast<const float4*>(po + static_cast<size_t>(ss) * R * D + c4 * 4);
-    }
-#pragma unroll
-    for (int u = 0; u < 4; ++u)
-      if (w[u] != 0.f) {
-        acc.x = fmaf(w[u], o[u].x, acc.x); acc.y = fmaf(w[u], o[u].y, acc.y);
-        acc.z = fmaf(w[u], o[u].z, acc.z); acc.w = fmaf(w[u], o[u].w, acc.w);
+        for (int u = 0; u < kEarly; ++u) o[u] = *reinterpret_cast<const float4*>(po + (s0 + min(s + u * NG, n - 1)) * q.po_step);
       }
+#pragma unroll
+      for (int u = 0; u < kEarly; ++u) {
+        float wu = __shfl(w, min(s + u * NG, n - 1), 64);
+        if (s + u * NG >= n) wu = 0.f;
+        if (wu != 0.f) {
+          acc.x = fmaf(wu, o[u].x, acc.x); acc.y = fmaf(wu, o[u].y, acc.y);
+          acc.z = fmaf(wu, o[u].z, acc.z); acc.w = fmaf(wu, o[u].w, acc.w);
+        }
+      }
+    }
   }
-  float4* gs = reinterpret_cast<float4*>(w_lds + ((a.wgrid + 3) & ~3));
-  gs[sg * C4 + c4] = acc;
+  gs[sg][c4] = acc;
+  den = wave_sum_dpp(den);
   __syncthreads();
   float4 sum = make_float4(0.f, 0.f, 0.f, 0.f);
   if (sg == 0) {
-    sum = gs[c4];
-    for (int u = 1; u < NG; ++u) {
-      const float4 v = gs[u * C4 + c4];
-      sum.x += v.x; sum.y += v.y; sum.z += v.z; sum.w += v.w;
+    float4 v[NG];
+#pragma unroll
+    for (int u = 0; u < NG; ++u) v[u] = gs[u][c4];
+    sum = v[0];
+#pragma unroll
+    for (int u = 1; u < NG; ++u) { sum.x += v[u].x; sum.y += v[u].y; sum.z += v[u].z; sum.w += v[u].w; }
+    if constexpr (sizeof(T) == 2) {
+      const float inv = 1.0f / den;            // (rounded to bf16 below)
+      sum.x *= inv; sum.y *= inv; sum.z *= inv; sum.w *= inv;
+    } else {
+      sum.x /= den; sum.y /= den; sum.z /= den; sum.w /= den;
     }
-    sum.x /= den; sum.y /= den; sum.z /= den; sum.w /= den;
   }
   if constexpr (D == 64 && sizeof(T) == 2) {
     if (a.use_mfma && threadIdx.x < 64 && any_not_finite((sum.x + sum.y) + (sum.z + sum.w))) {
@@ -327,77 +342,72 @@ __global__ __launch_bounds__(kCombThreads) void k_attn_combine(const AttnArgs a)
   }
   if (sg == 0) {
     T* dst = static_cast<T*>(a.out) + ((static_cast<size_t>(b) * a.n_q + i) * a.Hq + h) * D + c4 * 4;
-    Elem<T>::store(dst + 0, sum.x); Elem<T>::store(dst + 1, sum.y);
-    Elem<T>::store(dst + 2, sum.z); Elem<T>::store(dst + 3, sum.w);
-  }
-}
-
-size_t combine_lds_bytes(int wgrid) { return (static_cast<size_t>((wgrid + 3) & ~3) + kCombThreads * 4) * sizeof(float); }
-
-// acc += weight x partial output of the segments j .. j + U - 1 of at most 64 (n of them; lane i holds segment i's weight),
-// requested together and added one after the other
-template <int U, int EPL>
-__device__ __forceinline__ void combine_add(float (&acc)[EPL], const float* po, size_t stride, float w, int j, int n) {
-  float o[U][EPL], ws[U];
-#pragma unroll
-  for (int u = 0; u < U; ++u) {
-    const int jj = min(j + u, n - 1);
-    ws[u] = j + u < n ? __shfl(w, jj, 64) : 0.f;
-    const float* src = po + static_cast<size_t>(jj) * stride;
-#pragma unroll
-    for (int e = 0; e < EPL; ++e) o[u][e] = src[e];
-  }
-#pragma unroll
-  for (int u = 0; u < U; ++u)
-    if (ws[u] != 0.f) {
-#pragma unroll
-      for (int e = 0; e < EPL; ++e) acc[e] = fmaf(ws[u], o[u][e], acc[e]);
+    if constexpr (sizeof(T) == 2) {
+      *reinterpret_cast<uint2*>(dst) = make_uint2(pack_bf16x2(sum.x, sum.y), pack_bf16x2(sum.z, sum.w));
+    } else {
+      *reinterpret_cast<float4*>(dst) = sum;
     }
+  }
 }
 
-// The same with one wave per output row: for many rows, where a workgroup each spends its time starting.  Sixteen
-// segments are requested together, so that a unit of many segments in a batch of short ones costs a few memory round trips
-// (four at a time: one context of 32768 among 15 of 300, 2 queries, 41.7 us; 38.6 this way).
+// The same with one wave per output row: for many rows, where a workgroup each spends its time starting.  The first
+// segments' partial outputs are requested with the (max, sum) pairs, and sixteen together from there on, so that a unit of many
+// segments in a batch of short ones costs a few memory round trips (four at a time: one context of 32768 among 15 of 300, 2
+// queries, 41.7 us; 38.6 this way).
+constexpr int kRowEarly = 4;
+
 template <typename T, int D>
 __global__ __launch_bounds__(256) void k_attn_combine_rows(const AttnArgs a) {
   constexpr int EPL = D / 64;               // columns per lane
   const int lane = threadIdx.x & 63;
-  const int row = blockIdx.x * 4 + (threadIdx.x >> 6);
+  const int row = __builtin_amdgcn_readfirstlane(blockIdx.x * 4 + (threadIdx.x >> 6));
   if (row >= a.B * a.n_q * a.Hq) return;
   const int b = row / (a.n_q * a.Hq), ih = row - b * (a.n_q * a.Hq), i = ih / a.Hq, h = ih - i * a.Hq;
-  const int G = a.Hq / a.Hkv;
-  const int R = G * a.n_q;
-  const int g = h / G, r = i * G + h % G;
-  const int n_b = a.sched[b + 1] - a.sched[b];
-  const int Tg = a.Hkv * a.sched[a.B], W = a.sched[a.B + 1];
-  const int p_u = a.Hkv * a.sched[b] + g * n_b;
-  const int w_first = attn_sched_owner(p_u, Tg, W);
-  const int nact = attn_sched_owner(p_u + n_b - 1, Tg, W) - w_first + 1;
-  const size_t unit0 = static_cast<size_t>(w_first) + static_cast<size_t>(b) * a.Hkv + g;
-  const float* ml = a.part_ml + (unit0 * R + r) * 2;
-  const float* po = a.part_o + (unit0 * R + r) * D + lane * EPL;
-  float mmax = -INFINITY;
-  for (int s = lane; s < nact; s += 64) mmax = fmaxf(mmax, ml[static_cast<size_t>(s) * R * 2]);
-  mmax = wave_max(mmax);
+  const RowSegs q = row_segments<D>(a, b, i, h);
+  const float* po = q.po + lane * EPL;
+  float2 ml = *reinterpret_cast<const float2*>(q.ml + min(lane, q.n - 1) * q.ml_step);
+  float first[kRowEarly][EPL];
+#pragma unroll
+  for (int u = 0; u < kRowEarly; ++u)
+#pragma unroll
+    for (int e = 0; e < EPL; ++e) first[u][e] = po[min(u, q.n - 1) * q.po_step + e];
+  float mmax = ml.x;
+  for (int s = 64 + lane; s < q.n; s += 64) mmax = fmaxf(mmax, q.ml[s * q.ml_step]);
+  mmax = wave_max_dpp(mmax);
   float den = 0.f, acc[EPL];
 #pragma unroll
   for (int e = 0; e < EPL; ++e) acc[e] = 0.f;
-  for (int s0 = 0; s0 < nact; s0 += 64) {
-    const int s = s0 + lane;
-    float w = 0.f, l = 0.f;
-    if (s < nact) {
-      const float ms = ml[static_cast<size_t>(s) * R * 2];
-      if (ms != -INFINITY) {
-        w = a.use_mfma ? exp2f(ms - mmax) : expf(ms - mmax);
-        l = ml[static_cast<size_t>(s) * R * 2 + 1];
-      }
+  auto add = [&](float w, const float (&o)[EPL]) {
+    if (w != 0.f) {
+#pragma unroll
+      for (int e = 0; e < EPL; ++e) acc[e] = fmaf(w, o[e], acc[e]);
     }
-    den += wave_sum(w != 0.f ? w * l : 0.f);
-    const int n = min(64, nact - s0);
+  };
+  for (int s0 = 0; s0 < q.n; s0 += 64) {
+    if (s0 > 0) ml = *reinterpret_cast<const float2*>(q.ml + min(s0 + lane, q.n - 1) * q.ml_step);
+    const float w = s0 + lane < q.n && ml.x != -INFINITY ? seg_exp(a, ml.x - mmax) : 0.f;
+    den += w != 0.f ? w * ml.y : 0.f;       // (lane by lane, summed behind the loop)
+    auto weight = [&](int j) { return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(w), j)); };
+    const int n = min(64, q.n - s0);
     int j = 0;
-    for (; j + 8 < n; j += 16) combine_add<16, EPL>(acc, po + static_cast<size_t>(s0) * R * D, static_cast<size_t>(R) * D, w, j, n);
-    for (; j < n; j += 4) combine_add<4, EPL>(acc, po + static_cast<size_t>(s0) * R * D, static_cast<size_t>(R) * D, w, j, n);
+    if (s0 == 0) {
+#pragma unroll
+      for (int u = 0; u < kRowEarly; ++u)
+        if (u < n) add(weight(u), first[u]);
+      j = kRowEarly;
+    }
+    for (; j < n; j += 16) {
+      float o[16][EPL];
+#pragma unroll
+      for (int u = 0; u < 16; ++u)
+#pragma unroll
+        for (int e = 0; e < EPL; ++e) o[u][e] = po[(s0 + min(j + u, n - 1)) * q.po_step + e];
+#pragma unroll
+      for (int u = 0; u < 16; ++u)
+        if (j + u < n) add(weight(j + u), o[u]);
+    }
   }
+  den = wave_sum_dpp(den);
   if constexpr (D == 64 && sizeof(T) == 2) {
     if (a.use_mfma && any_not_finite(acc[0] / den)) {
       attn_row_again(a, b, i, h);
@@ -425,7 +435,7 @@ hipError_t launch_combine(const AttnArgs& a, hipStream_t s) {
   if (rows * units > 256 * static_cast<int64_t>(a.wgrid)) {
     hipLaunchKernelGGL((k_attn_combine_rows<T, D>), dim3(static_cast<unsigned>((rows + 3) / 4)), dim3(256), 0, s, a);
   } else {
-    hipLaunchKernelGGL((k_attn_combine<T, D>), dim3(a.Hq, a.n_q, a.B), dim3(kCombThreads), combine_lds_bytes(a.wgrid), s, a);
+    hipLaunchKernelGGL((k_attn_combine<T, D>), dim3(a.Hq, a.n_q, a.B), dim3(kCombThreads), 0, s, a);
   }
   return hipGetLastError();
 }
@@ -449,39 +459,63 @@ hipError_t launch_valu(const AttnArgs& a, hipStream_t s) {
 
 }  // namespace
 
-constexpr size_t kCombineLdsMax = 60 * 1024;
+// Padding of the units (attn_sched.hpp), in granules: what starting a segment costs.  Per layer, 0 / 1 / 2 / 3 granules, 8 KV heads, mean
+// context 300 .. 900, G = 4: 64 sequences x 1 query 26.0 / 24.1 / 24.3 / 24.7 us, x 11 42.9 / 42.6 / 42.4 / 42.0; 16 x 11 (900)
+// 30.8 / 29.9 / 28.9 / 29.0; 64-wide heads, 64 x 8 (600) 34.3 / 32.8 / 32.2 / 32.1.  With one sequence, whose units are few, it
+// does not matter.
+static int unit_pad(const AttnArgs& a) { return a.d == 64 ? 3 : 2; }
 
-static bool plan_as(AttnArgs& a, int num_cus, int use_mfma) {
+// Granules from which two workgroups per compute unit are worth their partial results, of which each writes R rows that are read
+// again.  Per layer, 256 / 512 workgroups, T granules: R = 4 rows: 1 sequence, T = 1800 19.4 / 18.8 us, 3200 26.6 / 24.8;
+// 20 rows: 1 sequence, 1800 20.0 / 20.8, 2400 23.4 / 23.5, 3200 27.5 / 26.6; 4 sequences, 1800 20.9 / 19.7; 44 rows: 1 sequence,
+// 2400 25.9 / 28.1, 4800 37.9 / 38.4; 16 sequences, 2400 28.1 / 28.9, 3200 32.8 / 33.2.  With more units than compute units
+// every workgroup writes several of them anyway, and the second one is at work while the first starts a unit: 64
+// sequences, 44 rows, 1200 34.0 / 33.0, 4800 54.7 / 50.1.  64-wide heads, granules of half the bytes, 32 rows: 1 sequence, 1200
+// 12.6 / 14.2, 2400 15.7 / 17.8, 4800 22.2 / 22.1; 64 sequences, 2400 28.9 / 26.0; 64 rows: 8 sequences, 4500 27.7 / 26.6 (there the
+// second workgroup's waves are wanted for the arithmetic as well).
+static int wide_from(const AttnArgs& a) {
+  if (!a.use_mfma || static_cast<int64_t>(a.B) * a.Hkv >= kAttnSpread) return 0;
+  return 1000 + std::min(a.G * a.n_q * (a.d == 64 ? 80 : 50), 2600);
+}
+
+// More workgroups than this are refused.
+constexpr int64_t kMaxGrid = 14336;
+
+static bool plan_as(AttnArgs& a, int num_cus, int use_mfma, int pad) {
   // The host knows only the upper bound l_max of the lengths; the kernels deal the keys that
   // are really there to the workgroups in equal shares.  Here only the number of workgroups is
   // set: as many as are resident at once (one or two of the matrix-core kernel per compute unit),
   // fewer when even the longest possible caches would leave them too few granules
-  // (attn_sched_workgroups), more when a share could otherwise exceed what one segment can hold.
+  // (attn_sched_line), more when a share could otherwise exceed what one segment can hold.
   a.use_mfma = use_mfma;
+  a.G = a.Hq / a.Hkv;
+  a.g_inv = (65536 + a.G - 1) / a.G;
+  a.pad = pad;
+  a.wide_from = wide_from(a);
   if (a.B > kAttnMaxSeqs || a.l_max < a.n_blk) return false;
   const int64_t units = static_cast<int64_t>(a.B) * a.Hkv;
   const int64_t gmax = (a.l_max + kAttnGran - 1) / kAttnGran;      // granules of the longest possible unit
-  const int64_t tmax = units * gmax;
-  if (tmax >= (1ll << 30)) return false;
+  if (units * (gmax + pad) >= (1ll << 30)) return false;
   a.stages = a.use_mfma ? attn_mfma_stages(a) : 0;
   const int64_t resident = static_cast<int64_t>(num_cus) * (a.use_mfma ? attn_mfma_per_cu(a) : 1);
-  int64_t w = attn_sched_workgroups(static_cast<int>(tmax), static_cast<int>(resident));
+  const AttnLine line = attn_sched_line(static_cast<int>(a.B * gmax), a.B, a.Hkv, pad, a.wide_from, static_cast<int>(resident));
+  int64_t w = line.W;
   if (a.use_mfma) {
     const int64_t seg_gran = attn_mfma_max_chunk(a) / kAttnGran;   // granules one segment may span
-    const int64_t need = (tmax + seg_gran - 1) / seg_gran;
+    const int64_t need = (line.T + seg_gran - 1) / seg_gran;
     if (w < need) w = need;
   }
-  if (combine_lds_bytes(static_cast<int>(w)) > kCombineLdsMax) return false;
+  if (w > kMaxGrid) return false;
   a.wgrid = static_cast<int>(w);
   return true;
 }
 
 bool attn_plan(AttnArgs& a, int num_cus) {
-  if (!attn_mfma_supported(a)) return plan_as(a, num_cus, 0);
+  if (!attn_mfma_supported(a)) return plan_as(a, num_cus, 0, 0);
   // The matrix-core kernel keeps the page ids of a segment in LDS, which bounds a segment and so asks for
   // many workgroups where the page tables could hold hundreds of millions of entries.  Where that is
-  // more than the merging kernel takes, 64-wide heads go to the ALU kernel, whose segments are unbounded.
-  return plan_as(a, num_cus, 1) || (a.d == 64 && plan_as(a, num_cus, 0));
+  // more than a launch has, 64-wide heads go to the ALU kernel, whose segments are unbounded.
+  return plan_as(a, num_cus, 1, unit_pad(a)) || plan_as(a, num_cus, 1, 0) || (a.d == 64 && plan_as(a, num_cus, 0, 0));
 }
 
 int attn_slots(const AttnArgs& a) { return a.wgrid + a.B * a.Hkv; }
@@ -493,7 +527,7 @@ size_t attn_workspace_bytes(const AttnArgs& a) {
   o = (o + 255) & ~static_cast<size_t>(255);
   size_t ml = slots * R * 2 * sizeof(float);
   ml = (ml + 255) & ~static_cast<size_t>(255);
-  size_t sc = static_cast<size_t>(a.B + 2) * sizeof(int);
+  size_t sc = static_cast<size_t>(a.B + 1) * sizeof(int);
   sc = (sc + 255) & ~static_cast<size_t>(255);
   return o + ml + sc;
 }

@@ -18,10 +18,20 @@
 //                 registers.
 // One workgroup barrier per tile step hands a landed tile to the waves and frees the slot
 // consumed one step earlier.  The two rings merge at the end in a fixed order.
+//
+// Short calls are a chain: lengths, split, queries and tiles, one or two tiles of arithmetic, merge.  So queries and tiles are
+// requested together, addresses that only later code needs are worked out behind the requests, and code that runs once is
+// kept short (it is fetched for that).  Calls of many rows are bound by the vector instructions of the softmax: one fused
+// multiply-add and one exponential per score, no maximum over the lanes unless a row's grew.  Whole calls, before / after this
+// form (with the work split that pads units, and the merge in one round of requests): 36 calls of 1 sequence x 4096 entries, 7
+// queries of 32 heads, 15.1 / 13.1 us each; 8 of 1000-8000, 64 rows of 64-wide heads, paged 29.6 / 26.2; 16 of 8192-32768, 72
+// rows, paged 251 / 238 (4.9 TB/s of cache entries); 16 of 250-750, 5 queries of 32 heads 20.2 / 17.0.
 #include "attn_sched.hpp"
 #include "common.hpp"
 #include "kernels.hpp"
 #include "stream.hpp"
+
+#include <float.h>
 
 namespace sx {
 
@@ -29,7 +39,6 @@ namespace {
 
 constexpr int kNK = 2;                 // tile rings (key groups) per workgroup
 constexpr int slot_bytes(int hd) { return 128 * hd; }   // one ring slot: 32 K rows then 32 V rows of hd bf16 values
-constexpr int o_row(int hd) { return hd + 4; }          // floats per row of the merge buffer (padded)
 // From kBigFrom waves per ring (more than 48 query rows per KV head) one workgroup is resident per
 // compute unit (its eight to sixteen waves need more than the 96-128 registers per lane that two
 // workgroups would leave them) and its rings take kBigStages slots; below that, two workgroups of
@@ -38,7 +47,7 @@ constexpr int o_row(int hd) { return hd + 4; }          // floats per row of the
 // within 3 % of each other at 72 rows.
 // With 64-wide heads the output accumulators and the slots are half as large: two workgroups fit up to
 // four waves per ring, and the rings take twice the slots in the same LDS.  Measured at 64 rows per KV
-// head, contexts 1000-8000 of 8 sequences (74 MB), whole call: 30 us; on the ALU kernel 365 us.
+// head, contexts 1000-8000 of 8 sequences (74 MB), whole call: 26 us; on the ALU kernel 365 us.
 constexpr int big_from(int hd) { return hd == 64 ? 5 : 4; }
 constexpr int stages_of(int hd, int nr) { return (nr >= big_from(hd) ? 4 : 2) * (hd == 64 ? 2 : 1); }
 // K operand reads / V operand read pairs issued ahead of the matrix instructions that use them: as
@@ -60,6 +69,10 @@ constexpr int kMaxChunkPages = 2048;   // page ids of one chunk kept in LDS (8 K
 
 typedef short s16x4_t __attribute__((ext_vector_type(4)));
 
+// Maxima that hand a NaN on: the instruction needs no quieting of its inputs, of which there would be one each.
+__device__ __forceinline__ float max_nan(float a, float b) { return __builtin_elementwise_maximum(a, b); }
+__device__ __forceinline__ float max3_nan(float a, float b, float c) { return max_nan(max_nan(a, b), c); }
+
 // XOR swizzle of the 16-byte chunks of a tile row.  K rows are read one row per lane (16 rows
 // at once): chunk ^ (key % 16) spreads them over all banks.  V rows are read by the transpose
 // load, 4 rows x 2 adjacent chunks at once: chunk ^ (2 (key % 8)) keeps those eight apart.
@@ -67,10 +80,6 @@ typedef short s16x4_t __attribute__((ext_vector_type(4)));
 // one half of them, the other bits of the key spread the chunks of that half.
 template <int HD> __device__ __forceinline__ int swz_k(int key) { return HD == 128 ? key & 15 : (key >> 1) & 7; }
 template <int HD> __device__ __forceinline__ int swz_v(int key) { return HD == 128 ? (key & 7) << 1 : ((key >> 1) & 3) << 1; }
-
-constexpr int front_bytes(int hd, int rp, int stages) {
-  return kNK * stages * slot_bytes(hd) > rp * o_row(hd) * 4 ? kNK * stages * slot_bytes(hd) : rp * o_row(hd) * 4;
-}
 
 // waves per SIMD the register allocation has to leave room for: the resident workgroups' waves on
 // four SIMDs
@@ -83,7 +92,7 @@ template <int HD, int NR, int RTW, int S, bool PAGED>
 __global__ __launch_bounds__(64 * kNK * NR, min_waves_per_simd(HD, NR)) void k_attn_ring(const AttnArgs a) {
   constexpr int RP = 16 * NR * RTW;             // query rows covered (padded)
   constexpr int kKAhead = k_ahead(HD, NR), kVAhead = v_ahead(HD, NR);
-  constexpr int kSlot = slot_bytes(HD), kORow = o_row(HD);
+  constexpr int kSlot = slot_bytes(HD);
   constexpr int kRowB = 2 * HD;                 // bytes of a cache row
   constexpr int kChunks = HD / 8;               // 16-byte chunks of a cache row
   constexpr int kKeysPP = 1024 / kRowB;         // keys of a 1 KB piece
@@ -95,56 +104,59 @@ __global__ __launch_bounds__(64 * kNK * NR, min_waves_per_simd(HD, NR)) void k_a
   // 1.660462e-3.  An infinite V entry is not what the two parts can multiply with: the merging kernels compute rows
   // that are not finite again.
   constexpr bool kSplitP = HD == 64;
+  // Slack of the softmax reference in log2 units: with probabilities of 16 bits it does not matter how far above 1 they
+  // reach (8 sequences of 1000-8000 entries, 64 rows per KV head: 27.8 -> 26.8 us, the same error).  bf16 ones are nearest where the
+  // largest are 1 or just below: a slack of 8 is 3 % faster at 72 rows per KV head and costs 6 % of the error against 64 bits
+  // (2.05e-3 -> 2.19e-3, 4096 entries), so they have none.
+  constexpr float kSlack = kSplitP ? 8.f : 0.f;
   constexpr int kKS = HD / 32, kDT = HD / 16;   // k steps of K Q^T, 16-wide column tiles of the output
-  // LDS: [ring 0: S slots][ring 1: S slots] (later overlaid by the merge buffer [RP][kORow]),
-  // then the (max, sum) table for the merge, the schedule's prefix table, the page ids of the segment
-  constexpr int kFront = front_bytes(HD, RP, S);
+  // LDS: [ring 0: S slots][ring 1: S slots] (free ones hold ring 1's sums for the merge), ring 1's (max, sum) per row, the
+  // schedule's prefix table, the page ids of the segment
+  constexpr int kFront = kNK * S * kSlot;
   extern __shared__ uint4 smem4[];
   char* smem = reinterpret_cast<char*>(smem4);
   float* ml_lds = reinterpret_cast<float*>(smem + kFront);
-  int* sched_lds = reinterpret_cast<int*>(smem + kFront + kNK * RP * 2 * sizeof(float));
+  int* sched_lds = reinterpret_cast<int*>(smem + kFront + RP * 2 * sizeof(float));
   int* pg_lds = sched_lds + attn_sched_words(a.B);
   const int lane = threadIdx.x & 63;
   const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int kg = wv / NR, rr = wv % NR;
-  const int G = a.Hq / a.Hkv;
+  const int G = a.G;
   const int R = G * a.n_q;
+  const int fr = lane & 15, fq = lane >> 4;
   attn_sched_build(a, sched_lds);
-  const int T = a.Hkv * sched_lds[a.B];
-  const int W = attn_sched_workgroups(T, a.wgrid);
+  const AttnLine line = attn_sched_line(__builtin_amdgcn_readfirstlane(sched_lds[a.B]), a.B, a.Hkv, a.pad, a.wide_from, a.wgrid);
   if (blockIdx.x == 0) {
     // the merging kernel reads the split back from here
     for (int i = threadIdx.x; i <= a.B; i += 64 * kNK * NR) a.sched[i] = sched_lds[i];
-    if (threadIdx.x == 0) a.sched[a.B + 1] = W;
   }
-  if (static_cast<int>(blockIdx.x) >= W) return;  // the whole workgroup leaves together
-  const int x_hi = attn_sched_lo(blockIdx.x + 1, T, W);
-  for (int x_cur = attn_sched_lo(blockIdx.x, T, W); x_cur < x_hi;) {
-  const AttnSeg seg = attn_sched_segment(a, sched_lds, x_cur, x_hi);
+  if (static_cast<int>(blockIdx.x) >= line.W) return;  // the whole workgroup leaves together
+  const int x_hi = attn_sched_lo(line, blockIdx.x + 1);
+  bool again = false;                           // a segment before this one used the rings
+  for (int x_cur = attn_sched_lo(line, blockIdx.x); x_cur < x_hi;) {
+  const AttnSeg seg = attn_sched_segment(a, sched_lds, line.pad, x_cur, x_hi);
   x_cur = seg.next;
+  if (seg.s1 <= seg.s0) continue;
   const int g = seg.g, b = seg.b;
-  const int L = seg.L;
-  const int s0 = seg.s0, s1 = seg.s1;
+  const int L = __builtin_amdgcn_readfirstlane(seg.L);
+  const int s0 = seg.s0, s1 = __builtin_amdgcn_readfirstlane(seg.s1);
   const int ntl = (s1 - s0 + 31) >> 5;          // 32-key tiles in this segment
   const int nit = (ntl + kNK - 1) / kNK;        // tile steps (the same for both rings)
-  const int fr = lane & 15, fq = lane >> 4;
   char* ring = smem + kg * (S * kSlot);
 
-  // ---- Q^T operand pieces and the mask words of this wave's rows
+  // ---- Q^T operand pieces and the mask words of this wave's rows (rows past the last one repeat it and are not stored)
   uint4 qf[kKS][RTW];
   uint64_t rowmask[RTW];
   int rho[RTW];
 #pragma unroll
   for (int t = 0; t < RTW; ++t) {
     rho[t] = 16 * (rr * RTW + t) + fr;
-    const bool valid = rho[t] < R;
-    const int i = valid ? rho[t] / G : 0;
-    const int hh = valid ? rho[t] - i * G : 0;
-    const bf16_t* qp = static_cast<const bf16_t*>(a.q) + ((static_cast<size_t>(b) * a.n_q + i) * a.Hq + g * G + hh) * HD + fq * 8;
+    const int r = min(rho[t], R - 1);
+    const int i = (r * a.g_inv) >> 16;          // r / G
+    const bf16_t* qp = static_cast<const bf16_t*>(a.q) + ((static_cast<size_t>(b) * a.n_q + i) * a.Hq + g * G + (r - i * G)) * HD + fq * 8;
 #pragma unroll
-    for (int ks = 0; ks < kKS; ++ks)
-      qf[ks][t] = valid ? *reinterpret_cast<const uint4*>(qp + ks * 32) : make_uint4(0, 0, 0, 0);
-    rowmask[t] = !valid ? 0ull : (a.mask ? a.mask[static_cast<size_t>(b) * a.mask_stride + i] : ((2ull << i) - 1ull));
+    for (int ks = 0; ks < kKS; ++ks) qf[ks][t] = *reinterpret_cast<const uint4*>(qp + ks * 32);
+    rowmask[t] = a.mask ? a.mask[static_cast<size_t>(b) * a.mask_stride + i] : ((2ull << i) - 1ull);
   }
 
   // ---- page ids of the segment, copied to LDS once: loads from there do not count against
@@ -158,92 +170,108 @@ __global__ __launch_bounds__(64 * kNK * NR, min_waves_per_simd(HD, NR)) void k_a
       pg_lds[i] = checked_page(ptab[i], a.n_pages, a.status);   // never leave the pool
     }
   }
-  __builtin_amdgcn_s_waitcnt(vmcnt_imm(0));    // from here on vmcnt counts tile loads only
-  __syncthreads();
+  if (PAGED || again) __syncthreads();          // the page ids are there, and the rings are free of the segment before
+  again = true;
 
   // ---- tile loads: the ring's waves take the one-KB pieces of a tile (K, then V: kTileP each) in
   // turn.  Piece j holds the kKeysPP keys from kKeysPP (j % kTileP) on; lane l fetches key
   // l / kChunks of them, 16-byte chunk (l % kChunks) ^ swizzle(key), and lands at piece base + 16 l, so
-  // that LDS entry [key][pos] holds chunk pos ^ swizzle(key).  The lane's byte offset inside a tile
-  // does not depend on the tile.
+  // that LDS entry [key][pos] holds chunk pos ^ swizzle(key).  The swizzle is the exclusive or of a lane's part and a piece's
+  // part, so a piece costs one instruction per lane and no registers between tiles.
   constexpr int kPieces = (2 * kTileP + NR - 1) / NR;   // pieces a wave issues per tile, at most
   const int lkey = lane / kChunks, lpos = lane % kChunks;
-  uint32_t lane_off[kPieces];
-#pragma unroll
-  for (int u = 0; u < kPieces; ++u) {
-    const int key = kKeysPP * ((rr + u * NR) & (kTileP - 1)) + lkey;
-    const int in_row = PAGED ? (key & (a.page_size - 1)) : key;
-    const int sw = ((rr + u * NR) & kTileP) ? swz_v<HD>(key) : swz_k<HD>(key);
-    lane_off[u] = static_cast<uint32_t>(in_row) * kRowB + static_cast<uint32_t>((lpos ^ sw) << 4);
-  }
-  const size_t seq_row = PAGED ? 0 : (static_cast<size_t>(b) * a.Hkv + g) * a.l_max;
-  auto issue = [&](int it) {
-    const int ti = it * kNK + kg;
-    if (it >= nit || ti >= ntl) return;        // uniform per wave
-    const int t0 = s0 + 32 * ti;
-    char* slot = ring + (it % S) * kSlot;
-    // rows of the pool that hold the tile's first and second 16 keys (pages of 16 * 2^n
-    // tokens: a 32-aligned tile touches at most the page of key 0 and the page of key 16)
-    size_t row_a, row_b;
+  const uint32_t lane_k = static_cast<uint32_t>(lkey) * kRowB + ((lpos ^ swz_k<HD>(lkey)) << 4);
+  const uint32_t lane_v = static_cast<uint32_t>(lkey) * kRowB + ((lpos ^ swz_v<HD>(lkey)) << 4);
+  // Byte offsets in the pool of a whole tile's first and second 16 keys (pages of 16 * 2^n tokens: a 32-aligned tile
+  // touches at most the page of key 0 and the page of key 16), uniform.
+  const int64_t seq_off = PAGED ? 0 : (static_cast<int64_t>(b) * a.Hkv + g) * a.l_max * kRowB;
+  int64_t off_a, off_b;
+  auto locate = [&](int it) {
+    const int t0 = s0 + 32 * (it * kNK + kg);
+    if (t0 >= s1) return;                        // uniform per wave
     if (PAGED) {
       const int p1 = min(t0 + 16, s1 - 1);
-      const int pg_a = pg_lds[(t0 >> ps_shift) - pg0], pg_b = pg_lds[(p1 >> ps_shift) - pg0];
-      row_a = (static_cast<size_t>(pg_a) * a.Hkv + g) * a.page_size;
-      row_b = (static_cast<size_t>(pg_b) * a.Hkv + g) * a.page_size;
+      const int pg_a = __builtin_amdgcn_readfirstlane(pg_lds[(t0 >> ps_shift) - pg0]), pg_b = __builtin_amdgcn_readfirstlane(pg_lds[(p1 >> ps_shift) - pg0]);
+      off_a = (static_cast<int64_t>(pg_a) * a.Hkv + g) * a.page_size * kRowB;
+      off_b = (static_cast<int64_t>(pg_b) * a.Hkv + g) * a.page_size * kRowB;
     } else {
-      row_a = row_b = seq_row;
+      off_a = off_b = seq_off;
     }
+  };
+  auto issue = [&](int it) {                     // (after locate of the same tile)
+    const int t0 = s0 + 32 * (it * kNK + kg);
+    if (t0 >= s1) return;
+    char* slot = ring + (it % S) * kSlot;
     if (t0 + 32 <= s1) {
       // whole tile inside the range: uniform base per piece + the lane's constant offset
-      const size_t in_page = PAGED ? static_cast<size_t>(t0 & (a.page_size - 1)) : static_cast<size_t>(t0);
+      const int64_t in_page = static_cast<int64_t>(PAGED ? t0 & (a.page_size - 1) : t0) * kRowB;
 #pragma unroll
       for (int u = 0; u < kPieces; ++u) {
         const int j = rr + u * NR;
         if (j < 2 * kTileP) {
           const bool second = PAGED && a.page_size == 16 && (j & (kTileP / 2));   // keys 16..31 sit in the next page
-          const char* base = static_cast<const char*>(j < kTileP ? a.k : a.v) + ((second ? row_b : row_a) + in_page) * kRowB;
-          load_to_lds16(base, lane_off[u], slot + j * 1024);
+          const int key = kKeysPP * (j & (kTileP - 1));                           // the piece's first key
+          const int row = PAGED ? key & (a.page_size - 1) : key;
+          const char* base = static_cast<const char*>(j < kTileP ? a.k : a.v) + ((second ? off_b : off_a) + in_page + row * kRowB);
+          load_to_lds16(base, j < kTileP ? lane_k ^ (swz_k<HD>(key) << 4) : lane_v ^ (swz_v<HD>(key) << 4), slot + j * 1024);
         }
       }
       return;
     }
     const int page0 = t0 >> ps_shift;
+    int lk = lkey;                               // (worked out here, once per segment at most)
+    asm volatile("" : "+v"(lk));
 #pragma unroll
     for (int u = 0; u < kPieces; ++u) {
       const int j = rr + u * NR;
       if (j < 2 * kTileP) {
-        const int key = kKeysPP * (j & (kTileP - 1)) + lkey;
+        const int key = kKeysPP * (j & (kTileP - 1)) + lk;
         const int p = min(t0 + key, s1 - 1);   // keys past the range are masked in the softmax
-        size_t row;
-        if (PAGED) row = ((p >> ps_shift) == page0 ? row_a : row_b) + (p & (a.page_size - 1));
-        else row = row_a + p;
-        const char* src = static_cast<const char*>(j < kTileP ? a.k : a.v) + row * kRowB + ((lpos ^ (j < kTileP ? swz_k<HD>(key) : swz_v<HD>(key))) << 4);
-        load_to_lds16(src, slot + j * 1024);
+        int64_t off;
+        if (PAGED) off = ((p >> ps_shift) == page0 ? off_a : off_b) + (p & (a.page_size - 1)) * kRowB;
+        else off = off_a + static_cast<int64_t>(p) * kRowB;
+        load_to_lds16(static_cast<const char*>(j < kTileP ? a.k : a.v) + off + ((lpos ^ (j < kTileP ? swz_k<HD>(key) : swz_v<HD>(key))) << 4), slot + j * 1024);
       }
     }
   };
   constexpr int kPiecesMin = 2 * kTileP / NR;  // pieces every wave of a ring issues per tile, at least
 
-  f32x4_t oacc[kDT][RTW];
+  f32x4_t oacc[kDT][RTW], lacc[RTW];
   float m_run[RTW], l_run[RTW];
 #pragma unroll
   for (int t = 0; t < RTW; ++t) {
-    m_run[t] = -INFINITY;
+    m_run[t] = -FLT_MAX;
     l_run[t] = 0.f;
+    lacc[t] = f32x4_t{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
     for (int dt = 0; dt < kDT; ++dt) oacc[dt][t] = f32x4_t{0.f, 0.f, 0.f, 0.f};
   }
   const float sl2 = a.scale * 1.44269504088896340736f;  // scores are kept in log2 units
 
-  // every slot is free here: a short segment has all its tiles in flight at once
-#pragma unroll
-  for (int it = 0; it < S; ++it) issue(it);
+  // every slot is free here: a short segment has all its tiles in flight at once, behind the queries and at the same time
+#pragma unroll 1
+  for (int it = 0; it < S; ++it) {
+    locate(it);
+    issue(it);
+  }
+  // (the lane's part of the operand addresses is worked out here, while the loads are on their way, and not in front of them)
+  int fr_t = fr, fq_t = fq;
+  asm volatile("" : "+v"(fr_t), "+v"(fq_t));
+  __builtin_amdgcn_sched_barrier(0);
+  // Of the reads' addresses a lane keeps one for K and one for V: a read is the exclusive or with its number and the slot's base,
+  // one instruction (held in registers they are 24, and the paged kernel of three waves a ring spills).
+  const int ve = fr_t >> 2, vc = fr_t & 3;
+  int k_at = fr_t * kRowB + ((fq_t ^ swz_k<HD>(fr_t)) << 4);
+  int v_at = (4 * fq_t + ve) * kRowB + (((vc >> 1) ^ swz_v<HD>(4 * fq_t + ve)) << 4) + ((vc & 1) << 3);
 
+  __builtin_amdgcn_s_waitcnt(vmcnt_imm(0));    // from here on vmcnt counts tile loads only
+
+#pragma unroll 1                              // (no first round of its own: code that is run once is fetched for that)
   for (int it = 0; it < nit; ++it) {
-    // this wave's pieces of tile `it` have landed once at most the pieces of the S-2 tiles (S-1 before
-    // the first) issued after it are outstanding (loads return in order); near the end simply wait for all
-    if (it == 0 && (S - 1) * kNK + kg < ntl) __builtin_amdgcn_s_waitcnt(vmcnt_imm((S - 1) * kPiecesMin));
-    else if (S > 2 && it > 0 && it + S - 1 < nit) __builtin_amdgcn_s_waitcnt(vmcnt_imm((S - 2) * kPiecesMin));
+    if (it > 0) locate(it + S - 1);
+    // this wave's pieces of tile `it` have landed once at most the pieces of the S-2 tiles
+    // issued after it are outstanding (loads return in order); near the end simply wait for all
+    if (S > 2 && it + S - 1 < nit) __builtin_amdgcn_s_waitcnt(vmcnt_imm((S - 2) * kPiecesMin));
     else __builtin_amdgcn_s_waitcnt(vmcnt_imm(0));
     // plain barrier (no memory fence: a fence would wait for the loads still in flight); the
     // wave-scope fences only keep the compiler from moving LDS accesses across it
@@ -256,6 +284,7 @@ __global__ __launch_bounds__(64 * kNK * NR, min_waves_per_simd(HD, NR)) void k_a
     const int t0 = s0 + 32 * ti;
     const char* k_lds = ring + (it % S) * kSlot;
     const char* v_lds = k_lds + kSlot / 2;
+    asm volatile("" : "+v"(k_at), "+v"(v_at));
 
     // ---- S^T = K Q^T for the two 16-key halves.  The K operand reads run kKAhead reads ahead of the
     // matrix instructions that use them, and the first V operand reads are issued here as well (they do
@@ -267,21 +296,16 @@ __global__ __launch_bounds__(64 * kNK * NR, min_waves_per_simd(HD, NR)) void k_a
 #pragma unroll
       for (int t = 0; t < RTW; ++t) sacc[j][t] = f32x4_t{0.f, 0.f, 0.f, 0.f};
     auto kread = [&](int i) {       // read i: k step i / 2, key half i % 2
-      const int ks = i >> 1, j = i & 1;
-      return reinterpret_cast<const uint4*>(k_lds)[(16 * j + fr) * kChunks + ((4 * ks + fq) ^ swz_k<HD>(fr))];
+      return *reinterpret_cast<const uint4*>(k_lds + (k_at ^ ((i >> 1) << 6)) + (i & 1) * 16 * kRowB);
     };
     // Transpose load of V: within 16 lanes, lane i = 4 e + c points at key e's four values
     // d0 + 4c .. d0 + 4c + 3 and lane j receives column d0 + j of keys e = 0..3.  Two loads give the
     // 8 keys of the operand in the order P^T uses: 4q..4q+3 of the first half, then of the second half.
-    const int ve = fr >> 2, vc = fr & 3;
-    const int key0 = 4 * fq + ve, key1 = 16 + key0;
     s16x4_t vlo[kDT], vhi[kDT];
     auto vread = [&](int dt) {
-      const int chunk = 2 * dt + (vc >> 1);
-      const char* p0 = v_lds + key0 * kRowB + ((chunk ^ swz_v<HD>(key0)) << 4) + ((vc & 1) << 3);
-      const char* p1 = v_lds + key1 * kRowB + ((chunk ^ swz_v<HD>(key1)) << 4) + ((vc & 1) << 3);
-      vlo[dt] = __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) s16x4_t*)(lds_ptr_t)p0);
-      vhi[dt] = __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) s16x4_t*)(lds_ptr_t)p1);
+      const char* p = v_lds + (v_at ^ (dt << 5));
+      vlo[dt] = __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) s16x4_t*)(lds_ptr_t)p);
+      vhi[dt] = __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) s16x4_t*)(lds_ptr_t)(p + 16 * kRowB));
     };
     constexpr int kReads = 2 * kKS;
     uint4 kf[kReads];
@@ -299,42 +323,47 @@ __global__ __launch_bounds__(64 * kNK * NR, min_waves_per_simd(HD, NR)) void k_a
       __builtin_amdgcn_sched_barrier(0);
     }
 
-    // ---- online softmax; lane (row, q) owns keys t0 + 16 j + 4 q + e of its row
-    const bool need_mask = t0 + 32 > min(L, s1);
+    // ---- online softmax; lane (row, q) owns keys t0 + 16 j + 4 q + e of its row.  The reference the exponents are taken
+    // against moves only when one of the wave's scores exceeds its row's by more than kSlack: tiles in which none does need
+    // neither the maximum over the row's lanes nor the rescaling.
+    const bool plain = t0 + 32 <= min(L, s1) && sl2 > 0.f;
     uint4 pf[RTW], pl[RTW];
-    float alpha[RTW];
-    bool rescale = false;
 #pragma unroll
     for (int t = 0; t < RTW; ++t) {
       float x[8];
 #pragma unroll
       for (int j = 0; j < 2; ++j)
 #pragma unroll
-        for (int e = 0; e < 4; ++e) x[4 * j + e] = sacc[j][t][e] * sl2;
-      if (need_mask) {
+        for (int e = 0; e < 4; ++e) x[4 * j + e] = sacc[j][t][e];
+      float unit = sl2;
+      if (!plain) {
+        unit = 1.f;
 #pragma unroll
         for (int j = 0; j < 2; ++j)
 #pragma unroll
           for (int e = 0; e < 4; ++e) {
-            const int p = t0 + 16 * j + 4 * fq + e;
+            const int p = t0 + 16 * j + 4 * fq_t + e;
             bool vis = p < s1;
             if (vis && p >= L) vis = (rowmask[t] >> (p - L)) & 1ull;
-            if (!vis) x[4 * j + e] = -INFINITY;
+            x[4 * j + e] = vis ? x[4 * j + e] * sl2 : -INFINITY;
           }
       }
-      float mt = fmaxf(fmaxf(fmaxf(x[0], x[1]), fmaxf(x[2], x[3])), fmaxf(fmaxf(x[4], x[5]), fmaxf(x[6], x[7])));
-      mt = quad_row_max(mt);
-      const float m_new = fmaxf(m_run[t], mt);
-      float al = 1.f;
-      float pr[8];
-      if (m_new == -INFINITY) {
+      float mt = max3_nan(max3_nan(x[0], x[1], x[2]), max3_nan(x[3], x[4], x[5]), max_nan(x[6], x[7])) * unit;
+      if (__builtin_amdgcn_ballot_w64(mt > m_run[t] + kSlack) != 0ull) {
+        const float m_new = fmaxf(m_run[t], quad_row_max(mt));
+        const float al = __builtin_amdgcn_exp2f(m_run[t] - m_new);
+        m_run[t] = m_new;
+        if constexpr (kSplitP) l_run[t] *= al;
+        else lacc[t][0] *= al;
 #pragma unroll
-        for (int e = 0; e < 8; ++e) pr[e] = 0.f;
-      } else {
-        al = __builtin_amdgcn_exp2f(m_run[t] - m_new);
-#pragma unroll
-        for (int e = 0; e < 8; ++e) pr[e] = __builtin_amdgcn_exp2f(x[e] - m_new);
+        for (int dt = 0; dt < kDT; ++dt) {
+          oacc[dt][t][0] *= al; oacc[dt][t][1] *= al;
+          oacc[dt][t][2] *= al; oacc[dt][t][3] *= al;
+        }
       }
+      float pr[8];
+#pragma unroll
+      for (int e = 0; e < 8; ++e) pr[e] = __builtin_amdgcn_exp2f(fmaf(x[e], unit, -m_run[t]));
       pf[t] = make_uint4(pack_bf16x2(pr[0], pr[1]), pack_bf16x2(pr[2], pr[3]), pack_bf16x2(pr[4], pr[5]),
                          pack_bf16x2(pr[6], pr[7]));
       if constexpr (kSplitP) {
@@ -342,20 +371,14 @@ __global__ __launch_bounds__(64 * kNK * NR, min_waves_per_simd(HD, NR)) void k_a
         unpack16(pf[t], hi);
         pl[t] = make_uint4(pack_bf16x2(pr[0] - hi[0], pr[1] - hi[1]), pack_bf16x2(pr[2] - hi[2], pr[3] - hi[3]),
                            pack_bf16x2(pr[4] - hi[4], pr[5] - hi[5]), pack_bf16x2(pr[6] - hi[6], pr[7] - hi[7]));
+        l_run[t] += ((pr[0] + pr[1]) + (pr[2] + pr[3])) + ((pr[4] + pr[5]) + (pr[6] + pr[7]));
+      } else {
+        // the probabilities as V is multiplied with them, summed in fp32 by a product with a column of ones: weights that are
+        // normalised with their own sum leave less of their rounding in the output than with the sum of the unrounded ones
+        const uint32_t one = 0x3F803F80u;
+        lacc[t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, make_uint4(one, one, one, one)),
+                                                          __builtin_bit_cast(bf16x8_t, pf[t]), lacc[t], 0, 0, 0);
       }
-      l_run[t] = l_run[t] * al + (((pr[0] + pr[1]) + (pr[2] + pr[3])) + ((pr[4] + pr[5]) + (pr[6] + pr[7])));
-      m_run[t] = m_new;
-      alpha[t] = al;
-      rescale = rescale || (al != 1.f);
-    }
-    if (__builtin_amdgcn_ballot_w64(rescale) != 0ull) {
-#pragma unroll
-      for (int t = 0; t < RTW; ++t)
-#pragma unroll
-        for (int dt = 0; dt < kDT; ++dt) {
-          oacc[dt][t][0] *= alpha[t]; oacc[dt][t][1] *= alpha[t];
-          oacc[dt][t][2] *= alpha[t]; oacc[dt][t][3] *= alpha[t];
-        }
     }
 
     // ---- O^T += V^T P^T, the V operand reads kVAhead matrix instructions ahead
@@ -375,72 +398,56 @@ __global__ __launch_bounds__(64 * kNK * NR, min_waves_per_simd(HD, NR)) void k_a
       __builtin_amdgcn_sched_barrier(0);
     }
   }
-  __builtin_amdgcn_s_waitcnt(vmcnt_imm(0));
 
-  // ---- merge the two rings of each row in a fixed order, then one partial per workgroup
-  float* o_lds = reinterpret_cast<float*>(smem);   // merge buffer [RP][kORow], overlays the rings
+  // ---- merge the two rings of each row: ring 1 leaves its sums in LDS, ring 0 adds them to its own (always in this order) and
+  // stores the segment's partial result.  Slots other than the last tile's are free since the last barrier: wave rr of ring 1
+  // takes piece rr of them, ring 1's first.  Within a row the 16-byte pieces are swizzled like the tiles.
+  constexpr int kOBytes = 64 * HD;               // 16 rows
+  constexpr int kPerSlot = kSlot / kOBytes;
+  static_assert(kSlot == 2 * kOBytes && NR * RTW <= 2 * kPerSlot * (S - 1), "the free slots hold ring 1's sums");
+  int fr_o = fr, fq_o = fq;                      // (addresses worked out here, see above)
+  asm volatile("" : "+v"(fr_o), "+v"(fq_o));
+  auto o_lds = [&](int t) {
+    const int n = rr * RTW + t, in = n % (kPerSlot * (S - 1));
+    return smem + (n < kPerSlot * (S - 1) ? S * kSlot : 0) + ((nit + in / kPerSlot) % S) * kSlot + in % kPerSlot * kOBytes + fr_o * (4 * HD);
+  };
 #pragma unroll
   for (int t = 0; t < RTW; ++t) {
-    float l = l_run[t];
-    l += __shfl_xor(l, 16, 64);
-    l += __shfl_xor(l, 32, 64);
-    if (fq == 0) {
-      ml_lds[(kg * RP + rho[t]) * 2 + 0] = m_run[t];
-      ml_lds[(kg * RP + rho[t]) * 2 + 1] = l;
+    l_run[t] = kSplitP ? quad_row_sum(l_run[t]) : lacc[t][0];
+    if (kg == 1) {
+      if (fq == 0) *reinterpret_cast<float2*>(ml_lds + 2 * rho[t]) = make_float2(m_run[t], l_run[t]);
+      char* dst = o_lds(t);
+#pragma unroll
+      for (int dt = 0; dt < kDT; ++dt)
+        *reinterpret_cast<float4*>(dst + (((4 * dt + fq_o) ^ fr_o) << 4)) = make_float4(oacc[dt][t][0], oacc[dt][t][1], oacc[dt][t][2], oacc[dt][t][3]);
     }
   }
-  __syncthreads();   // also: every wave is done with the rings
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
+  __builtin_amdgcn_s_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
+  if (kg == 1) continue;
   const size_t unit = static_cast<size_t>(blockIdx.x) + static_cast<size_t>(b) * a.Hkv + g;   // partial slot of segment (w, u)
-  float fself[RTW];
 #pragma unroll
   for (int t = 0; t < RTW; ++t) {
-    float mm = -INFINITY;
+    if (rho[t] >= R) continue;
+    const float2 ml = *reinterpret_cast<const float2*>(ml_lds + 2 * rho[t]);
+    const float mm = fmaxf(m_run[t], ml.x);
+    const float f0 = __builtin_amdgcn_exp2f(m_run[t] - mm), f1 = __builtin_amdgcn_exp2f(ml.x - mm);
+    if (fq == 0) *reinterpret_cast<float2*>(a.part_ml + (unit * R + rho[t]) * 2) = make_float2(mm, fmaf(f1, ml.y, f0 * l_run[t]));
+    float* dst = a.part_o + (unit * R + rho[t]) * HD + 4 * fq_o;
+    const char* src = o_lds(t);
 #pragma unroll
-    for (int w = 0; w < kNK; ++w) mm = fmaxf(mm, ml_lds[(w * RP + rho[t]) * 2]);
-    float lt = 0.f;
-    fself[t] = 0.f;
-#pragma unroll
-    for (int w = 0; w < kNK; ++w) {
-      const float mw = ml_lds[(w * RP + rho[t]) * 2];
-      const float fw = (mw == -INFINITY) ? 0.f : __builtin_amdgcn_exp2f(mw - mm);
-      lt = fmaf(fw, ml_lds[(w * RP + rho[t]) * 2 + 1], lt);
-      if (w == kg) fself[t] = fw;
-    }
-    if (kg == 0 && fq == 0 && rho[t] < R) {
-      a.part_ml[(unit * R + rho[t]) * 2 + 0] = mm;
-      a.part_ml[(unit * R + rho[t]) * 2 + 1] = lt;
+    for (int dt = 0; dt < kDT; ++dt) {
+      const float4 o = *reinterpret_cast<const float4*>(src + (((4 * dt + fq_o) ^ fr_o) << 4));
+      *reinterpret_cast<float4*>(dst + 16 * dt) = make_float4(fmaf(o.x, f1, oacc[dt][t][0] * f0), fmaf(o.y, f1, oacc[dt][t][1] * f0),
+                                                              fmaf(o.z, f1, oacc[dt][t][2] * f0), fmaf(o.w, f1, oacc[dt][t][3] * f0));
     }
   }
-  for (int w = 0; w < kNK; ++w) {
-    if (kg == w) {
-#pragma unroll
-      for (int t = 0; t < RTW; ++t)
-#pragma unroll
-        for (int dt = 0; dt < kDT; ++dt) {
-          float4* dst = reinterpret_cast<float4*>(o_lds + rho[t] * kORow + 16 * dt + 4 * fq);
-          float4 v = make_float4(oacc[dt][t][0] * fself[t], oacc[dt][t][1] * fself[t], oacc[dt][t][2] * fself[t],
-                                 oacc[dt][t][3] * fself[t]);
-          if (w != 0) {
-            const float4 o = *dst;
-            v.x += o.x; v.y += o.y; v.z += o.z; v.w += o.w;
-          }
-          *dst = v;
-        }
-    }
-    __syncthreads();
-  }
-  for (int idx = threadIdx.x; idx < R * (HD / 4); idx += 64 * kNK * NR) {
-    const int r = idx / (HD / 4), c4 = idx % (HD / 4);
-    *reinterpret_cast<float4*>(a.part_o + (unit * R + r) * HD + c4 * 4) =
-        *reinterpret_cast<const float4*>(o_lds + r * kORow + c4 * 4);
-  }
-  // a further segment refills the rings under the merge buffer: its first loads are issued after
-  // the barrier that follows the page-id copy, which every thread reaches after these reads
   }
 }
 
 constexpr size_t lds_bytes(int hd, int rp, int stages, int B, bool paged) {
-  return static_cast<size_t>(front_bytes(hd, rp, stages)) + static_cast<size_t>(kNK) * rp * 2 * sizeof(float) +
+  return static_cast<size_t>(kNK) * stages * slot_bytes(hd) + static_cast<size_t>(rp) * 2 * sizeof(float) +
          static_cast<size_t>(attn_sched_words(B)) * sizeof(int) + (paged ? static_cast<size_t>(kMaxChunkPages + 1) * sizeof(int) : 0);
 }
 

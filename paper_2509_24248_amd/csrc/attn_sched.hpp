@@ -4,12 +4,18 @@
 // The kernels do it themselves: the keys of every (sequence, KV head) unit are counted in
 // granules of 64, the units are laid end to end on one line of T granules (unit u = b * Hkv + g
 // starts at Hkv * S[b] + g * n_b, S = prefix sums of the sequences' granule counts n_b), and
-// workgroup w of W takes the granules [w T / W, (w + 1) T / W).  Every workgroup therefore has
+// each of W workgroups takes the next T / W granules, the first T % W of them one more.  Every workgroup therefore has
 // the same amount of cache to read whatever the mix of lengths, all of them are resident at
 // once, and nobody waits for a long sequence's last chunk.  A workgroup whose range crosses a
 // unit boundary finishes one unit's partial result and starts the next (a "segment" per unit).
 // Segment (w, u) writes partial slot w + u: both grow along the line, so the slots of one unit
 // are consecutive and no two segments share one; W + units slots are enough.
+//
+// Starting a segment costs as much as several granules (queries and first tiles from memory, nothing in flight
+// meanwhile), and with equal shares the workgroups that cross a unit's end are the last to finish: 8 sequences of 2k to 16k
+// entries, 8 KV heads, one query each, 512 workgroups: half of them done 44.7 us after the start, the last one 51.3.  So every
+// unit has `pad` granules of nothing in front of its keys: a workgroup that starts a unit has that much less to read, and
+// one whose share ends within them does not start it at all.
 #pragma once
 #include "common.hpp"
 #include "kernels.hpp"
@@ -51,70 +57,80 @@ __device__ __forceinline__ void attn_sched_build(const AttnArgs& a, int* S) {
         x = (n + kAttnGran - 1) / kAttnGran;
         attn_sched_short(a, S)[b] = static_cast<unsigned char>(x * kAttnGran - n);
       }
-#pragma unroll
-      for (int o = 1; o < 64; o <<= 1) {
-        const int y = __shfl_up(x, o, 64);
-        if (lane >= o) x += y;
-      }
+      x = wave_scan(x);
       if (b < a.B) S[b + 1] = run + x;
-      run += __shfl(x, 63, 64);
+      run += __builtin_amdgcn_readlane(x, 63);
     }
     if (lane == 0) S[0] = 0;
   }
   __syncthreads();
 }
 
-// Workgroups that take part: at least two granules each, one where the launch has a compute unit for every granule.
+// The line of a launch whose sequences have `gran` granules in all.  Workgroups that take part: one per granule while the launch
+// has a compute unit for each (no workgroup crosses a unit's end then: no padding); one per compute unit up to
+// `wide_from` granules; from there on as many as are resident, with at least two granules each.
 constexpr int kAttnSpread = 256;
-__host__ __device__ __forceinline__ int attn_sched_workgroups(int T, int wgrid) {
-  const int want = T <= kAttnSpread ? T : (T >> 1) < kAttnSpread ? kAttnSpread : T >> 1;
-  return want < 1 ? 1 : want < wgrid ? want : wgrid;
+struct AttnLine {
+  int T, W, pad;   // granules with the padding, workgroups, padding per unit
+  int q, r;        // T / W, T % W
+};
+__host__ __device__ __forceinline__ AttnLine attn_sched_line(int gran, int B, int Hkv, int pad, int wide_from, int wgrid) {
+  AttnLine l;
+  l.T = gran * Hkv;
+  l.pad = l.T <= kAttnSpread ? 0 : pad;
+  int want = l.T;
+  if (l.T > kAttnSpread) {
+    const bool wide = l.T >= wide_from;
+    l.T += B * Hkv * pad;
+    want = (l.T + 1) >> 1;
+    if (!wide || want < kAttnSpread) want = kAttnSpread;
+  }
+  l.W = want < 1 ? 1 : want < wgrid ? want : wgrid;
+  l.q = static_cast<int>(static_cast<uint32_t>(l.T) / static_cast<uint32_t>(l.W));   // at least 1: W <= T
+  l.r = l.T - l.q * l.W;
+  return l;
 }
 
-// a b / c for a >= 0, b, c >= 1 whose quotient fits 32 bits.  A 64-bit division is some 150 dependent instructions,
-// and these kernels start with two of them: 32 bits where the product allows it (uniform).
-__device__ __forceinline__ int mul_div(int a, int b, int add, int c) {
-  const int64_t x = static_cast<int64_t>(a) * b + add;
-  if (x <= 0x7fffffff) return static_cast<int>(static_cast<uint32_t>(x) / static_cast<uint32_t>(c));
-  return static_cast<int>(x / c);
-}
-
-__device__ __forceinline__ int attn_sched_lo(int w, int T, int W) { return mul_div(w, T, 0, W); }
-
-// first and last workgroup whose range holds a granule of [p, p + n)
-__device__ __forceinline__ int attn_sched_owner(int p, int T, int W) {
-  return mul_div(p + 1, W, -1, T);
+// First granule of workgroup w, and the workgroup that has granule p.  (One 32-bit division each for the line and the owner: the
+// products of an even deal, w T / W, need 64 bits, whose division is 150 dependent instructions, fetched for a single use.)
+__device__ __forceinline__ int attn_sched_lo(const AttnLine& l, int w) { return w * l.q + min(w, l.r); }
+__device__ __forceinline__ int attn_sched_owner(const AttnLine& l, int p) {
+  const int longer = l.r * (l.q + 1);
+  const bool in = p < longer;
+  const uint32_t k = static_cast<uint32_t>(in ? p : p - longer) / static_cast<uint32_t>(in ? l.q + 1 : l.q);
+  return static_cast<int>(k) + (in ? 0 : l.r);
 }
 
 struct AttnSeg {
   int b, g;      // unit
-  int s0, s1;    // keys [s0, s1) of the unit
+  int s0, s1;    // keys [s0, s1) of the unit, none if s1 <= s0
   int L;         // context length of the sequence (block entries follow)
   int next;      // granule on the line where the next segment starts
 };
 
-// The segment that starts at granule x of the line and ends at the unit's end or at `hi`.
-// Uniform over the workgroup; S in LDS.
-__device__ __forceinline__ AttnSeg attn_sched_segment(const AttnArgs& a, int* S, int x, int hi) {
+// The segment that starts at granule x of the line and ends at the unit's end or at `hi` (no keys where that is still
+// padding).  Uniform over the workgroup; S in LDS.
+__device__ __forceinline__ AttnSeg attn_sched_segment(const AttnArgs& a, int* S, int pad, int x, int hi) {
   const int lane = threadIdx.x & 63;
   int b = 0;
   for (int c = 0; c < a.B; c += 64) {
     const int i = c + lane;
-    const bool before = i < a.B && static_cast<int64_t>(a.Hkv) * S[i + 1] <= x;
+    const bool before = i < a.B && a.Hkv * (S[i + 1] + pad * (i + 1)) <= x;
     b += __popcll(__builtin_amdgcn_ballot_w64(before));
   }
   b = __builtin_amdgcn_readfirstlane(min(b, a.B - 1));
-  const int n = S[b + 1] - S[b];
-  const int rel = x - a.Hkv * S[b];
+  const int first = __builtin_amdgcn_readfirstlane(S[b]);
+  const int n = __builtin_amdgcn_readfirstlane(S[b + 1]) - first;
+  const int rel = x - a.Hkv * (first + pad * b);
   AttnSeg s;
   s.b = b;
-  s.g = min(rel / n, a.Hkv - 1);
-  const int g0 = min(rel - s.g * n, n - 1);     // first granule inside the unit
-  const int g1 = min(n, g0 + (hi - x));
+  s.g = min(static_cast<int>(static_cast<uint32_t>(rel) / static_cast<uint32_t>(n + pad)), a.Hkv - 1);
+  const int at = min(rel - s.g * (n + pad), n + pad - 1);   // granule of the unit, padding first
+  const int end = min(at + (hi - x), n + pad);
   s.L = n * kAttnGran - attn_sched_short(a, S)[b] - a.n_blk;
-  s.s0 = g0 * kAttnGran;
-  s.s1 = min(s.L + a.n_blk, g1 * kAttnGran);
-  s.next = x + max(g1 - g0, 1);                 // (the minima above cannot bind while S is the table of these lengths)
+  s.s0 = max(at - pad, 0) * kAttnGran;
+  s.s1 = min(s.L + a.n_blk, (end - pad) * kAttnGran);
+  s.next = x + max(end - at, 1);                // (the minima above cannot bind while S is the table of these lengths)
   return s;
 }
 

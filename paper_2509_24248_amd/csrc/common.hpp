@@ -73,6 +73,42 @@ __device__ __forceinline__ float quad_row_max(float v) {
   return fmaxf(__uint_as_float(b[0]), __uint_as_float(b[1]));
 }
 
+// Sum over the same four lanes.
+__device__ __forceinline__ float quad_row_sum(float v) {
+  const auto a = __builtin_amdgcn_permlane16_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+  v = __uint_as_float(a[0]) + __uint_as_float(a[1]);
+  const auto b = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+  return __uint_as_float(b[0]) + __uint_as_float(b[1]);
+}
+
+// Maximum and sum over a wave by rotations within the rows of 16 lanes and the swaps above: some 40 cycles where six shuffles
+// through LDS take 400.
+template <int CTRL> __device__ __forceinline__ float row_lane(float v) {
+  return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), CTRL, 0xf, 0xf, false));
+}
+__device__ __forceinline__ float wave_max_dpp(float v) {
+  v = fmaxf(v, row_lane<0x128>(v)); v = fmaxf(v, row_lane<0x124>(v));
+  v = fmaxf(v, row_lane<0x122>(v)); v = fmaxf(v, row_lane<0x121>(v));
+  return quad_row_max(v);
+}
+__device__ __forceinline__ float wave_sum_dpp(float v) {
+  v += row_lane<0x128>(v); v += row_lane<0x124>(v);
+  v += row_lane<0x122>(v); v += row_lane<0x121>(v);
+  return quad_row_sum(v);
+}
+
+// Inclusive prefix sum over a wave, likewise: shifts within the rows of 16 lanes, then the last lane of a row to the next one
+// (rows 1 and 3) and of the first two rows to the last two.
+__device__ __forceinline__ int wave_scan(int x) {
+  x += __builtin_amdgcn_update_dpp(0, x, 0x111, 0xf, 0xf, false);
+  x += __builtin_amdgcn_update_dpp(0, x, 0x112, 0xf, 0xf, false);
+  x += __builtin_amdgcn_update_dpp(0, x, 0x114, 0xf, 0xf, false);
+  x += __builtin_amdgcn_update_dpp(0, x, 0x118, 0xf, 0xf, false);
+  x += __builtin_amdgcn_update_dpp(0, x, 0x142, 0xa, 0xf, false);
+  x += __builtin_amdgcn_update_dpp(0, x, 0x143, 0xc, 0xf, false);
+  return x;
+}
+
 // (value, index) pair ordered by larger value, then lower index
 __device__ __forceinline__ bool better(float v, int i, float bv, int bi) {
   return v > bv || (v == bv && i < bi);

@@ -178,6 +178,9 @@ struct AttnArgs {
   const void* q;             // [B, n_q, Hq, d]
   const int32_t* ctx_len;    // [B] number of context entries before the block
   const uint64_t* mask;      // [B, n_q] or nullptr = chain
+  int G, g_inv;              // Hq / Hkv and ceil(65536 / G): r / G = r g_inv >> 16 for r < 128 (attn_plan)
+  int pad, wide_from;        // work split: padding per unit, granules from which more workgroups than compute units take part
+                             // (attn_sched.hpp)
   int n_blk;                 // block entries stored after the context (normally n_q; tree drafting:
                              // every node written so far, of which n_q are this call's queries)
   int mask_stride;           // mask words between two sequences' rows (n_q; 0 = all sequences share)
@@ -187,8 +190,8 @@ struct AttnArgs {
                              // are dealt to them in equal shares on the device (attn_sched.hpp)
   float* part_o;             // [wgrid + B*Hkv slots][R][d]
   float* part_ml;            // [wgrid + B*Hkv slots][R][2]  (running max, sum)
-  int* sched;                // [B + 2] written by the split kernel for the merging kernel: prefix sums of the
-                             // sequences' granule counts, then the number of workgroups that took part
+  int* sched;                // [B + 1] written by the split kernel for the merging kernel: prefix sums of the
+                             // sequences' granule counts
   int64_t n_pages;           // paged: pages in the pool (page ids are forced into it)
   int* status;               // device error word or nullptr: first out-of-range length / page id seen
   int stages;                // matrix-core kernel: slots per tile ring (attn_plan)

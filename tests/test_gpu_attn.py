@@ -120,6 +120,19 @@ def test_one_long_sequence_among_short_ones(dtype, d, n_q):
     check(shape, L, kv, gen.queries(shape, 3), None, label="one long sequence")
 
 
+@pytest.mark.parametrize("d,n_q,L,page", [(128, 3, (2045,), 0), (128, 3, (2046,), 0), (128, 3, (5000,), 16), (128, 3, (9000,), 0), (128, 3, (9300,), 16),
+                                          (128, 9, (0, 2000, 63, 64), 16), (128, 9, (1, 9000, 700), 0), (64, 3, (2046,), 32), (64, 3, (11000,), 0),
+                                          (64, 9, (0, 9000, 700), 16), (128, 1, (40,) * 70 + (6000,), 16)])
+def test_shares_at_the_edges_of_the_work_split(d, n_q, L, page):
+    # 8 KV heads: 256 granules of 64 keys and just above (a workgroup per granule; one per compute unit, units padded), just below and
+    # above the point from which more workgroups than compute units take part, units shorter than the padding beside long ones,
+    # and more sequences than a wave has lanes.  q.k is scaled up so that single keys decide and a lost or doubled tile shows.
+    shape = gen.scaled(gen.config(1), B=len(L), Hq=8, Hkv=8, d=d, n_q=n_q, k=max(n_q - 1, 1), ctx=(0, 1), page_size=page or 16)
+    L = np.array(L, np.int32)
+    kv = gen.kv_cache(shape, L, n_q, 13, paged=page > 0)
+    check(shape, L, kv, 4 * gen.queries(shape, 13), None, label="split edges")
+
+
 def test_paged_equals_contiguous_on_gpu():
     shape = gen.scaled(gen.config(2), B=4, Hq=8, Hkv=2, ctx=(30, 1200))
     L, kv, q, mask = case(shape, 3, paged=False)
