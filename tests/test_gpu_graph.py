@@ -229,6 +229,55 @@ def test_recorded_round_replays_to_the_same_bits(dtype, B):
             lib.specexit_graph_destroy(graph)
 
 
+@pytest.mark.parametrize("calls,foreign,where", [(1, False, "own"), (2, False, "null"), (2, False, "other"), (3, False, "null"), (1, True, "own")])
+def test_short_recordings_replay_like_long_ones(calls, foreign, where):
+    # one and two attention calls are two and four kernels, which are launched one by one when they are replayed; three
+    # calls, and a recording with a kernel that is not the library's, are launched as a graph
+    shape = gen.scaled(gen.config(1), B=2, Hq=8, Hkv=2, n_q=5, ctx=(100, 900))
+    lib, L = H.sx(), gen.context_lengths(shape, 6)
+    kv = gen.kv_cache(shape, L, shape.n_q, 6)
+    view, keep = H.kv_view_of(shape, kv)
+    ctx = H.dev(L.astype(np.int32))
+    qs = [H.dev(gen.queries(shape, 20 + i), shape) for i in range(calls)]
+    outs = [torch.zeros_like(q) for q in qs]
+    mark = torch.ones(8, device="cuda")
+    ws = H.workspace(lib.specexit_verify_attn_workspace_bytes(view, shape.B, shape.n_q, shape.Hq))
+    st, other = torch.cuda.Stream(), torch.cuda.Stream()
+
+    def run():
+        if foreign:
+            mark.mul_(2.0)
+        for q, o in zip(qs, outs):
+            lib.specexit_verify_attn(view, shape.B, shape.n_q, shape.Hq, q, ctx, None, shape.d ** -0.5, o, ws, stream=torch.cuda.current_stream())
+
+    with torch.cuda.stream(st):
+        run()
+        torch.cuda.synchronize()
+        lib.specexit_graph_begin(st)
+        run()
+        graph = lib.specexit_graph_end(st)
+    torch.cuda.synchronize()
+    try:
+        for rep in range(3):
+            print(f"  {calls} calls, foreign {foreign}, {where} stream, replay {rep}", flush=True)
+            for i, q in enumerate(qs):
+                q.copy_(H.dev(gen.queries(shape, 30 + 3 * rep + i), shape))
+                outs[i].zero_()
+            torch.cuda.synchronize()
+            lib.specexit_graph_launch(graph, {"own": st, "other": other, "null": None}[where])
+            torch.cuda.synchronize()
+            replayed = [H.host(o) for o in outs]
+            run()
+            torch.cuda.synchronize()
+            for a, b in zip(replayed, outs):
+                assert np.abs(a).max() > 0
+                np.testing.assert_array_equal(a, H.host(b))
+    finally:
+        lib.specexit_graph_destroy(graph)
+    if foreign:
+        assert (mark == 2.0 ** 7).all()            # the first run, and three replays and eager runs
+
+
 def test_graph_argument_errors():
     lib = H.sx()
     assert lib.LIB.specexit_graph_begin(None) == lib.EINVAL          # the null stream cannot be captured
