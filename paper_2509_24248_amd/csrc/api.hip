@@ -260,10 +260,13 @@ int32_t make_draft_plan(DraftPlan& p, const specexit_model_desc* d, const specex
   }
   p.gemv = p.mfma && gemv_supported(B, D, 2 * D) && gemv_supported(B, (dm.Hq + 2 * dm.Hkv) * dm.d, D) &&
            gemv_supported(B, D, Hd) && gemv_supported(B, 2 * I, D) && gemv_supported(B, D, I) && (dm.d % 2) == 0;
+  if (dm.dtype == SPECEXIT_F32)
+    p.gemv = gemv_f32_supported(B, D, 2 * D) && gemv_f32_supported(B, Nq, D) && gemv_f32_supported(B, D, Hd) && gemv_f32_supported(B, D, I) && (dm.d % 2) == 0;
   if (p.gemv) {
     auto plan_v = [&](GemvArgs& g, int N, int K) {
       memset(&g, 0, sizeof(g));
       g.N = N; g.K = K; g.M = B; g.nseg = 1;
+      g.f32 = dm.dtype == SPECEXIT_F32;
       g.seg_end[0] = g.seg_end[1] = g.seg_end[2] = N;
       gemv_plan(g, num_cus());
     };
@@ -296,6 +299,7 @@ int32_t make_draft_plan(DraftPlan& p, const specexit_model_desc* d, const specex
     if (p.gemv && p.vhead.grid > p.head_lists) p.head_lists = p.vhead.grid;
   } else {
     plan_gemm(p.head, dm.V + 3, D, B);
+    if (p.gemv) p.head_lists = p.vhead.grid;
   }
   p.partial_bytes = 0;
   if (p.mfma && !p.gemv) {
@@ -467,7 +471,7 @@ int32_t run_draft(DraftPlan& p, const specexit_draft_weights* w, const specexit_
     const int piece = 3 * num_cus();
     auto ssq_of = [&](int which) { return b.ssq + static_cast<size_t>(which) * B * piece; };
     GemvArgs g = p.vo;                        // a = x + W_o attn
-    g.w[0] = w->w_o; g.a_mode = 1; g.a_src = b.attn_out;
+    g.w[0] = w->w_o; g.a_mode = bf16 ? 1 : 0; g.a_src = b.attn_out;
     g.residual = b.x_buf; g.out_x = b.a_buf; g.out_ssq = ssq_of(1);
     if ((rc = check_hip(launch_gemv(g, s), "gemv o"))) return rc;
     g = p.vgu;                                // silu(W_gate m) * (W_up m), m = RMSNorm(a)
@@ -536,6 +540,13 @@ int32_t run_draft(DraftPlan& p, const specexit_draft_weights* w, const specexit_
       g.part_idx = b.part_idx;
       g.extra_out = b.extra;
       if ((rc = check_hip(launch_head_wide(g, s), "gemm head"))) return rc;
+    } else if (p.gemv) {
+      GemvArgs g = p.vhead;                   // fp32 logits, ranked below
+      g.w[0] = w->w_head;
+      g.a_mode = 3; g.a_src = p.head.a_src; g.a_ssq = p.head.a_ssq; g.a_nssq = p.head.a_nssq; g.a_gain = w->ln_final;
+      g.a_eps = dm.rms_eps;
+      g.epi = 4; g.out_x = b.partial;
+      if ((rc = check_hip(launch_gemv(g, s), "gemv head"))) return rc;
     } else if ((rc = run_gemm(p.head, bf16, w->w_head, nullptr, nullptr, b, s, "gemm head"))) {
       return rc;
     }

@@ -14,40 +14,73 @@ namespace sx {
 
 namespace {
 
-constexpr int kTK = 32;  // keys per tile of the ALU kernel
-
-template <typename T>
-__device__ __forceinline__ const T* kv_row(const AttnArgs& a, const void* pool, int b, int g, int64_t p) {
-  const T* base = static_cast<const T*>(pool);
+// Entry p of a unit: its row in the pools.
+__device__ __forceinline__ size_t kv_entry(const AttnArgs& a, int b, int g, int p) {
   if (a.paged) {
-    const int page = checked_page(a.page_table[static_cast<size_t>(b) * a.max_pages + p / a.page_size], a.n_pages, a.status);
-    return base + ((static_cast<size_t>(page) * a.Hkv + g) * a.page_size + p % a.page_size) * a.d;
+    const int in_seq = static_cast<int>(static_cast<uint32_t>(p) / static_cast<uint32_t>(a.page_size));
+    const int page = checked_page(a.page_table[static_cast<size_t>(b) * a.max_pages + in_seq], a.n_pages, a.status);
+    return (static_cast<size_t>(page) * a.Hkv + g) * a.page_size + (p - in_seq * a.page_size);
   }
-  return base + ((static_cast<size_t>(b) * a.Hkv + g) * a.l_max + p) * a.d;
+  return (static_cast<size_t>(b) * a.Hkv + g) * a.l_max + p;
 }
 
 // Plain-ALU kernel, any storage type: fp32 caches, and bf16 ones whose page size is no power of two.
+// A tile is a granule of 64 keys: a wave has a row's scores in its 64 lanes, so that the softmax needs no LDS round trip and a
+// tile two barriers.  The entries of the next tile are requested into registers before the current one is worked on, and those
+// of the first together with the queries: short launches are a chain of latencies (one granule per workgroup up to 256 of
+// them), long ones wait for memory otherwise.  Rows that are few leave threads over in P V: these take the keys in
+// groups, whose sums meet at the segment's end.  Whole calls, before (tiles of 32 keys, five barriers each, the softmax by a thread per row) / now:
+// fp32, 1 sequence of 256-512 entries, 8 queries of 8 heads, 64 wide 21.1 / 15.5 us; 2 of 1000-2000, 10 of 16, 64 wide 29.3 / 22.7; 4 of
+// 500-1000, 17 of 16, 64 wide 37.2 / 29.6; 8 of 1000-2000, 5 of 8, 128 wide, paged 48.0 / 46.5; the split kernel of 1 x 256
+// entries, 1 query 11.7 / 7.5.
+constexpr int kTK = kAttnGran;
+constexpr int kTP = kTK + 4;              // floats per row of probabilities (padded: several rows of it are read at once)
+constexpr size_t kValuLds = 150 * 1024;
+// LDS of the kernel: V tiles share the K tiles' place where both do not fit
+__host__ __device__ inline size_t valu_lds_bytes(int R, int d, int B, bool shared) {
+  return sizeof(float) * (static_cast<size_t>(R) * (d + kTP + 3) + kTK * (d + 4) + (shared ? 0 : kTK * d) + attn_sched_words(B));
+}
+
 template <typename T, int D>
 __global__ __launch_bounds__(256) void k_attn_split_valu(const AttnArgs a) {
   extern __shared__ float smem[];
-  const int G = a.Hq / a.Hkv;
+  const int G = a.G;
   const int R = G * a.n_q;
-  const int tid = threadIdx.x;
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const bool shared = valu_lds_bytes(R, D, a.B, false) > kValuLds;   // uniform
   constexpr int DP = D + 4;
-  float* Qs = smem;                 // [R][D]
-  float* Ks = Qs + R * D;           // [kTK][DP]
-  float* Vs = Ks + kTK * DP;        // [kTK][DP]
-  float* Ss = Vs + kTK * DP;        // [R][kTK]
-  float* Ms = Ss + R * kTK;         // [R] running max
-  float* Ls = Ms + R;               // [R] running sum
-  float* As = Ls + R;               // [R] rescale of this tile
-  int* sched_lds = reinterpret_cast<int*>(As + R);   // [2 B + 1]
+  float* Qs = smem;                       // [R][D]
+  float* Ks = Qs + R * D;                 // [kTK][DP]
+  float* Vs = shared ? Ks : Ks + kTK * DP;                   // [kTK][D]
+  float* Ss = Ks + kTK * DP + (shared ? 0 : kTK * D);        // [R][kTP] probabilities
+  float* Ms = Ss + R * kTP;               // [R] running max
+  float* Ls = Ms + R;                     // [R] running sum
+  float* As = Ls + R;                     // [R] rescale of this tile
+  int* sched_lds = reinterpret_cast<int*>(As + R);
   attn_sched_build(a, sched_lds);
-  const AttnLine line = attn_sched_line(sched_lds[a.B], a.B, a.Hkv, a.pad, a.wide_from, a.wgrid);
+  const AttnLine line = attn_sched_line(__builtin_amdgcn_readfirstlane(sched_lds[a.B]), a.B, a.Hkv, a.pad, a.wide_from, a.wgrid);
   if (blockIdx.x == 0) {
     for (int i = tid; i <= a.B; i += 256) a.sched[i] = sched_lds[i];
   }
   if (static_cast<int>(blockIdx.x) >= line.W) return;
+  // P V: thread (c4, r0) has columns 4 c4 .. + 3 of rows r0, r0 + RSTEP, ..; with at most half of RSTEP rows, KG groups of
+  // RP row slots take kTK / KG keys each
+  constexpr int C4 = D / 4;               // float4 columns
+  constexpr int RSTEP = 256 / C4;         // rows covered per pass
+  constexpr int MAXU = (128 + RSTEP - 1) / RSTEP;
+  const int c4 = tid % C4;
+  int KG = 1;
+  while (2 * KG * R <= RSTEP) KG *= 2;
+  const int RP = RSTEP / KG;
+  const int r0 = (tid / C4) % RP, kgrp = (tid / C4) / RP;
+  const int jlo = kgrp * (kTK / KG), jhi = jlo + kTK / KG;
+  constexpr int EPV = Elem<T>::kPer16B;
+  constexpr int VPR = D / EPV;            // 16-byte pieces of a cache row
+  constexpr int NL = kTK * VPR / 256;     // pieces of a K or V tile per thread
+  constexpr int JSTEP = 256 / VPR;        // keys between them
+  const int lj = tid / VPR, lc = tid % VPR;
+
   const int x_hi = attn_sched_lo(line, blockIdx.x + 1);
   for (int x_cur = attn_sched_lo(line, blockIdx.x); x_cur < x_hi;) {
   const AttnSeg seg = attn_sched_segment(a, sched_lds, line.pad, x_cur, x_hi);
@@ -55,121 +88,139 @@ __global__ __launch_bounds__(256) void k_attn_split_valu(const AttnArgs a) {
   if (seg.s1 <= seg.s0) continue;
   const int g = seg.g, b = seg.b, L = seg.L, s0 = seg.s0, s1 = seg.s1;
 
+  uint4 kr[NL], vr[NL];
+  auto fetch = [&](int t0) {              // (keys past the range repeat the last one; they are masked, their V is zeroed)
+#pragma unroll
+    for (int u = 0; u < NL; ++u) {
+      const size_t at = kv_entry(a, b, g, min(t0 + lj + u * JSTEP, s1 - 1)) * VPR + lc;
+      kr[u] = static_cast<const uint4*>(a.k)[at];
+      vr[u] = static_cast<const uint4*>(a.v)[at];
+    }
+  };
+  auto put = [&](float* dst, int stride, const uint4& raw, int j) {
+    float f[8];
+    if constexpr (EPV == 8) {
+      unpack16(raw, f);
+      *reinterpret_cast<float4*>(dst + j * stride + lc * 8 + 4) = make_float4(f[4], f[5], f[6], f[7]);
+    } else {
+      f[0] = __uint_as_float(raw.x); f[1] = __uint_as_float(raw.y); f[2] = __uint_as_float(raw.z); f[3] = __uint_as_float(raw.w);
+    }
+    *reinterpret_cast<float4*>(dst + j * stride + lc * EPV) = make_float4(f[0], f[1], f[2], f[3]);
+  };
+  auto put_v = [&](int t0) {
+#pragma unroll
+    for (int u = 0; u < NL; ++u) put(Vs, D, t0 + lj + u * JSTEP < s1 ? vr[u] : make_uint4(0u, 0u, 0u, 0u), lj + u * JSTEP);
+  };
+  fetch(s0);
   for (int idx = tid; idx < R * D; idx += 256) {
     const int r = idx / D, c = idx % D;
-    const int i = r / G, hh = r % G;
+    const int i = (r * a.g_inv) >> 16, hh = r - i * G;         // r / G
     const T* qp = static_cast<const T*>(a.q) + ((static_cast<size_t>(b) * a.n_q + i) * a.Hq + g * G + hh) * D;
     Qs[idx] = Elem<T>::load(qp + c);
   }
   for (int r = tid; r < R; r += 256) { Ms[r] = -INFINITY; Ls[r] = 0.f; }
-
-  constexpr int C4 = D / 4;               // float4 columns
-  constexpr int RSTEP = 256 / C4;         // rows covered per pass
-  constexpr int MAXU = (128 + RSTEP - 1) / RSTEP;
-  const int c4 = tid % C4, r0 = tid / C4;
   float4 o[MAXU];
 #pragma unroll
   for (int u = 0; u < MAXU; ++u) o[u] = make_float4(0.f, 0.f, 0.f, 0.f);
-  __syncthreads();
 
   for (int t0 = s0; t0 < s1; t0 += kTK) {
-    // stage K and V rows of this tile as fp32
-    for (int idx = tid; idx < kTK * (D / Elem<T>::kPer16B); idx += 256) {
-      constexpr int VPR = D / Elem<T>::kPer16B;
-      const int j = idx / VPR, vc = idx % VPR;
-      const int p = t0 + j;
-      float kf[8], vf[8];
-      if (p < s1) {
-        const uint4 kraw = reinterpret_cast<const uint4*>(kv_row<T>(a, a.k, b, g, p))[vc];
-        const uint4 vraw = reinterpret_cast<const uint4*>(kv_row<T>(a, a.v, b, g, p))[vc];
-        if (Elem<T>::kPer16B == 8) {
-          unpack16(kraw, kf);
-          unpack16(vraw, vf);
-        } else {
-          kf[0] = __uint_as_float(kraw.x); kf[1] = __uint_as_float(kraw.y);
-          kf[2] = __uint_as_float(kraw.z); kf[3] = __uint_as_float(kraw.w);
-          vf[0] = __uint_as_float(vraw.x); vf[1] = __uint_as_float(vraw.y);
-          vf[2] = __uint_as_float(vraw.z); vf[3] = __uint_as_float(vraw.w);
-        }
-      } else {
+    const bool more = t0 + kTK < s1;
+    if (t0 > s0) __syncthreads();         // the tile before is done with
 #pragma unroll
-        for (int e = 0; e < 8; ++e) { kf[e] = 0.f; vf[e] = 0.f; }
+    for (int u = 0; u < NL; ++u) put(Ks, DP, kr[u], lj + u * JSTEP);
+    if (!shared) {
+      put_v(t0);
+      if (more) fetch(t0 + kTK);
+    }
+    __syncthreads();
+    // scores and softmax: lane = key, wave w has rows w, w + 4, .., four at a time
+    const int p = t0 + lane;
+    const float4* kv = reinterpret_cast<const float4*>(Ks + lane * DP);
+    for (int rb = wv; rb < R; rb += 16) {
+      float acc[4] = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll 4
+      for (int c = 0; c < C4; ++c) {
+        const float4 y = kv[c];
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          const float4 x = *reinterpret_cast<const float4*>(Qs + min(rb + 4 * e, R - 1) * D + 4 * c);
+          acc[e] = fmaf(x.x, y.x, acc[e]); acc[e] = fmaf(x.y, y.y, acc[e]);
+          acc[e] = fmaf(x.z, y.z, acc[e]); acc[e] = fmaf(x.w, y.w, acc[e]);
+        }
       }
 #pragma unroll
-      for (int e = 0; e < Elem<T>::kPer16B; ++e) {
-        Ks[j * DP + vc * Elem<T>::kPer16B + e] = kf[e];
-        Vs[j * DP + vc * Elem<T>::kPer16B + e] = vf[e];
-      }
-    }
-    __syncthreads();
-    // scores with the block mask applied
-    for (int idx = tid; idx < R * kTK; idx += 256) {
-      const int r = idx / kTK, j = idx % kTK;
-      const int p = t0 + j;
-      bool vis = p < s1;
-      if (vis && p >= L) {
-        const int i = r / G;
-        const uint64_t row = a.mask ? a.mask[static_cast<size_t>(b) * a.mask_stride + i] : ((2ull << i) - 1ull);
-        vis = (row >> (p - L)) & 1ull;
-      }
-      float acc = 0.f;
-      if (vis) {
-        const float4* qv = reinterpret_cast<const float4*>(Qs + r * D);
-        const float4* kv = reinterpret_cast<const float4*>(Ks + j * DP);
-#pragma unroll 8
-        for (int c = 0; c < C4; ++c) {
-          const float4 x = qv[c], y = kv[c];
-          acc = fmaf(x.x, y.x, acc); acc = fmaf(x.y, y.y, acc);
-          acc = fmaf(x.z, y.z, acc); acc = fmaf(x.w, y.w, acc);
+      for (int e = 0; e < 4; ++e) {
+        const int r = rb + 4 * e;
+        if (r >= R) break;                // uniform
+        bool vis = p < s1;
+        if (vis && p >= L) {
+          const int i = (r * a.g_inv) >> 16;
+          const uint64_t row = a.mask ? a.mask[static_cast<size_t>(b) * a.mask_stride + i] : ((2ull << i) - 1ull);
+          vis = (row >> (p - L)) & 1ull;
+        }
+        const float x = vis ? acc[e] * a.scale : -INFINITY;
+        const float m_old = Ms[r];
+        const float m_new = fmaxf(m_old, wave_max_dpp(x));
+        float alpha = 1.f, pr = 0.f;
+        if (m_new != -INFINITY) {
+          alpha = m_old == -INFINITY ? 0.f : expf(m_old - m_new);
+          pr = expf(x - m_new);           // exp(-inf) = 0 for masked keys
+        }
+        const float sum = wave_sum_dpp(pr);
+        Ss[r * kTP + lane] = pr;
+        if (lane == 0) {
+          Ms[r] = m_new;
+          Ls[r] = Ls[r] * alpha + sum;
+          As[r] = alpha;
         }
       }
-      Ss[idx] = vis ? acc * a.scale : -INFINITY;
     }
     __syncthreads();
-    // online softmax bookkeeping, one thread per row
-    for (int r = tid; r < R; r += 256) {
-      float tmax = -INFINITY;
-      for (int j = 0; j < kTK; ++j) tmax = fmaxf(tmax, Ss[r * kTK + j]);
-      const float m_old = Ms[r];
-      const float m_new = fmaxf(m_old, tmax);
-      float alpha = 1.f, sum = 0.f;
-      if (m_new == -INFINITY) {
-        for (int j = 0; j < kTK; ++j) Ss[r * kTK + j] = 0.f;
-      } else {
-        alpha = (m_old == -INFINITY) ? 0.f : expf(m_old - m_new);
-        for (int j = 0; j < kTK; ++j) {
-          const float pj = expf(Ss[r * kTK + j] - m_new);  // exp(-inf) = 0 for masked keys
-          Ss[r * kTK + j] = pj;
-          sum += pj;
-        }
-      }
-      Ms[r] = m_new;
-      Ls[r] = Ls[r] * alpha + sum;
-      As[r] = alpha;
+    if (shared) {
+      put_v(t0);
+      if (more) fetch(t0 + kTK);
+      __syncthreads();
     }
-    __syncthreads();
 #pragma unroll
     for (int u = 0; u < MAXU; ++u) {
       const int r = r0 + u * RSTEP;
       if (r < R) {
         const float al = As[r];
         float4 acc = make_float4(o[u].x * al, o[u].y * al, o[u].z * al, o[u].w * al);
-        for (int j = 0; j < kTK; ++j) {
-          const float pj = Ss[r * kTK + j];
-          const float4 vv = *reinterpret_cast<const float4*>(Vs + j * DP + c4 * 4);
-          acc.x = fmaf(pj, vv.x, acc.x); acc.y = fmaf(pj, vv.y, acc.y);
-          acc.z = fmaf(pj, vv.z, acc.z); acc.w = fmaf(pj, vv.w, acc.w);
+#pragma unroll 2
+        for (int j = jlo; j < jhi; j += 4) {
+          const float4 pj = *reinterpret_cast<const float4*>(Ss + r * kTP + j);
+          const float w[4] = {pj.x, pj.y, pj.z, pj.w};
+#pragma unroll
+          for (int e = 0; e < 4; ++e) {
+            const float4 vv = *reinterpret_cast<const float4*>(Vs + (j + e) * D + c4 * 4);
+            acc.x = fmaf(w[e], vv.x, acc.x); acc.y = fmaf(w[e], vv.y, acc.y);
+            acc.z = fmaf(w[e], vv.z, acc.z); acc.w = fmaf(w[e], vv.w, acc.w);
+          }
         }
         o[u] = acc;
       }
     }
-    __syncthreads();
   }
   const size_t unit = static_cast<size_t>(blockIdx.x) + static_cast<size_t>(b) * a.Hkv + g;   // partial slot of segment (w, u)
+  if (KG > 1) {                           // uniform: at most RSTEP / 2 rows, one slot each
+    float4* meet = reinterpret_cast<float4*>(Ks);
+    __syncthreads();
+    meet[tid] = o[0];
+    __syncthreads();
+    if (kgrp == 0) {
+      for (int k = 1; k < KG; ++k) {
+        const float4 v = meet[tid + k * RP * C4];
+        o[0].x += v.x; o[0].y += v.y; o[0].z += v.z; o[0].w += v.w;
+      }
+    }
+  }
+  if (kgrp == 0) {
 #pragma unroll
-  for (int u = 0; u < MAXU; ++u) {
-    const int r = r0 + u * RSTEP;
-    if (r < R) *reinterpret_cast<float4*>(a.part_o + (unit * R + r) * D + c4 * 4) = o[u];
+    for (int u = 0; u < MAXU; ++u) {
+      const int r = r0 + u * RSTEP;
+      if (r < R && (u == 0 || KG == 1)) *reinterpret_cast<float4*>(a.part_o + (unit * R + r) * D + c4 * 4) = o[u];
+    }
   }
   for (int r = tid; r < R; r += 256) {
     a.part_ml[(unit * R + r) * 2 + 0] = Ms[r];
@@ -202,8 +253,8 @@ __device__ __forceinline__ void attn_row_again(const AttnArgs& a, int b, int i, 
   for (int p0 = 0; p0 < n; p0 += 8) {
     const int p = p0 + kq;
     const bool in = p < n;
-    const uint4 kr = *reinterpret_cast<const uint4*>(kv_row<bf16_t>(a, a.k, b, g, min(p, n - 1)) + 8 * c);
-    const uint4 vr = *reinterpret_cast<const uint4*>(kv_row<bf16_t>(a, a.v, b, g, min(p, n - 1)) + 8 * c);
+    const size_t at = kv_entry(a, b, g, min(p, n - 1)) * 8 + c;
+    const uint4 kr = static_cast<const uint4*>(a.k)[at], vr = static_cast<const uint4*>(a.v)[at];
     float kf[8], vf[8], x = 0.f;
     unpack16(kr, kf);
     unpack16(vr, vf);
@@ -440,18 +491,14 @@ hipError_t launch_combine(const AttnArgs& a, hipStream_t s) {
   return hipGetLastError();
 }
 
-size_t valu_smem_bytes(const AttnArgs& a) {
-  const int R = (a.Hq / a.Hkv) * a.n_q;
-  return sizeof(float) * (static_cast<size_t>(R) * a.d + 2 * kTK * (a.d + 4) + static_cast<size_t>(R) * kTK + 3 * R + attn_sched_words(a.B));
-}
-
 template <typename T, int D>
 hipError_t launch_valu(const AttnArgs& a, hipStream_t s) {
-  const size_t smem = valu_smem_bytes(a);
+  const int R = a.G * a.n_q;
+  const size_t smem = valu_lds_bytes(R, D, a.B, valu_lds_bytes(R, D, a.B, false) > kValuLds);
   // set once per process; a function-local static is initialised under the language's own lock,
   // so first calls from several host threads are safe
   static const hipError_t attr = hipFuncSetAttribute(reinterpret_cast<const void*>(&k_attn_split_valu<T, D>),
-                                       hipFuncAttributeMaxDynamicSharedMemorySize, 150 * 1024);
+                                       hipFuncAttributeMaxDynamicSharedMemorySize, kValuLds);
   if (attr != hipSuccess) return attr;
   hipLaunchKernelGGL((k_attn_split_valu<T, D>), dim3(a.wgrid), dim3(256), smem, s, a);
   return hipGetLastError();

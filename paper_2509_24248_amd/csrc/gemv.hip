@@ -44,12 +44,31 @@ __device__ __forceinline__ uint4 load_weights16(const char* p) {
   }
 }
 
-__device__ __forceinline__ const char* weight_row(const GemvArgs& g, int n) {
+__device__ __forceinline__ const char* weight_row(const GemvArgs& g, int n, int elem = 2) {
   int s = 0, start = 0;
 #pragma unroll
   for (int i = 0; i < 2; ++i)
     if (s + 1 < g.nseg && n >= g.seg_end[s]) { start = g.seg_end[s]; ++s; }
-  return static_cast<const char*>(g.w[s]) + static_cast<size_t>(n - start) * g.K * 2;
+  return static_cast<const char*>(g.w[s]) + static_cast<size_t>(n - start) * g.K * elem;
+}
+
+// Where head hh of the concatenated q|k|v rows goes for activation row m: its query row or cache entry (null: outside the cache)
+__device__ __forceinline__ void* rope_entry(const RopeArgs& ra, int m, int hh, int elem) {
+  if (hh < ra.Hq) return static_cast<char*>(ra.q_out) + (static_cast<size_t>(m) * ra.Hq + hh) * ra.d * elem;
+  const int b = m / ra.W;
+  const int slot = ra.pos[b] + (ra.node ? ra.node[m % ra.W] : 0);
+  if (slot < 0 || slot >= ra.l_max) return nullptr;
+  const bool is_k = hh < ra.Hq + ra.Hkv;
+  const int h = is_k ? hh - ra.Hq : hh - ra.Hq - ra.Hkv;
+  size_t off;
+  if (ra.paged) {
+    const int page = ra.page_table[static_cast<size_t>(b) * ra.max_pages + slot / ra.page_size];
+    if (!page_in_pool(page, ra.n_pages, ra.status)) return nullptr;
+    off = ((static_cast<size_t>(page) * ra.Hkv + h) * ra.page_size + slot % ra.page_size) * ra.d;
+  } else {
+    off = ((static_cast<size_t>(b) * ra.Hkv + h) * ra.l_max + slot) * ra.d;
+  }
+  return static_cast<char*>(is_k ? ra.kc : ra.vc) + off * elem;
 }
 
 constexpr int kHeadStepsInFlight = 2;
@@ -203,7 +222,6 @@ __global__ __launch_bounds__(512) void k_gemv(const GemvArgs g) {
         const int hh = n1 / ra.d, c = n1 - hh * ra.d;
         const int b = m / ra.W;
         const int ps = ra.pos[b] + ra.level;
-        const int slot = ra.pos[b] + (ra.node ? ra.node[m % ra.W] : 0);
         float x1 = v1, x2 = v2;
         if (hh < ra.Hq + ra.Hkv) {
           const double ang = static_cast<double>(ps) * ra.inv_freq[c];
@@ -213,23 +231,7 @@ __global__ __launch_bounds__(512) void k_gemv(const GemvArgs g) {
           x1 = v1 * cs - v2 * sn;
           x2 = v2 * cs + v1 * sn;
         }
-        bf16_t* dst = nullptr;
-        if (hh < ra.Hq) {
-          dst = static_cast<bf16_t*>(ra.q_out) + (static_cast<size_t>(m) * ra.Hq + hh) * ra.d;
-        } else if (slot >= 0 && slot < ra.l_max) {
-          const bool is_k = hh < ra.Hq + ra.Hkv;
-          const int h = is_k ? hh - ra.Hq : hh - ra.Hq - ra.Hkv;
-          size_t off;
-          bool ok = true;
-          if (ra.paged) {
-            const int page = ra.page_table[static_cast<size_t>(b) * ra.max_pages + slot / ra.page_size];
-            ok = page_in_pool(page, ra.n_pages, ra.status);
-            off = ((static_cast<size_t>(page) * ra.Hkv + h) * ra.page_size + slot % ra.page_size) * ra.d;
-          } else {
-            off = ((static_cast<size_t>(b) * ra.Hkv + h) * ra.l_max + slot) * ra.d;
-          }
-          if (ok) dst = static_cast<bf16_t*>(is_k ? ra.kc : ra.vc) + off;
-        }
+        bf16_t* dst = static_cast<bf16_t*>(rope_entry(ra, m, hh, 2));
         if (dst) {
           dst[c] = f32_to_bf16(x1);
           dst[c + half] = f32_to_bf16(x2);
@@ -291,6 +293,212 @@ hipError_t launch_mr(const GemvArgs& g, hipStream_t s) {
   return g.stream ? launch_mr_sif<MR, kStepsInFlight, true>(g, s) : launch_mr_sif<MR, kStepsInFlight, false>(g, s);
 }
 
+// ---- fp32 weights
+// The same chain of launches for fp32 models (the projections without a norm, rotary or gate kernel between them: nine
+// launches per draft step instead of fifteen).  Such models are small, every launch is latency: a step's kernels read 0.5 to
+// 10 MB each, mostly from the last-level cache, and take 2 to 4 us.  So the activations are staged as x gain, without waiting for the
+// row's sum of squares, whose factor 1 / rms enters after the dot product; the angle of the rotary pair is worked out
+// while the weights are on their way; lane m finishes activation row m.  LDS position of row m, element k: [k / 256][m][k % 256], so
+// that lane l's four values of a step are one float4.
+constexpr int kF32Steps = 4;       // 16-byte loads per row in flight
+constexpr int kF32Lds = 144 * 1024;
+constexpr int kF32Rows = 8;
+
+template <int MR, int EPI>
+__global__ __launch_bounds__(512) void k_gemv_f32(const GemvArgs g) {
+  extern __shared__ float lds[];
+  __shared__ float ssq_sh[8][MR];
+  __shared__ float bv_sh[8][MR];
+  __shared__ int bi_sh[8][MR];
+  const int lane = threadIdx.x & 63;
+  const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int nwaves = blockDim.x >> 6;
+  const int nt = blockDim.x;
+  const int K = g.K, K4 = K >> 2;
+  const int steps = K >> 8;                    // K is a multiple of 256
+  const int m0 = blockIdx.y * MR;              // this workgroup's activation rows (rows past the last one repeat it, dropped later)
+  const int mine = m0 + lane;                  // the row that this lane finishes
+  const bool owner = lane < MR && mine < g.M;
+
+  float sq[MR];
+#pragma unroll
+  for (int m = 0; m < MR; ++m) {
+    sq[m] = 0.f;
+    if (g.a_mode == 3)
+      for (int j = lane; j < g.a_nssq; j += 64) sq[m] += g.a_ssq[min(m0 + m, g.M - 1) * g.a_nssq + j];
+  }
+  for (int idx = threadIdx.x; idx < MR * K4; idx += nt) {
+    const int r = idx / K4, k = (idx - r * K4) << 2;
+    const int m = min(m0 + r, g.M - 1);
+    const float* src;
+    if (g.a_mode == 2) {
+      const int half = K >> 1;
+      src = k < half ? static_cast<const float*>(g.a_embed) + static_cast<size_t>(checked_token(g.a_tok[m], g.a_vocab, g.status)) * half + k
+                     : static_cast<const float*>(g.a_src) + static_cast<size_t>(m) * half + (k - half);
+    } else {
+      src = static_cast<const float*>(g.a_src) + static_cast<size_t>(m) * K + k;
+    }
+    float f[4];
+#pragma unroll
+    for (int e = 0; e < 4; ++e) f[e] = src[e];
+    if (g.a_mode == 3) {
+      const float* gain = static_cast<const float*>(g.a_gain) + k;
+#pragma unroll
+      for (int e = 0; e < 4; ++e) f[e] *= gain[e];
+    }
+    *reinterpret_cast<float4*>(lds + ((k >> 8) * MR + r) * 256 + (k & 255)) = make_float4(f[0], f[1], f[2], f[3]);
+  }
+  float rs[MR];
+#pragma unroll
+  for (int m = 0; m < MR; ++m) rs[m] = g.a_mode == 3 ? 1.0f / sqrtf(wave_sum_dpp(sq[m]) / static_cast<float>(K) + g.a_eps) : 1.f;
+  __syncthreads();
+
+  const int P = (g.N + 1) >> 1;                // (the head's row count can be odd: its last pair is half empty)
+  float ssq = 0.f, bestv = -INFINITY;
+  int besti = INT_MAX;
+  for (int p = blockIdx.x * nwaves + wv; p < P; p += gridDim.x * nwaves) {
+    int n1, n2;
+    if constexpr (EPI == 1) {
+      const int half = g.rope.d >> 1;
+      const int head = p / half;
+      n1 = head * g.rope.d + (p - head * half);
+      n2 = n1 + half;
+    } else if constexpr (EPI == 2) {
+      n1 = p;
+      n2 = P + p;
+    } else {
+      n1 = 2 * p;
+      n2 = n1 + 1;
+    }
+    const float4* r1 = reinterpret_cast<const float4*>(weight_row(g, n1, 4)) + lane;
+    const float4* r2 = reinterpret_cast<const float4*>(weight_row(g, min(n2, g.N - 1), 4)) + lane;   // a row past the end repeats the last one, unused
+    float acc1[MR], acc2[MR];
+#pragma unroll
+    for (int m = 0; m < MR; ++m) { acc1[m] = 0.f; acc2[m] = 0.f; }
+    float cs = 1.f, sn = 0.f;
+    for (int j0 = 0; j0 < steps; j0 += kF32Steps) {
+      float4 w1[kF32Steps], w2[kF32Steps];
+#pragma unroll
+      for (int u = 0; u < kF32Steps; ++u) {
+        const int j = min(j0 + u, steps - 1);
+        w1[u] = r1[j * 64];
+        w2[u] = r2[j * 64];
+      }
+      if constexpr (EPI == 1) {
+        if (j0 == 0 && n1 < (g.rope.Hq + g.rope.Hkv) * g.rope.d) {
+          // angle, sine and cosine in double: they are rounded once
+          const double ang = static_cast<double>(g.rope.pos[min(mine, g.M - 1) / g.rope.W] + g.rope.level) * g.rope.inv_freq[n1 % g.rope.d];
+          double s, c;
+          sincos(ang, &s, &c);
+          sn = static_cast<float>(s);
+          cs = static_cast<float>(c);
+        }
+      }
+#pragma unroll
+      for (int u = 0; u < kF32Steps; ++u) {
+        const int j = j0 + u;
+        if (j < steps) {
+#pragma unroll
+          for (int m = 0; m < MR; ++m) {
+            const float4 a = *reinterpret_cast<const float4*>(lds + (j * MR + m) * 256 + lane * 4);
+            acc1[m] = fmaf(a.x, w1[u].x, acc1[m]); acc1[m] = fmaf(a.y, w1[u].y, acc1[m]);
+            acc1[m] = fmaf(a.z, w1[u].z, acc1[m]); acc1[m] = fmaf(a.w, w1[u].w, acc1[m]);
+            acc2[m] = fmaf(a.x, w2[u].x, acc2[m]); acc2[m] = fmaf(a.y, w2[u].y, acc2[m]);
+            acc2[m] = fmaf(a.z, w2[u].z, acc2[m]); acc2[m] = fmaf(a.w, w2[u].w, acc2[m]);
+          }
+        }
+      }
+    }
+    float x1 = 0.f, x2 = 0.f;                  // lane m: row m0 + m
+#pragma unroll
+    for (int m = 0; m < MR; ++m) {
+      const float v1 = wave_sum_dpp(acc1[m]) * rs[m], v2 = wave_sum_dpp(acc2[m]) * rs[m];
+      if (lane == m) { x1 = v1; x2 = v2; }
+    }
+    if (!owner) continue;
+    if constexpr (EPI == 0) {
+      const size_t at = static_cast<size_t>(mine) * g.N + n1;
+      if (g.residual) {
+        x1 += g.residual[at];
+        x2 += g.residual[at + 1];
+      }
+      *reinterpret_cast<float2*>(g.out_x + at) = make_float2(x1, x2);
+      if (g.out_store) {
+        static_cast<float*>(g.out_store)[at] = x1;
+        static_cast<float*>(g.out_store)[at + 1] = x2;
+      }
+      ssq += x1 * x1 + x2 * x2;
+    } else if constexpr (EPI == 1) {
+      float* dst = static_cast<float*>(rope_entry(g.rope, mine, n1 / g.rope.d, 4));
+      if (dst) {
+        const int c = n1 % g.rope.d;
+        const bool turn = n1 < (g.rope.Hq + g.rope.Hkv) * g.rope.d;
+        dst[c] = turn ? x1 * cs - x2 * sn : x1;
+        dst[c + (g.rope.d >> 1)] = turn ? x2 * cs + x1 * sn : x2;
+      }
+    } else if constexpr (EPI == 2) {
+      g.out_x[static_cast<size_t>(mine) * P + p] = x1 * sigmoidf_(x1) * x2;
+    } else if constexpr (EPI == 3) {
+      if (n1 < g.V) { if (better(x1, n1, bestv, besti)) { bestv = x1; besti = n1; } }
+      else if (g.extra_out) g.extra_out[mine * g.n_extra + (n1 - g.V)] = x1;
+      if (n2 < g.N) {
+        if (n2 < g.V) { if (better(x2, n2, bestv, besti)) { bestv = x2; besti = n2; } }
+        else if (g.extra_out) g.extra_out[mine * g.n_extra + (n2 - g.V)] = x2;
+      }
+    } else {
+      const size_t at = static_cast<size_t>(mine) * g.N;
+      g.out_x[at + n1] = x1;
+      if (n2 < g.N) g.out_x[at + n2] = x2;
+    }
+  }
+
+  // ---- the workgroup's pieces of the rows' sums of squares, its best (value, index) per row (waves in a fixed order)
+  if constexpr (EPI == 0 || EPI == 3) {
+    if (lane < MR) {
+      ssq_sh[wv][lane] = ssq;
+      bv_sh[wv][lane] = bestv;
+      bi_sh[wv][lane] = besti;
+    }
+    __syncthreads();
+    if (wv == 0 && owner) {
+      const size_t at = static_cast<size_t>(mine) * gridDim.x + blockIdx.x;
+      if constexpr (EPI == 0) {
+        float t = 0.f;
+        for (int w = 0; w < nwaves; ++w) t += ssq_sh[w][lane];
+        if (g.out_ssq) g.out_ssq[at] = t;
+      } else {
+        float bv = bv_sh[0][lane];
+        int bi = bi_sh[0][lane];
+        for (int w = 1; w < nwaves; ++w)
+          if (better(bv_sh[w][lane], bi_sh[w][lane], bv, bi)) { bv = bv_sh[w][lane]; bi = bi_sh[w][lane]; }
+        g.part_val[at] = bv;
+        g.part_idx[at] = bi;
+      }
+    }
+  }
+}
+
+template <int MR, int EPI>
+hipError_t launch_f32_as(const GemvArgs& g, hipStream_t s) {
+  static const hipError_t attr = hipFuncSetAttribute(reinterpret_cast<const void*>(&k_gemv_f32<MR, EPI>),
+                                                     hipFuncAttributeMaxDynamicSharedMemorySize, kF32Lds);
+  if (attr != hipSuccess) return attr;
+  hipLaunchKernelGGL((k_gemv_f32<MR, EPI>), dim3(g.grid, (g.M + MR - 1) / MR), dim3(64 * g.waves), static_cast<size_t>(g.K) * MR * sizeof(float), s, g);
+  return hipGetLastError();
+}
+
+template <int MR>
+hipError_t launch_f32_mr(const GemvArgs& g, hipStream_t s) {
+  switch (g.epi) {
+    case 0: return launch_f32_as<MR, 0>(g, s);
+    case 1: return launch_f32_as<MR, 1>(g, s);
+    case 2: return launch_f32_as<MR, 2>(g, s);
+    case 3: return launch_f32_as<MR, 3>(g, s);
+    case 4: return launch_f32_as<MR, 4>(g, s);
+    default: return hipErrorInvalidValue;
+  }
+}
+
 }  // namespace
 
 size_t gemv_lds_bytes(const GemvArgs& g) {
@@ -304,12 +512,17 @@ bool gemv_supported(int M, int N, int K) {
   return M >= 1 && M <= 4 && (K % 512) == 0 && N >= 2 && gemv_lds_bytes(g) <= 144 * 1024;
 }
 
+bool gemv_f32_supported(int M, int N, int K) { return M >= 1 && M <= kF32Rows && K >= 256 && K % 256 == 0 && K <= kF32Lds / 16 && N >= 2; }
+
 // One pair per wave at a time, eight waves per workgroup sharing one staging of the activations
 // (smaller workgroups for the narrow projections were measured slower), at most three
-// workgroups per compute unit.
+// workgroups per compute unit.  fp32 projections of fewer pairs than fill the chip that way take smaller workgroups: K
+// and N of a tiny model leave 30 compute units at work otherwise.
 void gemv_plan(GemvArgs& g, int num_cus, int per_cu) {
   const int P = (g.N + 1) / 2;
   g.waves = 8;
+  if (g.f32)
+    while (g.waves > 2 && P < g.waves * num_cus) g.waves >>= 1;
   int grid = (P + g.waves - 1) / g.waves;
   const int cap = per_cu * num_cus;
   if (grid > cap) grid = cap;
@@ -318,6 +531,12 @@ void gemv_plan(GemvArgs& g, int num_cus, int per_cu) {
 }
 
 hipError_t launch_gemv(const GemvArgs& g, hipStream_t s) {
+  if (g.f32) {
+    if (!gemv_f32_supported(g.M, g.N, g.K)) return hipErrorInvalidValue;
+    if (g.M == 1) return launch_f32_mr<1>(g, s);
+    if (g.M == 2) return launch_f32_mr<2>(g, s);
+    return g.M <= 4 || g.K > kF32Lds / 32 ? launch_f32_mr<4>(g, s) : launch_f32_mr<8>(g, s);
+  }
   switch (g.M) {
     case 1: return launch_mr<1>(g, s);
     case 2: return launch_mr<2>(g, s);

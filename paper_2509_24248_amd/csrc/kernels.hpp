@@ -99,14 +99,15 @@ struct GemmArgs {
   float* logits_dbg;   // [M][V] or nullptr
 };
 
-// Row-streaming GEMV for steps of at most four rows (gemv.hip): no split over K, the
+// Row-streaming GEMV (gemv.hip) for bf16 steps of at most four rows and for fp32 ones: no split over K, the
 // epilogue runs in the wave that owns a pair of weight rows.
 struct GemvArgs {
+  int f32;               // weights, gains, stored rows and cache entries are fp32, else bf16
   const void* w[3];
   int seg_end[3];
   int nseg;
   int N, K, M;
-  int a_mode;            // 0 fp32 rows, 1 bf16 rows, 2 [embed[tok] ; hidden], 3 RMSNorm of fp32 rows
+  int a_mode;            // 0 fp32 rows, 1 bf16 rows (not with f32), 2 [embed[tok] ; hidden], 3 RMSNorm of fp32 rows
   const void* a_src;
   const void* a_embed;
   const int32_t* a_tok;  // mode 2: token ids [M], forced into 0 .. a_vocab-1
@@ -121,6 +122,7 @@ struct GemvArgs {
                          // 2: (gate p, up p) of the gate|up projection -> out_x[m][p] = silu(gate) * up
                          // 3: widened head: rows < V -> per-workgroup argmax candidates part_val / part_idx
                          //    [M][grid], rows V.. -> extra_out [M][n_extra]; N may be odd
+                         // 4: out_x[m][n] = sums, N may be odd (f32 only)
   const float* residual;
   float* out_x;
   void* out_store;
@@ -134,6 +136,7 @@ struct GemvArgs {
   int grid, waves;       // launch shape, from gemv_plan
 };
 bool gemv_supported(int M, int N, int K);
+bool gemv_f32_supported(int M, int N, int K);
 size_t gemv_lds_bytes(const GemvArgs& g);
 void gemv_plan(GemvArgs& g, int num_cus, int per_cu = 3);   // at most per_cu workgroups per compute unit
 hipError_t launch_gemv(const GemvArgs& g, hipStream_t s);
