@@ -258,15 +258,14 @@ int32_t make_draft_plan(DraftPlan& p, const specexit_model_desc* d, const specex
     three_blocks(p.gu, I, 2 * I, 2 * I, 2);
     plan_gemm(p.down, D, I, B);
   }
-  p.gemv = p.mfma && gemv_supported(B, D, 2 * D) && gemv_supported(B, (dm.Hq + 2 * dm.Hkv) * dm.d, D) &&
-           gemv_supported(B, D, Hd) && gemv_supported(B, 2 * I, D) && gemv_supported(B, D, I) && (dm.d % 2) == 0;
-  if (dm.dtype == SPECEXIT_F32)
-    p.gemv = gemv_f32_supported(B, D, 2 * D) && gemv_f32_supported(B, Nq, D) && gemv_f32_supported(B, D, Hd) && gemv_f32_supported(B, D, I) && (dm.d % 2) == 0;
+  const bool f32 = dm.dtype == SPECEXIT_F32;
+  p.gemv = (p.mfma || f32) && gemv_supported(f32, B, D, 2 * D) && gemv_supported(f32, B, Nq, D) && gemv_supported(f32, B, D, Hd) &&
+           gemv_supported(f32, B, 2 * I, D) && gemv_supported(f32, B, D, I) && (dm.d % 2) == 0;
   if (p.gemv) {
     auto plan_v = [&](GemvArgs& g, int N, int K) {
       memset(&g, 0, sizeof(g));
       g.N = N; g.K = K; g.M = B; g.nseg = 1;
-      g.f32 = dm.dtype == SPECEXIT_F32;
+      g.f32 = f32;
       g.seg_end[0] = g.seg_end[1] = g.seg_end[2] = N;
       gemv_plan(g, num_cus());
     };

@@ -31,6 +31,21 @@ __device__ __forceinline__ uint32_t pack_bf16x2(float a, float b) {
   return __builtin_bit_cast(uint32_t, __builtin_convertvector(v, bf16x2_t));
 }
 
+// Requests every 64-byte line of the kernel's arguments (`BYTES` of them) at once and waits.  They lie in memory that no cache
+// holds yet, and the compiler loads each where it is first needed: a chain of misses in a kernel that takes 4 us.
+template <int BYTES>
+__device__ __forceinline__ void arguments_at_once() {
+  typedef const __attribute__((address_space(4))) int* kernarg_t;
+  const kernarg_t p = (kernarg_t)__builtin_amdgcn_kernarg_segment_ptr();
+  constexpr int N = (BYTES + 63) / 64;
+  static_assert(N <= 16, "");
+  int v[16];
+#pragma unroll
+  for (int i = 0; i < 16; ++i) v[i] = p[(i < N ? i : 0) * 16];
+  asm volatile("" ::"s"(v[0]), "s"(v[1]), "s"(v[2]), "s"(v[3]), "s"(v[4]), "s"(v[5]), "s"(v[6]), "s"(v[7]), "s"(v[8]), "s"(v[9]), "s"(v[10]),
+               "s"(v[11]), "s"(v[12]), "s"(v[13]), "s"(v[14]), "s"(v[15]));
+}
+
 template <typename T> struct Elem;
 template <> struct Elem<float> {
   static constexpr int kPer16B = 4;

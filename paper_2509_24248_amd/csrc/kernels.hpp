@@ -135,9 +135,7 @@ struct GemvArgs {
   int stream;            // 1: weights read with non-temporal loads (read once; always for the head), 0: ordinary loads
   int grid, waves;       // launch shape, from gemv_plan
 };
-bool gemv_supported(int M, int N, int K);
-bool gemv_f32_supported(int M, int N, int K);
-size_t gemv_lds_bytes(const GemvArgs& g);
+bool gemv_supported(bool f32, int M, int N, int K);
 void gemv_plan(GemvArgs& g, int num_cus, int per_cu = 3);   // at most per_cu workgroups per compute unit
 hipError_t launch_gemv(const GemvArgs& g, hipStream_t s);
 

@@ -66,11 +66,11 @@ def test_tiny_fp32_config_chain_of_steps():
 
 
 @pytest.mark.parametrize("B,D,I,V,paged", [(1, 256, 256, 257, True), (2, 512, 1280, 1000, False), (3, 256, 768, 3001, False), (4, 512, 256, 64, True),
-                                           (5, 256, 512, 100, False), (8, 768, 2816, 5001, True), (9, 256, 5120, 2000, False), (17, 512, 512, 301, False),
+                                           (5, 256, 512, 100, False), (8, 768, 2816, 5001, True), (9, 256, 5120, 2000, False), (17, 512, 512, 301, False), (26, 256, 3328, 500, False), (26, 256, 3072, 500, True),
                                            (2, 320, 512, 1000, False)])
 def test_fp32_rows(B, D, I, V, paged):
     # one, two, four and eight rows per workgroup and their remainders; one to many steps of 256 weights; odd and even numbers of head
-    # rows; the last one has no multiple of 256 and takes the plain kernels.  Tolerance: 32-bit sums (rel_err's limit of fp32 storage)
+    # rows; the last one has no multiple of 256 and takes the plain kernels, as does one of many rows and a long K.  Tolerance: 32-bit sums (rel_err's limit of fp32 storage)
     shape = gen.scaled(gen.config(0), D=D, Hq=4, Hkv=2, d=64 if B % 2 else 128, I=I, V=V, B=B, ctx=(0, 200), k=2)
     w, kv, tok, g, pos = setup(shape, B, paged=paged, std=0.05)
     pos[0] = 0
@@ -78,7 +78,7 @@ def test_fp32_rows(B, D, I, V, paged):
     one_step(shape, w, kv, tok, g, pos, label="fp32 rows")
 
 
-@pytest.mark.parametrize("B,paged", [(1, False), (3, True), (9, False), (16, True)])
+@pytest.mark.parametrize("B,paged", [(1, False), (2, True), (3, True), (9, False), (16, True)])
 def test_small_bf16_mfma(B, paged):
     shape = gen.scaled(gen.config(2), D=256, Hq=4, Hkv=2, d=64, I=512, V=3000, B=B, ctx=(0, 300), k=2)
     w, kv, tok, g, pos = setup(shape, B, paged=paged, std=0.05)
