@@ -12,8 +12,8 @@
 //     loads their operand pieces of the next k block (L2 hits) while it works on this one, from a
 //     copy of the activations in operand order (k_pack_act, k_pack_norm) so that a load covers whole cache
 //     lines; up to 32 plain bf16 rows are read in place;
-//   - a pass takes 2 TG tiles through all k blocks, the two halves of a k block one after the other,
-//     so the activation pieces of a k block are fetched once for 256 weight rows; one LDS read (the
+//   - a pass takes 2 to 5 times TG tiles through all k blocks, the "halves" of a k block one after the other,
+//     so the activation pieces of a k block are fetched once for 256 to 640 weight rows; one LDS read (the
 //     transposed weight operand) feeds RT matrix instructions.
 // One workgroup barrier per stage hands a landed stage to the consumers and the stage read
 // before it back to the producers.  Every lane keeps the best of the logits it has seen; they become one
@@ -22,7 +22,7 @@
 // 230 us = 6.6 / 6.4 / 6.0 / 5.4 TB/s (one call after the other; 2 % less with single calls), where a kernel that staged
 // the activations in LDS for every eight weight tiles took 230 / 233 us for the first two and the same form with one wave
 // per 32 rows 225 us for the third.  Draft head with 8 / 64 fp32 rows, same size: 230 -> 183 and 503 -> 216 us (that kernel
-// read all 128 virtual rows from LDS for every tile: the LDS was the bound).  Many rows are slower: by leaving parts out
+// read all 128 virtual rows from LDS for every tile: the LDS was the bound); 64 rows 210 us with value and rest in one accumulator.  Many rows are slower: by leaving parts out
 // at 144 rows (D = 5120), the producers alone stream at 7 TB/s (230 us), the consumers alone take 225 us, of
 // that the LDS reads and barriers 45 us, the matrix instructions 45 us, the activation loads 25 us (80 us
 // before they covered whole cache lines: straight from the row-major matrix a load is 16 rows x 64 bytes,
@@ -79,15 +79,21 @@ struct Halves {
   __device__ __forceinline__ int first(int h) const { return t_lo + n * h / count; }
 };
 
-// The stages of a workgroup in the order they pass through the ring.  A pass takes two halves (the last
-// pass one, if the count is odd) through all k blocks, the halves of a k block one after the other, so that
-// the consumers fetch their activation pieces of a k block once for both.
-template <int LV>
+// A pass takes up to MAXH halves through all k blocks; the passes of a workgroup are as equal as they can be, the first ones
+// larger.  Number of halves of the pass that starts with half0 still to take `left` of them.
+template <int MAXH>
+__device__ __forceinline__ int pass_halves(int left) {
+  const int passes = (left + MAXH - 1) / MAXH;
+  return passes > 0 ? (left + passes - 1) / passes : 0;
+}
+
+// The stages of a workgroup in the order they pass through the ring: the halves of a k block one after the other, so that
+// the consumers fetch their activation pieces of a k block once for all halves of the pass.
+template <int MAXH, int LV>
 struct StageCursor {
   int half0, nh, h, n;   // first half and number of halves of the current pass; half within the pass; k blocks done
   KOrder<LV> k;
-  static constexpr int kNH = 2;
-  __device__ __forceinline__ StageCursor(int nhalf, int KB) : half0(0), nh(min(kNH, nhalf)), h(0), n(0), k(KB) {}
+  __device__ __forceinline__ StageCursor(int nhalf, int KB) : half0(0), nh(pass_halves<MAXH>(nhalf)), h(0), n(0), k(KB) {}
   __device__ __forceinline__ void advance(int nhalf, int KB) {
     if (++h < nh) return;
     h = 0;
@@ -95,7 +101,7 @@ struct StageCursor {
     if (++n < KB) return;
     n = 0;
     half0 += nh;
-    nh = min(kNH, nhalf - half0);
+    nh = pass_halves<MAXH>(nhalf - half0);
   }
 };
 
@@ -136,11 +142,11 @@ struct Best {
 // The consumer side of k_head_wide for a wave that owns RT row tiles of the operand (from tile rt0 on) and, of
 // every half, the JN weight tiles from jc0 on: one barrier per stage, a candidate update per pass.
 // PL = 2: tiles 2 o and 2 o + 1 are the bf16 value and the bf16 rounding of the rest of the same 16
-// activation rows, whose two products are added at the end.  Every lane keeps the TB best of what it has seen;
+// activation rows, whose two products add up in one accumulator.  Every lane keeps the TB best of what it has seen;
 // they are merged over the four lanes of a row when the workgroup's share is done.
 // A row has `slots` candidate slots per workgroup, one per column split; a wave that covers the whole half
 // (JN = TG) where others split it fills the remaining one with nothing.
-template <int RT, int JN, int TG, int S, int PL, int TB, int LV>
+template <int RT, int JN, int TG, int S, int PL, int TB, int MAXH, int LV>
 struct Consumer {
   static constexpr int kStage = TG * 4096;
   static constexpr int RO = RT / PL;        // 16-row tiles of results
@@ -185,13 +191,13 @@ struct Consumer {
   // one pass: NH halves starting at half `half0`
   template <int NH>
   __device__ __forceinline__ void pass(int half0) {
-    f32x4_t acc[RT][NH * JN];
+    f32x4_t acc[RO][NH * JN];     // (value and rest of a row add up in one place)
 #pragma unroll
-    for (int t = 0; t < RT; ++t)
+    for (int o = 0; o < RO; ++o)
 #pragma unroll
-      for (int j = 0; j < NH * JN; ++j) acc[t][j] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+      for (int j = 0; j < NH * JN; ++j) acc[o][j] = f32x4_t{0.f, 0.f, 0.f, 0.f};
 
-    f32x4_t left[LV > 0 ? LV : 1][RT][NH * JN];     // finished left siblings of the chunk tree, per level
+    f32x4_t left[LV > 0 ? LV : 1][RO][NH * JN];     // finished left siblings of the chunk tree, per level
 
     // The waves go through a stage's four k steps in read groups of CH tiles, the operand reads one
     // group ahead of the matrix instructions (k steps outermost: between two matrix instructions on the
@@ -239,11 +245,11 @@ struct Consumer {
           }
           __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-          for (int jj = 0; jj < CH; ++jj)
+          for (int t = 0; t < RT; ++t)
 #pragma unroll
-            for (int t = 0; t < RT; ++t)
-              acc[t][h * JN + j0 + jj] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, wf[c & 1][jj]),
-                                                                                 __builtin_bit_cast(bf16x8_t, b[t][s]), acc[t][h * JN + j0 + jj], 0, 0, 0);
+            for (int jj = 0; jj < CH; ++jj)
+              acc[t / PL][h * JN + j0 + jj] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, wf[c & 1][jj]),
+                                                                                      __builtin_bit_cast(bf16x8_t, b[t][s]), acc[t / PL][h * JN + j0 + jj], 0, 0, 0);
           // The next k block's activation pieces (1 KB of consecutive bytes per instruction, L2 hits that
           // take more than a microsecond under the weight stream).  Pieces 0 and 1, which the next block
           // needs first, are requested into spare registers at the start of this block and moved over when
@@ -275,15 +281,15 @@ struct Consumer {
             if (!up) continue;
             if (ci >> l & 1) {
 #pragma unroll
-              for (int t = 0; t < RT; ++t)
+              for (int o = 0; o < RO; ++o)
 #pragma unroll
-                for (int j = 0; j < NH * JN; ++j) acc[t][j] += left[l][t][j];
+                for (int j = 0; j < NH * JN; ++j) acc[o][j] += left[l][o][j];
             } else {
               up = false;
 #pragma unroll
-              for (int t = 0; t < RT; ++t)
+              for (int o = 0; o < RO; ++o)
 #pragma unroll
-                for (int j = 0; j < NH * JN; ++j) { left[l][t][j] = acc[t][j]; acc[t][j] = f32x4_t{0.f, 0.f, 0.f, 0.f}; }
+                for (int j = 0; j < NH * JN; ++j) { left[l][o][j] = acc[o][j]; acc[o][j] = f32x4_t{0.f, 0.f, 0.f, 0.f}; }
             }
           }
         }
@@ -313,8 +319,7 @@ struct Consumer {
           float4* mine = reinterpret_cast<float4*>(lds + S * kStage) + (threadIdx.x >> 6) * (JN * 64) + (threadIdx.x & 63);
 #pragma unroll
           for (int j = 0; j < JN; ++j) {
-            f32x4_t v = acc[PL * o][h * JN + j];
-            if constexpr (PL == 2) v += acc[2 * o + 1][h * JN + j];
+            const f32x4_t v = acc[o][h * JN + j];
             mine[j * 64] = make_float4(v[0], v[1], v[2], v[3]);
           }
           const int left_j = min(JN, tile1 - tile0);
@@ -331,8 +336,7 @@ struct Consumer {
             const bool inside = tile0 + j < tile1;           // uniform
 #pragma unroll
             for (int i = 0; i < 4; ++i) {
-              float val = acc[PL * o][h * JN + j][i];
-              if constexpr (PL == 2) val += acc[2 * o + 1][h * JN + j][i];
+              const float val = acc[o][h * JN + j][i];
               best[o].add(inside ? val : -INFINITY, nb + 16 * j + i);    // n grows with h, j and i
             }
           }
@@ -342,8 +346,7 @@ struct Consumer {
 #pragma unroll
             for (int i = 0; i < 4; ++i) {
               const int n = nb + 16 * j + i;
-              float val = acc[PL * o][h * JN + j][i];
-              if constexpr (PL == 2) val += acc[2 * o + 1][h * JN + j][i];
+              const float val = acc[o][h * JN + j][i];
               if (owner && tile0 + j < tile1 && n < g.N) {
                 if (n < g.V) {
                   if (g.logits_dbg) g.logits_dbg[static_cast<size_t>(m) * g.V + n] = val;
@@ -361,9 +364,14 @@ struct Consumer {
 
   __device__ __forceinline__ void run() {
 #pragma unroll 1
-    for (int half0 = 0; half0 < halves.count; half0 += 2) {
-      if (half0 + 1 < halves.count) pass<2>(half0);
+    for (int half0 = 0; half0 < halves.count;) {
+      const int nh = pass_halves<MAXH>(halves.count - half0);
+      if (MAXH >= 5 && nh == 5) pass<MAXH >= 5 ? 5 : 1>(half0);
+      else if (MAXH >= 4 && nh == 4) pass<MAXH >= 4 ? 4 : 1>(half0);
+      else if (MAXH >= 3 && nh == 3) pass<MAXH >= 3 ? 3 : 1>(half0);
+      else if (nh == 2) pass<2>(half0);
       else pass<1>(half0);
+      half0 += nh;
     }
     // the row's best over its four lanes, one candidate (list) per workgroup and column split
     const int slots = g.wide_slots;
@@ -469,13 +477,24 @@ __device__ __forceinline__ void wait_tiles(int n) {
   __builtin_amdgcn_s_waitcnt(vmcnt_imm(PER * N));
 }
 
+// Halves per pass: as many as the accumulators have registers for, because every pass fetches all activations again, through the
+// same path as the weights (V = 151936, D = 5120, 64 rows: 242 us, 227 with the fetches left out; 144 rows 281 and 241).  A
+// workgroup has five halves of that vocabulary.  Draft step, D = 4096, with two halves / three / five: 20 rows 337 / 330 / 326 us, 48
+// rows 366 / 359 / 353 (two row tiles of value and rest, half of the columns each); 64 rows 379 / 372 / - (all columns); LM
+// head of 64 rows, D = 4096 / 5120: 198 / 243 -> 192 / 237.  More than 64 rows: three row tiles per wave, with three
+// consumer waves of 512 registers and passes of 20 tiles, are slower (144 rows 281 -> 310).
+constexpr int max_halves(int RT, int CS, int PL, int LV) {
+  if (LV > 0 || RT != 2) return 2;
+  return PL == 2 ? (CS == 2 ? 5 : 3) : CS == 2 ? 3 : 2;
+}
+
 // RG groups of RT row tiles, each group's columns split over CS waves; then the producers.  SPLIT (CS = 1): the
 // last group's second row tile does not exist (an odd number of row tiles), and its one tile is shared with
 // a further wave after the producers, each taking half of the columns: no SIMD then carries three row
 // tiles' worth of matrix instructions.
 template <int RG, int RT, int CS, int PL, int TB, int TG, int S, bool SPLIT, int LV>
 __global__ __launch_bounds__(64 * (RG * CS + kProducers + (SPLIT ? 1 : 0))) void k_head_wide(const GemmArgs g) {
-  constexpr int NC = RG * CS;
+  constexpr int NC = RG * CS, MAXH = max_halves(RT, CS, PL, LV);
   static_assert((4 * TG) % kProducers == 0, "the pieces of a stage are dealt evenly to the producers");
   constexpr int PP = 4 * TG / kProducers;       // 1 KB pieces (4 weight rows x 256 bytes) per producer and stage
   static_assert((S - 2) * PP < 64, "the load counter has six bits");
@@ -504,7 +523,7 @@ __global__ __launch_bounds__(64 * (RG * CS + kProducers + (SPLIT ? 1 : 0))) void
     const int pw = wv - NC;
     static_assert(PP == 2 * TG, "each producer brings in half of every tile");
     const int per_stage = 2 * halves.most;
-    StageCursor<LV> cur(nhalf, KB);
+    StageCursor<MAXH, LV> cur(nhalf, KB);
     // the lane's offset in a tile: rows 4 (j % 4) .. of this producer's pieces, which alternate between two values
     const int r0 = 4 * pw + (lane >> 4), r1 = r0 + 8;
     const uint32_t lane_off0 = r0 * static_cast<uint32_t>(row_bytes) + (((lane & 15) ^ r0) << 4);
@@ -558,12 +577,12 @@ __global__ __launch_bounds__(64 * (RG * CS + kProducers + (SPLIT ? 1 : 0))) void
   constexpr int NT = RG * RT;      // row tiles of the packed activations
   if constexpr (SPLIT) {
     static_assert(RT == 2 && CS == 1 && PL == 1, "a split last tile is the first of a pair");
-    if (wv == NC - 1) Consumer<1, TG / 2, TG, S, PL, TB, LV>(g, lds, (NC - 1) * RT, 0, NT, lane, halves, KB).run();
-    else if (wv > NC) Consumer<1, TG / 2, TG, S, PL, TB, LV>(g, lds, (NC - 1) * RT, TG / 2, NT, lane, halves, KB).run();
-    else Consumer<RT, TG, TG, S, PL, TB, LV>(g, lds, wv * RT, 0, NT, lane, halves, KB).run();
+    if (wv == NC - 1) Consumer<1, TG / 2, TG, S, PL, TB, MAXH, LV>(g, lds, (NC - 1) * RT, 0, NT, lane, halves, KB).run();
+    else if (wv > NC) Consumer<1, TG / 2, TG, S, PL, TB, MAXH, LV>(g, lds, (NC - 1) * RT, TG / 2, NT, lane, halves, KB).run();
+    else Consumer<RT, TG, TG, S, PL, TB, MAXH, LV>(g, lds, wv * RT, 0, NT, lane, halves, KB).run();
   } else {
     constexpr int JN = TG / CS;
-    Consumer<RT, JN, TG, S, PL, TB, LV>(g, lds, (wv / CS) * RT, (wv % CS) * JN, NT, lane, halves, KB).run();
+    Consumer<RT, JN, TG, S, PL, TB, MAXH, LV>(g, lds, (wv / CS) * RT, (wv % CS) * JN, NT, lane, halves, KB).run();
   }
 }
 

@@ -96,6 +96,15 @@ def test_row_tile_edges(B, D):
     one_step(shape, w, kv, tok, g, pos, label="row tile edges")
 
 
+@pytest.mark.parametrize("B,V", [(20, 98400), (33, 151936), (20, 165001), (64, 82000), (64, 151936)])
+def test_head_passes_of_several_halves(B, V):
+    # the widened head over two planes: four and five halves in a pass, twice three; three, three and two of four row tiles
+    shape = gen.scaled(gen.config(2), D=256, Hq=4, Hkv=2, d=64, I=256, V=V, B=B, ctx=(0, 60), k=2)
+    w, kv, tok, g, pos = setup(shape, B, std=0.05)
+    w = force_draft_gap(shape, w, kv, tok, g, pos)
+    one_step(shape, w, kv, tok, g, pos, label="head passes")
+
+
 @pytest.mark.parametrize("B", [5, 9, 40])
 def test_odd_number_of_narrow_kv_heads(B):
     # the k block and the v block of the q|k|v projection then begin inside a group of 128 rows

@@ -99,6 +99,13 @@ def test_bf16_ragged_last_tile(M, V):
     assert err < 1e-3          # bf16 inputs are exact; only fp32 summation order differs
 
 
+@pytest.mark.parametrize("M,V", [(64, 82000), (64, 151936), (64, 165001), (144, 98400)])
+def test_bf16_passes_of_several_halves(M, V):
+    # three halves in a pass, three and two, twice three; two passes of two where a pass takes no more
+    err = run_case(gen.scaled(gen.config(1), V=V, D=128), M, 0, M + V, "passes of several halves")
+    assert err < 1e-3          # bf16 inputs are exact; only fp32 summation order differs
+
+
 @pytest.mark.parametrize("M", [2, 30])
 def test_tie_takes_lowest_index_across_workgroups_that_take_k_in_another_order(M):
     shape = gen.scaled(gen.config(1), V=40000, D=2048)
