@@ -547,6 +547,7 @@ static bool plan_as(AttnArgs& a, int num_cus, int use_mfma, int pad) {
   const int64_t resident = static_cast<int64_t>(num_cus) * (a.use_mfma ? attn_mfma_per_cu(a) : 1);
   const AttnLine line = attn_sched_line(static_cast<int>(a.B * gmax), a.B, a.Hkv, pad, a.wide_from, static_cast<int>(resident));
   int64_t w = line.W;
+  if (line.T > kAttnSpread && w < kAttnSpread) w = std::min<int64_t>(kAttnSpread, resident);   // (fewer granules may take more workgroups)
   if (a.use_mfma) {
     const int64_t seg_gran = attn_mfma_max_chunk(a) / kAttnGran;   // granules one segment may span
     const int64_t need = (line.T + seg_gran - 1) / seg_gran;

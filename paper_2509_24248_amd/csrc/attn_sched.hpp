@@ -69,10 +69,14 @@ __device__ __forceinline__ void attn_sched_build(const AttnArgs& a, int* S) {
 // The line of a launch whose sequences have `gran` granules in all.  Workgroups that take part: one per granule while the launch
 // has a compute unit for each (no workgroup crosses a unit's end then: no padding); one per compute unit up to
 // `wide_from` granules; from there on as many as are resident, with at least two granules each.
+// In the middle range the largest share, T / 256 rounded up, sets the time, so all workgroups have that and there are as few as it
+// takes: every partial result is read again.  (With 256 of them, the first T % 256 one granule larger, the last units of 1
+// sequence x 5610 entries, 4 KV heads, are 90 segments of one granule: 9 queries of 12 heads 13.6 us a layer,
+// 11.2 with 45 of two; 4500 entries 13.3 / 10.7, 8 KV heads, 32 heads 14.7 / 14.2.)
 constexpr int kAttnSpread = 256;
 struct AttnLine {
   int T, W, pad;   // granules with the padding, workgroups, padding per unit
-  int q, r;        // T / W, T % W
+  int q, r;        // granules per workgroup (the last one may have fewer), the first r of them one more
 };
 __host__ __device__ __forceinline__ AttnLine attn_sched_line(int gran, int B, int Hkv, int pad, int wide_from, int wgrid) {
   AttnLine l;
@@ -83,7 +87,13 @@ __host__ __device__ __forceinline__ AttnLine attn_sched_line(int gran, int B, in
     const bool wide = l.T >= wide_from;
     l.T += B * Hkv * pad;
     want = (l.T + 1) >> 1;
-    if (!wide || want < kAttnSpread) want = kAttnSpread;
+    if (!wide || want < kAttnSpread) {
+      l.q = (l.T + kAttnSpread - 1) / kAttnSpread;
+      l.r = 0;
+      l.W = static_cast<int>(static_cast<uint32_t>(l.T + l.q - 1) / static_cast<uint32_t>(l.q));
+      if (l.W <= wgrid) return l;
+      want = l.W;
+    }
   }
   l.W = want < 1 ? 1 : want < wgrid ? want : wgrid;
   l.q = static_cast<int>(static_cast<uint32_t>(l.T) / static_cast<uint32_t>(l.W));   // at least 1: W <= T
@@ -93,7 +103,7 @@ __host__ __device__ __forceinline__ AttnLine attn_sched_line(int gran, int B, in
 
 // First granule of workgroup w, and the workgroup that has granule p.  (One 32-bit division each for the line and the owner: the
 // products of an even deal, w T / W, need 64 bits, whose division is 150 dependent instructions, fetched for a single use.)
-__device__ __forceinline__ int attn_sched_lo(const AttnLine& l, int w) { return w * l.q + min(w, l.r); }
+__device__ __forceinline__ int attn_sched_lo(const AttnLine& l, int w) { return min(w * l.q + min(w, l.r), l.T); }
 __device__ __forceinline__ int attn_sched_owner(const AttnLine& l, int p) {
   const int longer = l.r * (l.q + 1);
   const bool in = p < longer;

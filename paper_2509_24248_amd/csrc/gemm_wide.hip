@@ -245,11 +245,12 @@ struct Consumer {
           }
           __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-          for (int t = 0; t < RT; ++t)
-#pragma unroll
-            for (int jj = 0; jj < CH; ++jj)
-              acc[t / PL][h * JN + j0 + jj] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, wf[c & 1][jj]),
-                                                                                      __builtin_bit_cast(bf16x8_t, b[t][s]), acc[t / PL][h * JN + j0 + jj], 0, 0, 0);
+          for (int i = 0; i < RT * CH; ++i) {
+            // (two planes: the instructions on one accumulator lie CH apart)
+            const int t = PL == 2 ? i / CH : i % RT, jj = PL == 2 ? i % CH : i / RT;
+            acc[t / PL][h * JN + j0 + jj] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, wf[c & 1][jj]),
+                                                                                    __builtin_bit_cast(bf16x8_t, b[t][s]), acc[t / PL][h * JN + j0 + jj], 0, 0, 0);
+          }
           // The next k block's activation pieces (1 KB of consecutive bytes per instruction, L2 hits that
           // take more than a microsecond under the weight stream).  Pieces 0 and 1, which the next block
           // needs first, are requested into spare registers at the start of this block and moved over when
