@@ -1,4 +1,5 @@
-// Row-wise glue of the draft step (Sec. 3.1; Alg. 1 first loop line) around the plain-ALU GEMMs: each kernel takes
+// Row-wise glue of the draft step (Sec. 3.1; Alg. 1 first loop line) around the plain-ALU GEMMs, for the shapes that neither
+// the row-streaming nor the matrix-core kernels take: each kernel takes
 // the fp32 rows of the GEMM before it, applies the layer's elementwise math and leaves the next GEMM's fp32 rows.
 #include "common.hpp"
 #include "kernels.hpp"

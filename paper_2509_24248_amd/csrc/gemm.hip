@@ -1,5 +1,5 @@
-// Plain fp32 ALU GEMM  out[m][n] = sum_k act[m][k] * w[n][k]  (fp32 weights, or any shape the matrix-core kernels
-// reject; HBM-bound, 16-byte loads coalesced along K), and the small kernels behind the heads: merging of
+// Plain fp32 ALU GEMM  out[m][n] = sum_k act[m][k] * w[n][k]  (the fp32 LM head, and any shape the row-streaming and
+// matrix-core kernels reject; HBM-bound, 16-byte loads coalesced along K), and the small kernels behind the heads: merging of
 // argmax / ranked candidates, signal activations.
 #include "common.hpp"
 #include "kernels.hpp"

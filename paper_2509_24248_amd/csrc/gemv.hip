@@ -377,7 +377,9 @@ template <typename T, int MR, bool STREAM>
 hipError_t launch_projection(const GemvArgs& g, hipStream_t s) {
   switch (g.epi * 4 + g.a_mode) {
     case 0: return launch_as<T, MR, kSteps, 0, 0, STREAM>(g, s);
-    case 1: return launch_as<T, MR, kSteps, 1, 0, STREAM>(g, s);
+    case 1:
+      if constexpr (sizeof(T) == 2) return launch_as<T, MR, kSteps, 1, 0, STREAM>(g, s);
+      return hipErrorInvalidValue;
     case 2: return launch_as<T, MR, kSteps, 2, 0, STREAM>(g, s);
     case 4 + 3:
       if constexpr (MR <= 4) return launch_as<T, MR, kSteps, 3, 1, STREAM>(g, s);

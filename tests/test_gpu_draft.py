@@ -175,7 +175,7 @@ def sampled_rows_step(shape, w, kv, tok, g, pos, rows, label):
 @pytest.mark.timeout(1500)
 def test_full_size_config_2_all_eight_rows():
     """Qwen3-8B-like sizes, B = 8, paged cache: the split-K matrix-core projections with their reducing
-    epilogues at full width (steps of up to four rows take the row-streaming path); every row compared."""
+    epilogues at full width (steps of one or two rows take the row-streaming path); every row compared."""
     shape = gen.config(2)
     w, kv, tok, g, pos = setup(shape, 0, paged=True, norms=False)
     rows = list(range(shape.B))
