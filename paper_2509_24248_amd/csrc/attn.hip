@@ -230,6 +230,167 @@ __global__ __launch_bounds__(256) void k_attn_split_valu(const AttnArgs a) {
   }
 }
 
+// The same for 128-wide heads with many rows, where P V is what takes the time: tiles of 32 keys, a thread per row for the softmax.
+// Whole calls, this one / the one above: fp32, 4 sequences of 900 entries, 68 rows per KV head 46.9 / 56.0 us; 3 of 40-8192, 100 rows
+// 111 / 140; bf16, 8 of 500-2000, 64 rows, pages of 48 201 / 244; fp32, 8 of 1500, 20 rows 42.7 / 41.8.
+constexpr int kManyRows = 32, kTKMany = 32;
+__host__ inline size_t many_lds_bytes(int R, int d, int B) {
+  return sizeof(float) * (static_cast<size_t>(R) * (d + kTKMany + 3) + 2 * kTKMany * (d + 4) + attn_sched_words(B));
+}
+
+template <typename T, int D>
+__global__ __launch_bounds__(256) void k_attn_split_rows(const AttnArgs a) {
+  extern __shared__ float smem[];
+  const int G = a.Hq / a.Hkv;
+  const int R = G * a.n_q;
+  const int tid = threadIdx.x;
+  constexpr int DP = D + 4;
+  float* Qs = smem;                 // [R][D]
+  float* Ks = Qs + R * D;           // [kTKMany][DP]
+  float* Vs = Ks + kTKMany * DP;        // [kTKMany][DP]
+  float* Ss = Vs + kTKMany * DP;        // [R][kTKMany]
+  float* Ms = Ss + R * kTKMany;         // [R] running max
+  float* Ls = Ms + R;               // [R] running sum
+  float* As = Ls + R;               // [R] rescale of this tile
+  int* sched_lds = reinterpret_cast<int*>(As + R);   // [2 B + 1]
+  attn_sched_build(a, sched_lds);
+  const AttnLine line = attn_sched_line(sched_lds[a.B], a.B, a.Hkv, a.pad, a.wide_from, a.wgrid);
+  if (blockIdx.x == 0) {
+    for (int i = tid; i <= a.B; i += 256) a.sched[i] = sched_lds[i];
+  }
+  if (static_cast<int>(blockIdx.x) >= line.W) return;
+  const int x_hi = attn_sched_lo(line, blockIdx.x + 1);
+  for (int x_cur = attn_sched_lo(line, blockIdx.x); x_cur < x_hi;) {
+  const AttnSeg seg = attn_sched_segment(a, sched_lds, line.pad, x_cur, x_hi);
+  x_cur = seg.next;
+  if (seg.s1 <= seg.s0) continue;
+  const int g = seg.g, b = seg.b, L = seg.L, s0 = seg.s0, s1 = seg.s1;
+
+  for (int idx = tid; idx < R * D; idx += 256) {
+    const int r = idx / D, c = idx % D;
+    const int i = r / G, hh = r % G;
+    const T* qp = static_cast<const T*>(a.q) + ((static_cast<size_t>(b) * a.n_q + i) * a.Hq + g * G + hh) * D;
+    Qs[idx] = Elem<T>::load(qp + c);
+  }
+  for (int r = tid; r < R; r += 256) { Ms[r] = -INFINITY; Ls[r] = 0.f; }
+
+  constexpr int C4 = D / 4;               // float4 columns
+  constexpr int RSTEP = 256 / C4;         // rows covered per pass
+  constexpr int MAXU = (128 + RSTEP - 1) / RSTEP;
+  const int c4 = tid % C4, r0 = tid / C4;
+  float4 o[MAXU];
+#pragma unroll
+  for (int u = 0; u < MAXU; ++u) o[u] = make_float4(0.f, 0.f, 0.f, 0.f);
+  __syncthreads();
+
+  for (int t0 = s0; t0 < s1; t0 += kTKMany) {
+    // stage K and V rows of this tile as fp32
+    for (int idx = tid; idx < kTKMany * (D / Elem<T>::kPer16B); idx += 256) {
+      constexpr int VPR = D / Elem<T>::kPer16B;
+      const int j = idx / VPR, vc = idx % VPR;
+      const int p = t0 + j;
+      float kf[8], vf[8];
+      if (p < s1) {
+        const size_t at = kv_entry(a, b, g, p) * VPR + vc;
+        const uint4 kraw = static_cast<const uint4*>(a.k)[at];
+        const uint4 vraw = static_cast<const uint4*>(a.v)[at];
+        if (Elem<T>::kPer16B == 8) {
+          unpack16(kraw, kf);
+          unpack16(vraw, vf);
+        } else {
+          kf[0] = __uint_as_float(kraw.x); kf[1] = __uint_as_float(kraw.y);
+          kf[2] = __uint_as_float(kraw.z); kf[3] = __uint_as_float(kraw.w);
+          vf[0] = __uint_as_float(vraw.x); vf[1] = __uint_as_float(vraw.y);
+          vf[2] = __uint_as_float(vraw.z); vf[3] = __uint_as_float(vraw.w);
+        }
+      } else {
+#pragma unroll
+        for (int e = 0; e < 8; ++e) { kf[e] = 0.f; vf[e] = 0.f; }
+      }
+#pragma unroll
+      for (int e = 0; e < Elem<T>::kPer16B; ++e) {
+        Ks[j * DP + vc * Elem<T>::kPer16B + e] = kf[e];
+        Vs[j * DP + vc * Elem<T>::kPer16B + e] = vf[e];
+      }
+    }
+    __syncthreads();
+    // scores with the block mask applied
+    for (int idx = tid; idx < R * kTKMany; idx += 256) {
+      const int r = idx / kTKMany, j = idx % kTKMany;
+      const int p = t0 + j;
+      bool vis = p < s1;
+      if (vis && p >= L) {
+        const int i = r / G;
+        const uint64_t row = a.mask ? a.mask[static_cast<size_t>(b) * a.mask_stride + i] : ((2ull << i) - 1ull);
+        vis = (row >> (p - L)) & 1ull;
+      }
+      float acc = 0.f;
+      if (vis) {
+        const float4* qv = reinterpret_cast<const float4*>(Qs + r * D);
+        const float4* kv = reinterpret_cast<const float4*>(Ks + j * DP);
+#pragma unroll 8
+        for (int c = 0; c < C4; ++c) {
+          const float4 x = qv[c], y = kv[c];
+          acc = fmaf(x.x, y.x, acc); acc = fmaf(x.y, y.y, acc);
+          acc = fmaf(x.z, y.z, acc); acc = fmaf(x.w, y.w, acc);
+        }
+      }
+      Ss[idx] = vis ? acc * a.scale : -INFINITY;
+    }
+    __syncthreads();
+    // online softmax bookkeeping, one thread per row
+    for (int r = tid; r < R; r += 256) {
+      float tmax = -INFINITY;
+      for (int j = 0; j < kTKMany; ++j) tmax = fmaxf(tmax, Ss[r * kTKMany + j]);
+      const float m_old = Ms[r];
+      const float m_new = fmaxf(m_old, tmax);
+      float alpha = 1.f, sum = 0.f;
+      if (m_new == -INFINITY) {
+        for (int j = 0; j < kTKMany; ++j) Ss[r * kTKMany + j] = 0.f;
+      } else {
+        alpha = (m_old == -INFINITY) ? 0.f : expf(m_old - m_new);
+        for (int j = 0; j < kTKMany; ++j) {
+          const float pj = expf(Ss[r * kTKMany + j] - m_new);  // exp(-inf) = 0 for masked keys
+          Ss[r * kTKMany + j] = pj;
+          sum += pj;
+        }
+      }
+      Ms[r] = m_new;
+      Ls[r] = Ls[r] * alpha + sum;
+      As[r] = alpha;
+    }
+    __syncthreads();
+#pragma unroll
+    for (int u = 0; u < MAXU; ++u) {
+      const int r = r0 + u * RSTEP;
+      if (r < R) {
+        const float al = As[r];
+        float4 acc = make_float4(o[u].x * al, o[u].y * al, o[u].z * al, o[u].w * al);
+        for (int j = 0; j < kTKMany; ++j) {
+          const float pj = Ss[r * kTKMany + j];
+          const float4 vv = *reinterpret_cast<const float4*>(Vs + j * DP + c4 * 4);
+          acc.x = fmaf(pj, vv.x, acc.x); acc.y = fmaf(pj, vv.y, acc.y);
+          acc.z = fmaf(pj, vv.z, acc.z); acc.w = fmaf(pj, vv.w, acc.w);
+        }
+        o[u] = acc;
+      }
+    }
+    __syncthreads();
+  }
+  const size_t unit = static_cast<size_t>(blockIdx.x) + static_cast<size_t>(b) * a.Hkv + g;   // partial slot of segment (w, u)
+#pragma unroll
+  for (int u = 0; u < MAXU; ++u) {
+    const int r = r0 + u * RSTEP;
+    if (r < R) *reinterpret_cast<float4*>(a.part_o + (unit * R + r) * D + c4 * 4) = o[u];
+  }
+  for (int r = tid; r < R; r += 256) {
+    a.part_ml[(unit * R + r) * 2 + 0] = Ms[r];
+    a.part_ml[(unit * R + r) * 2 + 1] = Ls[r];
+  }
+  __syncthreads();   // a further segment restarts the running maxima and sums
+  }
+}
+
 // One output row of a 64-wide bf16 launch again, by one wave, with fp32 probabilities.  The matrix-core kernel
 // multiplies V with a probability in two parts, of which the second is 0 or negative as often as not: an infinite V
 // entry then becomes inf - inf or 0 inf, although its probability is positive.  So the merging kernels hand every row
@@ -494,6 +655,15 @@ hipError_t launch_combine(const AttnArgs& a, hipStream_t s) {
 template <typename T, int D>
 hipError_t launch_valu(const AttnArgs& a, hipStream_t s) {
   const int R = a.G * a.n_q;
+  if constexpr (D == 128) {
+    if (R > kManyRows) {
+      static const hipError_t attr = hipFuncSetAttribute(reinterpret_cast<const void*>(&k_attn_split_rows<T, D>),
+                                                         hipFuncAttributeMaxDynamicSharedMemorySize, kValuLds);
+      if (attr != hipSuccess) return attr;
+      hipLaunchKernelGGL((k_attn_split_rows<T, D>), dim3(a.wgrid), dim3(256), many_lds_bytes(R, D, a.B), s, a);
+      return hipGetLastError();
+    }
+  }
   const size_t smem = valu_lds_bytes(R, D, a.B, valu_lds_bytes(R, D, a.B, false) > kValuLds);
   // set once per process; a function-local static is initialised under the language's own lock,
   // so first calls from several host threads are safe
