@@ -174,13 +174,21 @@ size_t specexit_draft_step_workspace_bytes(const specexit_model_desc *desc,
  * replays).  Each entry point must have been called once with the same shapes before the
  * capture (first calls set kernel attributes and query the device, which capture forbids), and
  * nothing else may use the stream or allocate device memory on this thread while capturing.
+ * A recording of up to four of the library's kernels, one after the other, is replayed by
+ * launching them; specexit_graph_kernels tells how many (0: it is launched as a graph).  Replays
+ * that several host threads start on one stream run one after the other, each of them whole.
+ * What is not ordered: other work that another host thread puts on the stream meanwhile may run
+ * between the kernels of a replay, and replays of one recording on different streams may overlap,
+ * in the buffers that they share.  Callers who do either order it themselves.
  * The graph owns no buffers; specexit_graph_destroy releases it.  Host pointers: `out` and the
  * graph handle.  Errors: SPECEXIT_EINVAL (null arguments), SPECEXIT_ELAUNCH (the runtime
- * refused; the capture is ended and dropped). */
+ * refused: a capture is ended and dropped; of a replay the kernels in front of the refused one
+ * may have been enqueued). */
 typedef struct specexit_graph specexit_graph;
 int32_t specexit_graph_begin(void *stream);
 int32_t specexit_graph_end(void *stream, specexit_graph **out);
 int32_t specexit_graph_launch(const specexit_graph *graph, void *stream);
+int32_t specexit_graph_kernels(const specexit_graph *graph);
 int32_t specexit_graph_destroy(specexit_graph *graph);
 
 /* Zero-fills a workspace (a small kernel on `stream`; see SPECEXIT_FLAG_WORKSPACE_PREPARED). */

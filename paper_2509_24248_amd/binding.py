@@ -25,7 +25,7 @@ EXPORTS = [
     "specexit_verify_attn", "specexit_verify_attn_workspace_bytes",
     "specexit_lmhead_argmax", "specexit_lmhead_argmax_workspace_bytes",
     "specexit_draft_tree_level", "specexit_draft_tree_level_workspace_bytes", "specexit_tree_gather",
-    "specexit_graph_begin", "specexit_graph_end", "specexit_graph_launch", "specexit_graph_destroy",
+    "specexit_graph_begin", "specexit_graph_end", "specexit_graph_launch", "specexit_graph_kernels", "specexit_graph_destroy",
     "specexit_workspace_prepare", "specexit_accept_exit", "specexit_kv_compact", "specexit_last_error", "specexit_version", "specexit_profile_events", "specexit_copy_probe",
     "specexit_workspace_bytes", "specexit_set_dev_status", "specexit_lmhead_argmax_noalloc",
 ]
@@ -101,6 +101,8 @@ def _load() -> C.CDLL:
     lib.specexit_graph_end.argtypes = [vp, C.POINTER(vp)]
     lib.specexit_graph_launch.restype = i32
     lib.specexit_graph_launch.argtypes = [vp, vp]
+    lib.specexit_graph_kernels.restype = i32
+    lib.specexit_graph_kernels.argtypes = [vp]
     lib.specexit_graph_destroy.restype = i32
     lib.specexit_graph_destroy.argtypes = [vp]
     lib.specexit_version.restype = u32
@@ -262,6 +264,14 @@ def specexit_graph_end(stream):
 
 def specexit_graph_launch(graph, stream=None) -> None:
     _check(LIB.specexit_graph_launch(graph, _stream(stream)))
+
+
+def specexit_graph_kernels(graph) -> int:
+    """Kernels that a replay launches one after the other; 0: it is launched as a graph."""
+    n = int(LIB.specexit_graph_kernels(graph))
+    if n < 0:
+        _check(n)
+    return n
 
 
 def specexit_graph_destroy(graph) -> None:

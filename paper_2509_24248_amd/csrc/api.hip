@@ -951,9 +951,20 @@ int32_t specexit_graph_end(void* stream, specexit_graph** out) {
   return SPECEXIT_OK;
 }
 
+// Replays of several host threads on one stream take turns, so that none of them puts its kernels between another's: neither
+// launches one by one nor, in ROCm 7.0, hipGraphLaunch keep other threads out by themselves (a thread that copies what two recorded
+// kernels count up, 1000 replays: 256 copies lay between the two kernels of a graph).  A lock per stream, more or less: streams
+// share 64 of them.
+static std::mutex g_replay_mu[64];
+static std::mutex& replay_lock(hipStream_t s) {
+  const uint64_t key = reinterpret_cast<uintptr_t>(s) * 0x9E3779B97F4A7C15ull;
+  return g_replay_mu[key >> 58];
+}
+
 int32_t specexit_graph_launch(const specexit_graph* graph, void* stream) {
   if (!graph) return fail(SPECEXIT_EINVAL, "graph_launch: null graph");
   const hipStream_t s = static_cast<hipStream_t>(stream);
+  std::lock_guard<std::mutex> lock(replay_lock(s));
   // one by one only where that is the same thing: a stream of the recording's device, which is the current one, not itself
   // under capture
   if (graph->n_direct) {
@@ -971,6 +982,11 @@ int32_t specexit_graph_launch(const specexit_graph* graph, void* stream) {
     (void)hipGetLastError();          // (a stream that these questions are not allowed of is hipGraphLaunch's to refuse)
   }
   return check_hip(hipGraphLaunch(graph->exec, s), "graph_launch");
+}
+
+int32_t specexit_graph_kernels(const specexit_graph* graph) {
+  if (!graph) return fail(SPECEXIT_EINVAL, "graph_kernels: null graph");
+  return static_cast<int32_t>(graph->n_direct);
 }
 
 int32_t specexit_graph_destroy(specexit_graph* graph) {

@@ -2,6 +2,8 @@
 matches the oracle's round on the same inputs (integers bit-exact, floats within tolerance), and
 gives, replay after replay, the bits of the same calls launched one by one -- also after the caller
 has refilled the input buffers, and with other work of the process in between."""
+import threading
+
 import numpy as np
 import pytest
 import torch
@@ -258,6 +260,7 @@ def test_short_recordings_replay_like_long_ones(calls, foreign, where):
         graph = lib.specexit_graph_end(st)
     torch.cuda.synchronize()
     try:
+        assert lib.specexit_graph_kernels(graph) == (2 * calls if calls <= 2 and not foreign else 0)
         for rep in range(3):
             print(f"  {calls} calls, foreign {foreign}, {where} stream, replay {rep}", flush=True)
             for i, q in enumerate(qs):
@@ -276,6 +279,50 @@ def test_short_recordings_replay_like_long_ones(calls, foreign, where):
         lib.specexit_graph_destroy(graph)
     if foreign:
         assert (mark == 2.0 ** 7).all()            # the first run, and three replays and eager runs
+
+
+@pytest.mark.parametrize("calls", [2, 6])
+def test_replays_of_two_host_threads_on_one_stream_stay_whole(calls):
+    # The recorded calls hand a length from one buffer to the other and back, one further each time: x -> y -> x ..  Another
+    # replay between two of them would take up the same x again, and steps would be lost.
+    n_q, B, n = 4, 3, 1500
+    lib = H.sx()
+    z = lambda shape, dt=torch.int32: torch.zeros(shape, dtype=dt, device="cuda")
+    tok, am, split, sig = z((B, n_q)), z((B, n_q)).fill_(1), z(1), z((B, 3), torch.float32)
+    ewma, n_obs, thinking = z((B, 3), torch.float32), z(B), z(B)
+    outs = [z(B), z((B, n_q)), z(B), z(B), z(B)]
+    length = [z(B), z(B)]
+    cfg = lib.exit_cfg(stop_think_token=1)
+    st = torch.cuda.Stream()
+    torch.cuda.synchronize()
+
+    def step(i):                                   # (no draft token is accepted: one entry further)
+        lib.specexit_accept_exit(cfg, B, n_q, tok, None, am, sig, length[i & 1], split, 0, ewma, n_obs, thinking, None, *outs, length[1 - (i & 1)], stream=st)
+
+    step(0)
+    torch.cuda.synchronize()
+    length[1].zero_()
+    torch.cuda.synchronize()
+    lib.specexit_graph_begin(st)
+    for i in range(calls):
+        step(i)
+    graph = lib.specexit_graph_end(st)
+
+    def replay():
+        for _ in range(n):
+            lib.specexit_graph_launch(graph, st)
+
+    try:
+        assert lib.specexit_graph_kernels(graph) == (calls if calls <= 4 else 0)
+        threads = [threading.Thread(target=replay) for _ in range(2)]
+        for t in threads:
+            t.start()
+        for t in threads:
+            t.join()
+        torch.cuda.synchronize()
+    finally:
+        lib.specexit_graph_destroy(graph)
+    assert (H.host(length[0]) == 2 * n * calls).all(), f"{2 * n * calls - H.host(length[0])} steps lost"
 
 
 def test_graph_argument_errors():
