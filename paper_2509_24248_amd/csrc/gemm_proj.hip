@@ -1,4 +1,4 @@
-// Projections of the draft layer for steps of more than two rows (bf16 weights, up to 64 activation rows):
+// Projections of the draft layer for the steps that the row-streaming kernel does not take (bf16 weights, up to 64 activation rows):
 // out[m][n] = sum_k act[m][k] * w[n][k], as partial sums over K ranges.
 //
 // HBM-bound (each weight byte is used for at most 128 products) and short, 10 to 90 us, so what counts is that

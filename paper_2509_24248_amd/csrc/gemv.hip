@@ -1,5 +1,5 @@
-// Row-streaming GEMV for the draft layer's projections and its widened head: bf16 steps of one or two rows (chain
-// drafting of one or two sequences) and fp32 ones.  out[m][n] = sum_k a[m][k] w[n][k].
+// Row-streaming GEMV for the draft layer's projections and its widened head: bf16 steps of up to four rows (chain
+// drafting of a few sequences) and fp32 ones.  out[m][n] = sum_k a[m][k] w[n][k].
 //
 // With so few activation rows the matrix cores buy nothing: the kernel is a pure weight
 // stream.  A wave takes two weight rows at a time and reads each along K with 16-byte loads,
@@ -356,7 +356,7 @@ __global__ __launch_bounds__(512) void k_gemv(const GemvArgs g) {
   }
 }
 
-constexpr int kLdsMax = 158 * 1024;
+constexpr int kLdsMax = 158 * 1024, kLdsMore = 144 * 1024;    // (of one and two rows, of three and four)
 constexpr int kMaxWaves = 8;             // per workgroup
 
 template <typename T, int MR, int SIF, int AMODE, int EPI, bool STREAM>
@@ -404,17 +404,19 @@ hipError_t launch_f32(const GemvArgs& g, hipStream_t s) {
 
 }  // namespace
 
-// bf16: from three rows on the matrix-core kernels are faster.  A draft step of 2 / 3 / 4 rows here and there, D = 1536 99.6 / 120 /
-// 148 us and 117 / 117 / 117; 2048 154 / 172 / 212 and 152 / 152 / 153; 2560 190 / 233 / 295 and 210 / 210 / 212; 4096 302 / 348 / -
-// and 305 / 305 / 307 (with three rows the multiplications take as long as the stream).
+// bf16 weights: up to four rows whose activations fit the LDS (three and four rows: 144 KB of it).  From three rows on the
+// matrix-core kernels are faster (a draft step of 2 / 3 / 4 rows here and there, D = 1536 100 / 120 / 149 us and 117 / 117 / 117; 2048
+// 152 / 174 / 210 and 152 / 151 / 152; 2560 191 / 233 / - and 210 / 210 / 211; 4096 300 / 346 / - and 305 / 306 / 308), but they take the
+// rows in two bf16 parts, where here everything stays in 32 bits: the signals of known rows, D = 2048, are off by 1e-7 here
+// and by 2.5e-6 there.
 // fp32: against the kernels of gemm.hip, whose activation rows come from the caches, a step of 24 rows, D = 1024, 181 us here
 // and 232 there, of 48 rows 302 and 323; of 48 rows with D = 2048, I = 4096 761 and 650, of 16 296 and 359.
-constexpr int kBf16Rows = 2, kF32Rows = 24, kF32RowsLongK = 3072;
+constexpr int kBf16Rows = 4, kF32Rows = 24, kF32RowsLongK = 3072;
 
 bool gemv_supported(bool f32, int M, int N, int K) {
   if (M < 1 || N < 2 || K < 1) return false;
   if (f32) return K % 256 == 0 && (M <= kF32Rows || K <= kF32RowsLongK) && K <= kLdsMax / (M <= 4 ? 16 : 32);    // four or eight rows in LDS
-  return M <= kBf16Rows && K % 512 == 0 && static_cast<size_t>(K) * M * 4 <= kLdsMax;
+  return M <= kBf16Rows && K % 512 == 0 && static_cast<size_t>(K) * M * 4 <= (M <= 2 ? kLdsMax : kLdsMore);
 }
 
 // One pair per wave at a time.  The waves of a compute unit share its pairs evenly, with at most 8 per_cu of them: a launch
@@ -439,7 +441,12 @@ hipError_t launch_gemv(const GemvArgs& g, hipStream_t s) {
     // (eight rows beside the rotation in double leave values in scratch memory)
     return g.M <= 4 || g.epi == 1 ? launch_f32<4>(g, s) : launch_f32<8>(g, s);
   }
-  return g.M == 1 ? launch_bf16<1>(g, s) : launch_bf16<2>(g, s);
+  switch (g.M) {
+    case 1: return launch_bf16<1>(g, s);
+    case 2: return launch_bf16<2>(g, s);
+    case 3: return launch_bf16<3>(g, s);
+    default: return launch_bf16<4>(g, s);
+  }
 }
 
 }  // namespace sx

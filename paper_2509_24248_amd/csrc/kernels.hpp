@@ -34,7 +34,7 @@ __host__ __device__ inline size_t packed_byte(int NT, int tile, int m, int k) {
   return ((static_cast<size_t>(k >> 7) * NT + tile) * 4 + ((k >> 5) & 3)) * 1024 + ((k >> 3) & 3) * 256 + (m & 15) * 16 + (k & 7) * 2;
 }
 
-// Projection of the draft layer over 3 and more rows (gemm_proj.hip): partial sums, added by the kernel behind it.
+// Projection of the draft layer over more rows than the row-streaming kernel takes (gemm_proj.hip): partial sums, added by the kernel behind it.
 struct ProjArgs {
   const void* w[3];    // up to three row blocks (q/k/v or gate/up share one launch)
   int seg_end[3];      // exclusive end row of each block in the concatenated row space, multiples of 16
@@ -99,7 +99,7 @@ struct GemmArgs {
   float* logits_dbg;   // [M][V] or nullptr
 };
 
-// Row-streaming GEMV (gemv.hip) for bf16 steps of one or two rows and for fp32 ones: no split over K, the
+// Row-streaming GEMV (gemv.hip) for bf16 steps of up to four rows and for fp32 ones: no split over K, the
 // epilogue runs in the wave that owns a pair of weight rows.
 struct GemvArgs {
   int f32;               // weights, gains, stored rows and cache entries are fp32, else bf16

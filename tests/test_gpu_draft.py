@@ -114,6 +114,41 @@ def test_odd_number_of_narrow_kv_heads(B):
     one_step(shape, w, kv, tok, g, pos, label="odd kv heads")
 
 
+def known_rows(D, B, seed):
+    """A step whose normed rows are known to the last bit: the layer passes the integers of hidden_in through (W_fc = [0 | 1], no
+    attention, no MLP), and their squares add up exactly in any order.  Returns the step's inputs, the normed rows in
+    32 bits and in 64, and the head's rows."""
+    shape = gen.scaled(gen.config(2), D=D, Hq=4, Hkv=2, d=128, I=512, V=500, B=B, ctx=(5, 20), k=2)
+    rng = np.random.default_rng(1000 * seed + B)
+    w = gen.draft_weights(shape, seed)
+    w["w_fc"] = np.concatenate([np.zeros((D, D), np.float32), np.eye(D, dtype=np.float32)], 1)
+    w["w_o"], w["w_down"] = np.zeros_like(w["w_o"]), np.zeros_like(w["w_down"])
+    gain = w["ln_final"] = gen.store(shape, rng.uniform(0.5, 1.5, D).astype(np.float32))
+    g = (rng.integers(1, 16, (B, D)) * rng.choice([-1, 1], (B, D))).astype(np.float32)
+    pos = gen.context_lengths(shape, seed)
+    gd = GpuDraft(shape, w, gen.kv_cache(shape, pos, shape.n_q, seed))
+    mean = (g.astype(np.float64) ** 2).mean(1, keepdims=True)
+    assert D & (D - 1) == 0 and mean.max() * D < 2 ** 24
+    n32 = g * (np.float32(1) / np.sqrt(mean.astype(np.float32) + np.float32(shape.rms_eps))) * gain
+    n64 = g * gain.astype(np.float64) / np.sqrt(mean + np.float64(np.float32(shape.rms_eps)))
+    return gd, (gen.token_ids(shape, B, seed), g, pos), n32, n64, w["w_head"].astype(np.float64)
+
+
+@pytest.mark.parametrize("B", [1, 2, 3, 4])
+def test_steps_of_few_rows_keep_32_bits(B):
+    # Steps of up to four rows multiply 32-bit values.  Sums of 2048 products in 32 bits, 32 of them in a row in each of 64 lanes, are
+    # off by 2^-24 sqrt(32 / 2) 0.4 = 1e-7 of their size, the rows' factor by 2^-24 at most; taken as two bf16 parts, the operands
+    # themselves would be off by some 2^-9 of 2^-9, 1.2e-6.
+    err = []
+    for seed in range(8):
+        gd, inputs, _, n64, head = known_rows(2048, B, seed)
+        ref = n64 @ head[gd.shape.V:].T
+        err.append((gd.step(*inputs)["sig_raw"] - ref) / (np.linalg.norm(n64, axis=1, keepdims=True) * head.std()))
+    err = np.sqrt((np.concatenate(err) ** 2).mean())
+    print(f"  {B} rows: {err:.2e}", flush=True)
+    assert err < 4e-7
+
+
 def test_small_bf16_alu_fallback():
     shape = gen.scaled(gen.config(1), D=192, Hq=4, Hkv=2, d=64, I=320, V=1000, B=2, ctx=(5, 90), k=2)
     w, kv, tok, g, pos = setup(shape, 1, std=0.05)
@@ -175,7 +210,7 @@ def sampled_rows_step(shape, w, kv, tok, g, pos, rows, label):
 @pytest.mark.timeout(1500)
 def test_full_size_config_2_all_eight_rows():
     """Qwen3-8B-like sizes, B = 8, paged cache: the split-K matrix-core projections with their reducing
-    epilogues at full width (steps of one or two rows take the row-streaming path); every row compared."""
+    epilogues at full width (steps of few rows take the row-streaming path); every row compared."""
     shape = gen.config(2)
     w, kv, tok, g, pos = setup(shape, 0, paged=True, norms=False)
     rows = list(range(shape.B))
