@@ -142,7 +142,8 @@ struct Best {
 // The consumer side of k_head_wide for a wave that owns RT row tiles of the operand (from tile rt0 on) and, of
 // every half, the JN weight tiles from jc0 on: one barrier per stage, a candidate update per pass.
 // PL = 2: tiles 2 o and 2 o + 1 are the bf16 value and the bf16 rounding of the rest of the same 16
-// activation rows, whose two products add up in one accumulator.  Every lane keeps the TB best of what it has seen;
+// activation rows.  Their products are added at the end where both have accumulators for the whole pass (up to 16 rows:
+// LV = 2); with more rows they add up in one, a k block at a time (kBlockSums).  Every lane keeps the TB best of what it has seen;
 // they are merged over the four lanes of a row when the workgroup's share is done.
 // A row has `slots` candidate slots per workgroup, one per column split; a wave that covers the whole half
 // (JN = TG) where others split it fills the remaining one with nothing.
@@ -150,6 +151,14 @@ template <int RT, int JN, int TG, int S, int PL, int TB, int MAXH, int LV>
 struct Consumer {
   static constexpr int kStage = TG * 4096;
   static constexpr int RO = RT / PL;        // 16-row tiles of results
+  // Value and rest of a draft row in one accumulator leave registers for passes of more halves, but in a sum over all of K every
+  // product of the rest is then rounded at the size of the value's sum, 256 roundings instead of 128 at D = 4096.  So the products of a k
+  // block are summed by themselves and added to the pass's accumulators: 32 roundings at that size.  Error of the ranked logits, D =
+  // 4096, 17 / 40 / 64 rows, against 64-bit sums of the same parts: 3.8e-7 / 3.8e-7 / 3.9e-7 with an accumulator each,
+  // 5.0e-7 / 5.2e-7 / 5.0e-7 with one, 2.1e-7 / 2.2e-7 / 2.3e-7 this way, in the same time (draft steps of 20 / 48 / 64 rows,
+  // V = 151936: 326 / 354 / 382 us with one accumulator, 326 / 355 / 380 this way).
+  static constexpr bool kBlockSums = PL == 2 && LV < 2;
+  static constexpr int RA = kBlockSums ? RO : RT;
   const GemmArgs& g;
   char* lds;
   int rt0, jc0, fr, fq, KB;
@@ -191,24 +200,28 @@ struct Consumer {
   // one pass: NH halves starting at half `half0`
   template <int NH>
   __device__ __forceinline__ void pass(int half0) {
-    f32x4_t acc[RO][NH * JN];     // (value and rest of a row add up in one place)
+    f32x4_t acc[RA][NH * JN];
 #pragma unroll
-    for (int o = 0; o < RO; ++o)
+    for (int o = 0; o < RA; ++o)
 #pragma unroll
       for (int j = 0; j < NH * JN; ++j) acc[o][j] = f32x4_t{0.f, 0.f, 0.f, 0.f};
 
-    f32x4_t left[LV > 0 ? LV : 1][RO][NH * JN];     // finished left siblings of the chunk tree, per level
+    f32x4_t left[LV > 0 ? LV : 1][RA][NH * JN];     // finished left siblings of the chunk tree, per level
 
     // The waves go through a stage's four k steps in read groups of CH tiles, the operand reads one
     // group ahead of the matrix instructions (k steps outermost: between two matrix instructions on the
-    // same accumulator lie those of all other tiles; the scheduler is kept from sinking the reads back
+    // same accumulator lie those of all other tiles; with block sums the tiles of a group outermost, so that one group's
+    // sums are under way at a time; the scheduler is kept from sinking the reads back
     // to their uses).  The barrier that hands over the next stage sits before the last group's matrix
     // instructions, whose operands are in registers by then: the first reads of the next stage are in
     // flight while those instructions run, so neither the LDS nor the matrix cores idle around a barrier.
     constexpr int CH = JN < 4 ? JN : 4;   // tiles per read group
     constexpr int GPS = JN / CH;          // read groups per k step
-    constexpr int NCH = 4 * GPS;          // read groups per stage: group c = k step c / GPS, this wave's tiles CH (c % GPS) ..
+    constexpr int NCH = 4 * GPS;          // read groups per stage
+    const auto step_of = [](int c) { return kBlockSums ? c & 3 : c / GPS; };             // k step and first tile of group c
+    const auto tile_of = [](int c) { return CH * (kBlockSums ? c >> 2 : c % GPS); };
     uint4 wf[2][CH];
+    f32x4_t blk[RO][CH];
     auto wait_stage = [&]() -> const uint4* {
       __builtin_amdgcn_s_waitcnt(0xC07F);            // lgkmcnt(0): this wave is done reading the stage it leaves
       __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
@@ -219,7 +232,7 @@ struct Consumer {
       return stage;
     };
     auto read_group = [&](uint4 (&dst)[CH], const uint4* stage, int c) {
-      const int s = c / GPS, j0 = CH * (c % GPS);
+      const int s = step_of(c), j0 = tile_of(c);
 #pragma unroll
       for (int jj = 0; jj < CH; ++jj) dst[jj] = stage[(jc0 + j0 + jj) * 256 + ((4 * s + fq) ^ fr)];
     };
@@ -236,7 +249,7 @@ struct Consumer {
       for (int h = 0; h < NH; ++h) {
 #pragma unroll
         for (int c = 0; c < NCH; ++c) {
-          const int s = c / GPS, j0 = CH * (c % GPS);
+          const int s = step_of(c), j0 = tile_of(c);
           if (c + 1 < NCH) {
             read_group(wf[(c + 1) & 1], stage, c + 1);
           } else if (h < NH - 1 || kb + 1 < KB) {
@@ -246,10 +259,11 @@ struct Consumer {
           __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
           for (int i = 0; i < RT * CH; ++i) {
-            // (two planes: the instructions on one accumulator lie CH apart)
-            const int t = PL == 2 ? i / CH : i % RT, jj = PL == 2 ? i % CH : i / RT;
-            acc[t / PL][h * JN + j0 + jj] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, wf[c & 1][jj]),
-                                                                                    __builtin_bit_cast(bf16x8_t, b[t][s]), acc[t / PL][h * JN + j0 + jj], 0, 0, 0);
+            // (block sums: the instructions on one accumulator lie CH apart)
+            const int t = kBlockSums ? i / CH : i % RT, jj = kBlockSums ? i % CH : i / RT;
+            f32x4_t& to = kBlockSums ? blk[t / PL][jj] : acc[t][h * JN + j0 + jj];
+            const f32x4_t from = kBlockSums && s == 0 && t % PL == 0 ? f32x4_t{0.f, 0.f, 0.f, 0.f} : to;
+            to = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, wf[c & 1][jj]), __builtin_bit_cast(bf16x8_t, b[t][s]), from, 0, 0, 0);
           }
           // The next k block's activation pieces (1 KB of consecutive bytes per instruction, L2 hits that
           // take more than a microsecond under the weight stream).  Pieces 0 and 1, which the next block
@@ -263,7 +277,19 @@ struct Consumer {
               bn[t][1] = apack[t][noff + s_stride];
             }
           }
-          if (h == NH - 1 && (c + 1) % GPS == 0) {
+          if constexpr (kBlockSums) {
+            if (s == 3) {
+#pragma unroll
+              for (int o = 0; o < RO; ++o)
+#pragma unroll
+                for (int jj = 0; jj < CH; ++jj) {
+                  f32x4_t& sum = acc[o][h * JN + j0 + jj];
+                  sum += blk[o][jj];
+                  asm volatile("" : "+v"(sum));    // (here: put off to the k block's end, the sums of all halves are live)
+                }
+            }
+          }
+          if (h == NH - 1 && (kBlockSums ? c >= NCH - 4 : (c + 1) % GPS == 0)) {
 #pragma unroll
             for (int t = 0; t < RT; ++t) {
               if (s < 2) b[t][s] = bn[t][s];
@@ -282,13 +308,13 @@ struct Consumer {
             if (!up) continue;
             if (ci >> l & 1) {
 #pragma unroll
-              for (int o = 0; o < RO; ++o)
+              for (int o = 0; o < RA; ++o)
 #pragma unroll
                 for (int j = 0; j < NH * JN; ++j) acc[o][j] += left[l][o][j];
             } else {
               up = false;
 #pragma unroll
-              for (int o = 0; o < RO; ++o)
+              for (int o = 0; o < RA; ++o)
 #pragma unroll
                 for (int j = 0; j < NH * JN; ++j) { left[l][o][j] = acc[o][j]; acc[o][j] = f32x4_t{0.f, 0.f, 0.f, 0.f}; }
             }
@@ -300,24 +326,31 @@ struct Consumer {
     // ---- epilogue: lane (c = lane % 16, q = lane / 16) holds weight rows 16 (tile0 + j) + 4 q + i of
     // activation row 16 (rt0 / PL + o) + c; rows below V enter the lane's best, the rows V.. are the
     // widened head's extra rows.
+    if constexpr (RA > RO) {
+      static_assert(RO == 1 || RA == RO, "value and rest of one row tile");
+#pragma unroll
+      for (int j = 0; j < NH * JN; ++j) acc[0][j] += acc[1][j];
+    }
+    int fr_e = fr, fq_e = fq;     // (what follows from them is worked out here and not held through the loop above)
+    asm volatile("" : "+v"(fr_e), "+v"(fq_e));
 #pragma unroll
     for (int h = 0; h < NH; ++h) {
       const int tile0 = halves.first(half0 + h) + jc0;      // this wave's first tile of the half
       const int tile1 = halves.first(half0 + h + 1);        // (the stage repeats the half's last tile from here on)
 #pragma unroll
       for (int o = 0; o < RO; ++o) {
-        const int m = 16 * (rt0 / PL + o) + fr;
+        const int m = 16 * (rt0 / PL + o) + fr_e;
         const bool owner = m < g.M;
         // tiles that lie wholly below the signal rows (all but the last of a launch) need no checks per
         // element: the consumers stand still during the epilogue while the ring fills up, so its length counts
         const bool plain = !g.logits_dbg && (tile0 + JN) * 16 <= g.V;    // uniform
-        const int nb = tile0 * 16 + 4 * fq;
+        const int nb = tile0 * 16 + 4 * fq_e;
         if constexpr (TB > 1) {
           // ranked candidates: the values pass through a corner of the LDS (this lane's own 16 bytes per tile), so
           // that the insertion exists once, in a loop.  Unrolled over the accumulators it is several KB of code
           // that arrives line by line behind the weight stream (16 rows, V = 151936, D = 4096: 213 us; 187 without
           // ranked candidates).
-          float4* mine = reinterpret_cast<float4*>(lds + S * kStage) + (threadIdx.x >> 6) * (JN * 64) + (threadIdx.x & 63);
+          float4* mine = reinterpret_cast<float4*>(lds + S * kStage) + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6) * (JN * 64) + 16 * fq_e + fr_e;
 #pragma unroll
           for (int j = 0; j < JN; ++j) {
             const f32x4_t v = acc[o][h * JN + j];
@@ -377,9 +410,11 @@ struct Consumer {
     // the row's best over its four lanes, one candidate (list) per workgroup and column split
     const int slots = g.wide_slots;
     const int top_b = TB > 1 ? g.top_b : 1;
+    int fr_e = fr;                // (likewise)
+    asm volatile("" : "+v"(fr_e));
 #pragma unroll
     for (int o = 0; o < RO; ++o) {
-      const int m = 16 * (rt0 / PL + o) + fr;
+      const int m = 16 * (rt0 / PL + o) + fr_e;
       const size_t at = (static_cast<size_t>(m) * gridDim.x + blockIdx.x) * slots * top_b;
       const int mine = jc0 / JN;
 #pragma unroll 1
@@ -601,8 +636,8 @@ constexpr int kWideTiles = 8, kWideStages = 4;
 // an odd last tile is shared by two waves instead, or all SIMDs are busy anyway.
 //
 // lv: levels of the chunk tree.  Two where the accumulators of a pass take at most 32 registers (one row tile per
-// wave, or the draft head's first).  Otherwise the finished siblings do not fit beside them: one level leaves 24 to 52
-// bytes a lane in scratch memory and costs 5 to 12 % (V = 40000, 64 rows, D = 2560 / 5120 46.8 / 84 us, 41 / 73 without it;
+// wave, or the draft head's first).  Otherwise the finished siblings do not fit beside them: one level leaves 16 to 20
+// bytes a lane of the LM head's kernels in scratch memory and costs 5 to 12 % (V = 40000, 64 rows, D = 2560 / 5120 46.8 / 84 us, 41 / 73 without it;
 // the draft step of D = 4096, 40 rows 383, 375).  It pays all the same where rows are 4 KB apart, and every workgroup on
 // the same k block keeps one memory channel busy: D = 2048, V = 151936, 40 / 64 / 80 rows 114 / 115 / 124 us, 133 / 141 / 138
 // without it; the draft step of 40 rows 188, 185 to 205.  (Half of an 8 KB row is where the same channel comes round

@@ -134,6 +134,26 @@ def known_rows(D, B, seed):
     return gd, (gen.token_ids(shape, B, seed), g, pos), n32, n64, w["w_head"].astype(np.float64)
 
 
+@pytest.mark.parametrize("B", [5, 16, 17, 40, 64])
+def test_sums_of_two_part_rows(B):
+    # The head's sums over K = 4096, given the two bf16 parts of the rows.  n roundings at the size of the sum so far, whose square grows
+    # evenly, add up to 2^-24 sqrt(n / 2) of the result.  Up to 16 rows: four chunks of half the size, 32 products of the
+    # values each, 4 (1/2)^2 32 / 2 = 16; the rest adds up by itself.  More rows: 32 blocks are added, 32 / 2 = 16, and in
+    # each 8 products of either part at 32^-1/2 of the size, 8 / 2 = 4 together.  (Both parts in one sum over all of K: 128.)
+    bound = 2.0 ** -24 * (16 if B <= 16 else 20) ** 0.5
+    err = []
+    for seed in range(4):
+        gd, (tok, g, pos), n32, _, head = known_rows(4096, B, seed)
+        hi = gen.round_to_bf16(n32)
+        parts = hi.astype(np.float64) + gen.round_to_bf16(n32 - hi)
+        got = gd.tree(tok, g, pos, np.array([-1, 0], np.int32), np.zeros(2, np.int32), 4)
+        ref = np.einsum("bd,bvd->bv", parts, head[got["cand_tok"][0]])
+        err.append((got["cand_logit"][0] - ref) / ref)
+    err = np.sqrt((np.concatenate(err) ** 2).mean())
+    print(f"  {B} rows: {err:.2e} of {bound:.2e}", flush=True)
+    assert err < bound
+
+
 @pytest.mark.parametrize("B", [1, 2, 3, 4])
 def test_steps_of_few_rows_keep_32_bits(B):
     # Steps of up to four rows multiply 32-bit values.  Sums of 2048 products in 32 bits, 32 of them in a row in each of 64 lanes, are
