@@ -61,7 +61,7 @@ __global__ __launch_bounds__(256) void k_attn_split_valu(const AttnArgs a) {
   attn_sched_build(a, sched_lds);
   const AttnLine line = attn_sched_line(__builtin_amdgcn_readfirstlane(sched_lds[a.B]), a.B, a.Hkv, a.pad, a.wide_from, a.wgrid);
   if (blockIdx.x == 0) {
-    for (int i = tid; i <= a.B; i += 256) a.sched[i] = sched_lds[i];
+    attn_sched_publish(a, sched_lds, line);
   }
   if (static_cast<int>(blockIdx.x) >= line.W) return;
   // P V: thread (c4, r0) has columns 4 c4 .. + 3 of rows r0, r0 + RSTEP, ..; with at most half of RSTEP rows, KG groups of
@@ -256,7 +256,7 @@ __global__ __launch_bounds__(256) void k_attn_split_rows(const AttnArgs a) {
   attn_sched_build(a, sched_lds);
   const AttnLine line = attn_sched_line(sched_lds[a.B], a.B, a.Hkv, a.pad, a.wide_from, a.wgrid);
   if (blockIdx.x == 0) {
-    for (int i = tid; i <= a.B; i += 256) a.sched[i] = sched_lds[i];
+    attn_sched_publish(a, sched_lds, line);
   }
   if (static_cast<int>(blockIdx.x) >= line.W) return;
   const int x_hi = attn_sched_lo(line, blockIdx.x + 1);
@@ -463,8 +463,8 @@ struct RowSegs {
 template <int D>
 __device__ __forceinline__ RowSegs row_segments(const AttnArgs& a, int b, int i, int h) {
   const int G = a.G, R = G * a.n_q, g = h / G, r = i * G + h - g * G;
-  const int s0 = a.sched[b], s1 = a.sched[b + 1], sB = a.sched[a.B];
-  const AttnLine line = attn_sched_line(sB, a.B, a.Hkv, a.pad, a.wide_from, a.wgrid);
+  const int s0 = a.sched[b], s1 = a.sched[b + 1];
+  const AttnLine line = attn_sched_read(a);
   const int p_u = a.Hkv * (s0 + line.pad * b) + g * (s1 - s0 + line.pad) + line.pad;     // the unit's first keys on the line
   const int w_first = attn_sched_owner(line, p_u);
   const size_t slot = static_cast<size_t>(w_first) + static_cast<size_t>(b) * a.Hkv + g;
@@ -695,9 +695,6 @@ static int wide_from(const AttnArgs& a) {
   return 1000 + std::min(a.G * a.n_q * (a.d == 64 ? 80 : 50), 2600);
 }
 
-// More workgroups than this are refused.
-constexpr int64_t kMaxGrid = 14336;
-
 static bool plan_as(AttnArgs& a, int num_cus, int use_mfma, int pad) {
   // The host knows only the upper bound l_max of the lengths; the kernels deal the keys that
   // are really there to the workgroups in equal shares.  Here only the number of workgroups is
@@ -723,7 +720,7 @@ static bool plan_as(AttnArgs& a, int num_cus, int use_mfma, int pad) {
     const int64_t need = (line.T + seg_gran - 1) / seg_gran;
     if (w < need) w = need;
   }
-  if (w > kMaxGrid) return false;
+  if (w > kAttnMaxGrid) return false;
   a.wgrid = static_cast<int>(w);
   return true;
 }
@@ -745,7 +742,7 @@ size_t attn_workspace_bytes(const AttnArgs& a) {
   o = (o + 255) & ~static_cast<size_t>(255);
   size_t ml = slots * R * 2 * sizeof(float);
   ml = (ml + 255) & ~static_cast<size_t>(255);
-  size_t sc = static_cast<size_t>(a.B + 1) * sizeof(int);
+  size_t sc = static_cast<size_t>(a.B + 1 + kAttnLineWords) * sizeof(int);
   sc = (sc + 255) & ~static_cast<size_t>(255);
   return o + ml + sc;
 }

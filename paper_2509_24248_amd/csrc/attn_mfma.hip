@@ -128,7 +128,7 @@ __global__ __launch_bounds__(64 * kNK * NR, min_waves_per_simd(HD, NR)) void k_a
   const AttnLine line = attn_sched_line(__builtin_amdgcn_readfirstlane(sched_lds[a.B]), a.B, a.Hkv, a.pad, a.wide_from, a.wgrid);
   if (blockIdx.x == 0) {
     // the merging kernel reads the split back from here
-    for (int i = threadIdx.x; i <= a.B; i += 64 * kNK * NR) a.sched[i] = sched_lds[i];
+    attn_sched_publish(a, sched_lds, line);
   }
   if (static_cast<int>(blockIdx.x) >= line.W) return;  // the whole workgroup leaves together
   const int x_hi = attn_sched_lo(line, blockIdx.x + 1);

@@ -4,7 +4,7 @@
 // The kernels do it themselves: the keys of every (sequence, KV head) unit are counted in
 // granules of 64, the units are laid end to end on one line of T granules (unit u = b * Hkv + g
 // starts at Hkv * S[b] + g * n_b, S = prefix sums of the sequences' granule counts n_b), and
-// each of W workgroups takes the next T / W granules, the first T % W of them one more.  Every workgroup therefore has
+// workgroup w of W takes the granules [w T / W, (w + 1) T / W).  Every workgroup therefore has
 // the same amount of cache to read whatever the mix of lengths, all of them are resident at
 // once, and nobody waits for a long sequence's last chunk.  A workgroup whose range crosses a
 // unit boundary finishes one unit's partial result and starts the next (a "segment" per unit).
@@ -67,17 +67,31 @@ __device__ __forceinline__ void attn_sched_build(const AttnArgs& a, int* S) {
 }
 
 // The line of a launch whose sequences have `gran` granules in all.  Workgroups that take part: one per granule while the launch
-// has a compute unit for each (no workgroup crosses a unit's end then: no padding); one per compute unit up to
-// `wide_from` granules; from there on as many as are resident, with at least two granules each.
-// In the middle range the largest share, T / 256 rounded up, sets the time, so all workgroups have that and there are as few as it
-// takes: every partial result is read again.  (With 256 of them, the first T % 256 one granule larger, the last units of 1
-// sequence x 5610 entries, 4 KV heads, are 90 segments of one granule: 9 queries of 12 heads 13.6 us a layer,
-// 11.2 with 45 of two; 4500 entries 13.3 / 10.7, 8 KV heads, 32 heads 14.7 / 14.2.)
+// has a compute unit for each (no workgroup crosses a unit's end then: no padding); up to `wide_from` granules as few as
+// keep the largest share at T / 256, rounded up, since that sets the time and every partial result is read again (1 sequence x 5610
+// entries, 4 KV heads, 9 queries of 12 heads: 12.5 us a layer with 256 workgroups, 11.2 with 180); from there on as many as
+// are resident, with at least two granules each.
+// In the middle range that is a whole number of workgroups per unit where 256 allow it: sequences of one length, whose units
+// are equal, then have no workgroup that crosses a unit's end.  (8 sequences x 2048 entries, 8 KV heads, 16 queries of 32 heads: 24.0
+// us a layer; 28.1 with 249 workgroups of nine granules each, whose every other one starts a second segment.)
 constexpr int kAttnSpread = 256;
+constexpr int kAttnMaxGrid = 14336;       // workgroups; more are refused
 struct AttnLine {
   int T, W, pad;   // granules with the padding, workgroups, padding per unit
-  int q, r;        // granules per workgroup (the last one may have fewer), the first r of them one more
+  int q, r;        // T / W and its remainder
 };
+__host__ __device__ __forceinline__ float attn_sched_rcp(int x) {
+#ifdef __HIP_DEVICE_COMPILE__
+  return __builtin_amdgcn_rcpf(static_cast<float>(x));
+#else
+  return 1.0f / static_cast<float>(x);
+#endif
+}
+// a / b, rounded down, for 0 <= a < 2^21, b >= 1: (a + 1/2) / b is at least 1 / 2b away from an integer, and the product with the
+// reciprocal is off by at most 2^-22 of itself.
+__host__ __device__ __forceinline__ int attn_sched_div(int a, int b) {
+  return static_cast<int>((static_cast<float>(a) + 0.5f) * attn_sched_rcp(b));
+}
 __host__ __device__ __forceinline__ AttnLine attn_sched_line(int gran, int B, int Hkv, int pad, int wide_from, int wgrid) {
   AttnLine l;
   l.T = gran * Hkv;
@@ -85,30 +99,53 @@ __host__ __device__ __forceinline__ AttnLine attn_sched_line(int gran, int B, in
   int want = l.T;
   if (l.T > kAttnSpread) {
     const bool wide = l.T >= wide_from;
-    l.T += B * Hkv * pad;
+    const int units = B * Hkv;
+    l.T += units * pad;
     want = (l.T + 1) >> 1;
-    if (!wide || want < kAttnSpread) {
-      l.q = (l.T + kAttnSpread - 1) / kAttnSpread;
-      l.r = 0;
-      l.W = static_cast<int>(static_cast<uint32_t>(l.T + l.q - 1) / static_cast<uint32_t>(l.q));
-      if (l.W <= wgrid) return l;
-      want = l.W;
+    if (!wide || want < kAttnSpread) {                                    // (T < 2^21)
+      const int most = (l.T + kAttnSpread - 1) / kAttnSpread;             // the largest share
+      want = units * attn_sched_div(l.T + units * most - 1, units * most);
+      if (want > kAttnSpread) want = attn_sched_div(l.T + most - 1, most);
     }
   }
   l.W = want < 1 ? 1 : want < wgrid ? want : wgrid;
-  l.q = static_cast<int>(static_cast<uint32_t>(l.T) / static_cast<uint32_t>(l.W));   // at least 1: W <= T
-  l.r = l.T - l.q * l.W;
+  l.q = l.T < 1 << 21 ? attn_sched_div(l.T, l.W) : static_cast<int>(static_cast<uint32_t>(l.T) / static_cast<uint32_t>(l.W));
+  l.r = l.T - l.q * l.W;                                                  // (q is at least 1: W <= T)
   return l;
 }
 
-// First granule of workgroup w, and the workgroup that has granule p.  (One 32-bit division each for the line and the owner: the
-// products of an even deal, w T / W, need 64 bits, whose division is 150 dependent instructions, fetched for a single use.)
-__device__ __forceinline__ int attn_sched_lo(const AttnLine& l, int w) { return min(w * l.q + min(w, l.r), l.T); }
-__device__ __forceinline__ int attn_sched_owner(const AttnLine& l, int p) {
-  const int longer = l.r * (l.q + 1);
-  const bool in = p < longer;
-  const uint32_t k = static_cast<uint32_t>(in ? p : p - longer) / static_cast<uint32_t>(in ? l.q + 1 : l.q);
-  return static_cast<int>(k) + (in ? 0 : l.r);
+// First granule of workgroup w, w T / W rounded down, and the workgroup that has granule p.  (An even deal: with the first T % W
+// workgroups one granule larger, 4 of which fit a unit of 67 granules evenly would have 68.  The products of the formula need 64
+// bits, whose division is 150 dependent instructions, fetched for a single use; w r is less than kAttnMaxGrid squared, the
+// quotient from floats off by one at most, and so is the owner, before the comparisons.)
+__host__ __device__ __forceinline__ int attn_sched_lo(const AttnLine& l, int w) {
+  const int x = w * l.r;
+  int k = attn_sched_div(x, l.W);
+  if (k * l.W > x) --k;
+  if ((k + 1) * l.W <= x) ++k;
+  return w * l.q + k;
+}
+__host__ __device__ __forceinline__ int attn_sched_owner(const AttnLine& l, int p) {
+  const int w = static_cast<int>(static_cast<float>(p + 1) * (static_cast<float>(l.W) * attn_sched_rcp(l.T)) + 0.25f);
+  return attn_sched_lo(l, w) <= p ? w : w - 1;
+}
+
+// The split as the merging kernel reads it back: the table's prefix sums, then the line.  (Worked out there again it is a chain of
+// divisions in front of everything else; these words arrive with the prefix sums.)
+constexpr int kAttnLineWords = 4;
+__device__ __forceinline__ void attn_sched_publish(const AttnArgs& a, const int* S, const AttnLine& l) {
+  for (int i = threadIdx.x; i <= a.B; i += blockDim.x) a.sched[i] = S[i];
+  if (threadIdx.x == 0) {
+    int* w = a.sched + a.B + 1;
+    w[0] = l.W; w[1] = l.q; w[2] = l.r; w[3] = l.pad;
+  }
+}
+__device__ __forceinline__ AttnLine attn_sched_read(const AttnArgs& a) {
+  const int* w = a.sched + a.B + 1;
+  AttnLine l;
+  l.W = w[0]; l.q = w[1]; l.r = w[2]; l.pad = w[3];
+  l.T = l.q * l.W + l.r;
+  return l;
 }
 
 struct AttnSeg {

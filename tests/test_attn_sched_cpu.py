@@ -1,0 +1,82 @@
+"""The attention kernels' work split (csrc/attn_sched.hpp), compiled for the host, against 64-bit arithmetic."""
+import os
+import shutil
+import subprocess
+
+import pytest
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
+
+PROGRAM = r"""
+#include "attn_sched.hpp"
+#include <stdio.h>
+#include <stdlib.h>
+using namespace sx;
+static long checked = 0, bad = 0;
+static void expect(bool ok, const char* what, long a, long b, long c, long d) {
+  ++checked;
+  if (!ok && ++bad < 10) printf("%s: %ld %ld %ld %ld\n", what, a, b, c, d);
+}
+static long below(long n) { return ((static_cast<long>(rand()) << 20) ^ rand()) % n; }
+
+// shares and owners of a line of T granules over W workgroups
+static void shares(const AttnLine& l) {
+  const long T = l.T, W = l.W;
+  expect(T == static_cast<long>(l.q) * W + l.r && l.q >= 1 && l.r >= 0 && l.r < W, "quotient", T, W, l.q, l.r);
+  expect(attn_sched_lo(l, 0) == 0 && attn_sched_lo(l, l.W) == l.T, "ends", T, W, 0, 0);
+  for (int i = 0; i < 40; ++i) {
+    const long w = i < 3 ? i % W : i < 6 ? W - 1 - i % 3 % W : below(W);
+    const long lo = w * T / W, hi = (w + 1) * T / W;
+    expect(attn_sched_lo(l, w) == lo && attn_sched_lo(l, w + 1) == hi, "share", T, W, w, attn_sched_lo(l, w));
+    for (long p : {lo, hi - 1, below(T)}) {
+      const long o = attn_sched_owner(l, p);
+      expect(o >= 0 && o < W && o * T / W <= p && p < (o + 1) * T / W, "owner", T, W, p, o);
+    }
+  }
+}
+
+int main() {
+  srand(1);
+  // the lines of launches: W from the sizes, for any lengths that the planned number of workgroups has to do for
+  for (int k = 0; k < 60000; ++k) {
+    const int B = k % 4 == 0 ? 1 + below(1024) : 1 + below(24), Hkv = 1 + below(k % 3 ? 8 : 64), pad = below(4);
+    const int gran = B + (k % 5 == 0 ? below(1l << 20) / Hkv : below(k % 2 ? 40 : 700));
+    const int wide_from = static_cast<long>(B) * Hkv >= kAttnSpread ? 0 : 1000 + below(2601), wgrid = k % 7 == 0 ? kAttnMaxGrid : k % 2 ? 256 : 512;
+    const AttnLine l = attn_sched_line(gran, B, Hkv, pad, wide_from, wgrid);
+    const long bare = static_cast<long>(gran) * Hkv, T = bare + (bare > kAttnSpread ? static_cast<long>(B) * Hkv * pad : 0);
+    expect(l.T == T && l.W >= 1 && l.W <= wgrid && l.W <= T, "line", gran, B, Hkv, l.W);
+    if (bare > kAttnSpread && bare < wide_from)       // the middle range: no share above what 256 workgroups would have
+      expect(l.W <= kAttnSpread && (T + l.W - 1) / l.W == (T + kAttnSpread - 1) / kAttnSpread, "largest share", T, l.W, B, Hkv);
+    shares(l);
+    // sequences of one length: where a whole number of workgroups per unit keeps the share, every unit begins a share
+    const long n = gran / B + l.pad, units = static_cast<long>(B) * Hkv;
+    if (gran % B == 0 && bare > kAttnSpread && bare < wide_from && l.W % units == 0)
+      for (long u = 0; u < units; ++u) {
+        const int w = attn_sched_owner(l, u * n);
+        expect(attn_sched_lo(l, w) == u * n, "unit start", T, l.W, u, w);
+      }
+  }
+  // any line, to the limits
+  for (long W = 1; W <= kAttnMaxGrid; W += W < 700 ? 1 : 37)
+    for (long T : {W, W + 1, 2 * W - 1, 2 * W, 2 * W + 1, 3 * W + W / 2, W + below(4000), W + below((1l << 30) - W), (1l << 30) - 1}) {
+      AttnLine l{};
+      l.T = T; l.W = W; l.q = T / W; l.r = T % W;
+      shares(l);
+    }
+  printf("%ld checks, %ld wrong\n", checked, bad);
+  return bad != 0;
+}
+"""
+
+
+@pytest.mark.skipif(not shutil.which(HIPCC), reason="no hipcc")
+def test_shares_and_owners_of_the_work_split(tmp_path):
+    src = tmp_path / "sched.hip"
+    src.write_text(PROGRAM)
+    exe = tmp_path / "sched"
+    subprocess.run([HIPCC, "-O2", "-std=c++17", "--offload-arch=gfx950", "--offload-host-only", "-I", os.path.join(ROOT, "paper_2509_24248_amd", "csrc"),
+                    str(src), "-o", str(exe)], check=True)
+    run = subprocess.run([str(exe)], capture_output=True, text=True, timeout=100)
+    assert run.returncode == 0, run.stdout
+    assert int(run.stdout.split()[0]) > 5_000_000

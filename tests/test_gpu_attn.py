@@ -135,10 +135,11 @@ def test_shares_at_the_edges_of_the_work_split(d, n_q, L, page):
 
 @pytest.mark.parametrize("dtype", ["bf16", "f32"])
 @pytest.mark.parametrize("B,lengths,longest", [(1, (4090,), 4096), (1, (4111,), 4111), (1, (5610,), 5610), (1, (3900,), 5610), (1, (8150,), 8150), (2, (4000, 200), 4000),
-                                               (3, (1500, 1600, 0), 1600)])
+                                               (3, (1500, 1600, 0), 1600), (5, (1000,) * 5, 1000), (8, (700,) * 8, 700)])
 def test_shares_of_the_middle_range(dtype, B, lengths, longest):
     # four KV heads: up to 256 granules a workgroup each, from 257 on equal shares of two, of three; a cache that could hold more granules
-    # than there are (the launch is sized for the cache), and a last workgroup with part of a share
+    # than there are (the launch is sized for the cache), shares that are not all equal; five and eight sequences of one length, a whole
+    # number of shares per unit
     shape = gen.scaled(gen.config(1), dtype=dtype, B=B, Hq=8, Hkv=4, d=64, n_q=3, ctx=(longest, longest))
     L, kv, q, mask = case(shape, 4)
     L[:] = lengths
