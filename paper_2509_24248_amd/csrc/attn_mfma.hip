@@ -248,9 +248,14 @@ __global__ __launch_bounds__(64 * kNK * NR, min_waves_per_simd(HD, NR)) void k_a
   }
   const float sl2 = a.scale * 1.44269504088896340736f;  // scores are kept in log2 units
 
-  // every slot is free here: a short segment has all its tiles in flight at once, behind the queries and at the same time
+  // Every slot is free here: a short segment has all its tiles in flight at once, behind the queries and at the same time.  In the
+  // deep rings of a longer one that is up to 128 KB in front of the first matrix instruction, and nothing is requested
+  // meanwhile: there the wait is for the queries and the first tile (a paged launch has the queries with the page ids), and the other
+  // tiles follow it.  8 sequences x 4096 entries, 64 rows, contiguous 35.2 -> 33.6 us, paged 38.5 -> 36.6 (two-slot
+  // rings gain nothing from it).
+  const int together = S == 2 ? S : PAGED ? 0 : nit < S ? S : 1;
 #pragma unroll 1
-  for (int it = 0; it < S; ++it) {
+  for (int it = 0; it < together; ++it) {
     locate(it);
     issue(it);
   }
@@ -265,14 +270,22 @@ __global__ __launch_bounds__(64 * kNK * NR, min_waves_per_simd(HD, NR)) void k_a
   int v_at = (4 * fq_t + ve) * kRowB + (((vc >> 1) ^ swz_v<HD>(4 * fq_t + ve)) << 4) + ((vc & 1) << 3);
 
   __builtin_amdgcn_s_waitcnt(vmcnt_imm(0));    // from here on vmcnt counts tile loads only
+  if constexpr (S > 2) {
+#pragma unroll 1
+    for (int it = together; it < S; ++it) {
+      locate(it);
+      issue(it);
+    }
+  }
 
 #pragma unroll 1                              // (no first round of its own: code that is run once is fetched for that)
   for (int it = 0; it < nit; ++it) {
     if (it > 0) locate(it + S - 1);
-    // this wave's pieces of tile `it` have landed once at most the pieces of the S-2 tiles
-    // issued after it are outstanding (loads return in order); near the end simply wait for all
-    if (S > 2 && it + S - 1 < nit) __builtin_amdgcn_s_waitcnt(vmcnt_imm((S - 2) * kPiecesMin));
-    else __builtin_amdgcn_s_waitcnt(vmcnt_imm(0));
+    // this wave's pieces of tile `it` have landed once at most the pieces of the S-2 tiles (S-1 before the first, if this ring
+    // has that many) issued after it are outstanding (loads return in order); near the end simply wait for all
+    if (S == 2 || it + S - 1 >= nit) __builtin_amdgcn_s_waitcnt(vmcnt_imm(0));
+    else if (it == 0 && (S - 1) * kNK + kg < ntl) __builtin_amdgcn_s_waitcnt(vmcnt_imm((S - 1) * kPiecesMin));
+    else __builtin_amdgcn_s_waitcnt(vmcnt_imm((S - 2) * kPiecesMin));
     // plain barrier (no memory fence: a fence would wait for the loads still in flight); the
     // wave-scope fences only keep the compiler from moving LDS accesses across it
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");

@@ -133,6 +133,20 @@ def test_shares_at_the_edges_of_the_work_split(d, n_q, L, page):
     check(shape, L, kv, 4 * gen.queries(shape, 13), None, label="split edges")
 
 
+@pytest.mark.parametrize("page", [0, 16])
+@pytest.mark.parametrize("d,n_q", [(128, 25), (128, 57), (64, 17), (64, 33)])
+@pytest.mark.parametrize("L", [(5000, 4973, 5041), (2600, 2631, 2664, 2697, 3000), (700, 3001, 1234, 4100)])
+def test_segments_around_the_depth_of_the_rings(d, n_q, page, L):
+    # rings of four and eight slots, eight KV heads: segments of 4 to 11 granules with shorter ones at the units' ends, whose last tile
+    # step has a tile for one ring or both, whole or not.  q.k is scaled up so that a lost or doubled tile shows.
+    shape = gen.scaled(gen.config(1), B=len(L), Hq=16, Hkv=8, d=d, n_q=n_q, k=n_q - 1, ctx=(0, 1), page_size=page or 16)
+    L = np.array(L, np.int32)
+    kv = gen.kv_cache(shape, L, n_q, 17, paged=page > 0)
+    rng = np.random.default_rng(n_q)
+    only = [(b, int(i), int(rng.integers(16))) for b in range(len(L)) for i in (0, n_q // 2, n_q - 1) for _ in range(8)]
+    check(shape, L, kv, 4 * gen.queries(shape, 17), None, only=only, label="ring depth")
+
+
 @pytest.mark.parametrize("dtype", ["bf16", "f32"])
 @pytest.mark.parametrize("B,lengths,longest", [(1, (4090,), 4096), (1, (4111,), 4111), (1, (5610,), 5610), (1, (3900,), 5610), (1, (8150,), 8150), (2, (4000, 200), 4000),
                                                (3, (1500, 1600, 0), 1600), (5, (1000,) * 5, 1000), (8, (700,) * 8, 700)])
