@@ -59,7 +59,7 @@ __global__ __launch_bounds__(256) void k_attn_split_valu(const AttnArgs a) {
   float* As = Ls + R;                     // [R] rescale of this tile
   int* sched_lds = reinterpret_cast<int*>(As + R);
   attn_sched_build(a, sched_lds);
-  const AttnLine line = attn_sched_line(__builtin_amdgcn_readfirstlane(sched_lds[a.B]), a.B, a.Hkv, a.pad, a.wide_from, a.wgrid);
+  const AttnLine line = attn_sched_line(__builtin_amdgcn_readfirstlane(sched_lds[a.B]), a.B, a.Hkv, a.pad, a.wide_from, a.use_mfma == kOnePart, a.wgrid);
   if (blockIdx.x == 0) {
     attn_sched_publish(a, sched_lds, line);
   }
@@ -254,7 +254,7 @@ __global__ __launch_bounds__(256) void k_attn_split_rows(const AttnArgs a) {
   float* As = Ls + R;               // [R] rescale of this tile
   int* sched_lds = reinterpret_cast<int*>(As + R);   // [2 B + 1]
   attn_sched_build(a, sched_lds);
-  const AttnLine line = attn_sched_line(sched_lds[a.B], a.B, a.Hkv, a.pad, a.wide_from, a.wgrid);
+  const AttnLine line = attn_sched_line(sched_lds[a.B], a.B, a.Hkv, a.pad, a.wide_from, a.use_mfma == kOnePart, a.wgrid);
   if (blockIdx.x == 0) {
     attn_sched_publish(a, sched_lds, line);
   }
@@ -391,30 +391,32 @@ __global__ __launch_bounds__(256) void k_attn_split_rows(const AttnArgs a) {
   }
 }
 
-// One output row of a 64-wide bf16 launch again, by one wave, with fp32 probabilities.  The matrix-core kernel
+// One output row of a launch with two-part probabilities again, by one wave, with fp32 ones.  The matrix-core kernel
 // multiplies V with a probability in two parts, of which the second is 0 or negative as often as not: an infinite V
 // entry then becomes inf - inf or 0 inf, although its probability is positive.  So the merging kernels hand every row
 // that is not finite to this function: infinities come out as the one product p v gives them, and NaN where the
 // inputs ask for it (a NaN among them, infinities of both signs, an infinite entry that the mask hides: 0 inf).
-// Eight lanes take a key, eight of its columns each; the running maximum moves every eight keys.  A launch without
+// A lane takes eight columns of a key, eight or four keys go together, and the running maximum moves with them.  A launch without
 // such rows pays for the test only (verify_attn, 8 sequences of 1000-8000 entries, 16 queries: 35.0 -> 35.7 us; 64 of
 // 500, 8 queries: 27 us either way); one in which every row is infinite takes 1.2 ms at the first of these sizes.
+template <int D>
 __device__ __forceinline__ void attn_row_again(const AttnArgs& a, int b, int i, int h) {
+  constexpr int LPK = D / 8, KPW = 64 / LPK;     // lanes of a key, keys of a wave
   const int lane = threadIdx.x & 63;
-  const int kq = lane >> 3, c = lane & 7;
+  const int kq = lane / LPK, c = lane % LPK;
   const int G = a.Hq / a.Hkv, g = h / G;
   const int L = attn_ctx_len(a, b), n = L + a.n_blk;
-  const size_t row = ((static_cast<size_t>(b) * a.n_q + i) * a.Hq + h) * 64;
+  const size_t row = ((static_cast<size_t>(b) * a.n_q + i) * a.Hq + h) * D;
   const uint64_t seen = a.mask ? a.mask[static_cast<size_t>(b) * a.mask_stride + i] : ((2ull << i) - 1ull);
   float q[8], acc[8], m = -INFINITY, sum = 0.f;
   unpack16(*reinterpret_cast<const uint4*>(static_cast<const bf16_t*>(a.q) + row + 8 * c), q);
 #pragma unroll
   for (int e = 0; e < 8; ++e) acc[e] = 0.f;
 #pragma unroll 1
-  for (int p0 = 0; p0 < n; p0 += 8) {
+  for (int p0 = 0; p0 < n; p0 += KPW) {
     const int p = p0 + kq;
     const bool in = p < n;
-    const size_t at = kv_entry(a, b, g, min(p, n - 1)) * 8 + c;
+    const size_t at = kv_entry(a, b, g, min(p, n - 1)) * LPK + c;
     const uint4 kr = static_cast<const uint4*>(a.k)[at], vr = static_cast<const uint4*>(a.v)[at];
     float kf[8], vf[8], x = 0.f;
     unpack16(kr, kf);
@@ -422,12 +424,12 @@ __device__ __forceinline__ void attn_row_again(const AttnArgs& a, int b, int i, 
 #pragma unroll
     for (int e = 0; e < 8; ++e) x = fmaf(q[e], kf[e], x);
 #pragma unroll
-    for (int o = 1; o < 8; o <<= 1) x += __shfl_xor(x, o, 64);
+    for (int o = 1; o < LPK; o <<= 1) x += __shfl_xor(x, o, 64);
     const bool vis = in && (p < L || (seen >> (p - L) & 1ull));
     x = vis ? x * a.scale : -INFINITY;
     float mt = x;
 #pragma unroll
-    for (int o = 8; o < 64; o <<= 1) mt = fmaxf(mt, __shfl_xor(mt, o, 64));
+    for (int o = LPK; o < 64; o <<= 1) mt = fmaxf(mt, __shfl_xor(mt, o, 64));
     const float m_new = fmaxf(m, mt);
     float al = 1.f, pr = 0.f;
     if (m_new != -INFINITY) {
@@ -440,11 +442,12 @@ __device__ __forceinline__ void attn_row_again(const AttnArgs& a, int b, int i, 
     for (int e = 0; e < 8; ++e) acc[e] = fmaf(pr, in ? vf[e] : 0.f, acc[e] * al);
   }
 #pragma unroll
-  for (int o = 8; o < 64; o <<= 1) {
+  for (int o = LPK; o < 64; o <<= 1) {
     sum += __shfl_xor(sum, o, 64);
 #pragma unroll
     for (int e = 0; e < 8; ++e) acc[e] += __shfl_xor(acc[e], o, 64);
   }
+  __threadfence();                  // the first result has been stored
   if (kq == 0) {
     bf16_t* dst = static_cast<bf16_t*>(a.out) + row + 8 * c;
 #pragma unroll
@@ -463,7 +466,8 @@ struct RowSegs {
 template <int D>
 __device__ __forceinline__ RowSegs row_segments(const AttnArgs& a, int b, int i, int h) {
   const int G = a.G, R = G * a.n_q, g = h / G, r = i * G + h - g * G;
-  const int s0 = a.sched[b], s1 = a.sched[b + 1];
+  const attn_sched_t S = (attn_sched_t)a.sched;
+  const int s0 = S[b], s1 = S[b + 1];
   const AttnLine line = attn_sched_read(a);
   const int p_u = a.Hkv * (s0 + line.pad * b) + g * (s1 - s0 + line.pad) + line.pad;     // the unit's first keys on the line
   const int w_first = attn_sched_owner(line, p_u);
@@ -492,6 +496,7 @@ __global__ __launch_bounds__(kCombThreads) void k_attn_combine(const AttnArgs a)
   constexpr int C4 = D / 4;                 // float4 columns of a row
   constexpr int NG = kCombThreads / C4;     // groups
   __shared__ float4 gs[NG][C4];
+  arguments_at_once<sizeof(AttnArgs)>();
   const int h = blockIdx.x, i = blockIdx.y, b = blockIdx.z;
   const int lane = threadIdx.x & 63;
   const RowSegs q = row_segments<D>(a, b, i, h);
@@ -546,12 +551,6 @@ __global__ __launch_bounds__(kCombThreads) void k_attn_combine(const AttnArgs a)
       sum.x /= den; sum.y /= den; sum.z /= den; sum.w /= den;
     }
   }
-  if constexpr (D == 64 && sizeof(T) == 2) {
-    if (a.use_mfma && threadIdx.x < 64 && any_not_finite((sum.x + sum.y) + (sum.z + sum.w))) {
-      attn_row_again(a, b, i, h);
-      return;
-    }
-  }
   if (sg == 0) {
     T* dst = static_cast<T*>(a.out) + ((static_cast<size_t>(b) * a.n_q + i) * a.Hq + h) * D + c4 * 4;
     if constexpr (sizeof(T) == 2) {
@@ -559,6 +558,9 @@ __global__ __launch_bounds__(kCombThreads) void k_attn_combine(const AttnArgs a)
     } else {
       *reinterpret_cast<float4*>(dst) = sum;
     }
+  }
+  if constexpr (sizeof(T) == 2) {             // (behind the store, off the way of it)
+    if (__builtin_expect(a.use_mfma == kTwoPart && threadIdx.x < 64 && any_not_finite((sum.x + sum.y) + (sum.z + sum.w)), 0)) attn_row_again<D>(a, b, i, h);
   }
 }
 
@@ -571,6 +573,7 @@ constexpr int kRowEarly = 4;
 template <typename T, int D>
 __global__ __launch_bounds__(256) void k_attn_combine_rows(const AttnArgs a) {
   constexpr int EPL = D / 64;               // columns per lane
+  arguments_at_once<sizeof(AttnArgs)>();
   const int lane = threadIdx.x & 63;
   const int row = __builtin_amdgcn_readfirstlane(blockIdx.x * 4 + (threadIdx.x >> 6));
   if (row >= a.B * a.n_q * a.Hq) return;
@@ -620,15 +623,12 @@ __global__ __launch_bounds__(256) void k_attn_combine_rows(const AttnArgs a) {
     }
   }
   den = wave_sum_dpp(den);
-  if constexpr (D == 64 && sizeof(T) == 2) {
-    if (a.use_mfma && any_not_finite(acc[0] / den)) {
-      attn_row_again(a, b, i, h);
-      return;
-    }
-  }
   T* dst = static_cast<T*>(a.out) + static_cast<size_t>(row) * D + lane * EPL;
 #pragma unroll
   for (int e = 0; e < EPL; ++e) Elem<T>::store(dst + e, acc[e] / den);
+  if constexpr (sizeof(T) == 2) {
+    if (__builtin_expect(a.use_mfma == kTwoPart && any_not_finite((D == 64 ? acc[0] : acc[0] + acc[EPL - 1]) / den), 0)) attn_row_again<D>(a, b, i, h);
+  }
 }
 
 template <typename T, int D>
@@ -701,7 +701,7 @@ static bool plan_as(AttnArgs& a, int num_cus, int use_mfma, int pad) {
   // set: as many as are resident at once (one or two of the matrix-core kernel per compute unit),
   // fewer when even the longest possible caches would leave them too few granules
   // (attn_sched_line), more when a share could otherwise exceed what one segment can hold.
-  a.use_mfma = use_mfma;
+  a.use_mfma = use_mfma ? (attn_mfma_two_part(a) ? kTwoPart : kOnePart) : 0;
   a.G = a.Hq / a.Hkv;
   a.g_inv = (65536 + a.G - 1) / a.G;
   a.pad = pad;
@@ -712,7 +712,7 @@ static bool plan_as(AttnArgs& a, int num_cus, int use_mfma, int pad) {
   if (units * (gmax + pad) >= (1ll << 30)) return false;
   a.stages = a.use_mfma ? attn_mfma_stages(a) : 0;
   const int64_t resident = static_cast<int64_t>(num_cus) * (a.use_mfma ? attn_mfma_per_cu(a) : 1);
-  const AttnLine line = attn_sched_line(static_cast<int>(a.B * gmax), a.B, a.Hkv, pad, a.wide_from, static_cast<int>(resident));
+  const AttnLine line = attn_sched_line(static_cast<int>(a.B * gmax), a.B, a.Hkv, pad, a.wide_from, a.use_mfma == kOnePart, static_cast<int>(resident));
   int64_t w = line.W;
   if (line.T > kAttnSpread && w < kAttnSpread) w = std::min<int64_t>(kAttnSpread, resident);   // (fewer granules may take more workgroups)
   if (a.use_mfma) {

@@ -49,6 +49,7 @@ constexpr int slot_bytes(int hd) { return 128 * hd; }   // one ring slot: 32 K r
 // four waves per ring, and the rings take twice the slots in the same LDS.  Measured at 64 rows per KV
 // head, contexts 1000-8000 of 8 sequences (74 MB), whole call: 26 us; on the ALU kernel 365 us.
 constexpr int big_from(int hd) { return hd == 64 ? 5 : 4; }
+constexpr bool two_part(int hd, int nr) { return hd == 64 || nr <= 3; }     // (see kSplitP)
 constexpr int stages_of(int hd, int nr) { return (nr >= big_from(hd) ? 4 : 2) * (hd == 64 ? 2 : 1); }
 // K operand reads / V operand read pairs issued ahead of the matrix instructions that use them: as
 // many as the registers allow (one resident workgroup: all eight K reads, four V pairs; 64-wide heads
@@ -97,13 +98,18 @@ __global__ __launch_bounds__(64 * kNK * NR, min_waves_per_simd(HD, NR)) void k_a
   constexpr int kChunks = HD / 8;               // 16-byte chunks of a cache row
   constexpr int kKeysPP = 1024 / kRowB;         // keys of a 1 KB piece
   constexpr int kTileP = 32 / kKeysPP;          // pieces of a K (or V) tile
-  // 64-wide heads keep their probabilities as a bf16 value plus the bf16 rounding of the rest, 16 to 17 bits: the ALU
+  // Probabilities as a bf16 value plus the bf16 rounding of the rest, 16 to 17 bits.  64-wide heads: the ALU
   // kernel that served them multiplied with fp32 probabilities.  What is lost (2^-17 relative per probability) is far below
   // the bf16 rounding of the output: error against 64 bits over eight inputs each, that kernel / this one, 8 contexts of
   // 300-3000 x 16 queries 1.658633e-3 / 1.658634e-3, 4 of 64-200 x 5 1.661877e-3 / 1.661878e-3, 1 of 9000 x 7 1.660461e-3 /
-  // 1.660462e-3.  An infinite V entry is not what the two parts can multiply with: the merging kernels compute rows
-  // that are not finite again.
-  constexpr bool kSplitP = HD == 64;
+  // 1.660462e-3.  128-wide heads of up to 48 rows: the matrix cores have the time (36 layers of 1 sequence x 4096 entries, 28 rows: 445
+  // us with one part, 449 with two; 8 of 4000-8000, 40 rows, paged 53 and 46, because two parts need no sum by matrix instructions
+  // and leave nothing in scratch memory), and with one part the error grows where the work split makes segments larger
+  // (2.055e-3 with the segments of an unpadded split, 2.077e-3 with today's; 1.657e-3 with two parts).  More rows: two parts
+  // cost 3 to 9 % (16 sequences of 8192-32768, 72 rows: 237 and 259 us), so the probabilities keep one.
+  // An infinite V entry is not what the two parts can multiply with: the merging kernels compute rows that are not finite
+  // again.
+  constexpr bool kSplitP = two_part(HD, NR);
   // Slack of the softmax reference in log2 units: with probabilities of 16 bits it does not matter how far above 1 they
   // reach (8 sequences of 1000-8000 entries, 64 rows per KV head: 27.8 -> 26.8 us, the same error).  bf16 ones are nearest where the
   // largest are 1 or just below: a slack of 8 is 3 % faster at 72 rows per KV head and costs 6 % of the error against 64 bits
@@ -125,7 +131,7 @@ __global__ __launch_bounds__(64 * kNK * NR, min_waves_per_simd(HD, NR)) void k_a
   const int R = G * a.n_q;
   const int fr = lane & 15, fq = lane >> 4;
   attn_sched_build(a, sched_lds);
-  const AttnLine line = attn_sched_line(__builtin_amdgcn_readfirstlane(sched_lds[a.B]), a.B, a.Hkv, a.pad, a.wide_from, a.wgrid);
+  const AttnLine line = attn_sched_line(__builtin_amdgcn_readfirstlane(sched_lds[a.B]), a.B, a.Hkv, a.pad, a.wide_from, a.use_mfma == kOnePart, a.wgrid);
   if (blockIdx.x == 0) {
     // the merging kernel reads the split back from here
     attn_sched_publish(a, sched_lds, line);
@@ -515,6 +521,7 @@ static int waves_per_ring(const AttnArgs& a) {
   return (row_tiles(a) + per - 1) / per;
 }
 int attn_mfma_per_cu(const AttnArgs& a) { return waves_per_ring(a) >= big_from(a.d) ? 1 : 2; }
+bool attn_mfma_two_part(const AttnArgs& a) { return two_part(a.d, waves_per_ring(a)); }
 int attn_mfma_stages(const AttnArgs& a) { return stages_of(a.d, waves_per_ring(a)); }
 
 size_t attn_mfma_lds_bytes(const AttnArgs& a) {

@@ -73,7 +73,10 @@ __device__ __forceinline__ void attn_sched_build(const AttnArgs& a, int* S) {
 // are resident, with at least two granules each.
 // In the middle range that is a whole number of workgroups per unit where 256 allow it: sequences of one length, whose units
 // are equal, then have no workgroup that crosses a unit's end.  (8 sequences x 2048 entries, 8 KV heads, 16 queries of 32 heads: 24.0
-// us a layer; 28.1 with 249 workgroups of nine granules each, whose every other one starts a second segment.)
+// us a layer; 28.1 with 249 workgroups of nine granules each, whose every other one starts a second segment.)  `spread` launches
+// take 256 all the same: their probabilities have 8 bits, the largest of a segment none to lose, so fewer segments are less exact (4
+// sequences x 600, 68 rows: error against 64 bits 2.059e-3 with the fewest workgroups, 2.044e-3 with 256, 2.039e-3 without
+// padding, where unequal lengths take 5 to 20 % longer; time within 5 % of one another either way).
 constexpr int kAttnSpread = 256;
 constexpr int kAttnMaxGrid = 14336;       // workgroups; more are refused
 struct AttnLine {
@@ -92,7 +95,7 @@ __host__ __device__ __forceinline__ float attn_sched_rcp(int x) {
 __host__ __device__ __forceinline__ int attn_sched_div(int a, int b) {
   return static_cast<int>((static_cast<float>(a) + 0.5f) * attn_sched_rcp(b));
 }
-__host__ __device__ __forceinline__ AttnLine attn_sched_line(int gran, int B, int Hkv, int pad, int wide_from, int wgrid) {
+__host__ __device__ __forceinline__ AttnLine attn_sched_line(int gran, int B, int Hkv, int pad, int wide_from, int spread, int wgrid) {
   AttnLine l;
   l.T = gran * Hkv;
   l.pad = l.T <= kAttnSpread ? 0 : pad;
@@ -104,7 +107,7 @@ __host__ __device__ __forceinline__ AttnLine attn_sched_line(int gran, int B, in
     want = (l.T + 1) >> 1;
     if (!wide || want < kAttnSpread) {                                    // (T < 2^21)
       const int most = (l.T + kAttnSpread - 1) / kAttnSpread;             // the largest share
-      want = units * attn_sched_div(l.T + units * most - 1, units * most);
+      want = spread ? kAttnSpread : units * attn_sched_div(l.T + units * most - 1, units * most);
       if (want > kAttnSpread) want = attn_sched_div(l.T + most - 1, most);
     }
   }
@@ -140,8 +143,10 @@ __device__ __forceinline__ void attn_sched_publish(const AttnArgs& a, const int*
     w[0] = l.W; w[1] = l.q; w[2] = l.r; w[3] = l.pad;
   }
 }
+// (through scalar loads: b is uniform, and nothing writes it while the merging kernel runs)
+typedef const __attribute__((address_space(4))) int* attn_sched_t;
 __device__ __forceinline__ AttnLine attn_sched_read(const AttnArgs& a) {
-  const int* w = a.sched + a.B + 1;
+  const attn_sched_t w = (attn_sched_t)a.sched + a.B + 1;
   AttnLine l;
   l.W = w[0]; l.q = w[1]; l.r = w[2]; l.pad = w[3];
   l.T = l.q * l.W + l.r;

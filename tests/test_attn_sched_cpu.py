@@ -43,7 +43,7 @@ int main() {
     const int B = k % 4 == 0 ? 1 + below(1024) : 1 + below(24), Hkv = 1 + below(k % 3 ? 8 : 64), pad = below(4);
     const int gran = B + (k % 5 == 0 ? below(1l << 20) / Hkv : below(k % 2 ? 40 : 700));
     const int wide_from = static_cast<long>(B) * Hkv >= kAttnSpread ? 0 : 1000 + below(2601), wgrid = k % 7 == 0 ? kAttnMaxGrid : k % 2 ? 256 : 512;
-    const AttnLine l = attn_sched_line(gran, B, Hkv, pad, wide_from, wgrid);
+    const AttnLine l = attn_sched_line(gran, B, Hkv, pad, wide_from, k % 3 == 1, wgrid);
     const long bare = static_cast<long>(gran) * Hkv, T = bare + (bare > kAttnSpread ? static_cast<long>(B) * Hkv * pad : 0);
     expect(l.T == T && l.W >= 1 && l.W <= wgrid && l.W <= T, "line", gran, B, Hkv, l.W);
     if (bare > kAttnSpread && bare < wide_from)       // the middle range: no share above what 256 workgroups would have

@@ -15,7 +15,6 @@ LIB = os.path.join(ROOT, "paper_2509_24248_amd", "libspecexit.so")
 # Bytes of scratch memory per lane, at most; kernels that are not listed use none.  Each entry is stated with its timing
 # beside the kernel.
 SPILLS = {
-    "k_attn_ring<128, 3, 1, 2, true>": 16,     # paged caches, 33..48 query rows per KV head
     # the one-level chunk tree of the heads, for weight rows 4 KB apart
     "k_head_wide<2, 2, 2, 1, 1, 8, 4, false, 1>": 16,
     "k_head_wide<3, 2, 2, 1, 1, 8, 4, false, 1>": 20,
