@@ -436,6 +436,7 @@ __device__ __forceinline__ void attn_row_again(const AttnArgs& a, int b, int i, 
       al = m == -INFINITY ? 0.f : expf(m - m_new);
       pr = expf(x - m_new);
     }
+    if (x != x) pr = x;                       // (also where no score has been a number yet)
     m = m_new;
     sum = fmaf(sum, al, pr);
 #pragma unroll
@@ -482,6 +483,10 @@ __device__ __forceinline__ RowSegs row_segments(const AttnArgs& a, int b, int i,
 }
 __device__ __forceinline__ float seg_exp(const AttnArgs& a, float x) { return a.use_mfma ? exp2f(x) : expf(x); }
 
+// A segment's part of the sum.  NaN counts whatever the weight: a maximum passes NaN over, so that a segment whose scores are NaN
+// can be left with the lowest one.
+__device__ __forceinline__ float seg_sum(float w, float l) { return w != 0.f || l != l ? w * l : 0.f; }
+
 // Merge the segments of one (sequence, query, head): exact log-sum-exp combination.  One workgroup per output row; groups
 // of lanes take every NG-th segment of one float4 column and are added in a fixed order.
 // Latency is all there is (a row reads 17 KB at 33 segments): the length table, the workgroups' range, one round to memory, a
@@ -514,7 +519,7 @@ __global__ __launch_bounds__(kCombThreads) void k_attn_combine(const AttnArgs a)
   for (int s0 = 0; s0 < q.n; s0 += 64) {
     if (s0 > 0) ml = *reinterpret_cast<const float2*>(q.ml + min(s0 + lane, q.n - 1) * q.ml_step);
     const float w = s0 + lane < q.n && ml.x != -INFINITY ? seg_exp(a, ml.x - mmax) : 0.f;
-    den += w != 0.f ? w * ml.y : 0.f;       // (lane by lane, summed behind the loop)
+    den += seg_sum(w, ml.y);                // (lane by lane, summed behind the loop)
     const int n = min(64, q.n - s0);
     for (int sb = 0; sb < n; sb += kEarly * NG) {     // (uniform: a shuffle reads lanes that take part only)
       const int s = sb + sg;
@@ -601,7 +606,7 @@ __global__ __launch_bounds__(256) void k_attn_combine_rows(const AttnArgs a) {
   for (int s0 = 0; s0 < q.n; s0 += 64) {
     if (s0 > 0) ml = *reinterpret_cast<const float2*>(q.ml + min(s0 + lane, q.n - 1) * q.ml_step);
     const float w = s0 + lane < q.n && ml.x != -INFINITY ? seg_exp(a, ml.x - mmax) : 0.f;
-    den += w != 0.f ? w * ml.y : 0.f;       // (lane by lane, summed behind the loop)
+    den += seg_sum(w, ml.y);                // (lane by lane, summed behind the loop)
     auto weight = [&](int j) { return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(w), j)); };
     const int n = min(64, q.n - s0);
     int j = 0;

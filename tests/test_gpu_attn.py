@@ -109,6 +109,18 @@ def test_infinite_values_of_narrow_heads(B, n_q, page, d):
     assert rel_err(got[plain], ref[plain]) < TOL["bf16"]
 
 
+@pytest.mark.parametrize("d,n_q,every", [(128, 16, 4), (128, 7, 4), (64, 7, 4), (128, 16, 1), (64, 7, 1)])
+def test_scores_that_are_nan_are_not_passed_over(d, n_q, every):
+    # keys with a NaN, at least one for each lane that a row's scores lie in, in the first of several segments: its maximum then knows
+    # no number, and its weight must not become 0.  Every query sees these keys, so all rows of their KV head are NaN.
+    shape = gen.scaled(gen.config(1), B=2, Hq=8, Hkv=2, d=d, n_q=n_q, k=n_q - 1, ctx=(300, 300))
+    L, kv, q, _ = case(shape, 8, paged=False)
+    kv.k[1, 0, 0:64:every, 3] = np.nan
+    got = gpu_verify_attn(shape, kv, q, L, None)
+    assert np.isnan(got[1, :, :4]).all()
+    assert np.isfinite(got[1, :, 4:]).all() and np.isfinite(got[0]).all()
+
+
 @pytest.mark.parametrize("n_q,L,paged", [(4, (3000,), False), (7, (4096,), False), (12, (900, 2500), True), (7, (700, 1500, 400, 1100, 900, 300), True)])
 def test_probabilities_of_few_wide_rows_have_two_parts(n_q, L, paged):
     # 128-wide heads of up to 48 rows per KV head: what is left of the error is the rounding of the output to bf16, 2^-9 / sqrt(3) of a
