@@ -1,9 +1,11 @@
 """GPU parity: specexit_verify_attn against the oracle."""
 import numpy as np
 import pytest
+import torch
 
 from workloads import gen
 
+import harness as H
 from harness import TOL, gpu_verify_attn, oracle_verify_attn, rel_err
 
 pytestmark = pytest.mark.gpu
@@ -195,6 +197,28 @@ def test_alu_kernels_of_wide_heads(dtype, n_q, page):
     L, kv, q, mask = case(shape, 6, paged=page > 0)
     L[0] = 0
     check(shape, L, kv, q, mask, label="wide heads on the ALUs")
+
+
+@pytest.mark.parametrize("dtype,d", [("bf16", 64), ("bf16", 128), ("f32", 64), ("f32", 128)])
+@pytest.mark.parametrize("B,n_q", [(2, 3), (40, 7)])
+def test_outputs_begin_at_any_element(dtype, d, B, n_q):
+    # merged by a workgroup per row and by a wave per row: the output buffer asks for no alignment beyond its elements'
+    shape = gen.scaled(gen.config(1), dtype=dtype, B=B, Hq=8, Hkv=2, d=d, n_q=n_q, ctx=(20, 400))
+    L, kv, q, _ = case(shape, 9)
+    lib = H.sx()
+    view, keep = H.kv_view_of(shape, kv)
+    qd, ctx = H.dev(q, shape), H.dev(L.astype(np.int32))
+    ws = H.workspace(lib.specexit_verify_attn_workspace_bytes(view, B, n_q, shape.Hq))
+    got = []
+    for first in (0, 1, 2, 3):
+        buf = torch.full((qd.numel() + 8,), 7.0, dtype=qd.dtype, device="cuda")
+        out = buf[first:first + qd.numel()].view(qd.shape)
+        lib.specexit_verify_attn(view, B, n_q, shape.Hq, qd, ctx, None, d ** -0.5, out, ws)
+        torch.cuda.synchronize()
+        assert bool((buf[:first] == 7.0).all()) and bool((buf[first + qd.numel():] == 7.0).all())
+        got.append(H.host(out))
+    for g in got[1:]:
+        np.testing.assert_array_equal(g, got[0])
 
 
 def test_paged_equals_contiguous_on_gpu():
