@@ -36,24 +36,28 @@ __device__ __forceinline__ size_t kv_entry(const AttnArgs& a, int b, int g, int 
 constexpr int kTK = kAttnGran;
 constexpr int kTP = kTK + 4;              // floats per row of probabilities (padded: several rows of it are read at once)
 constexpr size_t kValuLds = 150 * 1024;
-// LDS of the kernel: V tiles share the K tiles' place where both do not fit
-__host__ __device__ inline size_t valu_lds_bytes(int R, int d, int B, bool shared) {
-  return sizeof(float) * (static_cast<size_t>(R) * (d + kTP + 3) + kTK * (d + 4) + (shared ? 0 : kTK * d) + attn_sched_words(B));
+__host__ __device__ constexpr size_t valu_lds_bytes(int R, int d, int B) {
+  return sizeof(float) * (static_cast<size_t>(R) * (d + kTP + 3) + kTK * (d + 4) + kTK * d + attn_sched_words(B));
 }
+// Most rows that the kernel is built for: its accumulators are sized for them (with those of 128 rows for all, 128-wide heads
+// of 16 / 32 rows took 24 / 35 us where they take 19 / 28 now, 4 sequences of 900 entries, 16 heads over 4).  128-wide heads of more rows
+// go to the kernel below.
+__host__ __device__ constexpr int valu_rows_few(int d) { return d == 128 ? 32 : 64; }
+__host__ __device__ constexpr int valu_rows_most(int d) { return d == 128 ? 64 : 128; }
+static_assert(valu_lds_bytes(valu_rows_most(64), 64, kAttnMaxSeqs) <= kValuLds && valu_lds_bytes(valu_rows_most(128), 128, kAttnMaxSeqs) <= kValuLds, "K and V tiles fit beside the rows");
 
-template <typename T, int D>
+template <typename T, int D, int ROWS>
 __global__ __launch_bounds__(256) void k_attn_split_valu(const AttnArgs a) {
   extern __shared__ float smem[];
   const int G = a.G;
   const int R = G * a.n_q;
   const int tid = threadIdx.x, lane = tid & 63;
   const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const bool shared = valu_lds_bytes(R, D, a.B, false) > kValuLds;   // uniform
   constexpr int DP = D + 4;
   float* Qs = smem;                       // [R][D]
   float* Ks = Qs + R * D;                 // [kTK][DP]
-  float* Vs = shared ? Ks : Ks + kTK * DP;                   // [kTK][D]
-  float* Ss = Ks + kTK * DP + (shared ? 0 : kTK * D);        // [R][kTP] probabilities
+  float* Vs = Ks + kTK * DP;              // [kTK][D]
+  float* Ss = Vs + kTK * D;               // [R][kTP] probabilities
   float* Ms = Ss + R * kTP;               // [R] running max
   float* Ls = Ms + R;                     // [R] running sum
   float* As = Ls + R;                     // [R] rescale of this tile
@@ -68,7 +72,7 @@ __global__ __launch_bounds__(256) void k_attn_split_valu(const AttnArgs a) {
   // RP row slots take kTK / KG keys each
   constexpr int C4 = D / 4;               // float4 columns
   constexpr int RSTEP = 256 / C4;         // rows covered per pass
-  constexpr int MAXU = (128 + RSTEP - 1) / RSTEP;
+  constexpr int MAXU = ROWS / RSTEP;
   const int c4 = tid % C4;
   int KG = 1;
   while (2 * KG * R <= RSTEP) KG *= 2;
@@ -128,10 +132,8 @@ __global__ __launch_bounds__(256) void k_attn_split_valu(const AttnArgs a) {
     if (t0 > s0) __syncthreads();         // the tile before is done with
 #pragma unroll
     for (int u = 0; u < NL; ++u) put(Ks, DP, kr[u], lj + u * JSTEP);
-    if (!shared) {
-      put_v(t0);
-      if (more) fetch(t0 + kTK);
-    }
+    put_v(t0);
+    if (more) fetch(t0 + kTK);
     __syncthreads();
     // scores and softmax: lane = key, wave w has rows w, w + 4, .., four at a time
     const int p = t0 + lane;
@@ -176,11 +178,6 @@ __global__ __launch_bounds__(256) void k_attn_split_valu(const AttnArgs a) {
       }
     }
     __syncthreads();
-    if (shared) {
-      put_v(t0);
-      if (more) fetch(t0 + kTK);
-      __syncthreads();
-    }
 #pragma unroll
     for (int u = 0; u < MAXU; ++u) {
       const int r = r0 + u * RSTEP;
@@ -231,17 +228,19 @@ __global__ __launch_bounds__(256) void k_attn_split_valu(const AttnArgs a) {
 }
 
 // The same for 128-wide heads with many rows, where P V is what takes the time: tiles of 32 keys, a thread per row for the softmax.
-// Whole calls, this one / the one above: fp32, 4 sequences of 900 entries, 68 rows per KV head 46.9 / 56.0 us; 3 of 40-8192, 100 rows
-// 111 / 140; bf16, 8 of 500-2000, 64 rows, pages of 48 201 / 244; fp32, 8 of 1500, 20 rows 42.7 / 41.8.
-constexpr int kManyRows = 32, kTKMany = 32;
-__host__ inline size_t many_lds_bytes(int R, int d, int B) {
+// 48 / 64 / 68 / 96 rows per KV head, calls of 16 heads over 4, this one / the one above built for as many rows: fp32, 4 sequences of
+// 900 entries 41.1 / 37.6, 50.2 / 46.7, 53.5 / 63.0, 67.7 / 80.4 us; 8 of 500-2500 101 / 84, 144 / 120, 154 / 181, 197 / 235; bf16, pages of
+// 48, 4 of 900 40.4 / 36.2, 49.2 / 44.9, 52.7 / 49.2, 67.0 / 62.0 (there the line could lie higher).
+constexpr int kTKMany = 32;
+__host__ __device__ constexpr size_t many_lds_bytes(int R, int d, int B) {
   return sizeof(float) * (static_cast<size_t>(R) * (d + kTKMany + 3) + 2 * kTKMany * (d + 4) + attn_sched_words(B));
 }
+static_assert(many_lds_bytes(128, 128, kAttnMaxSeqs) <= kValuLds, "a tile fits beside the rows");
 
 template <typename T, int D>
 __global__ __launch_bounds__(256) void k_attn_split_rows(const AttnArgs a) {
   extern __shared__ float smem[];
-  const int G = a.Hq / a.Hkv;
+  const int G = a.G;
   const int R = G * a.n_q;
   const int tid = threadIdx.x;
   constexpr int DP = D + 4;
@@ -252,7 +251,7 @@ __global__ __launch_bounds__(256) void k_attn_split_rows(const AttnArgs a) {
   float* Ms = Ss + R * kTKMany;         // [R] running max
   float* Ls = Ms + R;               // [R] running sum
   float* As = Ls + R;               // [R] rescale of this tile
-  int* sched_lds = reinterpret_cast<int*>(As + R);   // [2 B + 1]
+  int* sched_lds = reinterpret_cast<int*>(As + R);
   attn_sched_build(a, sched_lds);
   const AttnLine line = attn_sched_line(sched_lds[a.B], a.B, a.Hkv, a.pad, a.wide_from, a.use_mfma == kOnePart, a.wgrid);
   if (blockIdx.x == 0) {
@@ -268,7 +267,7 @@ __global__ __launch_bounds__(256) void k_attn_split_rows(const AttnArgs a) {
 
   for (int idx = tid; idx < R * D; idx += 256) {
     const int r = idx / D, c = idx % D;
-    const int i = r / G, hh = r % G;
+    const int i = (r * a.g_inv) >> 16, hh = r - i * G;         // r / G
     const T* qp = static_cast<const T*>(a.q) + ((static_cast<size_t>(b) * a.n_q + i) * a.Hq + g * G + hh) * D;
     Qs[idx] = Elem<T>::load(qp + c);
   }
@@ -320,7 +319,7 @@ __global__ __launch_bounds__(256) void k_attn_split_rows(const AttnArgs a) {
       const int p = t0 + j;
       bool vis = p < s1;
       if (vis && p >= L) {
-        const int i = r / G;
+        const int i = (r * a.g_inv) >> 16;
         const uint64_t row = a.mask ? a.mask[static_cast<size_t>(b) * a.mask_stride + i] : ((2ull << i) - 1ull);
         vis = (row >> (p - L)) & 1ull;
       }
@@ -659,11 +658,22 @@ hipError_t launch_combine(const AttnArgs& a, hipStream_t s) {
   return hipGetLastError();
 }
 
+template <typename T, int D, int ROWS>
+hipError_t launch_valu_as(const AttnArgs& a, int R, hipStream_t s) {
+  // set once per process; a function-local static is initialised under the language's own lock,
+  // so first calls from several host threads are safe
+  static const hipError_t attr = hipFuncSetAttribute(reinterpret_cast<const void*>(&k_attn_split_valu<T, D, ROWS>),
+                                                     hipFuncAttributeMaxDynamicSharedMemorySize, kValuLds);
+  if (attr != hipSuccess) return attr;
+  hipLaunchKernelGGL((k_attn_split_valu<T, D, ROWS>), dim3(a.wgrid), dim3(256), valu_lds_bytes(R, D, a.B), s, a);
+  return hipGetLastError();
+}
+
 template <typename T, int D>
 hipError_t launch_valu(const AttnArgs& a, hipStream_t s) {
   const int R = a.G * a.n_q;
   if constexpr (D == 128) {
-    if (R > kManyRows) {
+    if (R > valu_rows_most(D)) {
       static const hipError_t attr = hipFuncSetAttribute(reinterpret_cast<const void*>(&k_attn_split_rows<T, D>),
                                                          hipFuncAttributeMaxDynamicSharedMemorySize, kValuLds);
       if (attr != hipSuccess) return attr;
@@ -671,14 +681,7 @@ hipError_t launch_valu(const AttnArgs& a, hipStream_t s) {
       return hipGetLastError();
     }
   }
-  const size_t smem = valu_lds_bytes(R, D, a.B, valu_lds_bytes(R, D, a.B, false) > kValuLds);
-  // set once per process; a function-local static is initialised under the language's own lock,
-  // so first calls from several host threads are safe
-  static const hipError_t attr = hipFuncSetAttribute(reinterpret_cast<const void*>(&k_attn_split_valu<T, D>),
-                                       hipFuncAttributeMaxDynamicSharedMemorySize, kValuLds);
-  if (attr != hipSuccess) return attr;
-  hipLaunchKernelGGL((k_attn_split_valu<T, D>), dim3(a.wgrid), dim3(256), smem, s, a);
-  return hipGetLastError();
+  return R <= valu_rows_few(D) ? launch_valu_as<T, D, valu_rows_few(D)>(a, R, s) : launch_valu_as<T, D, valu_rows_most(D)>(a, R, s);
 }
 
 }  // namespace

@@ -190,9 +190,11 @@ def test_shares_of_the_middle_range(dtype, B, lengths, longest):
     check(shape, L, kv, q, mask, label="middle range")
 
 
-@pytest.mark.parametrize("dtype,n_q,page", [("f32", 8, 0), ("f32", 9, 0), ("f32", 17, 48), ("f32", 32, 0), ("bf16", 8, 48), ("bf16", 9, 48), ("f32", 1, 48), ("f32", 2, 0)])
+@pytest.mark.parametrize("dtype,n_q,page", [("f32", 8, 0), ("f32", 9, 0), ("f32", 17, 48), ("f32", 32, 0), ("bf16", 8, 48), ("bf16", 9, 48), ("f32", 1, 48), ("f32", 2, 0),
+                                             ("f32", 16, 0), ("bf16", 16, 48), ("bf16", 17, 48)])
 def test_alu_kernels_of_wide_heads(dtype, n_q, page):
-    # four rows a query: 32 rows per KV head in tiles of 64 keys and 36 in tiles of 32, the most rows, and few whose keys the threads share
+    # four rows a query: 32 and 36 rows per KV head with accumulators for 32 and for 64, 64 and 68 in tiles of 64 and of 32 keys, the most
+    # rows, and few whose keys the threads share
     shape = gen.scaled(gen.config(1), dtype=dtype, B=3, Hq=8, Hkv=2, d=128, n_q=n_q, k=max(n_q - 1, 1), ctx=(0, 400), page_size=page or 16)
     L, kv, q, mask = case(shape, 6, paged=page > 0)
     L[0] = 0
