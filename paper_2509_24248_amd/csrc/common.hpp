@@ -71,11 +71,6 @@ __device__ __forceinline__ float wave_sum(float v) {
   for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
   return v;
 }
-__device__ __forceinline__ float wave_max(float v) {
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) v = fmaxf(v, __shfl_xor(v, o, 64));
-  return v;
-}
 
 // Maximum over the four lanes l, l ^ 16, l ^ 32, l ^ 48 (the four k groups of a matrix-core
 // accumulator column) without an LDS round trip: the swap instructions hand every lane both halves

@@ -16,7 +16,7 @@ struct RopeArgs {
   float theta;
   double inv_freq[64];       // theta^(-2c/d) for c < d/2, filled on the host
   int Hq, Hkv, d;
-  void* q_out;               // [rows][Hq][d] bf16
+  void* q_out;               // [rows][Hq][d], bf16 or (row-streaming kernel, fp32 model) fp32
   int paged;
   void *kc, *vc;
   const int32_t* page_table;
