@@ -14,8 +14,11 @@ stated sample of the same workload."""
 from __future__ import annotations
 
 import argparse
+import hashlib
 import json
 import os
+import re
+import struct
 import sys
 import time
 
@@ -307,13 +310,43 @@ def threads_used():
     return int(os.environ.get("OMP_NUM_THREADS", os.cpu_count() or 1))
 
 
-def stored_traffic(kernel_key, shape_name, folder=os.path.join(ROOT, "profiles"), lib=None):
+def kernel_digests(built):
+    """{symbol: first 16 hex digits of the SHA-256 of its machine code} of the kernels in a library's gfx950 code objects."""
+    out = {}
+    for m in re.finditer(b"__CLANG_OFFLOAD_BUNDLE__", built):
+        at = m.end()
+        n, at = struct.unpack_from("<Q", built, at)[0], at + 8
+        for _ in range(n if n <= 16 else 0):                 # (more: the marker as a string, not a bundle)
+            off, size, length = struct.unpack_from("<QQQ", built, at)
+            name, at = built[at + 24:at + 24 + length], at + 24 + length
+            if b"gfx950" not in name or not size:
+                continue
+            elf = built[m.start() + off:m.start() + off + size]
+            shoff, = struct.unpack_from("<Q", elf, 0x28)
+            entsize, count = struct.unpack_from("<HH", elf, 0x3A)
+            heads = [struct.unpack_from("<IIQQQQIIQQ", elf, shoff + i * entsize) for i in range(count)]
+            for h in heads:
+                if h[1] != 2:                                # SHT_SYMTAB
+                    continue
+                names = heads[h[6]][4]
+                for k in range(h[4], h[4] + h[5], h[9]):
+                    st_name, info, _, shndx, value, length = struct.unpack_from("<IBBHQQ", elf, k)
+                    if info & 15 != 2 or not 0 < shndx < count:        # STT_FUNC
+                        continue
+                    begin = heads[shndx][4] + value - heads[shndx][3]
+                    symbol = elf[names + st_name:elf.index(b"\0", names + st_name)].decode()
+                    out[symbol] = hashlib.sha256(elf[begin:begin + length]).hexdigest()[:16]
+    return out
+
+
+def stored_traffic(kernel_key, shape_name, folder=os.path.join(ROOT, "profiles"), lib=None, same_code=False):
     """HBM bytes per launch of a kernel from the committed counter summary (FETCH_SIZE + WRITE_SIZE
     runs of this same command, scaled by the copy probe).  None if there is no summary, or if it was taken on
-    kernels that the built library does not hold (any more): it names their symbols."""
+    kernels that the built library does not hold (any more): it names their symbols.  same_code: None also where a symbol
+    stands for other machine code by now, whose digest the summary states."""
     try:
         with open(os.path.join(folder, f"hbm_traffic_{kernel_key}_{shape_name}.txt")) as fh:
-            fields = [line.split() for line in fh if line.startswith(("symbol ", "bytes_per_launch "))]
+            fields = [line.split() for line in fh if line.startswith(("symbol ", "code ", "bytes_per_launch "))]
         with open(lib or os.path.join(ROOT, "paper_2509_24248_amd", "libspecexit.so"), "rb") as fh:
             built = fh.read()
     except OSError:
@@ -321,6 +354,10 @@ def stored_traffic(kernel_key, shape_name, folder=os.path.join(ROOT, "profiles")
     symbols = [f[1].encode() for f in fields if f[0] == "symbol"]
     if not symbols or any(s + b"\0" not in built for s in symbols):
         return None
+    if same_code:
+        digests = kernel_digests(built)
+        if [f[1] for f in fields if f[0] == "code"] != [digests.get(s.decode()) for s in symbols]:
+            return None
     return next((int(f[1]) for f in fields if f[0] == "bytes_per_launch"), None)
 
 
@@ -517,7 +554,7 @@ def main():
                          "flops_per_launch": sp["flops"], "achieved_TFLOPs": tfl, "frac_mfma_bf16_peak": tfl / MFMA_BF16_PEAK_TFLOPS,
                          # the most the matrix cores can be used while the weights / cache stream at HBM peak
                          "mfma_ceiling_at_hbm_peak": min(1.0, ai / RIDGE),
-                         "traffic_bytes_per_launch": stored_traffic(name, shape.name)}
+                         "traffic_bytes_per_launch": stored_traffic(name, shape.name, same_code=True)}
     top = max((n for n in kernels if not n.startswith("draft_proj")), key=lambda n: kernels[n]["share_of_round"])   # single kernels only
     kt = kernels[top]
     out = {

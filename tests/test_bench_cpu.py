@@ -25,3 +25,17 @@ def test_traffic_of_a_kernel_that_is_gone_is_not_quoted(tmp_path):
         (tmp_path / "hbm_traffic_head_gemm_x.txt").write_text("HBM traffic of ...\n" + "".join(f"symbol {s}\n" for s in symbols) + "bytes_per_launch 7\n")
         assert bench.stored_traffic("head_gemm", "x", str(tmp_path), str(lib)) == want
     assert bench.stored_traffic("head_gemm", "y", str(tmp_path), str(lib)) is None
+
+
+@pytest.mark.skipif(not os.path.exists(LIB), reason="libspecexit.so not built")
+def test_traffic_of_a_kernel_that_was_rewritten_is_not_quoted(tmp_path):
+    with open(LIB, "rb") as fh:
+        digests = bench.kernel_digests(fh.read())
+    assert len(digests) > 100 and len(set(digests.values())) > 100
+    a, b = sorted(s for s in digests if "k_attn_ring" in s)[:2]
+    right, other = digests[a], digests[b]
+    for lines, want in (([a, right], 7), ([a, other], None), ([a, None], None), ([a, right, b, other], 7), ([a, other, b, right], None)):
+        text = "".join(f"symbol {s}\n" + (f"code {d}\n" if d else "") for s, d in zip(lines[::2], lines[1::2]))
+        (tmp_path / "hbm_traffic_split_x.txt").write_text(text + "bytes_per_launch 7\n")
+        assert bench.stored_traffic("split", "x", str(tmp_path), same_code=True) == want
+        assert bench.stored_traffic("split", "x", str(tmp_path)) == 7
