@@ -19,7 +19,10 @@
 //
 // What bounds it: for the head the stream (V = 151936, D = 2560: 778 MB in 114.7 us, 6.8 TB/s), for the projections (0.5 to 100
 // MB) that a launch is a chain: arguments, activations, weights, sum, epilogue.  So the lines of the arguments are
-// requested together, the first weights behind the activations and before anything waits, the sum of squares behind both (under
+// requested together, the first weights behind the activations and the pieces of the sums of squares (loads return in the order of
+// their requests: with most pieces asked for behind the weights the barrier came 1.9 to 2.6 us later, as time stamps in the kernels showed; a
+// step of 1 / 8 rows, fp32, D = 512: 43 / 66 -> 41 / 61 us; a round of six steps, D = 2560, V = 151936: 1221 -> 1205; a barrier that keeps
+// every wave's weights behind all waves' activations: slower) and before anything waits (under
 // a norm x gain is staged, 1 / rms enters after the product), the residual, the rotation and the cache entry of a pair
 // while its weights are on their way, and a pair's first loads before the pair in front of it is summed.  Measured against the form
 // that did these one after the other (and fp32 models on one kernel per operation, fifteen launches a step instead of nine):
@@ -104,7 +107,7 @@ __global__ __launch_bounds__(512) void k_gemv(const GemvArgs g) {
   constexpr int EP = 16 / sizeof(T);           // elements per load
   constexpr int NE = EP / 4;                   // float4 of activations beside it
   extern __shared__ float lds[];
-  __shared__ float ssq_sh[8][MR];
+  __shared__ float ssq_sh[8][MR], rs_sh[MR];
   __shared__ float bv_sh[8][MR];
   __shared__ int bi_sh[8][MR];
   arguments_at_once<sizeof(GemvArgs)>();
@@ -119,9 +122,19 @@ __global__ __launch_bounds__(512) void k_gemv(const GemvArgs g) {
 
   // ---- stage the activations, without waiting for the rows' sums of squares: under a norm, x gain is staged and 1 / rms enters
   // behind the dot product.  Four units of a thread are requested together.
-  float sq[MR];
+  // The pieces of the sums are requested in front of the weights, since loads return in the order of their requests; a wave has one row
+  // (further rows and further pieces, which few shapes have, are added up before the weights are asked for).
+  constexpr int NP = 4;
+  const float* const pieces = AMODE == 3 ? g.a_ssq + min(m0 + min(wv, MR - 1), g.M - 1) * g.a_nssq : nullptr;
+  float sq[NP];
+  auto root = [&](int m, float t) {
+    const float rs = 1.0f / sqrtf(wave_sum_dpp(t) / static_cast<float>(K) + g.a_eps);
+    if (lane == 0) rs_sh[m] = rs;
+  };
+  if constexpr (AMODE == 3) {
 #pragma unroll
-  for (int m = 0; m < MR; ++m) sq[m] = AMODE == 3 && lane < g.a_nssq ? g.a_ssq[min(m0 + m, g.M - 1) * g.a_nssq + lane] : 0.f;
+    for (int u = 0; u < NP; ++u) sq[u] = pieces[min(lane + 64 * u, g.a_nssq - 1)];
+  }
   const int per_row = K / EP, units = MR * per_row;
   constexpr int U = 4;
   float f[U][EP], gn[U][EP];
@@ -171,6 +184,15 @@ __global__ __launch_bounds__(512) void k_gemv(const GemvArgs g) {
     stage_store(base);
   }
   stage_load(base);
+  float sq_more = 0.f;
+  if constexpr (AMODE == 3) {
+    for (int j = lane + 64 * NP; j < g.a_nssq; j += 64) sq_more += pieces[j];
+    for (int m = wv + nwaves; m < MR; m += nwaves) {
+      float t = 0.f;
+      for (int j = lane; j < g.a_nssq; j += 64) t += g.a_ssq[min(m0 + m, g.M - 1) * g.a_nssq + j];
+      root(m, t);
+    }
+  }
 
   // ---- pairs of rows, dealt round-robin over all waves of the launch: at any time the waves read
   // one moving window of neighbouring rows (measured 0.9 % on the round against a contiguous
@@ -209,16 +231,16 @@ __global__ __launch_bounds__(512) void k_gemv(const GemvArgs g) {
   request(0);
   __builtin_amdgcn_sched_barrier(0);
   stage_store(base);
-  float rs[MR];
+  if constexpr (AMODE == 3) {
+    float t = 0.f;
 #pragma unroll
-  for (int m = 0; m < MR; ++m) {
-    rs[m] = 1.f;
-    if constexpr (AMODE == 3) {
-      for (int j = lane + 64; j < g.a_nssq; j += 64) sq[m] += g.a_ssq[min(m0 + m, g.M - 1) * g.a_nssq + j];
-      rs[m] = 1.0f / sqrtf(wave_sum_dpp(sq[m]) / static_cast<float>(K) + g.a_eps);
-    }
+    for (int u = 0; u < NP; ++u) t += lane + 64 * u < g.a_nssq ? sq[u] : 0.f;
+    if (wv < MR) root(wv, t + sq_more);
   }
   __syncthreads();
+  float rs[MR];
+#pragma unroll
+  for (int m = 0; m < MR; ++m) rs[m] = AMODE == 3 ? rs_sh[m] : 1.f;
 
   float ssq = 0.f, bestv = -INFINITY;    // lane m: of row m0 + m
   int besti = INT_MAX;
