@@ -62,11 +62,8 @@ __global__ __launch_bounds__(256) void k_attn_split_valu(const AttnArgs a) {
   float* Ls = Ms + R;                     // [R] running sum
   float* As = Ls + R;                     // [R] rescale of this tile
   int* sched_lds = reinterpret_cast<int*>(As + R);
-  attn_sched_build(a, sched_lds);
-  const AttnLine line = attn_sched_line(__builtin_amdgcn_readfirstlane(sched_lds[a.B]), a.B, a.Hkv, a.pad, a.wide_from, a.use_mfma == kOnePart, a.wgrid);
-  if (blockIdx.x == 0) {
-    attn_sched_publish(a, sched_lds, line);
-  }
+  const AttnTable table = attn_sched_build(a, sched_lds);
+  const AttnLine line = attn_sched_line(a, table);
   if (static_cast<int>(blockIdx.x) >= line.W) return;
   // P V: thread (c4, r0) has columns 4 c4 .. + 3 of rows r0, r0 + RSTEP, ..; with at most half of RSTEP rows, KG groups of
   // RP row slots take kTK / KG keys each
@@ -86,10 +83,10 @@ __global__ __launch_bounds__(256) void k_attn_split_valu(const AttnArgs a) {
   const int lj = tid / VPR, lc = tid % VPR;
 
   const int x_hi = attn_sched_lo(line, blockIdx.x + 1);
-  for (int x_cur = attn_sched_lo(line, blockIdx.x); x_cur < x_hi;) {
-  const AttnSeg seg = attn_sched_segment(a, sched_lds, line.pad, x_cur, x_hi);
-  x_cur = seg.next;
-  if (seg.s1 <= seg.s0) continue;
+  AttnSeg seg = attn_sched_next(a, table, true, line.pad, attn_sched_lo(line, blockIdx.x), x_hi);
+  if (seg.next < x_hi) attn_sched_keep(a, table);
+  for (; seg.s1 > seg.s0; seg = attn_sched_next(a, table, false, line.pad, seg.next, x_hi)) {
+  attn_sched_publish(a, seg);
   const int g = seg.g, b = seg.b, L = seg.L, s0 = seg.s0, s1 = seg.s1;
 
   uint4 kr[NL], vr[NL];
@@ -252,17 +249,14 @@ __global__ __launch_bounds__(256) void k_attn_split_rows(const AttnArgs a) {
   float* Ls = Ms + R;               // [R] running sum
   float* As = Ls + R;               // [R] rescale of this tile
   int* sched_lds = reinterpret_cast<int*>(As + R);
-  attn_sched_build(a, sched_lds);
-  const AttnLine line = attn_sched_line(sched_lds[a.B], a.B, a.Hkv, a.pad, a.wide_from, a.use_mfma == kOnePart, a.wgrid);
-  if (blockIdx.x == 0) {
-    attn_sched_publish(a, sched_lds, line);
-  }
+  const AttnTable table = attn_sched_build(a, sched_lds);
+  const AttnLine line = attn_sched_line(a, table);
   if (static_cast<int>(blockIdx.x) >= line.W) return;
   const int x_hi = attn_sched_lo(line, blockIdx.x + 1);
-  for (int x_cur = attn_sched_lo(line, blockIdx.x); x_cur < x_hi;) {
-  const AttnSeg seg = attn_sched_segment(a, sched_lds, line.pad, x_cur, x_hi);
-  x_cur = seg.next;
-  if (seg.s1 <= seg.s0) continue;
+  AttnSeg seg = attn_sched_next(a, table, true, line.pad, attn_sched_lo(line, blockIdx.x), x_hi);
+  if (seg.next < x_hi) attn_sched_keep(a, table);
+  for (; seg.s1 > seg.s0; seg = attn_sched_next(a, table, false, line.pad, seg.next, x_hi)) {
+  attn_sched_publish(a, seg);
   const int g = seg.g, b = seg.b, L = seg.L, s0 = seg.s0, s1 = seg.s1;
 
   for (int idx = tid; idx < R * D; idx += 256) {
@@ -466,14 +460,13 @@ struct RowSegs {
 template <int D>
 __device__ __forceinline__ RowSegs row_segments(const AttnArgs& a, int b, int i, int h) {
   const int G = a.G, R = G * a.n_q, g = h / G, r = i * G + h - g * G;
-  const attn_sched_t S = (attn_sched_t)a.sched;
-  const int s0 = S[b], s1 = S[b + 1];
-  const AttnLine line = attn_sched_read(a);
-  const int p_u = a.Hkv * (s0 + line.pad * b) + g * (s1 - s0 + line.pad) + line.pad;     // the unit's first keys on the line
-  const int w_first = attn_sched_owner(line, p_u);
-  const size_t slot = static_cast<size_t>(w_first) + static_cast<size_t>(b) * a.Hkv + g;
+  typedef const __attribute__((address_space(4))) int* words_t;           // (scalar loads: nothing writes these words meanwhile)
+  const int u = b * a.Hkv + g;
+  const words_t ends = (words_t)a.sched + 2 * u;
+  const int w_first = ends[0], w_last = ends[1];
+  const size_t slot = static_cast<size_t>(w_first) + u;
   RowSegs q;
-  q.n = attn_sched_owner(line, p_u + s1 - s0 - 1) - w_first + 1;
+  q.n = w_last - w_first + 1;
   q.ml = a.part_ml + (slot * R + r) * 2;
   q.po = a.part_o + (slot * R + r) * D;
   q.ml_step = 2 * static_cast<size_t>(R);
@@ -752,7 +745,7 @@ size_t attn_workspace_bytes(const AttnArgs& a) {
   o = (o + 255) & ~static_cast<size_t>(255);
   size_t ml = slots * R * 2 * sizeof(float);
   ml = (ml + 255) & ~static_cast<size_t>(255);
-  size_t sc = static_cast<size_t>(a.B + 1 + kAttnLineWords) * sizeof(int);
+  size_t sc = static_cast<size_t>(a.B) * a.Hkv * 2 * sizeof(int);
   sc = (sc + 255) & ~static_cast<size_t>(255);
   return o + ml + sc;
 }

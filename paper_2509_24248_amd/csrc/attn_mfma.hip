@@ -84,7 +84,9 @@ template <int HD> __device__ __forceinline__ int swz_v(int key) { return HD == 1
 
 // waves per SIMD the register allocation has to leave room for: the resident workgroups' waves on
 // four SIMDs
-constexpr int min_waves_per_simd(int hd, int nr) { return ((nr < big_from(hd) ? 2 : 1) * kNK * nr + 3) / 4; }
+// (One wave a ring has room for any number, and the compiler then keeps the accumulators where every rescaling has to fetch them: 3
+// sequences of 1000-3000 entries, 12 rows, 13.5 -> 13.0 us a call with 256 registers.)
+constexpr int min_waves_per_simd(int hd, int nr) { return nr == 1 ? 2 : ((nr < big_from(hd) ? 2 : 1) * kNK * nr + 3) / 4; }
 
 // NR waves per ring, each owning RTW 16-row tiles of the queries (rows 16 (rr RTW + t) ..).
 // RTW = 2 halves the LDS reads per query row (K and V operands are fetched once per wave and
@@ -130,19 +132,15 @@ __global__ __launch_bounds__(64 * kNK * NR, min_waves_per_simd(HD, NR)) void k_a
   const int G = a.G;
   const int R = G * a.n_q;
   const int fr = lane & 15, fq = lane >> 4;
-  attn_sched_build(a, sched_lds);
-  const AttnLine line = attn_sched_line(__builtin_amdgcn_readfirstlane(sched_lds[a.B]), a.B, a.Hkv, a.pad, a.wide_from, a.use_mfma == kOnePart, a.wgrid);
-  if (blockIdx.x == 0) {
-    // the merging kernel reads the split back from here
-    attn_sched_publish(a, sched_lds, line);
-  }
+  const AttnTable table = attn_sched_build(a, sched_lds);
+  const AttnLine line = attn_sched_line(a, table);
   if (static_cast<int>(blockIdx.x) >= line.W) return;  // the whole workgroup leaves together
   const int x_hi = attn_sched_lo(line, blockIdx.x + 1);
   bool again = false;                           // a segment before this one used the rings
-  for (int x_cur = attn_sched_lo(line, blockIdx.x); x_cur < x_hi;) {
-  const AttnSeg seg = attn_sched_segment(a, sched_lds, line.pad, x_cur, x_hi);
-  x_cur = seg.next;
-  if (seg.s1 <= seg.s0) continue;
+  AttnSeg seg = attn_sched_next(a, table, true, line.pad, attn_sched_lo(line, blockIdx.x), x_hi);
+  if (seg.next < x_hi) attn_sched_keep(a, table);
+  for (; seg.s1 > seg.s0; seg = attn_sched_next(a, table, false, line.pad, seg.next, x_hi)) {
+  attn_sched_publish(a, seg);
   const int g = seg.g, b = seg.b;
   const int L = __builtin_amdgcn_readfirstlane(seg.L);
   const int s0 = seg.s0, s1 = __builtin_amdgcn_readfirstlane(seg.s1);
@@ -185,6 +183,14 @@ __global__ __launch_bounds__(64 * kNK * NR, min_waves_per_simd(HD, NR)) void k_a
   // that LDS entry [key][pos] holds chunk pos ^ swizzle(key).  The swizzle is the exclusive or of a lane's part and a piece's
   // part, so a piece costs one instruction per lane and no registers between tiles.
   constexpr int kPieces = (2 * kTileP + NR - 1) / NR;   // pieces a wave issues per tile, at most
+  // (where they divide evenly a wave has kPieces in a row, whose swizzles are then constants, since the first key is a multiple of
+  // 16: 0.5 to 1 % of a short call, whose first requests wait for this arithmetic)
+  constexpr bool kInRow = 2 * kTileP % NR == 0 && kPieces * kKeysPP % 16 == 0;
+  const int piece0 = kInRow ? rr * kPieces : rr;
+  constexpr int kPieceStep = kInRow ? 1 : NR;
+  const int key0 = kKeysPP * (piece0 & (kTileP - 1));
+  const bool only_v = NR > 1 && piece0 >= kTileP;        // (kInRow, several waves: a wave has K pieces or V pieces)
+  const char* const pool = static_cast<const char*>(only_v ? a.v : a.k);
   const int lkey = lane / kChunks, lpos = lane % kChunks;
   const uint32_t lane_k = static_cast<uint32_t>(lkey) * kRowB + ((lpos ^ swz_k<HD>(lkey)) << 4);
   const uint32_t lane_v = static_cast<uint32_t>(lkey) * kRowB + ((lpos ^ swz_v<HD>(lkey)) << 4);
@@ -211,9 +217,22 @@ __global__ __launch_bounds__(64 * kNK * NR, min_waves_per_simd(HD, NR)) void k_a
     if (t0 + 32 <= s1) {
       // whole tile inside the range: uniform base per piece + the lane's constant offset
       const int64_t in_page = static_cast<int64_t>(PAGED ? t0 & (a.page_size - 1) : t0) * kRowB;
+      if constexpr (kInRow) {
+#pragma unroll
+        for (int u = 0; u < kPieces; ++u) {
+          const int rel = kKeysPP * (u & (kTileP - 1));                           // keys behind key0
+          const bool is_v = NR > 1 ? only_v : u >= kTileP;
+          const int row = PAGED ? (key0 + rel) & (a.page_size - 1) : key0 + rel;
+          const char* base = (NR > 1 ? pool : static_cast<const char*>(is_v ? a.v : a.k)) +
+                             ((PAGED && a.page_size == 16 && key0 + rel >= 16 ? off_b : off_a) + in_page + row * kRowB);
+          const uint32_t lane_off = is_v ? lane_v ^ (swz_v<HD>(rel) << 4) : lane_k ^ (swz_k<HD>(rel) << 4);
+          load_to_lds16(base, lane_off, slot + (piece0 + u) * 1024);
+        }
+        return;
+      }
 #pragma unroll
       for (int u = 0; u < kPieces; ++u) {
-        const int j = rr + u * NR;
+        const int j = piece0 + u * kPieceStep;
         if (j < 2 * kTileP) {
           const bool second = PAGED && a.page_size == 16 && (j & (kTileP / 2));   // keys 16..31 sit in the next page
           const int key = kKeysPP * (j & (kTileP - 1));                           // the piece's first key
@@ -229,7 +248,7 @@ __global__ __launch_bounds__(64 * kNK * NR, min_waves_per_simd(HD, NR)) void k_a
     asm volatile("" : "+v"(lk));
 #pragma unroll
     for (int u = 0; u < kPieces; ++u) {
-      const int j = rr + u * NR;
+      const int j = piece0 + u * kPieceStep;
       if (j < 2 * kTileP) {
         const int key = kKeysPP * (j & (kTileP - 1)) + lk;
         const int p = min(t0 + key, s1 - 1);   // keys past the range are masked in the softmax

@@ -38,16 +38,32 @@ __device__ __forceinline__ int attn_ctx_len(const AttnArgs& a, int b) {
 // LDS words of the table below.
 __host__ __device__ constexpr int attn_sched_words(int B) { return (B + 1 + (B + 3) / 4 + 3) & ~3; }
 
-// Prefix sums S[0 .. B] of the sequences' granule counts and, behind them, a byte per sequence: how far its entries fall
+// Prefix sums S[0 .. B] of the sequences' granule counts in LDS and, behind them, a byte per sequence: how far its entries fall
 // short of full granules, which with the count gives its length back.  (Whole lengths take four times that, and with
 // more than 930 sequences a second workgroup of a paged launch then finds no room in the compute unit's LDS: B = 1000,
 // 4 queries of 8 heads, contexts 200-500: 141 us; 111 this way, and 114 -> 80 with 64-wide heads.)
+// Up to 64 sequences every wave has them in its lanes, for a workgroup's first segment: no barrier, and a lane read where the
+// table is an LDS round trip (with the words for the merging kernel below, 36 calls of 1 sequence x 4096 entries, 28 rows: 449 -> 435
+// us; 2 units of 600 entries, 28 rows, 12 calls 107 -> 102).  The table is written for workgroups with further segments: lanes
+// that are wanted behind a segment are registers through all of it, and three waves a ring have none to spare (40 rows, paged: 45 -> 53 us).
+struct AttnTable {
+  int* S;
+  int upto, len;             // up to 64 sequences, lane b: S[b + 1] and the entries of sequence b
+};
 __device__ __forceinline__ unsigned char* attn_sched_short(const AttnArgs& a, int* S) { return reinterpret_cast<unsigned char*>(S + a.B + 1); }
 
-// Built by the first wave; every thread of the workgroup calls this, and the table is ready when it returns.
-__device__ __forceinline__ void attn_sched_build(const AttnArgs& a, int* S) {
+// Every thread of the workgroup calls this.
+__device__ __forceinline__ AttnTable attn_sched_build(const AttnArgs& a, int* S) {
+  const int lane = threadIdx.x & 63;
+  AttnTable t;
+  t.S = S;
+  t.len = t.upto = 0;
+  if (a.B <= 64) {
+    if (lane < a.B) t.len = attn_ctx_len(a, lane) + a.n_blk;
+    t.upto = wave_scan((t.len + kAttnGran - 1) / kAttnGran);
+    return t;
+  }
   if (threadIdx.x < 64) {
-    const int lane = threadIdx.x;
     int run = 0;
     for (int c = 0; c < a.B; c += 64) {
       const int b = c + lane;
@@ -64,6 +80,18 @@ __device__ __forceinline__ void attn_sched_build(const AttnArgs& a, int* S) {
     if (lane == 0) S[0] = 0;
   }
   __syncthreads();
+  return t;
+}
+
+// For the further segments: the table of up to 64 sequences from the lanes to LDS, there behind the workgroup's next barrier.
+__device__ __forceinline__ void attn_sched_keep(const AttnArgs& a, const AttnTable& t) {
+  const int lane = threadIdx.x & 63;
+  if (a.B > 64 || threadIdx.x >= 64) return;
+  if (lane < a.B) {
+    t.S[lane + 1] = t.upto;
+    attn_sched_short(a, t.S)[lane] = static_cast<unsigned char>((t.len + kAttnGran - 1) / kAttnGran * kAttnGran - t.len);
+  }
+  if (lane == 0) t.S[0] = 0;
 }
 
 // The line of a launch whose sequences have `gran` granules in all.  Workgroups that take part: one per granule while the launch
@@ -133,24 +161,10 @@ __host__ __device__ __forceinline__ int attn_sched_owner(const AttnLine& l, int 
   return attn_sched_lo(l, w) <= p ? w : w - 1;
 }
 
-// The split as the merging kernel reads it back: the table's prefix sums, then the line.  (Worked out there again it is a chain of
-// divisions in front of everything else; these words arrive with the prefix sums.)
-constexpr int kAttnLineWords = 4;
-__device__ __forceinline__ void attn_sched_publish(const AttnArgs& a, const int* S, const AttnLine& l) {
-  for (int i = threadIdx.x; i <= a.B; i += blockDim.x) a.sched[i] = S[i];
-  if (threadIdx.x == 0) {
-    int* w = a.sched + a.B + 1;
-    w[0] = l.W; w[1] = l.q; w[2] = l.r; w[3] = l.pad;
-  }
-}
-// (through scalar loads: b is uniform, and nothing writes it while the merging kernel runs)
-typedef const __attribute__((address_space(4))) int* attn_sched_t;
-__device__ __forceinline__ AttnLine attn_sched_read(const AttnArgs& a) {
-  const attn_sched_t w = (attn_sched_t)a.sched + a.B + 1;
-  AttnLine l;
-  l.W = w[0]; l.q = w[1]; l.r = w[2]; l.pad = w[3];
-  l.T = l.q * l.W + l.r;
-  return l;
+// The line of a launch on the device.
+__device__ __forceinline__ AttnLine attn_sched_line(const AttnArgs& a, const AttnTable& t) {
+  const int gran = a.B <= 64 ? __builtin_amdgcn_readlane(t.upto, 63) : __builtin_amdgcn_readfirstlane(t.S[a.B]);
+  return attn_sched_line(gran, a.B, a.Hkv, a.pad, a.wide_from, a.use_mfma == kOnePart, a.wgrid);
 }
 
 struct AttnSeg {
@@ -161,29 +175,61 @@ struct AttnSeg {
 };
 
 // The segment that starts at granule x of the line and ends at the unit's end or at `hi` (no keys where that is still
-// padding).  Uniform over the workgroup; S in LDS.
-__device__ __forceinline__ AttnSeg attn_sched_segment(const AttnArgs& a, int* S, int pad, int x, int hi) {
+// padding).  Uniform over the workgroup.  `lanes`: the table in the lanes will do (see AttnTable).
+__device__ __forceinline__ AttnSeg attn_sched_segment(const AttnArgs& a, const AttnTable& t, bool lanes, int pad, int x, int hi) {
   const int lane = threadIdx.x & 63;
-  int b = 0;
-  for (int c = 0; c < a.B; c += 64) {
-    const int i = c + lane;
-    const bool before = i < a.B && a.Hkv * (S[i + 1] + pad * (i + 1)) <= x;
-    b += __popcll(__builtin_amdgcn_ballot_w64(before));
-  }
-  b = __builtin_amdgcn_readfirstlane(min(b, a.B - 1));
-  const int first = __builtin_amdgcn_readfirstlane(S[b]);
-  const int n = __builtin_amdgcn_readfirstlane(S[b + 1]) - first;
-  const int rel = x - a.Hkv * (first + pad * b);
   AttnSeg s;
-  s.b = b;
-  s.g = min(static_cast<int>(static_cast<uint32_t>(rel) / static_cast<uint32_t>(n + pad)), a.Hkv - 1);
+  int first, n;                                 // granules in front of the sequence, and of it
+  if (lanes && a.B <= 64) {
+    const int b = min(static_cast<int>(__popcll(__builtin_amdgcn_ballot_w64(lane < a.B && a.Hkv * (t.upto + pad * (lane + 1)) <= x))), a.B - 1);
+    first = b > 0 ? __builtin_amdgcn_readlane(t.upto, b - 1) : 0;
+    n = __builtin_amdgcn_readlane(t.upto, b) - first;
+    s.L = __builtin_amdgcn_readlane(t.len, b) - a.n_blk;
+    s.b = b;
+  } else {
+    int b = 0;
+    for (int c = 0; c < a.B; c += 64) {
+      const int i = c + lane;
+      const bool before = i < a.B && a.Hkv * (t.S[i + 1] + pad * (i + 1)) <= x;
+      b += static_cast<int>(__popcll(__builtin_amdgcn_ballot_w64(before)));
+    }
+    b = __builtin_amdgcn_readfirstlane(min(b, a.B - 1));
+    first = __builtin_amdgcn_readfirstlane(t.S[b]);
+    n = __builtin_amdgcn_readfirstlane(t.S[b + 1]) - first;
+    s.L = __builtin_amdgcn_readfirstlane(n * kAttnGran - attn_sched_short(a, t.S)[b] - a.n_blk);
+    s.b = b;
+  }
+  const int rel = x - a.Hkv * (first + pad * s.b);
+  const int g = rel < 1 << 21 ? attn_sched_div(rel, n + pad) : static_cast<int>(static_cast<uint32_t>(rel) / static_cast<uint32_t>(n + pad));
+  s.g = min(__builtin_amdgcn_readfirstlane(g), a.Hkv - 1);
   const int at = min(rel - s.g * (n + pad), n + pad - 1);   // granule of the unit, padding first
   const int end = min(at + (hi - x), n + pad);
-  s.L = n * kAttnGran - attn_sched_short(a, S)[b] - a.n_blk;
   s.s0 = max(at - pad, 0) * kAttnGran;
   s.s1 = min(s.L + a.n_blk, (end - pad) * kAttnGran);
-  s.next = x + max(end - at, 1);                // (the minima above cannot bind while S is the table of these lengths)
+  s.next = x + max(end - at, 1);                // (the minima above cannot bind while the table is that of these lengths)
   return s;
+}
+
+// The first segment with keys from granule x of a workgroup's share on; s1 <= s0 if there is none.
+__device__ __forceinline__ AttnSeg attn_sched_next(const AttnArgs& a, const AttnTable& t, bool lanes, int pad, int x, int hi) {
+  AttnSeg s;
+  s.s0 = s.s1 = 0;
+  while (x < hi) {
+    s = attn_sched_segment(a, t, lanes, pad, x, hi);
+    if (s.s1 > s.s0) break;
+    x = s.next;
+  }
+  return s;
+}
+
+// The workgroups that have a unit's first and last keys, for the merging kernel: [unit][2].  (From prefix sums and the line that kernel
+// worked the two out again, a chain of divisions in front of its first request: 36 calls as above 442 us, 435 this way.)
+__device__ __forceinline__ void attn_sched_publish(const AttnArgs& a, const AttnSeg& s) {
+  if (threadIdx.x == 0) {
+    int* p = a.sched + 2 * (s.b * a.Hkv + s.g);
+    if (s.s0 == 0) p[0] = blockIdx.x;
+    if (s.s1 == s.L + a.n_blk) p[1] = blockIdx.x;
+  }
 }
 
 }  // namespace sx

@@ -191,8 +191,8 @@ struct AttnArgs {
                              // are dealt to them in equal shares on the device (attn_sched.hpp)
   float* part_o;             // [wgrid + B*Hkv slots][R][d]
   float* part_ml;            // [wgrid + B*Hkv slots][R][2]  (running max, sum)
-  int* sched;                // written by the split kernel for the merging kernel: prefix sums of the sequences' granule
-                             // counts [B + 1], then the work split (attn_sched.hpp)
+  int* sched;                // written by the split kernel for the merging kernel: the first and the last workgroup of every
+                             // unit, [B*Hkv][2]
   int64_t n_pages;           // paged: pages in the pool (page ids are forced into it)
   int* status;               // device error word or nullptr: first out-of-range length / page id seen
   int stages;                // matrix-core kernel: slots per tile ring (attn_plan)
