@@ -4,8 +4,8 @@
 // segments, each a key range of one (sequence, KV head) unit, processed against all
 // R = G * n_q query rows that share that head, so the cache is read once.
 //
-// Inside a workgroup there are two independent tile rings (key groups); ring kg takes the
-// 32-key tiles kg, kg+2, ... of the chunk.  A ring is S slots in LDS (K tile + V tile: 16 KB
+// Inside a workgroup there are two independent tile rings (key groups), four with few query rows; ring kg takes the
+// 32-key tiles kg, kg+2 (kg+4), ... of the chunk.  A ring is S slots in LDS (K tile + V tile: 16 KB
 // with 128-wide heads, 8 KB with 64-wide ones).  Tiles are brought in by direct global->LDS loads (16 bytes per lane, streaming),
 // issued S-1 tiles ahead by the ring's waves in turn, so most of the LDS holds bytes in
 // flight.  Each of the ring's NR waves owns one or two 16-row tiles of the queries and computes them
@@ -17,7 +17,7 @@
 //                 load (ds_read_b64_tr_b16), B operand = P^T straight from the softmax
 //                 registers.
 // One workgroup barrier per tile step hands a landed tile to the waves and frees the slot
-// consumed one step earlier.  The two rings merge at the end in a fixed order.
+// consumed one step earlier (rings of one wave need none).  The rings merge at the end in a fixed order.
 //
 // Short calls are a chain: lengths, split, queries and tiles, one or two tiles of arithmetic, merge.  So queries and tiles are
 // requested together, addresses that only later code needs are worked out behind the requests, and code that runs once is
@@ -37,7 +37,12 @@ namespace sx {
 
 namespace {
 
-constexpr int kNK = 2;                 // tile rings (key groups) per workgroup
+// Tile rings (key groups) per workgroup: two of several waves each, or, up to 16 query rows per KV head, four of one wave, which
+// then wait for nobody: the wave that brings a tile in is the one that reads it, and one workgroup per compute unit has in flight what two
+// of two rings had, with half the partial results.  Layers of 8 KV heads, 2 rings / 4: 3 sequences of 1000-3000 entries, 12 rows,
+// contiguous / paged 13.0 -> 12.2 / 13.7 -> 13.2 us, 8 rows 12.7 -> 11.6; 1 of 5000, 12 rows 11.8 -> 11.3; 64-wide heads, 16 of 500-2500,
+// 16 rows 14.8 -> 14.1, 8 of 4000-8000, 12 rows 21.0 -> 19.7 (two workgroups of two-slot rings; one of four slots 20.6).
+constexpr int rings_of(int nr) { return nr == 1 ? 4 : 2; }
 constexpr int slot_bytes(int hd) { return 128 * hd; }   // one ring slot: 32 K rows then 32 V rows of hd bf16 values
 // From kBigFrom waves per ring (more than 48 query rows per KV head) one workgroup is resident per
 // compute unit (its eight to sixteen waves need more than the 96-128 registers per lane that two
@@ -50,7 +55,9 @@ constexpr int slot_bytes(int hd) { return 128 * hd; }   // one ring slot: 32 K r
 // head, contexts 1000-8000 of 8 sequences (74 MB), whole call: 26 us; on the ALU kernel 365 us.
 constexpr int big_from(int hd) { return hd == 64 ? 5 : 4; }
 constexpr bool two_part(int hd, int nr) { return hd == 64 || nr <= 3; }     // (see kSplitP)
-constexpr int stages_of(int hd, int nr) { return (nr >= big_from(hd) ? 4 : 2) * (hd == 64 ? 2 : 1); }
+// Four rings take two slots each.
+constexpr int stages_of(int hd, int nr) { return nr == 1 ? 2 : (nr >= big_from(hd) ? 4 : 2) * (hd == 64 ? 2 : 1); }
+constexpr int wgs_per_cu(int hd, int nr) { return nr >= big_from(hd) || (nr == 1 && hd == 128) ? 1 : 2; }
 // K operand reads / V operand read pairs issued ahead of the matrix instructions that use them: as
 // many as the registers allow (one resident workgroup: all eight K reads, four V pairs; 64-wide heads
 // have four of each)
@@ -67,6 +74,8 @@ constexpr int v_ahead(int hd, int nr) { return hd == 64 || nr >= big_from(hd) ? 
 constexpr int kPairFrom = 7;
 constexpr int tiles_per_wave(int hd, int tiles) { return hd == 128 && tiles >= kPairFrom ? 2 : 1; }
 constexpr int kMaxChunkPages = 2048;   // page ids of one chunk kept in LDS (8 KB)
+
+constexpr int ml_rows(int nr, int rp) { return nr == 1 ? rings_of(nr) * rp : rp; }   // (max, sum) pairs that the merge of the rings passes through LDS
 
 typedef short s16x4_t __attribute__((ext_vector_type(4)));
 
@@ -86,13 +95,14 @@ template <int HD> __device__ __forceinline__ int swz_v(int key) { return HD == 1
 // four SIMDs
 // (One wave a ring has room for any number, and the compiler then keeps the accumulators where every rescaling has to fetch them: 3
 // sequences of 1000-3000 entries, 12 rows, 13.5 -> 13.0 us a call with 256 registers.)
-constexpr int min_waves_per_simd(int hd, int nr) { return nr == 1 ? 2 : ((nr < big_from(hd) ? 2 : 1) * kNK * nr + 3) / 4; }
+constexpr int min_waves_per_simd(int hd, int nr) { return nr == 1 ? 2 : (wgs_per_cu(hd, nr) * rings_of(nr) * nr + 3) / 4; }
 
 // NR waves per ring, each owning RTW 16-row tiles of the queries (rows 16 (rr RTW + t) ..).
 // RTW = 2 halves the LDS reads per query row (K and V operands are fetched once per wave and
 // used for both row tiles) at the price of fewer, fatter waves (see kPairFrom).
 template <int HD, int NR, int RTW, int S, bool PAGED>
-__global__ __launch_bounds__(64 * kNK * NR, min_waves_per_simd(HD, NR)) void k_attn_ring(const AttnArgs a) {
+__global__ __launch_bounds__(64 * rings_of(NR) * NR, min_waves_per_simd(HD, NR)) void k_attn_ring(const AttnArgs a) {
+  constexpr int kNK = rings_of(NR);
   constexpr int RP = 16 * NR * RTW;             // query rows covered (padded)
   constexpr int kKAhead = k_ahead(HD, NR), kVAhead = v_ahead(HD, NR);
   constexpr int kSlot = slot_bytes(HD);
@@ -124,7 +134,7 @@ __global__ __launch_bounds__(64 * kNK * NR, min_waves_per_simd(HD, NR)) void k_a
   extern __shared__ uint4 smem4[];
   char* smem = reinterpret_cast<char*>(smem4);
   float* ml_lds = reinterpret_cast<float*>(smem + kFront);
-  int* sched_lds = reinterpret_cast<int*>(smem + kFront + RP * 2 * sizeof(float));
+  int* sched_lds = reinterpret_cast<int*>(smem + kFront + ml_rows(NR, RP) * 2 * sizeof(float));
   int* pg_lds = sched_lds + attn_sched_words(a.B);
   const int lane = threadIdx.x & 63;
   const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -145,7 +155,7 @@ __global__ __launch_bounds__(64 * kNK * NR, min_waves_per_simd(HD, NR)) void k_a
   const int L = __builtin_amdgcn_readfirstlane(seg.L);
   const int s0 = seg.s0, s1 = __builtin_amdgcn_readfirstlane(seg.s1);
   const int ntl = (s1 - s0 + 31) >> 5;          // 32-key tiles in this segment
-  const int nit = (ntl + kNK - 1) / kNK;        // tile steps (the same for both rings)
+  const int nit = (ntl + kNK - 1) / kNK;        // tile steps (the same for all rings)
   char* ring = smem + kg * (S * kSlot);
 
   // ---- Q^T operand pieces and the mask words of this wave's rows (rows past the last one repeat it and are not stored)
@@ -314,7 +324,8 @@ __global__ __launch_bounds__(64 * kNK * NR, min_waves_per_simd(HD, NR)) void k_a
     // plain barrier (no memory fence: a fence would wait for the loads still in flight); the
     // wave-scope fences only keep the compiler from moving LDS accesses across it
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_s_barrier();              // tile `it` complete; slot of tile it-1 free
+    if constexpr (NR > 1) __builtin_amdgcn_s_barrier();   // tile `it` complete; slot of tile it-1 free
+    else __builtin_amdgcn_s_waitcnt(0xC07F);   // lgkmcnt(0): (of one wave, tile it-1 is read)
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
     if (it > 0) issue(it + S - 1);
     const int ti = it * kNK + kg;
@@ -437,10 +448,11 @@ __global__ __launch_bounds__(64 * kNK * NR, min_waves_per_simd(HD, NR)) void k_a
     }
   }
 
+  constexpr int kOBytes = 64 * HD;               // 16 rows
+  if constexpr (NR > 1) {
   // ---- merge the two rings of each row: ring 1 leaves its sums in LDS, ring 0 adds them to its own (always in this order) and
   // stores the segment's partial result.  Slots other than the last tile's are free since the last barrier: wave rr of ring 1
   // takes piece rr of them, ring 1's first.  Within a row the 16-byte pieces are swizzled like the tiles.
-  constexpr int kOBytes = 64 * HD;               // 16 rows
   constexpr int kPerSlot = kSlot / kOBytes;
   static_assert(kSlot == 2 * kOBytes && NR * RTW <= 2 * kPerSlot * (S - 1), "the free slots hold ring 1's sums");
   int fr_o = fr, fq_o = fq;                      // (addresses worked out here, see above)
@@ -481,25 +493,65 @@ __global__ __launch_bounds__(64 * kNK * NR, min_waves_per_simd(HD, NR)) void k_a
                                                               fmaf(o.z, f1, oacc[dt][t][2] * f0), fmaf(o.w, f1, oacc[dt][t][3] * f0));
     }
   }
+  } else {
+    // ---- merge the four rings: each leaves its sums in its own slots, the 16-byte pieces of a row swizzled like the tiles, and every
+    // wave adds some rows, in the order of the rings
+    static_assert(RTW == 1 && kOBytes <= S * kSlot, "a ring's slots hold its sums");
+    constexpr int C4 = HD / 4, RPW = 64 / C4;     // 16-byte pieces of a row, rows that a wave adds at a time
+    const float l = kSplitP ? quad_row_sum(l_run[0]) : lacc[0][0];
+    int fr_o = fr, fq_o = fq;                     // (addresses worked out here, see above)
+    asm volatile("" : "+v"(fr_o), "+v"(fq_o));
+    if (fq == 0) *reinterpret_cast<float2*>(ml_lds + 2 * (kg * RP + fr_o)) = make_float2(m_run[0], l);
+#pragma unroll
+    for (int dt = 0; dt < kDT; ++dt)
+      *reinterpret_cast<float4*>(ring + fr_o * (4 * HD) + (((4 * dt + fq_o) ^ fr_o) << 4)) = make_float4(oacc[dt][0][0], oacc[dt][0][1], oacc[dt][0][2], oacc[dt][0][3]);
+    __syncthreads();
+    const size_t unit = static_cast<size_t>(blockIdx.x) + static_cast<size_t>(b) * a.Hkv + g;   // partial slot of segment (w, u)
+    const int c4 = lane % C4;
+#pragma unroll 1
+    for (int r = RPW * wv + lane / C4; r < R; r += RPW * kNK) {
+      float2 ml[kNK];
+      float4 o[kNK];
+#pragma unroll
+      for (int k = 0; k < kNK; ++k) {
+        ml[k] = *reinterpret_cast<const float2*>(ml_lds + 2 * (k * RP + r));
+        o[k] = *reinterpret_cast<const float4*>(smem + k * (S * kSlot) + r * (4 * HD) + ((c4 ^ r) << 4));
+      }
+      float mm = ml[0].x;
+#pragma unroll
+      for (int k = 1; k < kNK; ++k) mm = fmaxf(mm, ml[k].x);
+      float sum = 0.f;
+      float4 v = make_float4(0.f, 0.f, 0.f, 0.f);
+#pragma unroll
+      for (int k = 0; k < kNK; ++k) {
+        const float f = __builtin_amdgcn_exp2f(ml[k].x - mm);
+        sum = fmaf(f, ml[k].y, sum);
+        v.x = fmaf(f, o[k].x, v.x); v.y = fmaf(f, o[k].y, v.y);
+        v.z = fmaf(f, o[k].z, v.z); v.w = fmaf(f, o[k].w, v.w);
+      }
+      *reinterpret_cast<float4*>(a.part_o + (unit * R + r) * HD + 4 * c4) = v;
+      if (c4 == 0) *reinterpret_cast<float2*>(a.part_ml + (unit * R + r) * 2) = make_float2(mm, sum);
+    }
+  }
   }
 }
 
-constexpr size_t lds_bytes(int hd, int rp, int stages, int B, bool paged) {
-  return static_cast<size_t>(kNK) * stages * slot_bytes(hd) + static_cast<size_t>(rp) * 2 * sizeof(float) +
+constexpr size_t lds_bytes(int hd, int nr, int rp, int stages, int B, bool paged) {
+  return static_cast<size_t>(rings_of(nr)) * stages * slot_bytes(hd) + static_cast<size_t>(ml_rows(nr, rp)) * 2 * sizeof(float) +
          static_cast<size_t>(attn_sched_words(B)) * sizeof(int) + (paged ? static_cast<size_t>(kMaxChunkPages + 1) * sizeof(int) : 0);
 }
 
 template <int HD, int NR, int RTW, int S, bool PAGED>
 hipError_t launch_one(const AttnArgs& a, hipStream_t s) {
   // as many workgroups as attn_mfma_per_cu counts on fit the 160 KB of a compute unit, at any number of sequences
-  static_assert(lds_bytes(HD, 16 * NR * RTW, S, kAttnMaxSeqs, PAGED) * (NR >= big_from(HD) ? 1 : 2) <= 160 * 1024, "the LDS of a compute unit");
+  static_assert(lds_bytes(HD, NR, 16 * NR * RTW, S, kAttnMaxSeqs, PAGED) * wgs_per_cu(HD, NR) <= 160 * 1024, "the LDS of a compute unit");
   static_assert(NR * RTW <= 8, "at most 128 query rows");
   // set once per process; a function-local static is initialised under the language's own lock,
   // so first calls from several host threads are safe
   static const hipError_t attr = hipFuncSetAttribute(reinterpret_cast<const void*>(&k_attn_ring<HD, NR, RTW, S, PAGED>),
                                              hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
   if (attr != hipSuccess) return attr;
-  hipLaunchKernelGGL((k_attn_ring<HD, NR, RTW, S, PAGED>), dim3(a.wgrid), dim3(64 * kNK * NR), attn_mfma_lds_bytes(a), s, a);
+  hipLaunchKernelGGL((k_attn_ring<HD, NR, RTW, S, PAGED>), dim3(a.wgrid), dim3(64 * rings_of(NR) * NR), attn_mfma_lds_bytes(a), s, a);
   return hipGetLastError();
 }
 
@@ -539,13 +591,13 @@ static int waves_per_ring(const AttnArgs& a) {
   const int per = tiles_per_wave(a.d, row_tiles(a));
   return (row_tiles(a) + per - 1) / per;
 }
-int attn_mfma_per_cu(const AttnArgs& a) { return waves_per_ring(a) >= big_from(a.d) ? 1 : 2; }
+int attn_mfma_per_cu(const AttnArgs& a) { return wgs_per_cu(a.d, waves_per_ring(a)); }
 bool attn_mfma_two_part(const AttnArgs& a) { return two_part(a.d, waves_per_ring(a)); }
 int attn_mfma_stages(const AttnArgs& a) { return stages_of(a.d, waves_per_ring(a)); }
 
 size_t attn_mfma_lds_bytes(const AttnArgs& a) {
   const int rp = 16 * waves_per_ring(a) * tiles_per_wave(a.d, row_tiles(a));
-  return lds_bytes(a.d, rp, a.stages, a.B, a.paged);
+  return lds_bytes(a.d, waves_per_ring(a), rp, a.stages, a.B, a.paged);
 }
 
 int attn_mfma_max_chunk(const AttnArgs& a) { return a.paged ? kMaxChunkPages * a.page_size : (1 << 30); }

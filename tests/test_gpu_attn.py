@@ -279,3 +279,17 @@ def test_full_size_sampled(index):
     only = sample_triples(shape, 48, index)
     only += [(int(np.argmax(L)), shape.n_q - 1, 0), (int(np.argmin(L)), 0, shape.Hq - 1)]
     check(shape, L, kv, q, mask, only=only, label=f"config {index} sampled")
+
+
+@pytest.mark.parametrize("n_q,Hq,d,page", [(1, 2, 128, 0), (1, 8, 128, 16), (4, 8, 128, 0), (4, 8, 64, 64), (2, 16, 64, 0), (5, 6, 128, 32)])
+@pytest.mark.parametrize("B", [9, 64, 65])
+def test_few_rows_at_ring_and_share_edges(B, n_q, Hq, d, page):
+    # up to 16 rows per KV head: four rings of one wave, of which some have no tile, one or several, in segments that end inside a
+    # unit or go on with the next.  64 sequences are the most whose lengths a workgroup's first segment takes from its lanes; the other
+    # segments, and more sequences, take them from the table.
+    shape = gen.scaled(gen.config(1), B=B, Hq=Hq, Hkv=2, d=d, n_q=n_q, k=max(n_q - 1, 1), ctx=(0, 700), page_size=page or 16)
+    L, kv, q, mask = case(shape, 17, tree=n_q == 4, paged=page > 0)
+    for b, n in enumerate((0, 31, 32, 33, 96, 97, 128, 129, 256)):
+        L[b] = n
+    err = check(shape, L, kv, q, mask, label=f"few rows, d {d} page {page}")
+    assert err < 2.0 ** -8          # two-part probabilities: the bf16 rounding of the output, at most 2^-9 of the largest value
