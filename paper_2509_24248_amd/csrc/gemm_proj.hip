@@ -310,64 +310,43 @@ __global__ __launch_bounds__(64 * (RG * KS + kProducers)) void k_proj(const Proj
 
 // ---- the kernels behind a projection
 
-// First and last workgroup that hold blocks of group g.  (T < 2^22 blocks and W <= 1024: 32 bits would not hold
-// the products, and a 64-bit division is a hundred instructions, so the quotient comes from fp64, which holds
-// them exactly; one step puts right what its rounding may do.)
-__device__ __forceinline__ int proj_owner(const ProjSum& p, int64_t x) {
-  const int64_t a = (x + 1) * p.W - 1;
-  int q = static_cast<int>(static_cast<double>(a) * p.inv_T);
-  if (static_cast<int64_t>(q) * p.T > a) --q;
-  if (static_cast<int64_t>(q + 1) * p.T <= a) ++q;
-  return q;
-}
-__device__ __forceinline__ void proj_owners(const ProjSum& p, int g, int& w0, int& w1) {
-  const int64_t x0 = static_cast<int64_t>(g) * p.KB;
-  w0 = proj_owner(p, x0);
-  w1 = proj_owner(p, x0 + p.KB - 1);
+// Where the partial sums of columns n .. of row m begin, and how many slots they lie in.
+struct ProjSlots {
+  const float* src;
+  uint32_t step;          // from one slot to the next, in floats
+  int n;
+};
+
+__device__ __forceinline__ ProjSlots proj_slots(const ProjSum& p, int m, int n) {
+  const int g = n >> 7, x0 = g * p.KB;
+  const int w0 = proj_owner(p.T, p.inv_T, p.W, x0);
+  ProjSlots r;
+  r.step = static_cast<uint32_t>(p.M) * 128;
+  r.src = p.partial + static_cast<size_t>(w0 + g) * r.step + m * 128 + (n & 127);
+  r.n = proj_owner(p.T, p.inv_T, p.W, x0 + p.KB - 1) - w0 + 1;
+  return r;
 }
 
-// Sum of the segments' partial sums of four columns n .. n + 3 (n a multiple of 4) of row m, in slot order.
-__device__ __forceinline__ float4 proj_sum4(const ProjSum& p, int m, int n) {
-  const int g = n >> 7;
-  int w0, w1;
-  proj_owners(p, g, w0, w1);
-  const size_t step = static_cast<size_t>(p.M) * 128;
-  const float* src = p.partial + (static_cast<size_t>(w0) + g) * step + m * 128 + (n & 127);
-  const int cnt = w1 - w0 + 1;
-  float4 sum = make_float4(0.f, 0.f, 0.f, 0.f);
-  for (int i = 0; i < cnt; i += 8) {
-    float4 v[8];
+// Sum of the slots, in their order, of VEC columns.  The first U are requested by `request`, so that a caller has those of several
+// sums on their way at once; more are fetched when they are added.
+template <int U, typename VEC>
+struct ProjTerms {
+  VEC v[U];
+  __device__ __forceinline__ void request(const ProjSlots& s, int off = 0) {
 #pragma unroll
-    for (int u = 0; u < 8; ++u) v[u] = *reinterpret_cast<const float4*>(src + static_cast<size_t>(min(i + u, cnt - 1)) * step);
-#pragma unroll
-    for (int u = 0; u < 8; ++u)
-      if (i + u < cnt) { sum.x += v[u].x; sum.y += v[u].y; sum.z += v[u].z; sum.w += v[u].w; }
+    for (int u = 0; u < U; ++u) v[u] = *reinterpret_cast<const VEC*>(s.src + off + static_cast<size_t>(min(u, s.n - 1)) * s.step);
   }
-  return sum;
-}
-
-// The same for the two columns n and n + half of one head (a head of at most 128 columns lies in one group)
-__device__ __forceinline__ void proj_sum_pair(const ProjSum& p, int m, int n, int half, float& s1, float& s2) {
-  const int g = n >> 7;
-  int w0, w1;
-  proj_owners(p, g, w0, w1);
-  const size_t step = static_cast<size_t>(p.M) * 128;
-  const float* src = p.partial + (static_cast<size_t>(w0) + g) * step + m * 128 + (n & 127);
-  const int cnt = w1 - w0 + 1;
-  s1 = s2 = 0.f;
-  for (int i = 0; i < cnt; i += 8) {
-    float v[8], w[8];
+  static __device__ __forceinline__ void add(float4& a, const float4& b) { a.x += b.x; a.y += b.y; a.z += b.z; a.w += b.w; }
+  static __device__ __forceinline__ void add(float& a, const float& b) { a += b; }
+  __device__ __forceinline__ VEC sum(const ProjSlots& s, int off = 0) const {
+    VEC t = v[0];
 #pragma unroll
-    for (int u = 0; u < 8; ++u) {
-      const float* q = src + static_cast<size_t>(min(i + u, cnt - 1)) * step;
-      v[u] = q[0];
-      w[u] = q[half];
-    }
-#pragma unroll
-    for (int u = 0; u < 8; ++u)
-      if (i + u < cnt) { s1 += v[u]; s2 += w[u]; }
+    for (int u = 1; u < U; ++u)
+      if (u < s.n) add(t, v[u]);
+    for (int i = U; i < s.n; ++i) add(t, *reinterpret_cast<const VEC*>(s.src + off + static_cast<size_t>(i) * s.step));
+    return t;
   }
-}
+};
 
 // Four values of row m, columns k .. k + 3, into the packed operand order as value and rest (two planes)
 __device__ __forceinline__ void pack4(char* dst, int NT, int m, int k, const float (&f)[4]) {
@@ -386,79 +365,105 @@ constexpr int kRowIters = 2;        // float4 per thread: rows up to 8192 wide
 
 // One workgroup per row: sums (+ residual) -> x (fp32), optionally the storage type, and the RMSNorm of the
 // row as the next projection's operand.
+template <int U>
 __global__ __launch_bounds__(kRowThreads) void k_proj_norm(const ProjSum ps, int N, const float* __restrict__ residual, const bf16_t* __restrict__ gain,
                                                            float eps, float* __restrict__ out_x, bf16_t* __restrict__ out_store,
                                                            char* __restrict__ packed, int NT) {
-  __shared__ float sh[kRowThreads / 64];
+  constexpr int NW = kRowThreads / 64;
+  __shared__ float4 sh[NW / 4];
   const int m = blockIdx.x;
-  float4 v[kRowIters];
+  float4 v[kRowIters], r[kRowIters];
   uint2 gn[kRowIters];
+  ProjSlots slots[kRowIters];
+  ProjTerms<U, float4> terms[kRowIters];
+#pragma unroll
+  for (int it = 0; it < kRowIters; ++it) {
+    const int n = (threadIdx.x + it * kRowThreads) * 4;
+    if (n < N) {
+      slots[it] = proj_slots(ps, m, n);
+      terms[it].request(slots[it]);
+      gn[it] = *reinterpret_cast<const uint2*>(gain + n);
+      r[it] = residual ? *reinterpret_cast<const float4*>(residual + static_cast<size_t>(m) * N + n) : make_float4(0.f, 0.f, 0.f, 0.f);
+    }
+  }
   float ssq = 0.f;
 #pragma unroll
   for (int it = 0; it < kRowIters; ++it) {
     const int n = (threadIdx.x + it * kRowThreads) * 4;
-    v[it] = make_float4(0.f, 0.f, 0.f, 0.f);
-    gn[it] = make_uint2(0, 0);
     if (n < N) {
-      gn[it] = *reinterpret_cast<const uint2*>(gain + n);
-      float4 r = make_float4(0.f, 0.f, 0.f, 0.f);
-      if (residual) r = *reinterpret_cast<const float4*>(residual + static_cast<size_t>(m) * N + n);
-      float4 s = proj_sum4(ps, m, n);
-      s.x += r.x; s.y += r.y; s.z += r.z; s.w += r.w;
+      float4 s = terms[it].sum(slots[it]);
+      s.x += r[it].x; s.y += r[it].y; s.z += r[it].z; s.w += r[it].w;
       v[it] = s;
       ssq += s.x * s.x + s.y * s.y + s.z * s.z + s.w * s.w;
-      if (out_x) *reinterpret_cast<float4*>(out_x + static_cast<size_t>(m) * N + n) = s;
-      if (out_store)
-        *reinterpret_cast<uint2*>(out_store + static_cast<size_t>(m) * N + n) = make_uint2(pack_bf16x2(s.x, s.y), pack_bf16x2(s.z, s.w));
     }
   }
-  ssq = wave_sum(ssq);
-  if ((threadIdx.x & 63) == 0) sh[threadIdx.x >> 6] = ssq;
+  ssq = wave_sum_dpp(ssq);
+  if ((threadIdx.x & 63) == 0) reinterpret_cast<float*>(sh)[threadIdx.x >> 6] = ssq;
   __syncthreads();
   float tot = 0.f;
 #pragma unroll
-  for (int w = 0; w < kRowThreads / 64; ++w) tot += sh[w];
+  for (int w = 0; w < NW / 4; ++w) {
+    const float4 t = sh[w];
+    tot += t.x; tot += t.y; tot += t.z; tot += t.w;
+  }
   const float rs = 1.0f / sqrtf(tot / static_cast<float>(N) + eps);
 #pragma unroll
   for (int it = 0; it < kRowIters; ++it) {
     const int n = (threadIdx.x + it * kRowThreads) * 4;
     if (n < N) {
-      const float f[4] = {v[it].x * rs * __uint_as_float(gn[it].x << 16), v[it].y * rs * __uint_as_float(gn[it].x & 0xFFFF0000u),
-                          v[it].z * rs * __uint_as_float(gn[it].y << 16), v[it].w * rs * __uint_as_float(gn[it].y & 0xFFFF0000u)};
+      const float4 s = v[it];
+      const float f[4] = {s.x * rs * __uint_as_float(gn[it].x << 16), s.y * rs * __uint_as_float(gn[it].x & 0xFFFF0000u),
+                          s.z * rs * __uint_as_float(gn[it].y << 16), s.w * rs * __uint_as_float(gn[it].y & 0xFFFF0000u)};
       pack4(packed, NT, m, n, f);
+      if (out_x) *reinterpret_cast<float4*>(out_x + static_cast<size_t>(m) * N + n) = s;
+      if (out_store)
+        *reinterpret_cast<uint2*>(out_store + static_cast<size_t>(m) * N + n) = make_uint2(pack_bf16x2(s.x, s.y), pack_bf16x2(s.z, s.w));
     }
   }
 }
 
 // silu(gate) * up of the concatenated gate|up projection -> operand of the down projection
+template <int U>
 __global__ __launch_bounds__(256) void k_proj_silu(const ProjSum ps, int I, char* __restrict__ packed, int NT) {
   const int m = blockIdx.y, k = (blockIdx.x * 256 + threadIdx.x) * 4;
   if (k >= I) return;
-  const float4 gt = proj_sum4(ps, m, k), up = proj_sum4(ps, m, I + k);
+  const ProjSlots sg = proj_slots(ps, m, k), su = proj_slots(ps, m, I + k);
+  ProjTerms<U, float4> tg, tu;
+  tg.request(sg);
+  tu.request(su);
+  const float4 gt = tg.sum(sg), up = tu.sum(su);
   const float f[4] = {gt.x * sigmoidf_(gt.x) * up.x, gt.y * sigmoidf_(gt.y) * up.y, gt.z * sigmoidf_(gt.z) * up.z, gt.w * sigmoidf_(gt.w) * up.w};
   pack4(packed, NT, m, k, f);
 }
 
 // q | k | v heads: rotary embedding (pairs c, c + d/2; v as it is), q rows and cache entries.  A thread takes one pair.
+template <int U>
 __global__ __launch_bounds__(256) void k_proj_rope(const ProjSum ps, const RopeArgs ra) {
   const int half = ra.d >> 1;
   const int idx = blockIdx.x * 256 + threadIdx.x;
   const int m = blockIdx.y;
   const int hh = idx / half, c = idx - hh * half;
   if (hh >= ra.Hq + 2 * ra.Hkv) return;
+  // (a head of at most 128 columns lies in one group)
+  const ProjSlots sl = proj_slots(ps, m, hh * ra.d + c);
+  ProjTerms<U, float> t1, t2;
+  t1.request(sl);
+  t2.request(sl, half);
   const int b = m / ra.W;
   const int pos = ra.pos[b];
   const int slot = pos + (ra.node ? ra.node[m % ra.W] : 0);
-  float x1, x2;
-  proj_sum_pair(ps, m, hh * ra.d + c, half, x1, x2);
-  if (hh < ra.Hq + ra.Hkv) {
+  const bool turn = hh < ra.Hq + ra.Hkv;
+  float cs = 1.f, sn = 0.f;
+  if (turn) {
     // angle in double (long positions keep their phase), reduced to [-pi, pi] in double,
     // sine and cosine of the remainder in float
     const double ang = static_cast<double>(pos + ra.level) * ra.inv_freq[c];
     const double turns = rint(ang * 0.15915494309189535);
     const float red_ang = static_cast<float>(fma(-turns, 6.283185307179586, ang));
-    float cs, sn;
     sincosf(red_ang, &sn, &cs);
+  }
+  float x1 = t1.sum(sl), x2 = t2.sum(sl, half);
+  if (turn) {
     const float r1 = x1 * cs - x2 * sn;
     x2 = x2 * cs + x1 * sn;
     x1 = r1;
@@ -498,12 +503,18 @@ ProjSum sum_of(const ProjArgs& g) {
   ProjSum p;
   p.partial = g.partial;
   p.KB = g.K >> 7;
-  p.T = static_cast<int64_t>(proj_groups(g.N)) * p.KB;
-  p.inv_T = 1.0 / static_cast<double>(p.T);
+  p.T = proj_groups(g.N) * p.KB;
+  p.inv_T = proj_inverse(p.T);
   p.W = g.W;
   p.M = g.M;
   return p;
 }
+
+// Slots that a group's sums can lie in, at most: the kernels behind a projection request that many at once, 2, 4 or 8 (more in
+// turn), for all the sums of a thread.  (Eight whatever the shape, one sum after the other, and the owners from fp64: the gate and up sums of
+// D = 4096, I = 12288, which lie in two or three, 8 / 64 rows 3.0 / 4.25 us in the kernel, 1.6 / 2.7 now; the norms 3.5 / 4.2
+// there and 2.6-2.9 / 3.0-3.5 now.)
+int most_slots(const ProjSum& p) { return static_cast<int>(static_cast<int64_t>(p.KB - 1) * p.W / p.T) + 2; }
 
 }  // namespace
 
@@ -536,23 +547,40 @@ hipError_t launch_proj(const ProjArgs& g, hipStream_t s) {
   }
 }
 
+template <int U>
+static void start_norm(const ProjSum& p, const ProjArgs& g, const float* residual, const void* gain, float eps, float* out_x, void* out_store, void* packed, hipStream_t s) {
+  hipLaunchKernelGGL(k_proj_norm<U>, dim3(g.M), dim3(kRowThreads), 0, s, p, g.N, residual, static_cast<const bf16_t*>(gain), eps, out_x,
+                     static_cast<bf16_t*>(out_store), static_cast<char*>(packed), packed_tiles(g.M, 2));
+}
+
 hipError_t launch_proj_norm(const ProjArgs& g, const float* residual, const void* gain, float eps, float* out_x, void* out_store, void* packed,
                             hipStream_t s) {
   if (g.N > kRowThreads * kRowIters * 4) return hipErrorInvalidValue;
-  hipLaunchKernelGGL(k_proj_norm, dim3(g.M), dim3(kRowThreads), 0, s, sum_of(g), g.N, residual, static_cast<const bf16_t*>(gain), eps, out_x,
-                     static_cast<bf16_t*>(out_store), static_cast<char*>(packed), packed_tiles(g.M, 2));
+  const ProjSum p = sum_of(g);
+  const int most = most_slots(p);
+  (most <= 2 ? start_norm<2> : most <= 4 ? start_norm<4> : start_norm<8>)(p, g, residual, gain, eps, out_x, out_store, packed, s);
   return hipGetLastError();
 }
 
 hipError_t launch_proj_silu(const ProjArgs& g, void* packed, hipStream_t s) {
   const int I = g.N / 2;
-  hipLaunchKernelGGL(k_proj_silu, dim3((I / 4 + 255) / 256, g.M), dim3(256), 0, s, sum_of(g), I, static_cast<char*>(packed), packed_tiles(g.M, 2));
+  const ProjSum p = sum_of(g);
+  const dim3 grid((I / 4 + 255) / 256, g.M);
+  const int most = most_slots(p), NT = packed_tiles(g.M, 2);
+  if (most <= 2) hipLaunchKernelGGL(k_proj_silu<2>, grid, dim3(256), 0, s, p, I, static_cast<char*>(packed), NT);
+  else if (most <= 4) hipLaunchKernelGGL(k_proj_silu<4>, grid, dim3(256), 0, s, p, I, static_cast<char*>(packed), NT);
+  else hipLaunchKernelGGL(k_proj_silu<8>, grid, dim3(256), 0, s, p, I, static_cast<char*>(packed), NT);
   return hipGetLastError();
 }
 
 hipError_t launch_proj_rope(const ProjArgs& g, const RopeArgs& ra, hipStream_t s) {
   const int items = (ra.Hq + 2 * ra.Hkv) * (ra.d >> 1);
-  hipLaunchKernelGGL(k_proj_rope, dim3((items + 255) / 256, g.M), dim3(256), 0, s, sum_of(g), ra);
+  const ProjSum p = sum_of(g);
+  const dim3 grid((items + 255) / 256, g.M);
+  const int most = most_slots(p);
+  if (most <= 2) hipLaunchKernelGGL(k_proj_rope<2>, grid, dim3(256), 0, s, p, ra);
+  else if (most <= 4) hipLaunchKernelGGL(k_proj_rope<4>, grid, dim3(256), 0, s, p, ra);
+  else hipLaunchKernelGGL(k_proj_rope<8>, grid, dim3(256), 0, s, p, ra);
   return hipGetLastError();
 }
 

@@ -53,11 +53,19 @@ struct ProjArgs {
 // where the partial sums of a projection lie (see gemm_proj.hip)
 struct ProjSum {
   const float* partial;   // [slot][M][128]
-  int64_t T;              // blocks of the projection
-  double inv_T;           // 1 / T
+  int T;                  // blocks of the projection
+  uint32_t inv_T;         // 2^32 / T, rounded down
   int KB, W, M;           // k blocks of a group, workgroups, rows
 };
 __host__ __device__ inline int proj_groups(int N) { return N / 128; }
+// Workgroup that has block x of T dealt to W: the last that starts at or before it, (x + 1) W - 1 over T, rounded down.  (The product
+// with 2^32 / T is off by one at most; T W < 2^32 as long as the weights are less than 137 GB with 1024 workgroups, 550 GB with 256.)
+__host__ __device__ inline uint32_t proj_inverse(int T) { return T > 1 ? static_cast<uint32_t>((1ull << 32) / static_cast<uint64_t>(T)) : 0u; }
+__host__ __device__ inline int proj_owner(int T, uint32_t inv_T, int W, int x) {
+  const uint32_t a = static_cast<uint32_t>(x + 1) * static_cast<uint32_t>(W) - 1;
+  const uint32_t q = static_cast<uint32_t>((static_cast<uint64_t>(a) * inv_T) >> 32);
+  return static_cast<int>(a - q * static_cast<uint32_t>(T) >= static_cast<uint32_t>(T) ? q + 1 : q);
+}
 bool proj_supported(int M, int N, int K);
 void proj_plan(ProjArgs& g, int num_cus);
 size_t proj_partial_bytes(const ProjArgs& g);

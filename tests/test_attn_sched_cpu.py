@@ -80,3 +80,41 @@ def test_shares_and_owners_of_the_work_split(tmp_path):
     run = subprocess.run([str(exe)], capture_output=True, text=True, timeout=100)
     assert run.returncode == 0, run.stdout
     assert int(run.stdout.split()[0]) > 5_000_000
+
+
+OWNERS = r"""
+#include "kernels.hpp"
+#include <stdio.h>
+#include <stdlib.h>
+using namespace sx;
+int main() {
+  srand(2);
+  long checked = 0, bad = 0;
+  for (int k = 0; k < 200000; ++k) {
+    const long most = k % 3 == 0 ? 1l << 22 : k % 3 == 1 ? 60000 : 300;
+    const long T = 1 + ((static_cast<long>(rand()) << 16) ^ rand()) % most;
+    const long W = T < 4 ? 1 : 1 + rand() % (T / 2 < 1023 ? T / 2 : 1023);
+    const uint32_t inv = proj_inverse(T);
+    for (int i = 0; i < 12; ++i) {
+      const long w = rand() % W, start = w * T / W;
+      const long x = i == 0 ? 0 : i == 1 ? T - 1 : i < 6 ? start : i < 9 ? (start > 0 ? start - 1 : 0) : rand() % T;
+      const long o = proj_owner(T, inv, W, x);
+      ++checked;
+      if (o < 0 || o >= W || o * T / W > x || (o + 1) * T / W <= x) if (++bad < 10) printf("T %ld W %ld x %ld: %ld\n", T, W, x, o);
+    }
+  }
+  printf("%ld checks, %ld wrong\n", checked, bad);
+  return bad != 0;
+}
+"""
+
+
+@pytest.mark.skipif(not shutil.which(HIPCC), reason="no hipcc")
+def test_owners_of_the_projections_blocks(tmp_path):
+    src = tmp_path / "owners.hip"
+    src.write_text(OWNERS)
+    exe = tmp_path / "owners"
+    subprocess.run([HIPCC, "-O2", "-std=c++17", "--offload-arch=gfx950", "--offload-host-only", "-I", os.path.join(ROOT, "paper_2509_24248_amd", "csrc"),
+                    str(src), "-o", str(exe)], check=True)
+    run = subprocess.run([str(exe)], capture_output=True, text=True, timeout=100)
+    assert run.returncode == 0, run.stdout

@@ -96,6 +96,17 @@ def test_row_tile_edges(B, D):
     one_step(shape, w, kv, tok, g, pos, label="row tile edges")
 
 
+@pytest.mark.parametrize("B", [5, 20])
+@pytest.mark.parametrize("D,I", [(256, 8192), (1024, 1024), (128, 16384)])
+def test_sums_over_few_and_many_slots(B, D, I):
+    # partial sums of a projection in two to more than eight places: many groups of few k blocks (gate and up), few groups of many (down),
+    # rows of more than one float4 per thread excepted, which the full-size cases have
+    shape = gen.scaled(gen.config(2), D=D, Hq=2, Hkv=1, d=128, I=I, V=500, B=B, ctx=(0, 60), k=2)
+    w, kv, tok, g, pos = setup(shape, B, std=0.05)
+    w = force_draft_gap(shape, w, kv, tok, g, pos)
+    one_step(shape, w, kv, tok, g, pos, label="slots")
+
+
 @pytest.mark.parametrize("B,V", [(20, 98400), (33, 151936), (20, 165001), (64, 82000), (64, 151936)])
 def test_head_passes_of_several_halves(B, V):
     # the widened head over two planes: four and five halves in a pass, twice three; three, three and two of four row tiles
