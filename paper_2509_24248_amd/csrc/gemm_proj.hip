@@ -17,7 +17,8 @@
 // staged the activations of every K range in LDS for each 128 rows and let the last workgroup of a group add
 // up the ranges: 8B-like layer (452 MB), 8 rows 129 -> 121 us, 64 rows 355 -> 177 us; 32B-like (1080 MB), 16
 // rows 247 -> 220 us.  The large ones reach 6 TB/s (gate/up of the 32B-like layer: 524 MB in 86 us); the rest is
-// what starting and draining ten short kernels costs (4 to 7 us for each of the five that add up).
+// what starting and draining ten short kernels costs (of the five that add up 1.6 to 3.5 us each and 1.7 us to the next kernel; a
+// projection about 3 us beside its stream).
 #include "kernels.hpp"
 #include "stream.hpp"
 
