@@ -107,7 +107,19 @@ __device__ __forceinline__ float wave_sum_dpp(float v) {
   return quad_row_sum(v);
 }
 
-// Inclusive prefix sum over a wave, likewise: shifts within the rows of 16 lanes, then the last lane of a row to the next one
+// The sum in the order of wave_sum, lanes 32 apart first: the same bits.  (Once lanes 8 apart hold equal values, those that a rotation
+// by 4 brings are the ones 4 apart, and so on.)
+__device__ __forceinline__ float wave_sum_halves(float v) {
+  const auto a = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+  v = __uint_as_float(a[0]) + __uint_as_float(a[1]);
+  const auto b = __builtin_amdgcn_permlane16_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+  v = __uint_as_float(b[0]) + __uint_as_float(b[1]);
+  v += row_lane<0x128>(v); v += row_lane<0x124>(v);
+  v += row_lane<0x122>(v); v += row_lane<0x121>(v);
+  return v;
+}
+
+// Inclusive prefix sum over a wave, by lanes as well: shifts within the rows of 16 lanes, then the last lane of a row to the next one
 // (rows 1 and 3) and of the first two rows to the last two.
 __device__ __forceinline__ int wave_scan(int x) {
   x += __builtin_amdgcn_update_dpp(0, x, 0x111, 0xf, 0xf, false);

@@ -398,7 +398,7 @@ __global__ __launch_bounds__(kRowThreads) void k_proj_norm(const ProjSum ps, int
       ssq += s.x * s.x + s.y * s.y + s.z * s.z + s.w * s.w;
     }
   }
-  ssq = wave_sum_dpp(ssq);
+  ssq = wave_sum_halves(ssq);
   if ((threadIdx.x & 63) == 0) reinterpret_cast<float*>(sh)[threadIdx.x >> 6] = ssq;
   __syncthreads();
   float tot = 0.f;

@@ -1,0 +1,54 @@
+"""Outputs that must not move by a bit from build to build: digests of whole calls on seeded inputs.
+
+The ranked candidates and the tokens of a draft are whole numbers that follow from float sums: where two logits lie closer
+than a sum's rounding, another order of addition names another token.  So these calls keep the order of every sum.  The digests were
+taken on an MI355X (256 compute units) from the build in which sequences of one length were first dealt to workgroups evenly and the
+draft heads' products summed by k block; kernels changed since give the same bits.  A change that has to add in another order says
+which sum it is and why, shows the 64-bit logits of every id that differs, and takes the digest anew."""
+import hashlib
+
+import numpy as np
+import pytest
+
+from workloads import gen
+
+import harness as H
+
+pytestmark = pytest.mark.gpu
+
+
+def digest(arrays):
+    h = hashlib.sha256()
+    for a in arrays:
+        h.update(np.ascontiguousarray(a).tobytes())
+    return h.hexdigest()[:16]
+
+
+def draft_inputs(shape, paged, seed):
+    w = gen.draft_weights(shape, seed, std=0.05)
+    w.update(gen.perturbed_norm_vectors(shape, seed))
+    L = gen.context_lengths(shape, seed)
+    return w, gen.kv_cache(shape, L, shape.n_q, seed, paged=paged), gen.token_ids(shape, shape.B, seed), gen.hidden_rows(shape, shape.B, seed), L
+
+
+def step(index, paged=False, seed=3, **kw):
+    shape = gen.scaled(gen.config(index), k=2, **kw)
+    w, kv, tok, g, L = draft_inputs(shape, paged, seed)
+    gd = H.GpuDraft(shape, w, kv)
+    out = gd.step(tok, g, L)
+    return digest([out[n] for n in ("hidden_out", "next_tok", "sig_raw", "sig")] + list(gd.cache()))
+
+
+CASES = {
+    # sums over a row by a workgroup per row
+    "step of 8 rows": (lambda: step(2, D=1024, Hq=8, Hkv=2, d=128, I=1536, V=30000, B=8, ctx=(0, 60)), "8378dd9450f6341b"),
+    "step of 20 rows, paged": (lambda: step(2, paged=True, D=768, Hq=8, Hkv=2, d=64, I=1536, V=30000, B=20, ctx=(0, 60)), "8979e8f368224ea6"),
+}
+
+
+@pytest.mark.parametrize("name", list(CASES))
+def test_same_bits(name):
+    call, want = CASES[name]
+    got = call()
+    print(f"same bits, {name}: {got}", flush=True)
+    assert got == want
