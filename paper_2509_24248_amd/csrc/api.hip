@@ -125,7 +125,7 @@ int32_t check_kv(const specexit_kv_view* kv, const char* who) {
   return SPECEXIT_OK;
 }
 
-int32_t fill_attn(AttnArgs& a, const specexit_kv_view* kv, int32_t B, int32_t n_q, int32_t n_q_heads, const char* who) {
+int32_t fill_attn(AttnArgs& a, const specexit_kv_view* kv, int32_t B, int32_t n_q, int32_t n_q_heads, bool draft, const char* who) {
   int32_t rc = check_kv(kv, who);
   if (rc) return rc;
   if (B < 1) return fail(SPECEXIT_EINVAL, "%s: B < 1", who);
@@ -146,6 +146,7 @@ int32_t fill_attn(AttnArgs& a, const specexit_kv_view* kv, int32_t B, int32_t n_
   a.n_q = n_q;
   a.n_blk = n_q;
   a.mask_stride = n_q;
+  a.draft = draft;
   a.Hq = n_q_heads;
   a.Hkv = kv->n_kv_heads;
   a.d = kv->head_dim;
@@ -223,7 +224,7 @@ int32_t make_draft_plan(DraftPlan& p, const specexit_model_desc* d, const specex
   if (d->vocab < 1) return fail(SPECEXIT_EINVAL, "draft_step: vocab < 1");
   if (d->vocab < top_b) return fail(SPECEXIT_EINVAL, "draft_step: top_b %d exceeds the vocabulary (%d)", top_b, d->vocab);
   if (d->rem_activation < 0 || d->rem_activation > 2) return fail(SPECEXIT_EINVAL, "draft_step: rem_activation %d", d->rem_activation);
-  int32_t rc = fill_attn(p.attn, kv, nseq, W, d->n_q_heads, "draft_step");
+  int32_t rc = fill_attn(p.attn, kv, nseq, W, d->n_q_heads, true, "draft_step");
   if (rc) return rc;
   if (kv->dtype != d->dtype || kv->n_kv_heads != d->n_kv_heads || kv->head_dim != d->head_dim)
     return fail(SPECEXIT_EINVAL, "draft_step: draft kv view does not match the model desc");
@@ -686,7 +687,7 @@ int32_t specexit_draft_tree_level(const specexit_model_desc* desc, const specexi
 
 size_t specexit_verify_attn_workspace_bytes(const specexit_kv_view* kv, int32_t B, int32_t n_q, int32_t n_q_heads) {
   AttnArgs a;
-  if (fill_attn(a, kv, B, n_q, n_q_heads, "verify_attn")) return 0;
+  if (fill_attn(a, kv, B, n_q, n_q_heads, false, "verify_attn")) return 0;
   return attn_workspace_bytes(a);
 }
 
@@ -694,7 +695,7 @@ int32_t specexit_verify_attn(const specexit_kv_view* kv, int32_t B, int32_t n_q,
                              const int32_t* ctx_len, const uint64_t* mask, float scale, void* out,
                              void* workspace, size_t workspace_bytes, uint32_t flags, void* stream) {
   AttnArgs a;
-  int32_t rc = fill_attn(a, kv, B, n_q, n_q_heads, "verify_attn");
+  int32_t rc = fill_attn(a, kv, B, n_q, n_q_heads, false, "verify_attn");
   if (rc) return rc;
   if (!q || !ctx_len || !out) return fail(SPECEXIT_EINVAL, "verify_attn: a required pointer is null");
   if (!(scale > 0.f)) return fail(SPECEXIT_EINVAL, "verify_attn: scale must be positive");

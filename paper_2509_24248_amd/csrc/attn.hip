@@ -713,6 +713,7 @@ static bool plan_as(AttnArgs& a, int num_cus, int use_mfma, int pad) {
   const int64_t units = static_cast<int64_t>(a.B) * a.Hkv;
   const int64_t gmax = (a.l_max + kAttnGran - 1) / kAttnGran;      // granules of the longest possible unit
   if (units * (gmax + pad) >= (1ll << 30)) return false;
+  a.rings = a.use_mfma ? attn_mfma_rings(a) : 0;
   a.stages = a.use_mfma ? attn_mfma_stages(a) : 0;
   const int64_t resident = static_cast<int64_t>(num_cus) * (a.use_mfma ? attn_mfma_per_cu(a) : 1);
   const AttnLine line = attn_sched_line(static_cast<int>(a.B * gmax), a.B, a.Hkv, pad, a.wide_from, a.use_mfma == kOnePart, static_cast<int>(resident));

@@ -4,8 +4,8 @@
 // segments, each a key range of one (sequence, KV head) unit, processed against all
 // R = G * n_q query rows that share that head, so the cache is read once.
 //
-// Inside a workgroup there are two independent tile rings (key groups), four with few query rows; ring kg takes the
-// 32-key tiles kg, kg+2 (kg+4), ... of the chunk.  A ring is S slots in LDS (K tile + V tile: 16 KB
+// Inside a workgroup there are two independent tile rings (key groups), four in verifications of few query rows; ring kg
+// takes the 32-key tiles kg, kg+2 (kg+4), ... of the chunk.  A ring is S slots in LDS (K tile + V tile: 16 KB
 // with 128-wide heads, 8 KB with 64-wide ones).  Tiles are brought in by direct global->LDS loads (16 bytes per lane, streaming),
 // issued S-1 tiles ahead by the ring's waves in turn, so most of the LDS holds bytes in
 // flight.  Each of the ring's NR waves owns one or two 16-row tiles of the queries and computes them
@@ -37,12 +37,15 @@ namespace sx {
 
 namespace {
 
-// Tile rings (key groups) per workgroup: two of several waves each, or, up to 16 query rows per KV head, four of one wave, which
-// then wait for nobody: the wave that brings a tile in is the one that reads it, and one workgroup per compute unit has in flight what two
-// of two rings had, with half the partial results.  Layers of 8 KV heads, 2 rings / 4: 3 sequences of 1000-3000 entries, 12 rows,
-// contiguous / paged 13.0 -> 12.2 / 13.7 -> 13.2 us, 8 rows 12.7 -> 11.6; 1 of 5000, 12 rows 11.8 -> 11.3; 64-wide heads, 16 of 500-2500,
-// 16 rows 14.8 -> 14.1, 8 of 4000-8000, 12 rows 21.0 -> 19.7 (two workgroups of two-slot rings; one of four slots 20.6).
-constexpr int rings_of(int nr) { return nr == 1 ? 4 : 2; }
+// Tile rings (key groups) per workgroup, NK: two of several waves each, or, in verifications of up to 16 query rows per KV head, four of one
+// wave, which then wait for nobody: the wave that brings a tile in is the one that reads it, and one workgroup per compute unit has in
+// flight what two of two rings had, with half the partial results.  Layers of 8 KV heads, 2 rings / 4: 3 sequences of 1000-3000 entries,
+// 12 rows, contiguous / paged 13.0 -> 12.2 / 13.7 -> 13.2 us, 8 rows 12.7 -> 11.6; 1 of 5000, 12 rows 11.8 -> 11.3; 64-wide heads, 16 of
+// 500-2500, 16 rows 14.8 -> 14.1, 8 of 4000-8000, 12 rows 21.0 -> 19.7 (two workgroups of two-slot rings; one of four slots 20.6).
+// Draft steps and tree levels (AttnArgs::draft) keep two rings whatever the rows: four add the keys in another order, and a call that
+// ranks its own logits then names other tokens where two of them are closer than that rounding (2 of 48 candidates of a level of 4 x 4
+// nodes, V = 151936).  That costs a round of six steps, D = 2560, 1 % of its time.
+constexpr int kFewRings = 4;
 constexpr int slot_bytes(int hd) { return 128 * hd; }   // one ring slot: 32 K rows then 32 V rows of hd bf16 values
 // From kBigFrom waves per ring (more than 48 query rows per KV head) one workgroup is resident per
 // compute unit (its eight to sixteen waves need more than the 96-128 registers per lane that two
@@ -56,8 +59,8 @@ constexpr int slot_bytes(int hd) { return 128 * hd; }   // one ring slot: 32 K r
 constexpr int big_from(int hd) { return hd == 64 ? 5 : 4; }
 constexpr bool two_part(int hd, int nr) { return hd == 64 || nr <= 3; }     // (see kSplitP)
 // Four rings take two slots each.
-constexpr int stages_of(int hd, int nr) { return nr == 1 ? 2 : (nr >= big_from(hd) ? 4 : 2) * (hd == 64 ? 2 : 1); }
-constexpr int wgs_per_cu(int hd, int nr) { return nr >= big_from(hd) || (nr == 1 && hd == 128) ? 1 : 2; }
+constexpr int stages_of(int hd, int nr, int nk) { return nk == kFewRings ? 2 : (nr >= big_from(hd) ? 4 : 2) * (hd == 64 ? 2 : 1); }
+constexpr int wgs_per_cu(int hd, int nr, int nk) { return nr >= big_from(hd) || (nk == kFewRings && hd == 128) ? 1 : 2; }
 // K operand reads / V operand read pairs issued ahead of the matrix instructions that use them: as
 // many as the registers allow (one resident workgroup: all eight K reads, four V pairs; 64-wide heads
 // have four of each)
@@ -75,7 +78,7 @@ constexpr int kPairFrom = 7;
 constexpr int tiles_per_wave(int hd, int tiles) { return hd == 128 && tiles >= kPairFrom ? 2 : 1; }
 constexpr int kMaxChunkPages = 2048;   // page ids of one chunk kept in LDS (8 KB)
 
-constexpr int ml_rows(int nr, int rp) { return nr == 1 ? rings_of(nr) * rp : rp; }   // (max, sum) pairs that the merge of the rings passes through LDS
+constexpr int ml_rows(int nk, int rp) { return nk == kFewRings ? nk * rp : rp; }   // (max, sum) pairs that the merge of the rings passes through LDS
 
 typedef short s16x4_t __attribute__((ext_vector_type(4)));
 
@@ -95,14 +98,13 @@ template <int HD> __device__ __forceinline__ int swz_v(int key) { return HD == 1
 // four SIMDs
 // (One wave a ring has room for any number, and the compiler then keeps the accumulators where every rescaling has to fetch them: 3
 // sequences of 1000-3000 entries, 12 rows, 13.5 -> 13.0 us a call with 256 registers.)
-constexpr int min_waves_per_simd(int hd, int nr) { return nr == 1 ? 2 : (wgs_per_cu(hd, nr) * rings_of(nr) * nr + 3) / 4; }
+constexpr int min_waves_per_simd(int hd, int nr, int nk) { return nr == 1 ? 2 : (wgs_per_cu(hd, nr, nk) * nk * nr + 3) / 4; }
 
 // NR waves per ring, each owning RTW 16-row tiles of the queries (rows 16 (rr RTW + t) ..).
 // RTW = 2 halves the LDS reads per query row (K and V operands are fetched once per wave and
 // used for both row tiles) at the price of fewer, fatter waves (see kPairFrom).
-template <int HD, int NR, int RTW, int S, bool PAGED>
-__global__ __launch_bounds__(64 * rings_of(NR) * NR, min_waves_per_simd(HD, NR)) void k_attn_ring(const AttnArgs a) {
-  constexpr int kNK = rings_of(NR);
+template <int HD, int NR, int RTW, int S, int NK, bool PAGED>
+__global__ __launch_bounds__(64 * NK * NR, min_waves_per_simd(HD, NR, NK)) void k_attn_ring(const AttnArgs a) {
   constexpr int RP = 16 * NR * RTW;             // query rows covered (padded)
   constexpr int kKAhead = k_ahead(HD, NR), kVAhead = v_ahead(HD, NR);
   constexpr int kSlot = slot_bytes(HD);
@@ -130,11 +132,11 @@ __global__ __launch_bounds__(64 * rings_of(NR) * NR, min_waves_per_simd(HD, NR))
   constexpr int kKS = HD / 32, kDT = HD / 16;   // k steps of K Q^T, 16-wide column tiles of the output
   // LDS: [ring 0: S slots][ring 1: S slots] (free ones hold ring 1's sums for the merge), ring 1's (max, sum) per row, the
   // schedule's prefix table, the page ids of the segment
-  constexpr int kFront = kNK * S * kSlot;
+  constexpr int kFront = NK * S * kSlot;
   extern __shared__ uint4 smem4[];
   char* smem = reinterpret_cast<char*>(smem4);
   float* ml_lds = reinterpret_cast<float*>(smem + kFront);
-  int* sched_lds = reinterpret_cast<int*>(smem + kFront + ml_rows(NR, RP) * 2 * sizeof(float));
+  int* sched_lds = reinterpret_cast<int*>(smem + kFront + ml_rows(NK, RP) * 2 * sizeof(float));
   int* pg_lds = sched_lds + attn_sched_words(a.B);
   const int lane = threadIdx.x & 63;
   const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -155,7 +157,7 @@ __global__ __launch_bounds__(64 * rings_of(NR) * NR, min_waves_per_simd(HD, NR))
   const int L = __builtin_amdgcn_readfirstlane(seg.L);
   const int s0 = seg.s0, s1 = __builtin_amdgcn_readfirstlane(seg.s1);
   const int ntl = (s1 - s0 + 31) >> 5;          // 32-key tiles in this segment
-  const int nit = (ntl + kNK - 1) / kNK;        // tile steps (the same for all rings)
+  const int nit = (ntl + NK - 1) / NK;          // tile steps (the same for all rings)
   char* ring = smem + kg * (S * kSlot);
 
   // ---- Q^T operand pieces and the mask words of this wave's rows (rows past the last one repeat it and are not stored)
@@ -180,7 +182,7 @@ __global__ __launch_bounds__(64 * rings_of(NR) * NR, min_waves_per_simd(HD, NR))
   if (PAGED) {
     const int npg = ((s1 - 1) >> ps_shift) - pg0 + 1;
     const int32_t* ptab = a.page_table + static_cast<size_t>(b) * a.max_pages + pg0;
-    for (int i = threadIdx.x; i < npg; i += 64 * kNK * NR) {
+    for (int i = threadIdx.x; i < npg; i += 64 * NK * NR) {
       pg_lds[i] = checked_page(ptab[i], a.n_pages, a.status);   // never leave the pool
     }
   }
@@ -209,7 +211,7 @@ __global__ __launch_bounds__(64 * rings_of(NR) * NR, min_waves_per_simd(HD, NR))
   const int64_t seq_off = PAGED ? 0 : (static_cast<int64_t>(b) * a.Hkv + g) * a.l_max * kRowB;
   int64_t off_a, off_b;
   auto locate = [&](int it) {
-    const int t0 = s0 + 32 * (it * kNK + kg);
+    const int t0 = s0 + 32 * (it * NK + kg);
     if (t0 >= s1) return;                        // uniform per wave
     if (PAGED) {
       const int p1 = min(t0 + 16, s1 - 1);
@@ -221,7 +223,7 @@ __global__ __launch_bounds__(64 * rings_of(NR) * NR, min_waves_per_simd(HD, NR))
     }
   };
   auto issue = [&](int it) {                     // (after locate of the same tile)
-    const int t0 = s0 + 32 * (it * kNK + kg);
+    const int t0 = s0 + 32 * (it * NK + kg);
     if (t0 >= s1) return;
     char* slot = ring + (it % S) * kSlot;
     if (t0 + 32 <= s1) {
@@ -319,7 +321,7 @@ __global__ __launch_bounds__(64 * rings_of(NR) * NR, min_waves_per_simd(HD, NR))
     // this wave's pieces of tile `it` have landed once at most the pieces of the S-2 tiles (S-1 before the first, if this ring
     // has that many) issued after it are outstanding (loads return in order); near the end simply wait for all
     if (S == 2 || it + S - 1 >= nit) __builtin_amdgcn_s_waitcnt(vmcnt_imm(0));
-    else if (it == 0 && (S - 1) * kNK + kg < ntl) __builtin_amdgcn_s_waitcnt(vmcnt_imm((S - 1) * kPiecesMin));
+    else if (it == 0 && (S - 1) * NK + kg < ntl) __builtin_amdgcn_s_waitcnt(vmcnt_imm((S - 1) * kPiecesMin));
     else __builtin_amdgcn_s_waitcnt(vmcnt_imm((S - 2) * kPiecesMin));
     // plain barrier (no memory fence: a fence would wait for the loads still in flight); the
     // wave-scope fences only keep the compiler from moving LDS accesses across it
@@ -328,7 +330,7 @@ __global__ __launch_bounds__(64 * rings_of(NR) * NR, min_waves_per_simd(HD, NR))
     else __builtin_amdgcn_s_waitcnt(0xC07F);   // lgkmcnt(0): (of one wave, tile it-1 is read)
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
     if (it > 0) issue(it + S - 1);
-    const int ti = it * kNK + kg;
+    const int ti = it * NK + kg;
     if (ti >= ntl) continue;
     const int t0 = s0 + 32 * ti;
     const char* k_lds = ring + (it % S) * kSlot;
@@ -449,7 +451,7 @@ __global__ __launch_bounds__(64 * rings_of(NR) * NR, min_waves_per_simd(HD, NR))
   }
 
   constexpr int kOBytes = 64 * HD;               // 16 rows
-  if constexpr (NR > 1) {
+  if constexpr (NK == 2) {
   // ---- merge the two rings of each row: ring 1 leaves its sums in LDS, ring 0 adds them to its own (always in this order) and
   // stores the segment's partial result.  Slots other than the last tile's are free since the last barrier: wave rr of ring 1
   // takes piece rr of them, ring 1's first.  Within a row the 16-byte pieces are swizzled like the tiles.
@@ -496,7 +498,7 @@ __global__ __launch_bounds__(64 * rings_of(NR) * NR, min_waves_per_simd(HD, NR))
   } else {
     // ---- merge the four rings: each leaves its sums in its own slots, the 16-byte pieces of a row swizzled like the tiles, and every
     // wave adds some rows, in the order of the rings
-    static_assert(RTW == 1 && kOBytes <= S * kSlot, "a ring's slots hold its sums");
+    static_assert(NR == 1 && RTW == 1 && kOBytes <= S * kSlot, "a ring's slots hold its sums");
     constexpr int C4 = HD / 4, RPW = 64 / C4;     // 16-byte pieces of a row, rows that a wave adds at a time
     const float l = kSplitP ? quad_row_sum(l_run[0]) : lacc[0][0];
     int fr_o = fr, fq_o = fq;                     // (addresses worked out here, see above)
@@ -509,21 +511,21 @@ __global__ __launch_bounds__(64 * rings_of(NR) * NR, min_waves_per_simd(HD, NR))
     const size_t unit = static_cast<size_t>(blockIdx.x) + static_cast<size_t>(b) * a.Hkv + g;   // partial slot of segment (w, u)
     const int c4 = lane % C4;
 #pragma unroll 1
-    for (int r = RPW * wv + lane / C4; r < R; r += RPW * kNK) {
-      float2 ml[kNK];
-      float4 o[kNK];
+    for (int r = RPW * wv + lane / C4; r < R; r += RPW * NK) {
+      float2 ml[NK];
+      float4 o[NK];
 #pragma unroll
-      for (int k = 0; k < kNK; ++k) {
+      for (int k = 0; k < NK; ++k) {
         ml[k] = *reinterpret_cast<const float2*>(ml_lds + 2 * (k * RP + r));
         o[k] = *reinterpret_cast<const float4*>(smem + k * (S * kSlot) + r * (4 * HD) + ((c4 ^ r) << 4));
       }
       float mm = ml[0].x;
 #pragma unroll
-      for (int k = 1; k < kNK; ++k) mm = fmaxf(mm, ml[k].x);
+      for (int k = 1; k < NK; ++k) mm = fmaxf(mm, ml[k].x);
       float sum = 0.f;
       float4 v = make_float4(0.f, 0.f, 0.f, 0.f);
 #pragma unroll
-      for (int k = 0; k < kNK; ++k) {
+      for (int k = 0; k < NK; ++k) {
         const float f = __builtin_amdgcn_exp2f(ml[k].x - mm);
         sum = fmaf(f, ml[k].y, sum);
         v.x = fmaf(f, o[k].x, v.x); v.y = fmaf(f, o[k].y, v.y);
@@ -536,29 +538,38 @@ __global__ __launch_bounds__(64 * rings_of(NR) * NR, min_waves_per_simd(HD, NR))
   }
 }
 
-constexpr size_t lds_bytes(int hd, int nr, int rp, int stages, int B, bool paged) {
-  return static_cast<size_t>(rings_of(nr)) * stages * slot_bytes(hd) + static_cast<size_t>(ml_rows(nr, rp)) * 2 * sizeof(float) +
+constexpr size_t lds_bytes(int hd, int nk, int rp, int stages, int B, bool paged) {
+  return static_cast<size_t>(nk) * stages * slot_bytes(hd) + static_cast<size_t>(ml_rows(nk, rp)) * 2 * sizeof(float) +
          static_cast<size_t>(attn_sched_words(B)) * sizeof(int) + (paged ? static_cast<size_t>(kMaxChunkPages + 1) * sizeof(int) : 0);
 }
 
-template <int HD, int NR, int RTW, int S, bool PAGED>
+template <int HD, int NR, int RTW, int S, int NK, bool PAGED>
 hipError_t launch_one(const AttnArgs& a, hipStream_t s) {
   // as many workgroups as attn_mfma_per_cu counts on fit the 160 KB of a compute unit, at any number of sequences
-  static_assert(lds_bytes(HD, NR, 16 * NR * RTW, S, kAttnMaxSeqs, PAGED) * wgs_per_cu(HD, NR) <= 160 * 1024, "the LDS of a compute unit");
+  static_assert(lds_bytes(HD, NK, 16 * NR * RTW, S, kAttnMaxSeqs, PAGED) * wgs_per_cu(HD, NR, NK) <= 160 * 1024, "the LDS of a compute unit");
   static_assert(NR * RTW <= 8, "at most 128 query rows");
   // set once per process; a function-local static is initialised under the language's own lock,
   // so first calls from several host threads are safe
-  static const hipError_t attr = hipFuncSetAttribute(reinterpret_cast<const void*>(&k_attn_ring<HD, NR, RTW, S, PAGED>),
+  static const hipError_t attr = hipFuncSetAttribute(reinterpret_cast<const void*>(&k_attn_ring<HD, NR, RTW, S, NK, PAGED>),
                                              hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
   if (attr != hipSuccess) return attr;
-  hipLaunchKernelGGL((k_attn_ring<HD, NR, RTW, S, PAGED>), dim3(a.wgrid), dim3(64 * rings_of(NR) * NR), attn_mfma_lds_bytes(a), s, a);
+  hipLaunchKernelGGL((k_attn_ring<HD, NR, RTW, S, NK, PAGED>), dim3(a.wgrid), dim3(64 * NK * NR), attn_mfma_lds_bytes(a), s, a);
   return hipGetLastError();
+}
+
+template <int HD, int NR, int RTW, int NK>
+hipError_t launch_rings(const AttnArgs& a, hipStream_t s) {
+  constexpr int S = stages_of(HD, NR, NK);
+  return a.paged ? launch_one<HD, NR, RTW, S, NK, true>(a, s) : launch_one<HD, NR, RTW, S, NK, false>(a, s);
 }
 
 template <int HD, int TILES>
 hipError_t launch_tiles(const AttnArgs& a, hipStream_t s) {
-  constexpr int RTW = tiles_per_wave(HD, TILES), NR = (TILES + RTW - 1) / RTW, S = stages_of(HD, NR);
-  return a.paged ? launch_one<HD, NR, RTW, S, true>(a, s) : launch_one<HD, NR, RTW, S, false>(a, s);
+  constexpr int RTW = tiles_per_wave(HD, TILES), NR = (TILES + RTW - 1) / RTW;
+  if constexpr (NR == 1) {
+    if (a.rings == kFewRings) return launch_rings<HD, NR, RTW, kFewRings>(a, s);
+  }
+  return launch_rings<HD, NR, RTW, 2>(a, s);
 }
 
 template <int HD>
@@ -585,19 +596,20 @@ bool attn_mfma_supported(const AttnArgs& a) {
   return a.dtype == 1 && (a.d == 128 || a.d == 64) && R <= 128 && (!a.paged || (pow2 && a.page_size >= 16));
 }
 
-// Workgroups per compute unit and ring depth (see big_from).
+// Rings, workgroups per compute unit and ring depth (see kFewRings and big_from).
 static int row_tiles(const AttnArgs& a) { return ((a.Hq / a.Hkv) * a.n_q + 15) / 16; }
 static int waves_per_ring(const AttnArgs& a) {
   const int per = tiles_per_wave(a.d, row_tiles(a));
   return (row_tiles(a) + per - 1) / per;
 }
-int attn_mfma_per_cu(const AttnArgs& a) { return wgs_per_cu(a.d, waves_per_ring(a)); }
+int attn_mfma_rings(const AttnArgs& a) { return waves_per_ring(a) == 1 && !a.draft ? kFewRings : 2; }
+int attn_mfma_per_cu(const AttnArgs& a) { return wgs_per_cu(a.d, waves_per_ring(a), a.rings); }
 bool attn_mfma_two_part(const AttnArgs& a) { return two_part(a.d, waves_per_ring(a)); }
-int attn_mfma_stages(const AttnArgs& a) { return stages_of(a.d, waves_per_ring(a)); }
+int attn_mfma_stages(const AttnArgs& a) { return stages_of(a.d, waves_per_ring(a), a.rings); }
 
 size_t attn_mfma_lds_bytes(const AttnArgs& a) {
   const int rp = 16 * waves_per_ring(a) * tiles_per_wave(a.d, row_tiles(a));
-  return lds_bytes(a.d, waves_per_ring(a), rp, a.stages, a.B, a.paged);
+  return lds_bytes(a.d, a.rings, rp, a.stages, a.B, a.paged);
 }
 
 int attn_mfma_max_chunk(const AttnArgs& a) { return a.paged ? kMaxChunkPages * a.page_size : (1 << 30); }

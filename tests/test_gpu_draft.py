@@ -96,6 +96,19 @@ def test_row_tile_edges(B, D):
     one_step(shape, w, kv, tok, g, pos, label="row tile edges")
 
 
+@pytest.mark.parametrize("Hq,d,page", [(2, 128, 0), (8, 128, 16), (32, 128, 32), (8, 64, 64), (32, 64, 0)])
+@pytest.mark.parametrize("B,L", [(9, (0, 31, 32, 33, 96, 97, 128, 129, 256)), (40, (64, 1, 700, 127)), (3, (9000, 1, 2047))])
+def test_attention_of_few_rows_at_ring_and_share_edges(B, L, Hq, d, page):
+    # draft steps have two rings, of one wave up to 16 rows per KV head: rings without a tile, with one or several, segments that end inside
+    # a unit or go on with the next, shares of one granule and of many
+    shape = gen.scaled(gen.config(2), D=256, Hq=Hq, Hkv=2, d=d, I=512, V=1000, B=B, ctx=(0, 500), k=2, page_size=page or 16)
+    w, kv, tok, g, pos = setup(shape, 19, std=0.05)
+    pos[:len(L)] = L
+    kv = gen.kv_cache(shape, pos, shape.k + 1, 19, paged=page > 0)
+    w = force_draft_gap(shape, w, kv, tok, g, pos)
+    one_step(shape, w, kv, tok, g, pos, label=f"few rows, d {d} page {page}")
+
+
 @pytest.mark.parametrize("B", [5, 20])
 @pytest.mark.parametrize("D,I", [(256, 8192), (1024, 1024), (128, 16384)])
 def test_sums_over_few_and_many_slots(B, D, I):

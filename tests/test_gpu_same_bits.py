@@ -39,10 +39,22 @@ def step(index, paged=False, seed=3, **kw):
     return digest([out[n] for n in ("hidden_out", "next_tok", "sig_raw", "sig")] + list(gd.cache()))
 
 
+def tree(ctx, B=2):
+    shape = gen.scaled(gen.config(3), D=1024, Hq=8, Hkv=2, d=128, I=1536, V=30000, B=B, ctx=ctx, n_q=16, k=5)
+    parent, rank = gen.level_ordered_tree(shape, 1)
+    w, kv, tok, g, L = draft_inputs(shape, False, 3)
+    got = H.GpuDraft(shape, w, kv).tree(tok, g, L, parent, rank, 3)
+    return digest([got["block_tok"]] + [got[n][c] for n in ("hidden_out", "cand_tok", "cand_logit", "sig_raw", "sig") for c in sorted(got[n])])
+
+
 CASES = {
     # sums over a row by a workgroup per row
     "step of 8 rows": (lambda: step(2, D=1024, Hq=8, Hkv=2, d=128, I=1536, V=30000, B=8, ctx=(0, 60)), "8378dd9450f6341b"),
     "step of 20 rows, paged": (lambda: step(2, paged=True, D=768, Hq=8, Hkv=2, d=64, I=1536, V=30000, B=20, ctx=(0, 60)), "8979e8f368224ea6"),
+    # attention of up to 16 rows per KV head: the order of its tiles, rings and segments, in units of one granule and of many
+    "step of 8 rows, long": (lambda: step(2, paged=True, D=1024, Hq=8, Hkv=2, d=128, I=1536, V=30000, B=8, ctx=(3000, 6000)), "d57e24910efc3518"),
+    "tree": (lambda: tree((0, 60)), "d8b47615b09c91fa"),
+    "tree, long": (lambda: tree((6000, 8000)), "7560e2211ff9c041"),
 }
 
 
