@@ -123,9 +123,11 @@ __global__ __launch_bounds__(512) void k_gemv(const GemvArgs g) {
   // ---- stage the activations, without waiting for the rows' sums of squares: under a norm, x gain is staged and 1 / rms enters
   // behind the dot product.  Four units of a thread are requested together.
   // The pieces of the sums are requested in front of the weights, since loads return in the order of their requests; a wave has one row
-  // (further rows and further pieces, which few shapes have, are added up before the weights are asked for).
+  // (further rows, which few shapes have, are added up before the weights are asked for).  A lane adds its pieces in their
+  // order: those beyond the first NP are fetched behind the weights.
   // (Up to 512 pieces of bf16 models: D = 5120 has that many, a round of three steps 1522 -> 1504 us; fp32 models have 256 at most up to
-  // D = 4096, and 1 % more to do with eight.)
+  // D = 4096, and 1 % more to do with eight.  A piece is a workgroup's, of which D <= 8192 gives 512 on 256 compute units: the loop behind
+  // the weights runs for fp32 models of more than 4096.)
   constexpr int NP = sizeof(T) == 2 ? 8 : 4;
   const float* const pieces = AMODE == 3 ? g.a_ssq + min(m0 + min(wv, MR - 1), g.M - 1) * g.a_nssq : nullptr;
   float sq[NP];
@@ -186,9 +188,7 @@ __global__ __launch_bounds__(512) void k_gemv(const GemvArgs g) {
     stage_store(base);
   }
   stage_load(base);
-  float sq_more = 0.f;
   if constexpr (AMODE == 3) {
-    for (int j = lane + 64 * NP; j < g.a_nssq; j += 64) sq_more += pieces[j];
     for (int m = wv + nwaves; m < MR; m += nwaves) {
       float t = 0.f;
       for (int j = lane; j < g.a_nssq; j += 64) t += g.a_ssq[min(m0 + m, g.M - 1) * g.a_nssq + j];
@@ -237,7 +237,8 @@ __global__ __launch_bounds__(512) void k_gemv(const GemvArgs g) {
     float t = 0.f;
 #pragma unroll
     for (int u = 0; u < NP; ++u) t += lane + 64 * u < g.a_nssq ? sq[u] : 0.f;
-    if (wv < MR) root(wv, t + sq_more);
+    for (int j = lane + 64 * NP; j < g.a_nssq; j += 64) t += pieces[j];
+    if (wv < MR) root(wv, t);
   }
   __syncthreads();
   float rs[MR];

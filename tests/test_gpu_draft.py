@@ -78,6 +78,19 @@ def test_fp32_rows(B, D, I, V, paged):
     one_step(shape, w, kv, tok, g, pos, label="fp32 rows")
 
 
+@pytest.mark.parametrize("dtype,B,D", [("bf16", 1, 5120), ("bf16", 2, 5120), ("f32", 1, 4352), ("f32", 3, 4608)])
+def test_sums_of_squares_in_more_pieces_than_256(dtype, B, D):
+    # the row stream adds a piece per workgroup of the projection in front: 288 to 512 here, of bf16 models all requested together, of fp32
+    # ones those beyond 256 by a loop.  With w_o = 0 no 16-bit value stands between the inputs and the signals, so they are 32-bit sums for
+    # bf16 models too: one piece of 512 left out or taken twice is 1e-3 of 1 / rms.
+    shape = gen.scaled(gen.config(4 if dtype == "bf16" else 0), D=D, Hq=4, Hkv=2, d=128, I=512, V=500, B=B, ctx=(0, 60), k=2)
+    w, kv, tok, g, pos = setup(shape, B, std=0.05)
+    w["w_o"] = np.zeros_like(w["w_o"])
+    w = force_draft_gap(shape, w, kv, tok, g, pos)
+    ref, got, _, _ = one_step(shape, w, kv, tok, g, pos, label="pieces")
+    assert rel_err(got["sig_raw"], ref["sig_raw"]) < TOL["f32"]
+
+
 @pytest.mark.parametrize("B,paged", [(1, False), (2, True), (3, True), (9, False), (16, True)])
 def test_small_bf16_mfma(B, paged):
     shape = gen.scaled(gen.config(2), D=256, Hq=4, Hkv=2, d=64, I=512, V=3000, B=B, ctx=(0, 300), k=2)

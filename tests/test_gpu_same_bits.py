@@ -55,6 +55,11 @@ CASES = {
     "step of 8 rows, long": (lambda: step(2, paged=True, D=1024, Hq=8, Hkv=2, d=128, I=1536, V=30000, B=8, ctx=(3000, 6000)), "d57e24910efc3518"),
     "tree": (lambda: tree((0, 60)), "d8b47615b09c91fa"),
     "tree, long": (lambda: tree((6000, 8000)), "7560e2211ff9c041"),
+    # the pieces of a row's sum of squares on the row stream: up to 512 of bf16 models, more than the 256 that fp32 ones request early
+    "step of 1 row, D = 5120": (lambda: step(4, D=5120, Hq=4, Hkv=2, d=128, I=512, V=300, B=1, ctx=(0, 100)), "086ad13251ca8de7"),
+    "step of 2 rows, D = 5120": (lambda: step(4, D=5120, Hq=4, Hkv=2, d=128, I=512, V=300, B=2, ctx=(0, 100)), "21d5f6032905d504"),
+    "fp32 step of 3 rows, D = 4608": (lambda: step(0, seed=0, D=4608, Hq=4, Hkv=2, d=64, I=512, V=300, B=3, ctx=(0, 100)), "b4fffa8f16edb591"),
+    "fp32 step of 4 rows, D = 4864": (lambda: step(0, seed=4, D=4864, Hq=4, Hkv=2, d=128, I=512, V=300, B=4, ctx=(0, 100)), "e561b07df3e84b22"),
 }
 
 
