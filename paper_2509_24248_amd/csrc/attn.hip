@@ -693,8 +693,14 @@ static int unit_pad(const AttnArgs& a) { return a.d == 64 ? 3 : 2; }
 // sequences, 44 rows, 1200 34.0 / 33.0, 4800 54.7 / 50.1.  64-wide heads, granules of half the bytes, 32 rows: 1 sequence, 1200
 // 12.6 / 14.2, 2400 15.7 / 17.8, 4800 22.2 / 22.1; 64 sequences, 2400 28.9 / 26.0; 64 rows: 8 sequences, 4500 27.7 / 26.6 (there the
 // second workgroup's waves are wanted for the arithmetic as well).
+// (The figures of 4 rows are a draft step's.)  Verifications of up to 16 rows of 128-wide heads have one workgroup per compute unit at
+// any length: from the line on all 256 take part, below it the fewest with the same largest share, whose number suits units of one
+// length.  The fewest instead of 256, 3 to 12 sequences of equal and of unequal lengths, 8 KV heads, 8 rows: T = 1630-1850 -1 %, 2300
+// -1 %, 2400 +0.6 %, 3000 -0.4 %, 4300 +0.8 %, 6800 -0.2 %; 6 of 3000 entries (T = 2256) 19.9 -> 19.0 us, 16 rows, paged, 23.1 -> 20.8.
+constexpr int kAllFrom = 2400;
 static int wide_from(const AttnArgs& a) {
   if (!a.use_mfma || static_cast<int64_t>(a.B) * a.Hkv >= kAttnSpread) return 0;
+  if (a.rings > 2 && attn_mfma_per_cu(a) == 1) return kAllFrom;
   return 1000 + std::min(a.G * a.n_q * (a.d == 64 ? 80 : 50), 2600);
 }
 
@@ -708,12 +714,12 @@ static bool plan_as(AttnArgs& a, int num_cus, int use_mfma, int pad) {
   a.G = a.Hq / a.Hkv;
   a.g_inv = (65536 + a.G - 1) / a.G;
   a.pad = pad;
-  a.wide_from = wide_from(a);
   if (a.B > kAttnMaxSeqs || a.l_max < a.n_blk) return false;
   const int64_t units = static_cast<int64_t>(a.B) * a.Hkv;
   const int64_t gmax = (a.l_max + kAttnGran - 1) / kAttnGran;      // granules of the longest possible unit
   if (units * (gmax + pad) >= (1ll << 30)) return false;
   a.rings = a.use_mfma ? attn_mfma_rings(a) : 0;
+  a.wide_from = wide_from(a);
   a.stages = a.use_mfma ? attn_mfma_stages(a) : 0;
   const int64_t resident = static_cast<int64_t>(num_cus) * (a.use_mfma ? attn_mfma_per_cu(a) : 1);
   const AttnLine line = attn_sched_line(static_cast<int>(a.B * gmax), a.B, a.Hkv, pad, a.wide_from, a.use_mfma == kOnePart, static_cast<int>(resident));

@@ -152,11 +152,12 @@ def test_one_long_sequence_among_short_ones(dtype, d, n_q):
 
 @pytest.mark.parametrize("d,n_q,L,page", [(128, 3, (2045,), 0), (128, 3, (2046,), 0), (128, 3, (5000,), 16), (128, 3, (9000,), 0), (128, 3, (9300,), 16),
                                           (128, 9, (0, 2000, 63, 64), 16), (128, 9, (1, 9000, 700), 0), (64, 3, (2046,), 32), (64, 3, (11000,), 0),
-                                          (64, 9, (0, 9000, 700), 16), (128, 1, (40,) * 70 + (6000,), 16)])
+                                          (64, 9, (0, 9000, 700), 16), (128, 1, (40,) * 70 + (6000,), 16), (128, 4, (3000,) * 6, 16), (128, 2, (9650, 9400), 16), (128, 2, (9650, 9500), 0),
+                                          (128, 20, (8100, 7700), 0), (128, 20, (8100, 7800), 16)])
 def test_shares_at_the_edges_of_the_work_split(d, n_q, L, page):
     # 8 KV heads: 256 granules of 64 keys and just above (a workgroup per granule; one per compute unit, units padded), just below and
-    # above the point from which more workgroups than compute units take part, units shorter than the padding beside long ones,
-    # and more sequences than a wave has lanes.  q.k is scaled up so that single keys decide and a lost or doubled tile shows.
+    # above the point from which more workgroups than compute units take part (one per compute unit up to 16 rows: all of them), units
+    # shorter than the padding beside long ones, and more sequences than a wave has lanes.  q.k is scaled up so that single keys decide and a lost or doubled tile shows.
     shape = gen.scaled(gen.config(1), B=len(L), Hq=8, Hkv=8, d=d, n_q=n_q, k=max(n_q - 1, 1), ctx=(0, 1), page_size=page or 16)
     L = np.array(L, np.int32)
     kv = gen.kv_cache(shape, L, n_q, 13, paged=page > 0)
