@@ -193,7 +193,6 @@ struct AttnArgs {
   int n_blk;                 // block entries stored after the context (normally n_q; tree drafting:
                              // every node written so far, of which n_q are this call's queries)
   int mask_stride;           // mask words between two sequences' rows (n_q; 0 = all sequences share)
-  int draft;                 // the call goes on to rank logits that follow from the output (a draft step or tree level)
   float scale;
   void* out;                 // [B, n_q, Hq, d] in dtype
   int wgrid;                 // workgroups of the split kernel; the keys of all (sequence, KV head) units
@@ -204,8 +203,11 @@ struct AttnArgs {
                              // unit, [B*Hkv][2]
   int64_t n_pages;           // paged: pages in the pool (page ids are forced into it)
   int* status;               // device error word or nullptr: first out-of-range length / page id seen
-  int rings, stages;         // matrix-core kernel: tile rings of a workgroup, slots of a ring (attn_plan)
+  int stages;                // matrix-core kernel: slots per tile ring (attn_plan)
   int use_mfma;              // 0, or matrix-core kernel (bf16; its maxima are in log2 units): kOnePart or kTwoPart
+  // (read by the host only, so that the kernels' arguments keep their lines)
+  int draft;                 // the call goes on to rank logits that follow from the output (a draft step or tree level)
+  int rings;                 // matrix-core kernel: tile rings of a workgroup (attn_plan)
 };
 constexpr int kOnePart = 1, kTwoPart = 2;       // parts of bf16 that the matrix-core kernel has its probabilities in
 bool attn_mfma_supported(const AttnArgs& a);
