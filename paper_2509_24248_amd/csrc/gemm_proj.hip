@@ -328,23 +328,27 @@ __device__ __forceinline__ ProjSlots proj_slots(const ProjSum& p, int m, int n) 
   return r;
 }
 
-// Sum of the slots, in their order, of VEC columns.  The first U are requested by `request`, so that a caller has those of several
-// sums on their way at once; more are fetched when they are added.
-template <int U, typename VEC>
+// Sum of the slots, in their order, of VEC columns.  The first kSlotsEarly are requested by `request` (the last one again where there are
+// fewer), so that a caller has those of several sums on their way at once; more are fetched when they are added.  (One sum's eight after the
+// other's, and the owners from fp64, traced / this way: D = 4096, I = 12288, 8 rows, the three norms 5.5-5.8 / 5.2 us, 64 rows 7.2-7.3 /
+// 6.2-6.6 and the gate 8.2 / 7.3; D = 5120, 16 rows 6.2-6.6 / 5.1-5.7.  Kernels for two and four slots where a shape has no
+// more: 353.0 us a step of 8 rows, 353.2 with one form; 64 rows 447 and 448.)
+constexpr int kSlotsEarly = 8;
+template <typename VEC>
 struct ProjTerms {
-  VEC v[U];
+  VEC v[kSlotsEarly];
   __device__ __forceinline__ void request(const ProjSlots& s, int off = 0) {
 #pragma unroll
-    for (int u = 0; u < U; ++u) v[u] = *reinterpret_cast<const VEC*>(s.src + off + static_cast<size_t>(min(u, s.n - 1)) * s.step);
+    for (int u = 0; u < kSlotsEarly; ++u) v[u] = *reinterpret_cast<const VEC*>(s.src + off + static_cast<size_t>(min(u, s.n - 1)) * s.step);
   }
   static __device__ __forceinline__ void add(float4& a, const float4& b) { a.x += b.x; a.y += b.y; a.z += b.z; a.w += b.w; }
   static __device__ __forceinline__ void add(float& a, const float& b) { a += b; }
   __device__ __forceinline__ VEC sum(const ProjSlots& s, int off = 0) const {
     VEC t = v[0];
 #pragma unroll
-    for (int u = 1; u < U; ++u)
+    for (int u = 1; u < kSlotsEarly; ++u)
       if (u < s.n) add(t, v[u]);
-    for (int i = U; i < s.n; ++i) add(t, *reinterpret_cast<const VEC*>(s.src + off + static_cast<size_t>(i) * s.step));
+    for (int i = kSlotsEarly; i < s.n; ++i) add(t, *reinterpret_cast<const VEC*>(s.src + off + static_cast<size_t>(i) * s.step));
     return t;
   }
 };
@@ -366,7 +370,6 @@ constexpr int kRowIters = 2;        // float4 per thread: rows up to 8192 wide
 
 // One workgroup per row: sums (+ residual) -> x (fp32), optionally the storage type, and the RMSNorm of the
 // row as the next projection's operand.
-template <int U>
 __global__ __launch_bounds__(kRowThreads) void k_proj_norm(const ProjSum ps, int N, const float* __restrict__ residual, const bf16_t* __restrict__ gain,
                                                            float eps, float* __restrict__ out_x, bf16_t* __restrict__ out_store,
                                                            char* __restrict__ packed, int NT) {
@@ -376,7 +379,7 @@ __global__ __launch_bounds__(kRowThreads) void k_proj_norm(const ProjSum ps, int
   float4 v[kRowIters], r[kRowIters];
   uint2 gn[kRowIters];
   ProjSlots slots[kRowIters];
-  ProjTerms<U, float4> terms[kRowIters];
+  ProjTerms<float4> terms[kRowIters];
 #pragma unroll
   for (int it = 0; it < kRowIters; ++it) {
     const int n = (threadIdx.x + it * kRowThreads) * 4;
@@ -424,12 +427,11 @@ __global__ __launch_bounds__(kRowThreads) void k_proj_norm(const ProjSum ps, int
 }
 
 // silu(gate) * up of the concatenated gate|up projection -> operand of the down projection
-template <int U>
 __global__ __launch_bounds__(256) void k_proj_silu(const ProjSum ps, int I, char* __restrict__ packed, int NT) {
   const int m = blockIdx.y, k = (blockIdx.x * 256 + threadIdx.x) * 4;
   if (k >= I) return;
   const ProjSlots sg = proj_slots(ps, m, k), su = proj_slots(ps, m, I + k);
-  ProjTerms<U, float4> tg, tu;
+  ProjTerms<float4> tg, tu;
   tg.request(sg);
   tu.request(su);
   const float4 gt = tg.sum(sg), up = tu.sum(su);
@@ -438,7 +440,6 @@ __global__ __launch_bounds__(256) void k_proj_silu(const ProjSum ps, int I, char
 }
 
 // q | k | v heads: rotary embedding (pairs c, c + d/2; v as it is), q rows and cache entries.  A thread takes one pair.
-template <int U>
 __global__ __launch_bounds__(256) void k_proj_rope(const ProjSum ps, const RopeArgs ra) {
   const int half = ra.d >> 1;
   const int idx = blockIdx.x * 256 + threadIdx.x;
@@ -447,7 +448,7 @@ __global__ __launch_bounds__(256) void k_proj_rope(const ProjSum ps, const RopeA
   if (hh >= ra.Hq + 2 * ra.Hkv) return;
   // (a head of at most 128 columns lies in one group)
   const ProjSlots sl = proj_slots(ps, m, hh * ra.d + c);
-  ProjTerms<U, float> t1, t2;
+  ProjTerms<float> t1, t2;
   t1.request(sl);
   t2.request(sl, half);
   const int b = m / ra.W;
@@ -511,12 +512,6 @@ ProjSum sum_of(const ProjArgs& g) {
   return p;
 }
 
-// Slots that a group's sums can lie in, at most: the kernels behind a projection request that many at once, 2, 4 or 8 (more in
-// turn), for all the sums of a thread.  (Eight whatever the shape, one sum after the other, and the owners from fp64: the gate and up sums of
-// D = 4096, I = 12288, which lie in two or three, 8 / 64 rows 3.0 / 4.25 us in the kernel, 1.6 / 2.7 now; the norms 3.5 / 4.2
-// there and 2.6-2.9 / 3.0-3.5 now.)
-int most_slots(const ProjSum& p) { return static_cast<int>(static_cast<int64_t>(p.KB - 1) * p.W / p.T) + 2; }
-
 }  // namespace
 
 bool proj_supported(int M, int N, int K) { return M >= 1 && M <= 64 && N % 128 == 0 && N >= 128 && K % 128 == 0 && K >= 128; }
@@ -548,40 +543,23 @@ hipError_t launch_proj(const ProjArgs& g, hipStream_t s) {
   }
 }
 
-template <int U>
-static void start_norm(const ProjSum& p, const ProjArgs& g, const float* residual, const void* gain, float eps, float* out_x, void* out_store, void* packed, hipStream_t s) {
-  hipLaunchKernelGGL(k_proj_norm<U>, dim3(g.M), dim3(kRowThreads), 0, s, p, g.N, residual, static_cast<const bf16_t*>(gain), eps, out_x,
-                     static_cast<bf16_t*>(out_store), static_cast<char*>(packed), packed_tiles(g.M, 2));
-}
-
 hipError_t launch_proj_norm(const ProjArgs& g, const float* residual, const void* gain, float eps, float* out_x, void* out_store, void* packed,
                             hipStream_t s) {
   if (g.N > kRowThreads * kRowIters * 4) return hipErrorInvalidValue;
-  const ProjSum p = sum_of(g);
-  const int most = most_slots(p);
-  (most <= 2 ? start_norm<2> : most <= 4 ? start_norm<4> : start_norm<8>)(p, g, residual, gain, eps, out_x, out_store, packed, s);
+  hipLaunchKernelGGL(k_proj_norm, dim3(g.M), dim3(kRowThreads), 0, s, sum_of(g), g.N, residual, static_cast<const bf16_t*>(gain), eps, out_x,
+                     static_cast<bf16_t*>(out_store), static_cast<char*>(packed), packed_tiles(g.M, 2));
   return hipGetLastError();
 }
 
 hipError_t launch_proj_silu(const ProjArgs& g, void* packed, hipStream_t s) {
   const int I = g.N / 2;
-  const ProjSum p = sum_of(g);
-  const dim3 grid((I / 4 + 255) / 256, g.M);
-  const int most = most_slots(p), NT = packed_tiles(g.M, 2);
-  if (most <= 2) hipLaunchKernelGGL(k_proj_silu<2>, grid, dim3(256), 0, s, p, I, static_cast<char*>(packed), NT);
-  else if (most <= 4) hipLaunchKernelGGL(k_proj_silu<4>, grid, dim3(256), 0, s, p, I, static_cast<char*>(packed), NT);
-  else hipLaunchKernelGGL(k_proj_silu<8>, grid, dim3(256), 0, s, p, I, static_cast<char*>(packed), NT);
+  hipLaunchKernelGGL(k_proj_silu, dim3((I / 4 + 255) / 256, g.M), dim3(256), 0, s, sum_of(g), I, static_cast<char*>(packed), packed_tiles(g.M, 2));
   return hipGetLastError();
 }
 
 hipError_t launch_proj_rope(const ProjArgs& g, const RopeArgs& ra, hipStream_t s) {
   const int items = (ra.Hq + 2 * ra.Hkv) * (ra.d >> 1);
-  const ProjSum p = sum_of(g);
-  const dim3 grid((items + 255) / 256, g.M);
-  const int most = most_slots(p);
-  if (most <= 2) hipLaunchKernelGGL(k_proj_rope<2>, grid, dim3(256), 0, s, p, ra);
-  else if (most <= 4) hipLaunchKernelGGL(k_proj_rope<4>, grid, dim3(256), 0, s, p, ra);
-  else hipLaunchKernelGGL(k_proj_rope<8>, grid, dim3(256), 0, s, p, ra);
+  hipLaunchKernelGGL(k_proj_rope, dim3((items + 255) / 256, g.M), dim3(256), 0, s, sum_of(g), ra);
   return hipGetLastError();
 }
 
