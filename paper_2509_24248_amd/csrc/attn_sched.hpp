@@ -145,20 +145,15 @@ __host__ __device__ __forceinline__ AttnLine attn_sched_line(int gran, int B, in
   return l;
 }
 
-// First granule of workgroup w, w T / W rounded down, and the workgroup that has granule p.  (An even deal: with the first T % W
-// workgroups one granule larger, 4 of which fit a unit of 67 granules evenly would have 68.  The products of the formula need 64
-// bits, whose division is 150 dependent instructions, fetched for a single use; w r is less than kAttnMaxGrid squared, the
-// quotient from floats off by one at most, and so is the owner, before the comparisons.)
+// First granule of workgroup w, w T / W rounded down.  (An even deal: with the first T % W workgroups one granule larger, 4 of which
+// fit a unit of 67 granules evenly would have 68.  The products of the formula need 64 bits, whose division is 150 dependent
+// instructions, fetched for a single use; w r is less than kAttnMaxGrid squared, the quotient from floats off by one at most before the comparisons.)
 __host__ __device__ __forceinline__ int attn_sched_lo(const AttnLine& l, int w) {
   const int x = w * l.r;
   int k = attn_sched_div(x, l.W);
   if (k * l.W > x) --k;
   if ((k + 1) * l.W <= x) ++k;
   return w * l.q + k;
-}
-__host__ __device__ __forceinline__ int attn_sched_owner(const AttnLine& l, int p) {
-  const int w = static_cast<int>(static_cast<float>(p + 1) * (static_cast<float>(l.W) * attn_sched_rcp(l.T)) + 0.25f);
-  return attn_sched_lo(l, w) <= p ? w : w - 1;
 }
 
 // The line of a launch on the device.
@@ -174,20 +169,42 @@ struct AttnSeg {
   int next;      // granule on the line where the next segment starts
 };
 
-// The segment that starts at granule x of the line and ends at the unit's end or at `hi` (no keys where that is still
-// padding).  Uniform over the workgroup.  `lanes`: the table in the lanes will do (see AttnTable).
+__host__ __device__ __forceinline__ int attn_sched_uniform(int x) {
+#ifdef __HIP_DEVICE_COMPILE__
+  return __builtin_amdgcn_readfirstlane(x);
+#else
+  return x;
+#endif
+}
+
+// The segment that starts at granule x of the line, which is one of sequence b's (`first` granules in front of the sequence, n of it
+// in each of its Hkv units, L entries in front of n_blk of the block), and ends at the unit's end or at `hi`; no keys where that is
+// still padding.
+__host__ __device__ __forceinline__ AttnSeg attn_sched_cut(int Hkv, int n_blk, int pad, int b, int first, int n, int L, int x, int hi) {
+  AttnSeg s;
+  s.b = b;
+  s.L = L;
+  const int rel = x - Hkv * (first + pad * b);
+  const int g = rel < 1 << 21 ? attn_sched_div(rel, n + pad) : static_cast<int>(static_cast<uint32_t>(rel) / static_cast<uint32_t>(n + pad));
+  s.g = min(attn_sched_uniform(g), Hkv - 1);
+  const int at = min(rel - s.g * (n + pad), n + pad - 1);   // granule of the unit, padding first
+  const int end = min(at + (hi - x), n + pad);
+  s.s0 = max(at - pad, 0) * kAttnGran;
+  s.s1 = min(L + n_blk, (end - pad) * kAttnGran);
+  s.next = x + max(end - at, 1);                // (the minima above cannot bind while the table is that of these lengths)
+  return s;
+}
+
+// The segment from granule x on, on the device.  Uniform over the workgroup.  `lanes`: the table in the lanes will do (see AttnTable).
 __device__ __forceinline__ AttnSeg attn_sched_segment(const AttnArgs& a, const AttnTable& t, bool lanes, int pad, int x, int hi) {
   const int lane = threadIdx.x & 63;
-  AttnSeg s;
-  int first, n;                                 // granules in front of the sequence, and of it
+  int b = 0, first, n, L;
   if (lanes && a.B <= 64) {
-    const int b = min(static_cast<int>(__popcll(__builtin_amdgcn_ballot_w64(lane < a.B && a.Hkv * (t.upto + pad * (lane + 1)) <= x))), a.B - 1);
+    b = min(static_cast<int>(__popcll(__builtin_amdgcn_ballot_w64(lane < a.B && a.Hkv * (t.upto + pad * (lane + 1)) <= x))), a.B - 1);
     first = b > 0 ? __builtin_amdgcn_readlane(t.upto, b - 1) : 0;
     n = __builtin_amdgcn_readlane(t.upto, b) - first;
-    s.L = __builtin_amdgcn_readlane(t.len, b) - a.n_blk;
-    s.b = b;
+    L = __builtin_amdgcn_readlane(t.len, b) - a.n_blk;
   } else {
-    int b = 0;
     for (int c = 0; c < a.B; c += 64) {
       const int i = c + lane;
       const bool before = i < a.B && a.Hkv * (t.S[i + 1] + pad * (i + 1)) <= x;
@@ -196,18 +213,9 @@ __device__ __forceinline__ AttnSeg attn_sched_segment(const AttnArgs& a, const A
     b = __builtin_amdgcn_readfirstlane(min(b, a.B - 1));
     first = __builtin_amdgcn_readfirstlane(t.S[b]);
     n = __builtin_amdgcn_readfirstlane(t.S[b + 1]) - first;
-    s.L = __builtin_amdgcn_readfirstlane(n * kAttnGran - attn_sched_short(a, t.S)[b] - a.n_blk);
-    s.b = b;
+    L = __builtin_amdgcn_readfirstlane(n * kAttnGran - attn_sched_short(a, t.S)[b] - a.n_blk);
   }
-  const int rel = x - a.Hkv * (first + pad * s.b);
-  const int g = rel < 1 << 21 ? attn_sched_div(rel, n + pad) : static_cast<int>(static_cast<uint32_t>(rel) / static_cast<uint32_t>(n + pad));
-  s.g = min(__builtin_amdgcn_readfirstlane(g), a.Hkv - 1);
-  const int at = min(rel - s.g * (n + pad), n + pad - 1);   // granule of the unit, padding first
-  const int end = min(at + (hi - x), n + pad);
-  s.s0 = max(at - pad, 0) * kAttnGran;
-  s.s1 = min(s.L + a.n_blk, (end - pad) * kAttnGran);
-  s.next = x + max(end - at, 1);                // (the minima above cannot bind while the table is that of these lengths)
-  return s;
+  return attn_sched_cut(a.Hkv, a.n_blk, pad, b, first, n, L, x, hi);
 }
 
 // The first segment with keys from granule x of a workgroup's share on; s1 <= s0 if there is none.

@@ -20,7 +20,7 @@ static void expect(bool ok, const char* what, long a, long b, long c, long d) {
 }
 static long below(long n) { return ((static_cast<long>(rand()) << 20) ^ rand()) % n; }
 
-// shares and owners of a line of T granules over W workgroups
+// shares of a line of T granules over W workgroups
 static void shares(const AttnLine& l) {
   const long T = l.T, W = l.W;
   expect(T == static_cast<long>(l.q) * W + l.r && l.q >= 1 && l.r >= 0 && l.r < W, "quotient", T, W, l.q, l.r);
@@ -29,11 +29,39 @@ static void shares(const AttnLine& l) {
     const long w = i < 3 ? i % W : i < 6 ? W - 1 - i % 3 % W : below(W);
     const long lo = w * T / W, hi = (w + 1) * T / W;
     expect(attn_sched_lo(l, w) == lo && attn_sched_lo(l, w + 1) == hi, "share", T, W, w, attn_sched_lo(l, w));
-    for (long p : {lo, hi - 1, below(T)}) {
-      const long o = attn_sched_owner(l, p);
-      expect(o >= 0 && o < W && o * T / W <= p && p < (o + 1) * T / W, "owner", T, W, p, o);
+  }
+}
+
+// The segments of all workgroups of a launch over `len` entries (the block's n_blk included) per sequence, as the split kernels walk them:
+// every unit's keys are taken once and in order, one workgroup finds the first of them and one the last (what the merging kernel is
+// told), and those between take the slots between.
+static void segments(const int* len, int B, int Hkv, int n_blk, int pad, int wide_from, int spread, int wgrid) {
+  static int S[1025], keys[1024 * 64], first[1024 * 64], last[1024 * 64], seen[1024 * 64];
+  S[0] = 0;
+  for (int b = 0; b < B; ++b) S[b + 1] = S[b] + (len[b] + kAttnGran - 1) / kAttnGran;
+  const AttnLine l = attn_sched_line(S[B], B, Hkv, pad, wide_from, spread, wgrid);
+  for (int u = 0; u < B * Hkv; ++u) { keys[u] = seen[u] = 0; first[u] = last[u] = -1; }
+  long slot = -1;
+  for (int w = 0; w < l.W; ++w) {
+    const int hi = attn_sched_lo(l, w + 1);
+    for (int x = attn_sched_lo(l, w), b = 0; x < hi;) {
+      while (b < B - 1 && static_cast<long>(Hkv) * (S[b + 1] + l.pad * (b + 1)) <= x) ++b;
+      const AttnSeg s = attn_sched_cut(Hkv, n_blk, l.pad, b, S[b], S[b + 1] - S[b], len[b] - n_blk, x, hi);
+      expect(s.next > x && s.next <= hi, "next", x, hi, s.next, l.W);
+      x = s.next;
+      if (s.s1 <= s.s0) continue;
+      const int u = s.b * Hkv + s.g;
+      expect(s.g >= 0 && s.g < Hkv && s.s0 == keys[u] && s.s1 <= len[b], "keys", u, s.s0, s.s1, keys[u]);
+      keys[u] = s.s1;
+      if (s.s0 == 0) { expect(first[u] < 0, "one first", u, first[u], w, 0); first[u] = w; }
+      if (s.s1 == s.L + n_blk) { expect(last[u] < 0, "one last", u, last[u], w, 0); last[u] = w; }
+      expect(first[u] >= 0 && w == first[u] + seen[u], "consecutive", u, first[u], seen[u], w);
+      ++seen[u];
+      expect(w + u > slot && w + u < l.W + B * Hkv, "slot", w, u, slot, l.W);
+      slot = w + u;
     }
   }
+  for (int u = 0; u < B * Hkv; ++u) expect(keys[u] == len[u / Hkv] && last[u] == first[u] + seen[u] - 1, "whole unit", u, keys[u], len[u / Hkv], last[u]);
 }
 
 int main() {
@@ -53,9 +81,18 @@ int main() {
     const long n = gran / B + l.pad, units = static_cast<long>(B) * Hkv;
     if (gran % B == 0 && bare > kAttnSpread && bare < wide_from && l.W % units == 0)
       for (long u = 0; u < units; ++u) {
-        const int w = attn_sched_owner(l, u * n);
+        const int w = (u * n * l.W + T - 1) / T;
         expect(attn_sched_lo(l, w) == u * n, "unit start", T, l.W, u, w);
       }
+  }
+  // the segments of launches: few and many sequences, empty, equal and very unequal ones, with and without padding
+  static int len[1024];
+  for (int k = 0; k < 6000; ++k) {
+    const int B = k % 50 == 0 ? 1 + below(1024) : 1 + below(k % 2 ? 8 : 70), Hkv = 1 + below(k % 10 ? 8 : 64), n_blk = 1 + below(64);
+    const int most = k % 3 == 0 ? 100 : k % 3 == 1 ? 3000 : 40000, same = below(most);
+    for (int b = 0; b < B; ++b) len[b] = n_blk + (k % 4 == 0 ? same : below(5) ? below(most) : 0);
+    if (k % 500 == 7 && Hkv <= 8) len[below(B)] = n_blk + (1 << 29) + below(100000);      // (more granules than the divisions by floats take)
+    segments(len, B, Hkv, n_blk, below(4), static_cast<long>(B) * Hkv >= kAttnSpread ? 0 : k % 2 ? 2400 : 1000 + below(2601), k % 7 == 1, k % 11 == 0 ? kAttnMaxGrid : k % 2 ? 256 : 512);
   }
   // any line, to the limits
   for (long W = 1; W <= kAttnMaxGrid; W += W < 700 ? 1 : 37)
@@ -71,7 +108,7 @@ int main() {
 
 
 @pytest.mark.skipif(not shutil.which(HIPCC), reason="no hipcc")
-def test_shares_and_owners_of_the_work_split(tmp_path):
+def test_shares_and_segments_of_the_work_split(tmp_path):
     src = tmp_path / "sched.hip"
     src.write_text(PROGRAM)
     exe = tmp_path / "sched"
