@@ -203,12 +203,12 @@ struct AttnArgs {
                              // unit, [B*Hkv][2]
   int64_t n_pages;           // paged: pages in the pool (page ids are forced into it)
   int* status;               // device error word or nullptr: first out-of-range length / page id seen
-  int stages;                // matrix-core kernel: slots per tile ring (attn_plan)
+  // for the host; in bytes, so that the arguments of the kernels are three 64-byte lines
+  int8_t rings, stages;      // matrix-core kernel: tile rings of a workgroup, slots of a ring (attn_plan)
+  bool draft;                // the call goes on to rank logits that follow from the output (a draft step or tree level)
   int use_mfma;              // 0, or matrix-core kernel (bf16; its maxima are in log2 units): kOnePart or kTwoPart
-  // (read by the host only, so that the kernels' arguments keep their lines)
-  int draft;                 // the call goes on to rank logits that follow from the output (a draft step or tree level)
-  int rings;                 // matrix-core kernel: tile rings of a workgroup (attn_plan)
 };
+static_assert(sizeof(AttnArgs) <= 192, "a fourth line costs every launch of the merging kernels 40 ns");
 constexpr int kOnePart = 1, kTwoPart = 2;       // parts of bf16 that the matrix-core kernel has its probabilities in
 bool attn_mfma_supported(const AttnArgs& a);
 size_t attn_mfma_lds_bytes(const AttnArgs& a);  // dynamic LDS of the matrix-core kernel as planned
