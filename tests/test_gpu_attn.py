@@ -139,13 +139,16 @@ def test_probabilities_of_few_wide_rows_have_two_parts(n_q, L, paged):
     assert err < 1.05 * rounding
 
 
-@pytest.mark.parametrize("dtype,d,n_q", [("bf16", 64, 3), ("bf16", 128, 3), ("f32", 64, 3), ("bf16", 64, 5), ("bf16", 128, 5)])
-def test_one_long_sequence_among_short_ones(dtype, d, n_q):
-    # one unit with more segments than a wave has lanes among many of one or two: merged by a wave per output row (fp32, whose
-    # launch has 256 workgroups, and five queries on 512) and by a workgroup per row (three queries on 512)
-    shape = gen.scaled(gen.config(1), dtype=dtype, B=70, Hq=4, Hkv=2, d=d, n_q=n_q, ctx=(0, 40))
+@pytest.mark.parametrize("dtype,d,n_q,B,long", [("bf16", 64, 3, 70, 9000), ("bf16", 128, 3, 70, 9000), ("f32", 64, 3, 70, 9000), ("bf16", 64, 5, 70, 9000),
+                                               ("bf16", 128, 5, 70, 9000), ("bf16", 128, 3, 50, 20000), ("bf16", 128, 9, 40, 9000), ("f32", 128, 3, 50, 20000)])
+def test_one_long_sequence_among_short_ones(dtype, d, n_q, B, long):
+    # one unit with more segments than a wave has lanes among many of one or two.  Merged by a wave per output row from 256 rows per segment
+    # of an average unit on: rows x units above 256 times the launch's workgroups, which are 256 for fp32 and for 128-wide heads of up to
+    # 16 rows per KV head, 512 else.  So a workgroup per row has the 64-wide heads of three queries (840 x 140 against 256 x 512) and the
+    # 128-wide ones of fifty and forty sequences (600 x 100 against 256 x 256; 1440 x 80 of 18 rows per KV head against 256 x 512).
+    shape = gen.scaled(gen.config(1), dtype=dtype, B=B, Hq=4, Hkv=2, d=d, n_q=n_q, ctx=(0, 40))
     L = gen.context_lengths(shape, 3)
-    L[33] = 9000
+    L[33] = long
     kv = gen.kv_cache(shape, L, shape.n_q, 3, paged=True)
     check(shape, L, kv, gen.queries(shape, 3), None, label="one long sequence")
 
