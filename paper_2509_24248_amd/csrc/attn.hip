@@ -481,7 +481,7 @@ __device__ __forceinline__ float seg_sum(float w, float l) { return w != 0.f || 
 
 // Merge the segments of one (sequence, query, head): exact log-sum-exp combination.  One workgroup per output row; groups
 // of lanes take every NG-th segment of one float4 column and are added in a fixed order.
-// Latency is all there is (a row reads 17 KB at 33 segments): the length table, the workgroups' range, one round to memory, a
+// Latency is all there is (a row reads 17 KB at 33 segments): the two words with the unit's workgroups, one round to memory, a
 // meeting of the groups.  The first kEarly partial outputs of every group are requested together with the (max, sum) pairs,
 // every wave works out all weights for itself (lane s holds those of segments s, s + 64, ..), and the maximum and the sum over
 // the lanes are taken without LDS: no barrier before the one at which the groups meet.  Segments beyond 64 in rounds.

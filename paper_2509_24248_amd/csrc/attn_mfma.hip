@@ -44,13 +44,13 @@ namespace {
 // 500-2500, 16 rows 14.8 -> 14.1, 8 of 4000-8000, 12 rows 21.0 -> 19.7 (two workgroups of two-slot rings; one of four slots 20.6).
 // Draft steps and tree levels (AttnArgs::draft) keep two rings whatever the rows: four add the keys in another order, and a call that
 // ranks its own logits then names other tokens where two of them are closer than that rounding (2 of 48 candidates of a level of 4 x 4
-// nodes, V = 151936).  That costs a round of six steps, D = 2560, 1 % of its time.
+// nodes, V = 151936).  That costs a round of six steps, D = 2560, 0.3 % of its time (1199 -> 1203 us).
 constexpr int kFewRings = 4;
 constexpr int slot_bytes(int hd) { return 128 * hd; }   // one ring slot: 32 K rows then 32 V rows of hd bf16 values
-// From kBigFrom waves per ring (more than 48 query rows per KV head) one workgroup is resident per
+// From big_from waves per ring (128-wide heads: more than 48 query rows per KV head) one workgroup is resident per
 // compute unit (its eight to sixteen waves need more than the 96-128 registers per lane that two
-// workgroups would leave them) and its rings take kBigStages slots; below that, two workgroups of
-// two-slot rings.  Measured at 64 / 72 rows per KV head (8B-like tree block / 32B-like chain block):
+// workgroups would leave them) and its two rings take four slots; below that, two workgroups of two
+// two-slot rings (or one of four such rings, see above).  Measured at 64 / 72 rows per KV head (8B-like tree block / 32B-like chain block):
 // two resident workgroups with spills 41.6 us against 31.3 us with one; two, three and four slots
 // within 3 % of each other at 72 rows.
 // With 64-wide heads the output accumulators and the slots are half as large: two workgroups fit up to
@@ -72,8 +72,7 @@ constexpr int v_ahead(int hd, int nr) { return hd == 64 || nr >= big_from(hd) ? 
 // Whole calls, contiguous / paged: 16 sequences of 4000-16000 entries, 64 query heads, 104 rows 182 / 192 -> 152 / 161 us,
 // 128 rows 164 / 175 -> 166 / 174; 32 query heads, 8 sequences of 2000-8000, 128 rows 64 / 69 -> 58 / 60; 1 of 20000, 100
 // rows 43.5 / 44 -> 35.5 / 36; a 16-node tree over 4 sequences of 300-900, 128 rows 35.5 -> 31.8.  With fewer rows nothing
-// spills and one tile per wave is faster (measured at 72 rows).  Paged caches at 33..48 rows keep 16 bytes a lane in scratch
-// memory: without the last slot's early request they would not, at the same time (40 rows 53.8 / 53.5 us).
+// spills and one tile per wave is faster (measured at 72 rows).
 constexpr int kPairFrom = 7;
 constexpr int tiles_per_wave(int hd, int tiles) { return hd == 128 && tiles >= kPairFrom ? 2 : 1; }
 constexpr int kMaxChunkPages = 2048;   // page ids of one chunk kept in LDS (8 KB)
@@ -130,8 +129,8 @@ __global__ __launch_bounds__(64 * NK * NR, min_waves_per_simd(HD, NR, NK)) void 
   // (2.05e-3 -> 2.19e-3, 4096 entries), so they have none.
   constexpr float kSlack = kSplitP ? 8.f : 0.f;
   constexpr int kKS = HD / 32, kDT = HD / 16;   // k steps of K Q^T, 16-wide column tiles of the output
-  // LDS: [ring 0: S slots][ring 1: S slots] (free ones hold ring 1's sums for the merge), ring 1's (max, sum) per row, the
-  // schedule's prefix table, the page ids of the segment
+  // LDS: the rings' slots, S each (for the merge of two rings free ones hold ring 1's sums, for that of four each ring's its own), (max, sum)
+  // per row, of ring 1 or of each of the four, the schedule's prefix table, the page ids of the segment
   constexpr int kFront = NK * S * kSlot;
   extern __shared__ uint4 smem4[];
   char* smem = reinterpret_cast<char*>(smem4);
