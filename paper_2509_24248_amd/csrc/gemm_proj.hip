@@ -466,8 +466,9 @@ __global__ __launch_bounds__(256) void k_proj_rope(const ProjSum ps, const RopeA
   }
   float x1 = t1.sum(sl), x2 = t2.sum(sl, half);
   if (turn) {
-    const float r1 = x1 * cs - x2 * sn;
-    x2 = x2 * cs + x1 * sn;
+    // (written out: which of the two products a compiler fuses into the sum depends on the code around it)
+    const float r1 = fmaf(x1, cs, -(x2 * sn));
+    x2 = fmaf(x2, cs, x1 * sn);
     x1 = r1;
   }
   bf16_t* dst;

@@ -51,6 +51,9 @@ CASES = {
     # sums over a row by a workgroup per row
     "step of 8 rows": (lambda: step(2, D=1024, Hq=8, Hkv=2, d=128, I=1536, V=30000, B=8, ctx=(0, 60)), "8378dd9450f6341b"),
     "step of 20 rows, paged": (lambda: step(2, paged=True, D=768, Hq=8, Hkv=2, d=64, I=1536, V=30000, B=20, ctx=(0, 60)), "8979e8f368224ea6"),
+    # rotary embedding: which of a sum's two products is rounded first shows in one of 30000 cache entries
+    "step of 64 rows, 16 KV heads": (lambda: step(2, paged=True, seed=2, D=256, Hq=16, Hkv=16, d=128, I=512, V=1000, B=64, ctx=(0, 200)), "06cff609ec2facf0"),
+    "step of 64 rows, 64-wide heads": (lambda: step(2, paged=True, seed=1, D=256, Hq=16, Hkv=16, d=64, I=512, V=1000, B=64, ctx=(0, 200)), "6bc2b1c36d2446dd"),
     # attention of up to 16 rows per KV head: the order of its tiles, rings and segments, in units of one granule and of many
     "step of 8 rows, long": (lambda: step(2, paged=True, D=1024, Hq=8, Hkv=2, d=128, I=1536, V=30000, B=8, ctx=(3000, 6000)), "d57e24910efc3518"),
     "tree": (lambda: tree((0, 60)), "d8b47615b09c91fa"),
